@@ -75,17 +75,20 @@ enum { GERBIL_PLAIN = 0, GERBIL_BATCHED = 1 };
  * other orders of Sec. 3.1, or by the caller); bin = rank mod n_bins. */
 enum { GERBIL_ORDER_KMC2 = 0, GERBIL_ORDER_LEX = 1, GERBIL_ORDER_TABLE = 2 };
 
-/* Where hash tables live. LDS (and AUTO): every bin, or hash slice of a large
- * bin, is split by key hash into sub-tables that one workgroup counts in LDS
- * (the hasher threads of Sec. 2.3.2 with their own tables). HBM: one
- * open-addressing table per bin in device memory, probed by every workgroup. */
+/* Where hash tables live. LDS (and AUTO): every bin is split into sub-tables
+ * that one workgroup counts in LDS (the hasher threads of Sec. 2.3.2 with
+ * their own tables): BATCHED, k >= 20, by a second minimizer, so that runs of
+ * k-mers move as one descriptor; PLAIN, shorter keys and what the second
+ * minimizer repeats too often, by key hash. HBM: one open-addressing table per
+ * bin in device memory, probed by every workgroup. */
 enum { GERBIL_TABLE_AUTO = 0, GERBIL_TABLE_HBM = 1, GERBIL_TABLE_LDS = 2 };
 
 /* Run parameters; mirrors the command line of App. A. Zero means default. */
 typedef struct {
     uint32_t k;              /* k-mer length, 2 <= k <= 480 (App. A `-k`: 8..479). LDS tables take
-                                k <= 256; AUTO uses HBM tables above that, and TABLE_LDS with
-                                k > 256 is GERBIL_EUNSUPPORTED                                    */
+                                k <= 256, AUTO counts longer keys in LDS too when BATCHED and in
+                                HBM tables when PLAIN; TABLE_LDS with k > 256 is
+                                GERBIL_EUNSUPPORTED                                               */
     uint32_t m;              /* minimizer length, 1 <= m <= 15, m < k (App. A `-m`)              */
     uint32_t n_bins;         /* number of bins, 1..4096 (App. A `-f`, default 512)               */
     uint32_t threshold;      /* output iff count >= threshold, >= 1 (App. A `-l`, default 3)     */
@@ -98,19 +101,22 @@ typedef struct {
     uint32_t table;          /* GERBIL_TABLE_*                                                   */
     float load_factor;       /* k-mers per table slot when tables are sized: HBM tables (0, 0.95]
                                 (k-mers bound the distinct keys), default 0.5; LDS sub-tables
-                                (0, 4], default 0.8 (occurrences repeat, so more than one per
-                                slot can fit; distinct keys beyond the slots take the emergency
-                                area)                                                             */
+                                (0, 4], default 0.68 (BATCHED, k >= 20) or 0.8 (occurrences
+                                repeat, so more than one per slot can fit; distinct keys beyond
+                                the slots take the emergency area)                                                             */
     uint32_t max_probes;     /* theta of Alg. 1: trials before the emergency path; 0 = default
                                 (8 buckets of 8 slots in HBM tables, 64 slots in LDS tables)     */
     uint32_t block;          /* threads per workgroup for counting, 64..1024 in steps of 64. HBM
-                                tables: 0 = 256. LDS tables, BATCHED: 512 runs two 512-thread
-                                workgroups per CU with 80 KB of LDS each (half-size tables whose
-                                stages overlap on the CU); any other value one 1024-thread
-                                workgroup per CU with 160 KB. LDS tables, PLAIN: always 1024     */
+                                tables: 0 = 256. LDS tables, BATCHED, k >= 20: 1024 runs one
+                                1024-thread workgroup per CU with 160 KB of LDS, any other value
+                                two of 512 with 80 KB each (half-size tables whose stages overlap
+                                on the CU); k < 20: 512 runs two workgroups, any other value one.
+                                LDS tables, PLAIN: always 1024                                    */
     uint32_t pool;           /* BATCHED: hash tables resident at once. LDS tables: key slots (ranks
-                                scattered and not yet counted), 0 = 16, best a multiple of 8 (one
-                                work queue per XCD); HBM tables: 0 = chosen from budget          */
+                                scattered by key hash and not yet counted), best a multiple of 8
+                                (one work queue per XCD), 0 = 16, or 8 where they only serve what
+                                the second minimizer repeats too often (k >= 20); HBM tables: 0 =
+                                chosen from budget                                                */
     uint64_t overflow_cap;   /* emergency-area capacity in k-mer occurrences, rounded up to a power
                                 of two, at most 2^31; 0 = 2^20. The workspace holds the area and
                                 its counting table of twice as many slots                        */
@@ -120,10 +126,10 @@ typedef struct {
                                   after the main counting kernel(s): the persistent kernel (BATCHED)
                                   or the per-bin insert and dump launches (PLAIN); NULL = none      */
     uint64_t* stage_clocks;  /* optional device uint64[8], zeroed by the caller: busy time (in
-                                units of the 100 MHz wall clock) of the four LDS stages (count,
-                                scan, scatter, table) in [0..3] and their item counts in [4..7];
+                                units of the 100 MHz wall clock) of the four LDS stages (count
+                                or split, scan, scatter, table) in [0..3] and their item counts in [4..7];
                                 NULL = none                                                       */
-    uint32_t size_sample;    /* LDS tables: sub-table runs are sized from a sample, every
+    uint32_t size_sample;    /* LDS tables, partition by key hash: sub-table runs are sized from a sample, every
                                 size_sample-th segment of 32/size_sample k-mers (a run holds
                                 size_sample x its sampled keys plus a four-sigma margin; if a run
                                 still overflows, all of its keys take the emergency area, so

@@ -12,6 +12,7 @@
 #include "../../include/gerbil.h"
 #include "common.h"
 #include "internal.h"
+#include "pieces.h"
 
 using namespace gerbil;
 
@@ -219,6 +220,10 @@ constexpr uint32_t kDefaultKeySlots = 2 * kLdsQueues;
 constexpr uint32_t kDefaultLdsTheta = 64;   // single-slot probes are cheap in LDS
 constexpr double kDefaultLdsFill = 0.8;     // k-mers per LDS slot (distinct keys are fewer)
 
+// Key slots of the LDS path when it only counts what the piece partition leaves.
+constexpr uint32_t kFallbackKeySlots = kLdsQueues;
+constexpr uint32_t kFallbackPool = 3;   // HBM tables of the same
+
 struct LdsSizing {
     uint32_t block, max_sub;   // workgroup shape (LdsShape)
     bool packed;               // packed table slots (lds_packed)
@@ -234,7 +239,7 @@ uint32_t lds_block(const gerbil_params* p) {
 
 constexpr uint32_t kDefaultSizeSample = 8;
 
-LdsSizing lds_sizing(const gerbil_params* p, uint64_t n_bytes) {
+LdsSizing lds_sizing(const gerbil_params* p, uint64_t n_bytes, uint32_t key_slots = kDefaultKeySlots) {
     LdsSizing z;
     const uint32_t W = words_for(p->k);
     z.block = lds_block(p);
@@ -250,7 +255,7 @@ LdsSizing lds_sizing(const gerbil_params* p, uint64_t n_bytes) {
     z.ranks_cap = (uint32_t)std::min<uint64_t>(p->n_bins + n_bytes / per_slice + 1, 1u << 20);
     z.sp_cap = n_bytes / z.target + 2ull * z.ranks_cap + 1;
     if (p->mode == GERBIL_BATCHED) {
-        uint32_t q = p->pool ? p->pool : kDefaultKeySlots;
+        uint32_t q = p->pool ? p->pool : key_slots;
         z.Q = std::max<uint32_t>(1, std::min(q, z.ranks_cap));
     } else {
         z.Q = 1;
@@ -313,6 +318,122 @@ uint64_t lds_fixed(const LdsSizing& z, void* ws, uint64_t start, LdsLayout* L) {
     l.keys = ws ? (uint64_t*)((uint8_t*)ws + start + c.used) : nullptr;
     if (L) *L = l;
     return c.used;
+}
+
+// ---------------------------------------------------------------- pieces
+// The batched schedule partitions bins by sub-minimizers (pieces.h) whenever
+// LDS tables are allowed, keys of any length included: its tables refer to
+// the bases instead of holding keys. Keys below kPieceMinK stay with the
+// key partition (LDS path).
+constexpr double kPieceFill = 0.68;  // k-mers per slot: a sub-table holds some ten sub-minimizers' k-mers, so
+                                     // its size spreads by about a third around this
+
+struct PieceSizing {
+    uint32_t block, C, target, half_target, max_kmers, slice_kmers, heavy_kmers, max_halves;
+    uint32_t m2, n0, split_lds, piece_fx, group_log2, items_cap;
+    uint64_t sp_cap;
+};
+
+bool use_pieces(const gerbil_params* p, uint64_t n_bytes) {
+    return p->mode == GERBIL_BATCHED && p->table != GERBIL_TABLE_HBM && p->k >= kPieceMinK && n_bytes < (1ull << 38);
+}
+
+PieceSizing piece_sizing(const gerbil_params* p, const gerbil_bins* bins) {
+    PieceSizing z;
+    z.block = p->block == 1024 ? 1024u : 512u;
+    z.m2 = sub_minimizer_len(p->k);
+    const uint32_t w2 = sub_window(p->k, z.m2), w = p->k - p->m + 1;
+    // The LDS left by the fixed parts holds the staged bases and the slots. A
+    // piece has about 0.8 / (2 / (w2 + 1) + 2 / (w + 1)) k-mers (cuts of either
+    // minimizer, and read ends); its bases get room for 2.2 times the mean
+    // sub-table (what does not fit goes to the fallback, and a fallback of HBM
+    // tables is slow enough for a wider margin), the slots 1 / kPieceFill.
+    const double per_kmer = (2.0 / (w2 + 1) + 2.0 / (w + 1)) / 0.8;
+    const double halves = std::min(p->k / 16.0 + 2.0, (1.0 + per_kmer * (p->k + 29)) / 16.0);
+    const double margin = words_for(p->k) <= GERBIL_MAX_LDS_W ? 2.2 : 3.5;
+    const double pool = z.block == 1024 ? SubShape<1024>::pool : SubShape<512>::pool;
+    const double n = pool / (8.0 / kPieceFill + 4.0 * margin * halves);
+    z.max_halves = 2 * (uint32_t)(margin * halves * n / 2.0);
+    z.half_target = std::max<uint32_t>(1u, (uint32_t)(z.max_halves / margin));
+    z.C = ((uint32_t)pool - 4 * z.max_halves) / 8;
+    for (;; z.C--) {   // a prime, so that double hashing has a full period
+        bool prime = true;
+        for (uint32_t d = 2; prime && d * d <= z.C; d++) prime = z.C % d != 0;
+        if (prime) break;
+    }
+    const double fill = p->load_factor > 0 ? p->load_factor : kPieceFill;
+    z.target = std::min<uint32_t>(40000u, std::max<uint32_t>(64u, (uint32_t)(z.C * fill)));
+    z.max_kmers = std::max<uint32_t>((uint32_t)(0.95 * z.C), z.target + z.target / 4);
+    z.slice_kmers = std::max<uint32_t>((uint32_t)(0.75 * z.C), z.target);
+    // counts are 16 bits wide; more than four tables' worth goes to the fallback
+    z.heavy_kmers = std::min<uint32_t>(60000u, std::max<uint32_t>(4 * z.C, z.target + z.target / 2));
+    // a turn of n windows costs n + w2 - 1 m2-mers: wide windows take the longest turns, at two
+    // workgroups per CU; 48 windows leave LDS for a third, and super-mers are seldom longer
+    z.n0 = std::min(w2 >= kPieceMax ? kPieceMax : 48u, w2);
+    z.split_lds = split_lds_bytes(z.n0);
+    // random sub-minimizers change every (w2 + 1) / 2 windows
+    z.piece_fx = (uint32_t)(65536.0 * 2.15 / (w2 + 1));
+    uint32_t g = 0;
+    while ((1u << g) < (p->k + 24) / 16 && g < 6) g++;   // half words of an ordinary piece
+    z.group_log2 = g;
+    z.items_cap = piece_items_cap(bins->cap_superm, p->n_bins);
+    // any bins of n_bytes bases: every base a k-mer, cap_superm super-mers; the
+    // number of a large bin's sub-tables is rounded up to a power of two
+    const uint64_t E = bins->cap_superm + ((bins->n_bytes * z.piece_fx) >> 16);
+    z.sp_cap = 2 * (bins->n_bytes / z.target + piece_halves(bins->n_bytes, E, p->k) / z.half_target) +
+               2ull * p->n_bins + 2;
+    return z;
+}
+
+struct PieceLayout {
+    uint32_t *nsub, *spbase, *item_first, *bin_fail, *item_n, *sub_cur;
+    uint64_t *scal, *item_start, *sub_cnt, *sub_off, *fb_ptr, *fb_n, *fb_kmers;
+};
+
+uint64_t piece_fixed(const PieceSizing& z, uint32_t n_bins, void* ws, uint64_t start, PieceLayout* L) {
+    Carve c(ws ? (uint8_t*)ws + start : nullptr);
+    PieceLayout l;
+    l.nsub = c.take<uint32_t>(n_bins);
+    l.spbase = c.take<uint32_t>(n_bins + 1);
+    l.item_first = c.take<uint32_t>(n_bins + 1);
+    l.bin_fail = c.take<uint32_t>(n_bins);
+    l.scal = c.take<uint64_t>(kScalCount);
+    l.item_start = c.take<uint64_t>(z.items_cap);
+    l.item_n = c.take<uint32_t>(z.items_cap);
+    l.sub_cnt = c.take<uint64_t>(z.sp_cap);
+    l.sub_off = c.take<uint64_t>(z.sp_cap);
+    l.sub_cur = c.take<uint32_t>(z.sp_cap);
+    l.fb_ptr = c.take<uint64_t>(n_bins);
+    l.fb_n = c.take<uint64_t>(n_bins);
+    l.fb_kmers = c.take<uint64_t>(n_bins);
+    if (L) *L = l;
+    return c.used;
+}
+
+// The rest of the workspace holds the pieces by sub-table, then a region used
+// twice: by the list of pieces in split order until they are scattered, then
+// by the fallback's key slots or tables. Its size is all that a call knows, so
+// the pieces take a fixed share of it and the query asks for enough of both.
+constexpr uint64_t kPieceShareLds = 16;   // one piece per 16 bytes: half of the region
+constexpr uint64_t kPieceShareHbm = 64;   // HBM tables are much larger than the pieces: an eighth
+uint64_t piece_region(uint64_t list_slots, uint64_t fallback_bytes, uint64_t share) {
+    return align_up(std::max(list_slots * share, (fallback_bytes * share + share - 9) / (share - 8)) + share + 2 * kAlign);
+}
+struct PieceRegion {
+    uint64_t cap;         // pieces
+    uint64_t* pieces;
+    uint64_t* second;     // list, or the fallback's memory
+    uint64_t second_bytes;
+};
+PieceRegion piece_carve(void* ws, uint64_t used, uint64_t ws_bytes, uint64_t share) {
+    PieceRegion r;
+    const uint64_t R = ws_bytes > used + kAlign ? ws_bytes - used - kAlign : 0;
+    r.cap = R / share;
+    r.pieces = (uint64_t*)((uint8_t*)ws + used);
+    const uint64_t first = align_up(8 * r.cap);
+    r.second = (uint64_t*)((uint8_t*)ws + used + first);
+    r.second_bytes = R + kAlign > first ? R + kAlign - first : 0;
+    return r;
 }
 
 int32_t hip_status(hipError_t e) { return e == hipSuccess ? GERBIL_OK : GERBIL_EDEVICE; }
@@ -378,29 +499,21 @@ CountArgs count_args(const gerbil_params* p, const gerbil_bins* bins, const gerb
     return a;
 }
 
-// LDS sub-table path: plan on the device, then one persistent launch
-// (BATCHED) or four launches per rank (PLAIN).
-int32_t count_lds(const gerbil_bins* bins, const gerbil_params* p, void* ws, uint64_t ws_bytes, uint64_t* keys,
-                  uint32_t* counts, uint64_t cap, gerbil_counted* state, hipStream_t stream) {
-    const uint32_t W = words_for(p->k);
-    const bool batched = p->mode == GERBIL_BATCHED;
-    const uint64_t ovf_cap = ovf_capacity(p);
-    const LdsSizing z = lds_sizing(p, bins->n_bytes);
-    CountLayout L;
-    const uint64_t fixed0 = count_fixed(W, ovf_cap, p->n_bins, false, ws, &L);
-    LdsLayout LL;
-    const uint64_t fixed = fixed0 + lds_fixed(z, ws, fixed0, &LL);
-    if (fixed + kAlign > ws_bytes) return GERBIL_EINVAL;
-    const uint64_t key_bytes = 8ull * (W - 1) + tail_bytes_for(p->k);
-    uint64_t slot_keys = (ws_bytes - fixed - kAlign) / ((uint64_t)z.Q * key_bytes);
-    while (slot_keys && (uint64_t)z.Q * slot_words_for(slot_keys, p->k) * 8ull > ws_bytes - fixed - kAlign) slot_keys--;
-    if (slot_keys < 1) return GERBIL_EINVAL;
-    if (slot_keys > 0xFFFFFFFFull) slot_keys = 0xFFFFFFFFull;   // run offsets are 32-bit inside a slot
-    fill_state(state, p, bins, cap, ovf_cap, L);
-    CountArgs a = count_args(p, bins, state, keys, counts, cap, L);
+// Keys per slot of Q key slots in `bytes` bytes (0: none).
+uint64_t slot_keys_in(uint64_t bytes, uint32_t Q, uint32_t k) {
+    const uint64_t key_bytes = 8ull * (words_for(k) - 1) + tail_bytes_for(k);
+    uint64_t slot_keys = bytes / ((uint64_t)Q * key_bytes);
+    while (slot_keys && (uint64_t)Q * slot_words_for(slot_keys, k) * 8ull > bytes) slot_keys--;
+    return std::min<uint64_t>(slot_keys, 0xFFFFFFFFull);   // run offsets are 32-bit inside a slot
+}
 
-    // one 1024-thread workgroup per CU, or two of 512
-    const uint32_t grid = batched ? (uint32_t)device_cus() * (kLdsBlock / z.block) : 1u;
+// Workgroups of the persistent launch: one of 1024 threads per CU, or two of 512.
+uint32_t lds_grid(const LdsSizing& z) { return (uint32_t)device_cus() * (kLdsBlock / z.block); }
+
+LdsArgs lds_args(const gerbil_bins* bins, const gerbil_params* p, const LdsSizing& z, const LdsLayout& LL,
+                 uint64_t slot_keys, const gerbil_counted* state) {
+    const bool batched = p->mode == GERBIL_BATCHED;
+    const uint32_t grid = batched ? lds_grid(z) : 1u;
     LdsArgs l;
     l.block = z.block;
     l.n_queues = std::max<uint32_t>(1, std::min(kLdsQueues, grid));
@@ -440,12 +553,35 @@ int32_t count_lds(const gerbil_bins* bins, const gerbil_params* p, void* ws, uin
     l.cursor = LL.cursor;
     l.n_superm = bins->n_superm;
     l.superm_cap = bins->cap_superm;
+    l.fb = FallbackBins{nullptr, nullptr, nullptr};
     l.status = state->status;
+    return l;
+}
+
+// LDS sub-table path: plan on the device, then one persistent launch
+// (BATCHED) or four launches per rank (PLAIN).
+int32_t count_lds(const gerbil_bins* bins, const gerbil_params* p, void* ws, uint64_t ws_bytes, uint64_t* keys,
+                  uint32_t* counts, uint64_t cap, gerbil_counted* state, hipStream_t stream) {
+    const uint32_t W = words_for(p->k);
+    const bool batched = p->mode == GERBIL_BATCHED;
+    const uint64_t ovf_cap = ovf_capacity(p);
+    const LdsSizing z = lds_sizing(p, bins->n_bytes);
+    CountLayout L;
+    const uint64_t fixed0 = count_fixed(W, ovf_cap, p->n_bins, false, ws, &L);
+    LdsLayout LL;
+    const uint64_t fixed = fixed0 + lds_fixed(z, ws, fixed0, &LL);
+    if (fixed + kAlign > ws_bytes) return GERBIL_EINVAL;
+    const uint64_t slot_keys = slot_keys_in(ws_bytes - fixed - kAlign, z.Q, p->k);
+    if (slot_keys < 1) return GERBIL_EINVAL;
+    fill_state(state, p, bins, cap, ovf_cap, L);
+    CountArgs a = count_args(p, bins, state, keys, counts, cap, L);
+    const LdsArgs l = lds_args(bins, p, z, LL, slot_keys, state);
 
     hipError_t e = launch_fill_u64(L.scalars, 8, 0, stream);
     if (e == hipSuccess) e = launch_fill_u64(L.hist, kHistInternal, 0, stream);
     if (e == hipSuccess) e = launch_lds_plan(l, stream);
     if (e != hipSuccess) return GERBIL_EDEVICE;
+    const uint32_t grid = lds_grid(z);
     if (batched) {
         if (p->timing_events) e = hipEventRecord(p->timing_events[0], stream);
         if (e == hipSuccess) e = launch_lds_persistent(a, l, grid, stream);
@@ -470,6 +606,157 @@ int32_t count_lds(const gerbil_bins* bins, const gerbil_params* p, void* ws, uin
         }
         if (e == hipSuccess && p->timing_events) e = hipEventRecord(p->timing_events[1], stream);
     }
+    if (e == hipSuccess) e = launch_overflow(a, stream);
+    return hip_status(e);
+}
+
+PersistArgs persist_args(const gerbil_bins* bins, const gerbil_params* p, const CountLayout& L, uint8_t* pool,
+                         uint64_t slots, uint32_t Q, const gerbil_counted* state) {
+    PersistArgs q;
+    q.pool = pool;
+    q.slots = slots;
+    q.Q = Q;
+    q.lag = Q / 2;
+    q.n_bins = bins->n_bins;
+    // threads per workgroup: 256, 512 or 1024 (other values take 256)
+    q.ins_chunk = p->block == 512 || p->block == 1024 ? p->block : 256u;
+    q.cmp_chunk = kCmpChunk;
+    q.load = std::min(load_of(p), 0.95f);   // (an LDS fill above one does not fit these tables)
+    q.bin_off = bins->bin_off;
+    q.bin_kmers = bins->bin_kmers;
+    q.order = L.order;
+    q.nb = L.nb;
+    q.n_ins = L.n_ins;
+    q.n_cmp = L.n_cmp;
+    q.ins_done = L.ins_done;
+    q.cmp_done = L.cmp_done;
+    q.seg_code = L.seg_code;
+    q.seg_start = L.seg_start;
+    q.cursor = L.cursor;
+    q.n_superm = bins->n_superm;
+    q.superm_cap = bins->cap_superm;
+    q.fb = FallbackBins{nullptr, nullptr, nullptr};
+    q.status = state->status;
+    return q;
+}
+
+// Slots of each of Q HBM tables in `bytes` bytes (0: less than a bucket).
+uint64_t pool_slots_in(uint64_t bytes, uint32_t Q, uint32_t W) {
+    const uint64_t per_table = bytes / Q;
+    uint64_t s = per_table / (8ull * W + 4);
+    while (s >= kBucket && pool_table_bytes(s, W) > per_table) s -= s / 64 + 1;
+    s -= s % kBucket;
+    return s / kBucket > 0xFFFFFFFFull ? 0 : s;
+}
+
+uint32_t fallback_pool(const gerbil_params* p) { return std::min(p->pool ? p->pool : kFallbackPool, p->n_bins); }
+
+// BATCHED with LDS tables: the piece partition, its table kernel, then the
+// key partition (or, above GERBIL_MAX_LDS_W words, HBM tables) for the heavy
+// rest, which is usually empty.
+int32_t count_pieces(const gerbil_bins* bins, const gerbil_params* p, void* ws, uint64_t ws_bytes, uint64_t* keys,
+                     uint32_t* counts, uint64_t cap, gerbil_counted* state, hipStream_t stream) {
+    const uint32_t W = words_for(p->k);
+    const bool lds_fb = W <= GERBIL_MAX_LDS_W;
+    const uint64_t ovf_cap = ovf_capacity(p);
+    const PieceSizing z = piece_sizing(p, bins);
+    const LdsSizing zl = lds_sizing(p, bins->n_bytes, kFallbackKeySlots);
+    CountLayout L;
+    uint64_t used = count_fixed(W, ovf_cap, p->n_bins, !lds_fb, ws, &L);
+    PieceLayout PL;
+    used += piece_fixed(z, p->n_bins, ws, used, &PL);
+    LdsLayout LL;
+    if (lds_fb) used += lds_fixed(zl, ws, used, &LL);
+    const PieceRegion r = piece_carve(ws, used, ws_bytes, lds_fb ? kPieceShareLds : kPieceShareHbm);
+    if (r.cap < 1 || r.second_bytes < 8 * r.cap) return GERBIL_EINVAL;
+    const uint32_t Q = fallback_pool(p);
+    const uint64_t fb_size = lds_fb ? slot_keys_in(r.second_bytes, zl.Q, p->k) : pool_slots_in(r.second_bytes, Q, W);
+    if (fb_size < (lds_fb ? 1u : kBucket)) return GERBIL_EINVAL;
+    fill_state(state, p, bins, cap, ovf_cap, L);
+    CountArgs a = count_args(p, bins, state, keys, counts, cap, L);
+
+    PieceArgs q;
+    q.packed = bins->packed;
+    q.n_bytes = bins->n_bytes;
+    q.desc = bins->desc;
+    q.bin_off = bins->bin_off;
+    q.bin_kmers = bins->bin_kmers;
+    q.n_superm = bins->n_superm;
+    q.superm_cap = bins->cap_superm;
+    q.k = p->k;
+    q.m2 = z.m2;
+    q.w2 = sub_window(p->k, z.m2);
+    q.n_bins = p->n_bins;
+    q.status = state->status;
+    q.n0 = z.n0;
+    q.split_lds = z.split_lds;
+    q.target = z.target;
+    q.half_target = z.half_target;
+    q.max_kmers = z.max_kmers;
+    q.slice_kmers = z.slice_kmers;
+    q.heavy_kmers = z.heavy_kmers;
+    q.max_halves = z.max_halves;
+    q.piece_fx = z.piece_fx;
+    q.sp_cap = (uint32_t)std::min<uint64_t>(z.sp_cap, 0xFFFFFFFFull);
+    q.items_cap = z.items_cap;
+    q.cap = r.cap;
+    q.nsub = PL.nsub;
+    q.spbase = PL.spbase;
+    q.item_first = PL.item_first;
+    q.scal = PL.scal;
+    q.bin_fail = PL.bin_fail;
+    q.item_start = PL.item_start;
+    q.item_n = PL.item_n;
+    q.list = r.second;
+    q.sub_cnt = PL.sub_cnt;
+    q.sub_off = PL.sub_off;
+    q.sub_cur = PL.sub_cur;
+    q.pieces = r.pieces;
+    q.fb_ptr = PL.fb_ptr;
+    q.fb_n = PL.fb_n;
+    q.fb_kmers = PL.fb_kmers;
+    q.stage_clocks = p->stage_clocks;
+
+    SubArgs t;
+    t.pieces = r.pieces;
+    t.sub_cnt = PL.sub_cnt;
+    t.sub_off = PL.sub_off;
+    t.n_sub = PL.scal + kScalSubs;
+    t.slots = z.C;
+    t.halves = z.max_halves;
+    t.theta = p->max_probes ? p->max_probes : kDefaultLdsTheta;
+    t.max_kmers = z.max_kmers;
+    t.slice_kmers = z.slice_kmers;
+    t.group_log2 = z.group_log2;
+    t.probe_hist = p->probe_hist;
+    t.stage_clocks = p->stage_clocks;
+
+    const uint32_t cus = (uint32_t)device_cus();
+    const FallbackBins fb{PL.fb_ptr, PL.fb_n, PL.scal + kScalFallback};
+    hipError_t e = launch_piece_plan(q, L.scalars, L.hist, stream);
+    if (e == hipSuccess && p->timing_events) e = hipEventRecord(p->timing_events[0], stream);
+    if (e == hipSuccess) e = launch_split(q, cus, stream);
+    if (e == hipSuccess) e = launch_sub_scan(q, stream);
+    if (e == hipSuccess) e = launch_piece_scatter(q, cus, stream);
+    if (e == hipSuccess) e = launch_sub_tables(a, t, z.block, cus, stream);
+    if (lds_fb) {
+        LdsArgs l = lds_args(bins, p, zl, LL, fb_size, state);
+        l.keys = r.second;
+        l.bin_kmers = PL.fb_kmers;
+        l.fb = fb;
+        if (e == hipSuccess) e = launch_lds_plan(l, stream);
+        if (e == hipSuccess) e = launch_lds_persistent(a, l, lds_grid(zl), stream);
+    } else {
+        PersistArgs h = persist_args(bins, p, L, (uint8_t*)r.second, fb_size, Q, state);
+        h.bin_kmers = PL.fb_kmers;
+        h.fb = fb;
+        a.theta = kDefaultTheta;   // buckets, where max_probes counts slots
+        if (e == hipSuccess) e = launch_pool_clear(h.pool, h.slots, W, Q, fb.any, stream);
+        if (e == hipSuccess) e = launch_plan(h, stream);
+        if (e == hipSuccess)
+            e = launch_count_persistent(a, h, cus * persistent_blocks_per_cu(W, h.ins_chunk), h.ins_chunk, stream);
+    }
+    if (e == hipSuccess && p->timing_events) e = hipEventRecord(p->timing_events[1], stream);
     if (e == hipSuccess) e = launch_overflow(a, stream);
     return hip_status(e);
 }
@@ -607,8 +894,31 @@ int32_t gerbil_count_workspace(const gerbil_bins* bins, const gerbil_params* p, 
         hipStreamSynchronize(stream) != hipSuccess)
         return GERBIL_EDEVICE;
     uint64_t mx = 1;
-    for (uint64_t v : kmers) mx = std::max(mx, v);
+    uint64_t total = 0;
+    for (uint64_t v : kmers) {
+        mx = std::max(mx, v);
+        total += v;
+    }
     const uint32_t W = words_for(p->k);
+    if (use_pieces(p, bins->n_bytes)) {
+        uint64_t n_superm = 0;
+        if (hipMemcpyAsync(&n_superm, bins->n_superm, 8, hipMemcpyDeviceToHost, stream) != hipSuccess ||
+            hipStreamSynchronize(stream) != hipSuccess)
+            return GERBIL_EDEVICE;
+        n_superm = std::min(n_superm, bins->cap_superm);
+        const bool lds_fb = W <= GERBIL_MAX_LDS_W;
+        const PieceSizing z = piece_sizing(p, bins);
+        const LdsSizing zl = lds_sizing(p, bins->n_bytes, kFallbackKeySlots);
+        uint64_t fixed = count_fixed(W, ovf_capacity(p), p->n_bins, !lds_fb, nullptr, nullptr);
+        fixed += piece_fixed(z, p->n_bins, nullptr, 0, nullptr);
+        if (lds_fb) fixed += lds_fixed(zl, nullptr, 0, nullptr);
+        const uint64_t slots = piece_list_slots(n_superm, total, z.piece_fx, z.n0, p->k - p->m + 1 > z.n0, p->n_bins);
+        const uint64_t fb = lds_fb ? (uint64_t)zl.Q * slot_words_for(lds_slot_keys(mx, zl), p->k) * 8ull + kAlign
+                                   : (uint64_t)fallback_pool(p) *
+                                         pool_table_bytes(slots_for(mx, std::min(load_of(p), 0.95f)), W);
+        *bytes = fixed + piece_region(slots, fb, lds_fb ? kPieceShareLds : kPieceShareHbm) + kAlign;
+        return GERBIL_OK;
+    }
     if (use_lds(p)) {
         LdsSizing z = lds_sizing(p, bins->n_bytes);
         uint64_t fixed = count_fixed(W, ovf_capacity(p), p->n_bins, false, nullptr, nullptr);
@@ -634,20 +944,15 @@ int32_t gerbil_count(const gerbil_bins* bins, const gerbil_params* p, void* ws, 
     const bool batched = p->mode == GERBIL_BATCHED;
     const float load = load_of(p);
     const uint64_t ovf_cap = ovf_capacity(p);
+    if (use_pieces(p, bins->n_bytes)) return count_pieces(bins, p, ws, ws_bytes, keys, counts, cap, state, stream);
     if (use_lds(p)) return count_lds(bins, p, ws, ws_bytes, keys, counts, cap, state, stream);
     const uint32_t Q = pool_size(p);
     CountLayout L;
     const uint64_t fixed = count_fixed(W, ovf_cap, n_bins, batched, ws, &L);
     if (fixed > ws_bytes) return GERBIL_EINVAL;
     // The pool takes the rest of the workspace: Q tables of `slots` slots.
-    uint64_t slots = 0;
-    {
-        uint64_t per_table = (ws_bytes - fixed) / Q;
-        uint64_t s_guess = per_table / (8ull * W + 4);
-        while (s_guess >= kBucket && pool_table_bytes(s_guess, W) > per_table) s_guess -= s_guess / 64 + 1;
-        slots = s_guess - s_guess % kBucket;
-    }
-    if (slots < kBucket || slots / kBucket > 0xFFFFFFFFull) return GERBIL_EINVAL;
+    const uint64_t slots = pool_slots_in(ws_bytes - fixed, Q, W);
+    if (slots < kBucket) return GERBIL_EINVAL;
 
     std::vector<uint64_t> off, kmers;
     uint64_t n_superm = 0;
@@ -664,80 +969,17 @@ int32_t gerbil_count(const gerbil_bins* bins, const gerbil_params* p, void* ws, 
         if (e != hipSuccess) return GERBIL_EDEVICE;
     }
 
-    memset(state, 0, sizeof(*state));
-    state->k = p->k;
-    state->W = W;
-    state->threshold = p->threshold;
-    state->hist_len = kHistInternal;
-    state->cap = cap;
-    state->overflow_cap = ovf_cap;
-    state->n_out = L.scalars;
-    state->n_overflow = L.scalars + 1;
-    state->max_count = L.scalars + 2;
-    state->status = (uint32_t*)(L.scalars + 3);
-    state->hist = L.hist;
-    state->n_superm = bins->n_superm;
-    state->bin_status = bins->status;
-
-    CountArgs a;
-    a.packed = bins->packed;
-    a.n_bytes = bins->n_bytes;
-    a.desc = bins->desc;
-    a.k = p->k;
-    a.W = W;
-    a.threshold = p->threshold;
-    a.theta = p->max_probes ? p->max_probes : kDefaultTheta;
-    a.canonical = p->canonical;
-    a.seed = kHashSeed;
-    a.ovf_keys = L.ovf_keys;
-    a.ovf_state = L.ovf_state;
-    a.ovf_tkeys = L.ovf_tkeys;
-    a.ovf_tcnt = L.ovf_tcnt;
-    a.ovf_cap = ovf_cap;
-    a.n_ovf = state->n_overflow;
-    a.out_keys = keys;
-    a.out_counts = counts;
-    a.cap = cap;
-    a.n_out = state->n_out;
-    a.hist = L.hist;
-    a.max_count = state->max_count;
-    a.status = state->status;
+    fill_state(state, p, bins, cap, ovf_cap, L);
+    const CountArgs a = count_args(p, bins, state, keys, counts, cap, L);
 
     e = launch_fill_u64(L.scalars, 8, 0, stream);
     if (e == hipSuccess) e = launch_fill_u64(L.hist, kHistInternal, 0, stream);
-    for (uint32_t j = 0; j < Q && e == hipSuccess; j++) {
-        Table t = pool_table(L.pool, slots, W, j);
-        e = launch_fill_u64(t.w0, slots, GERBIL_EMPTY, stream);
-        if (e == hipSuccess) e = launch_fill_u32(t.cnt, slots, 0, stream);
-    }
+    if (e == hipSuccess) e = launch_pool_clear(L.pool, slots, W, Q, nullptr, stream);
     if (e != hipSuccess) return GERBIL_EDEVICE;
 
     if (batched) {
-        PersistArgs q;
-        q.pool = L.pool;
-        q.slots = slots;
-        q.Q = Q;
-        q.lag = Q / 2;
-        q.n_bins = n_bins;
-        // threads per workgroup: 256, 512 or 1024 (other values take 256)
-        const uint32_t hb = p->block == 512 || p->block == 1024 ? p->block : 256u;
-        q.ins_chunk = hb;
-        q.cmp_chunk = kCmpChunk;
-        q.load = load;
-        q.bin_off = bins->bin_off;
-        q.bin_kmers = bins->bin_kmers;
-        q.order = L.order;
-        q.nb = L.nb;
-        q.n_ins = L.n_ins;
-        q.n_cmp = L.n_cmp;
-        q.ins_done = L.ins_done;
-        q.cmp_done = L.cmp_done;
-        q.seg_code = L.seg_code;
-        q.seg_start = L.seg_start;
-        q.cursor = L.cursor;
-        q.n_superm = bins->n_superm;
-        q.superm_cap = bins->cap_superm;
-        q.status = state->status;
+        const PersistArgs q = persist_args(bins, p, L, L.pool, slots, Q, state);
+        const uint32_t hb = q.ins_chunk;
         e = launch_plan(q, stream);
         uint32_t grid = (uint32_t)device_cus() * persistent_blocks_per_cu(W, hb);
         if (e == hipSuccess && p->timing_events) e = hipEventRecord(p->timing_events[0], stream);

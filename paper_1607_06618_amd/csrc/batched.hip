@@ -37,6 +37,13 @@ __global__ void __launch_bounds__(kPlanBlock) k_plan(PersistArgs q) {
     __shared__ uint64_t part[kPlanBlock];
     __shared__ uint32_t segn[2 * kMaxBins];   // items per queue segment
     const uint32_t tid = threadIdx.x, n = q.n_bins;
+    if (q.fb.any && *q.fb.any == 0) {   // nothing to count
+        if (tid == 0) {
+            q.seg_start[2 * n] = 0;
+            *q.cursor = 0;
+        }
+        return;
+    }
     uint32_t N = 1;
     while (N < n) N <<= 1;
     for (uint32_t i = tid; i < N; i += kPlanBlock) {
@@ -68,7 +75,7 @@ __global__ void __launch_bounds__(kPlanBlock) k_plan(PersistArgs q) {
     // per-rank items and their queue positions
     for (uint32_t i = tid; i < n; i += kPlanBlock) {
         uint32_t b = sval[i];
-        uint64_t nd = q.bin_off[b + 1] - q.bin_off[b];
+        uint64_t nd = bin_descs(q.fb, q.bin_off, b);
         uint64_t km = q.bin_kmers[b];
         uint64_t want = (uint64_t)((double)km / (double)q.load / kBucket) + 1;
         uint64_t p2 = 1;
@@ -117,6 +124,23 @@ __global__ void __launch_bounds__(kPlanBlock) k_plan(PersistArgs q) {
     if (tid == 0) *q.cursor = 0;
 }
 
+__global__ void __launch_bounds__(256) k_pool_clear(uint8_t* pool, uint64_t slots, uint32_t W, const uint64_t* any) {
+    if (any && *any == 0) return;
+    const Table t = pool_table(pool, slots, W, blockIdx.y);
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < slots; i += (uint64_t)gridDim.x * 256) {
+        t.w0[i] = GERBIL_EMPTY;
+        t.cnt[i] = 0u;
+    }
+}
+
+hipError_t launch_pool_clear(uint8_t* pool, uint64_t slots, uint32_t W, uint32_t Q, const uint64_t* any,
+                             hipStream_t s) {
+    const uint64_t blocks = (slots + 255) / 256;
+    hipLaunchKernelGGL(k_pool_clear, dim3((uint32_t)(blocks < 4096 ? blocks : 4096), Q), dim3(256), 0, s, pool, slots,
+                       W, any);
+    return hipGetLastError();
+}
+
 hipError_t launch_plan(const PersistArgs& q, hipStream_t s) {
     hipLaunchKernelGGL(k_plan, dim3(1), dim3(kPlanBlock), 0, s, q);
     return hipGetLastError();
@@ -156,12 +180,11 @@ __global__ void __launch_bounds__(B) k_count_persistent(CountArgs a, PersistArgs
             // insert item: needs a clean table
             if (tid == 0 && rank >= q.Q) wait_done(q.cmp_done + (rank - q.Q), q.n_cmp[rank - q.Q], kWaitLimit, a.status, ST_SPIN);
             __syncthreads();
-            const uint64_t d_end = q.bin_off[bin + 1];
-            const uint64_t i = q.bin_off[bin] + local * q.ins_chunk + tid;
+            const uint64_t i = local * q.ins_chunk + tid;
             uint32_t n = 0;
             int64_t st = 0;
-            if (i < d_end) {
-                uint64_t d = a.desc[i];
+            if (i < bin_descs(q.fb, q.bin_off, bin)) {
+                uint64_t d = bin_first(q.fb, a.desc, q.bin_off, bin)[i];
                 st = (int64_t)(d >> 24);
                 n = (uint32_t)(d & 0xFFFFFFu);
             }

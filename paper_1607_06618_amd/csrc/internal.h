@@ -107,6 +107,21 @@ __host__ __device__ inline Table pool_table(uint8_t* pool, uint64_t slots, uint3
     return t;
 }
 
+// Descriptors to count per bin when a schedule runs as the fallback of the
+// piece partition (pieces.h); all NULL when it counts the bins themselves.
+struct FallbackBins {
+    const uint64_t* ptr;   // [n_bins] device address of the bin's first descriptor
+    const uint64_t* n;     // [n_bins] descriptors
+    const uint64_t* any;   // scalar: 0 if no bin has any (the plan then schedules nothing)
+};
+__device__ __forceinline__ uint64_t bin_descs(const FallbackBins& fb, const uint64_t* bin_off, uint32_t b) {
+    return fb.n ? fb.n[b] : bin_off[b + 1] - bin_off[b];
+}
+__device__ __forceinline__ const uint64_t* bin_first(const FallbackBins& fb, const uint64_t* desc,
+                                                     const uint64_t* bin_off, uint32_t b) {
+    return fb.ptr ? (const uint64_t*)fb.ptr[b] : desc + bin_off[b];
+}
+
 // BATCHED schedule: every bin in one persistent launch.
 struct PersistArgs {
     uint8_t* pool;            // Q tables of `slots` slots each
@@ -130,8 +145,11 @@ struct PersistArgs {
     uint64_t* cursor;         // work-stealing cursor
     const uint64_t* n_superm; // descriptors found by the binning
     uint64_t superm_cap;      // descriptors stored; nothing is scheduled if exceeded
+    FallbackBins fb;          // what to count, when this launch is the fallback of the piece partition
     uint32_t* status;
 };
+// Clear the Q tables of a pool (nothing when `any` is given and holds 0).
+hipError_t launch_pool_clear(uint8_t* pool, uint64_t slots, uint32_t W, uint32_t Q, const uint64_t* any, hipStream_t s);
 hipError_t launch_plan(const PersistArgs& q, hipStream_t s);
 hipError_t launch_count_persistent(const CountArgs& a, const PersistArgs& q, uint32_t grid, uint32_t block,
                                    hipStream_t s);
@@ -250,6 +268,7 @@ struct LdsArgs {
     uint64_t* cursor;         // [kLdsQueues * kCursorStride]: queue q at q * kCursorStride
     const uint64_t* n_superm;
     uint64_t superm_cap;
+    FallbackBins fb;          // what to count, when this launch is the fallback of the piece partition
     uint32_t* status;
 };
 hipError_t launch_lds_plan(const LdsArgs& l, hipStream_t s);

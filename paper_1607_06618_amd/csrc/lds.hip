@@ -42,6 +42,17 @@ __global__ void __launch_bounds__(1024) k_lds_plan(LdsArgs l) {
     __shared__ uint64_t part[1024];
     __shared__ uint32_t s_total;
     const uint32_t tid = threadIdx.x, n = l.n_bins;
+    if (l.fb.any && *l.fb.any == 0) {   // nothing to count: every queue is empty
+        if (tid < l.n_queues) {
+            l.seg_start[tid] = 0;
+            l.cursor[tid * kCursorStride] = 0;
+        }
+        if (tid == 0) {
+            *l.n_ranks = 0;
+            *l.n_seg = 0;
+        }
+        return;
+    }
     uint32_t N = 1;
     while (N < n) N <<= 1;
     for (uint32_t i = tid; i < N; i += 1024) {
@@ -95,7 +106,7 @@ __global__ void __launch_bounds__(1024) k_lds_plan(LdsArgs l) {
             if (i >= n) break;
             uint32_t b = sval[i];
             uint64_t V = slices(i);
-            uint64_t nd = l.bin_off[b + 1] - l.bin_off[b];
+            uint64_t nd = bin_descs(l.fb, l.bin_off, b);
             uint64_t kest = (skey[i] + V - 1) / V;
             uint64_t P = (kest + l.target - 1) / l.target;
             if (P < 1) P = 1;
@@ -233,9 +244,8 @@ template <uint32_t B>
 __device__ __forceinline__ uint32_t load_chunk_seg(const CountArgs& a, const LdsArgs& l, uint32_t b, uint32_t chunk,
                                                    uint32_t L, uint64_t* sdesc, uint32_t* sgpre, uint32_t* wsum) {
     const uint32_t tid = threadIdx.x;
-    const uint64_t d_end = l.bin_off[b + 1];
-    const uint64_t i = l.bin_off[b] + (uint64_t)chunk * B + tid;
-    const uint64_t d = i < d_end ? a.desc[i] : 0ull;
+    const uint64_t i = (uint64_t)chunk * B + tid;
+    const uint64_t d = i < bin_descs(l.fb, l.bin_off, b) ? bin_first(l.fb, a.desc, l.bin_off, b)[i] : 0ull;
     const uint32_t n = (uint32_t)(d & 0xFFFFFFu);
     uint32_t total;
     const uint32_t pre = block_excl_scan((n + L - 1) / L, wsum, total);
@@ -1094,9 +1104,10 @@ __global__ void __launch_bounds__(B, 4) k_lds_persistent(CountArgs a, LdsArgs l)
     static_assert(kLdsHist * 4 + 24 <= kProbeHistAt && kProbeHistAt + 4 * kProbeHist <= kLdsReserved - 4,
                   "queue scalars and probe counts exceed the reserved LDS");
     const uint32_t tid = threadIdx.x;
+    const uint32_t ns = *l.n_seg;
+    if (ns == 0) return;   // nothing to count (a fallback launch without work)
     hist_begin<B>(l, s);
     uint32_t wmax = 0;
-    const uint32_t ns = *l.n_seg;
     const uint32_t NQ = l.n_queues;
     const uint32_t L = l.lag;
     if (tid < 64) {

@@ -1,0 +1,554 @@
+// The partition of the bins into sub-tables by sub-minimizers (pieces.h), in
+// four launches with no host synchronisation:
+//   plan     sub-tables per bin, work items (runs of descriptors of one bin);
+//   split    super-mers cut into pieces, k-mers and pieces per sub-table;
+//   scan     a contiguous run of pieces for every sub-table; the heavy ones
+//            (more k-mers or bases than a workgroup's LDS takes even in slices:
+//            strongly repeated sub-minimizers) are set apart for the fallback;
+//   scatter  every piece to its sub-table's run.
+// A bin whose pieces do not fit the list (which is sized for random
+// sub-minimizers) is left to the fallback as a whole, so every input is
+// counted exactly whatever its sub-minimizers look like.
+#include "pieces.h"
+#include "table.h"
+
+namespace gerbil {
+
+namespace {
+
+constexpr uint32_t kPlanB = 1024;
+constexpr uint32_t kSplitB = 256;
+constexpr uint32_t kScanB = 256;
+constexpr uint32_t kScatB = 512;
+constexpr uint32_t kItemDescs = 8192;      // descriptors per item at most (at least 256)
+constexpr uint32_t kItemGoal = 2048;       // items wanted
+constexpr uint32_t kItemSlack = 64;        // list slots of an item over its expected pieces
+constexpr uint32_t kScatSubs = 4096;       // sub-tables of a bin privatised in LDS by the scatter
+
+}  // namespace
+
+uint64_t piece_list_slots(uint64_t n_superm, uint64_t kmers, uint32_t piece_fx, uint32_t n0, bool cut, uint32_t n_bins) {
+    // a super-mer of n k-mers takes ceil(n / n0) lanes' turns: at most one more for every n0 k-mers
+    const uint64_t e = n_superm + ((kmers * piece_fx) >> 16) + (cut ? kmers / n0 : 0);
+    return e + e / 16 + (uint64_t)kItemSlack * piece_items_cap(n_superm, n_bins);
+}
+uint32_t piece_items_cap(uint64_t n_superm, uint32_t n_bins) {
+    return (uint32_t)(n_superm / kItemDescs + 2 * kItemGoal + n_bins + 8);
+}
+
+// Inclusive sums of one value per thread in part[kPlanB] (all threads call it).
+__device__ __forceinline__ void plan_scan(uint64_t* part, uint64_t v) {
+    const uint32_t tid = threadIdx.x;
+    part[tid] = v;
+    __syncthreads();
+    for (uint32_t off = 1; off < kPlanB; off <<= 1) {
+        const uint64_t y = tid >= off ? part[tid - off] : 0ull;
+        __syncthreads();
+        part[tid] += y;
+        __syncthreads();
+    }
+}
+
+// Workgroup 0 plans; the others clear what the later launches add to.
+__global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* zero_scalars, uint64_t* zero_hist) {
+    const uint32_t tid = threadIdx.x;
+    if (blockIdx.x > 0) {
+        const uint64_t g = (uint64_t)(blockIdx.x - 1) * kPlanB + tid, G = (uint64_t)(gridDim.x - 1) * kPlanB;
+        for (uint64_t i = g; i < q.sp_cap; i += G) {
+            q.sub_cnt[i] = 0;
+            q.sub_cur[i] = 0;
+        }
+        for (uint64_t i = g; i < kHistInternal; i += G) zero_hist[i] = 0;
+        return;
+    }
+    __shared__ uint64_t part[kPlanB];
+    if (tid < 8) zero_scalars[tid] = 0;
+    if (tid < kScalCount) q.scal[tid] = 0;
+    const uint32_t n = q.n_bins, per = (n + kPlanB - 1) / kPlanB;
+    const bool overfull = *q.n_superm > q.superm_cap;   // descriptors past the capacity were never stored
+    const uint64_t S = overfull ? 0 : q.bin_off[n];
+    uint32_t descs = (uint32_t)((S / kItemGoal + 63) & ~63ull);
+    descs = descs < 256 ? 256 : descs > kItemDescs ? kItemDescs : descs;
+    auto subs = [&](uint32_t b) -> uint32_t {
+        const uint64_t ns = q.bin_off[b + 1] - q.bin_off[b], K = q.bin_kmers[b];
+        if (overfull || ns == 0) return 0;
+        const uint64_t E = ns + ((K * q.piece_fx) >> 16);
+        uint64_t P = (K + q.target - 1) / q.target;
+        const uint64_t Pw = (piece_halves(K, E, q.k) + q.half_target - 1) / q.half_target;
+        if (Pw > P) P = Pw;
+        if (P > kExactSubs) {
+            uint64_t p2 = kExactSubs;
+            while (p2 < P && p2 < kMaxSubs) p2 *= 2;
+            P = p2;
+        }
+        return (uint32_t)(P ? P : 1);
+    };
+    uint64_t sp = 0, it = 0;
+    for (uint32_t e = 0; e < per; e++) {
+        const uint32_t b = tid * per + e;
+        if (b >= n) break;
+        sp += subs(b);
+        it += overfull ? 0 : (q.bin_off[b + 1] - q.bin_off[b] + descs - 1) / descs;
+    }
+    plan_scan(part, it);
+    uint64_t it0 = part[tid] - it;
+    const uint64_t n_items = part[kPlanB - 1];
+    __syncthreads();
+    plan_scan(part, sp);
+    uint64_t sp0 = part[tid] - sp;
+    const uint64_t n_sp = part[kPlanB - 1];
+    // sub-tables and items that do not fit their arrays (sized for any bins of
+    // this many bases, so only for parameters far from the default): nothing
+    // is split, and the fallback counts every bin
+    const bool none = n_sp > q.sp_cap || n_items > q.items_cap;
+    for (uint32_t e = 0; e < per; e++) {
+        const uint32_t b = tid * per + e;
+        if (b >= n) break;
+        const uint32_t P = none ? 0u : subs(b);
+        q.nsub[b] = P;
+        q.spbase[b] = none ? 0u : (uint32_t)sp0;
+        q.item_first[b] = none ? 0u : (uint32_t)it0;
+        q.bin_fail[b] = none ? 1u : 0u;
+        sp0 += P;
+        it0 += overfull ? 0 : (q.bin_off[b + 1] - q.bin_off[b] + descs - 1) / descs;
+    }
+    if (tid == 0) {
+        q.spbase[n] = none ? 0u : (uint32_t)n_sp;
+        q.item_first[n] = none ? 0u : (uint32_t)n_items;
+        q.scal[kScalSubs] = none ? 0 : n_sp;
+        q.scal[kScalItems] = none ? 0 : n_items;
+        q.scal[kScalDescs] = descs;
+        if (overfull) set_status(q.status, ST_SUPERM_CAP);
+    }
+}
+
+// Bin of item `it`: last b with first[b] <= it (bins without items share their successor's start).
+__device__ __forceinline__ uint32_t item_bin(const uint32_t* first, uint32_t n, uint32_t it) {
+    uint32_t lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (first[mid] <= it) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// (hi:lo) >> s, low word, 0 <= s < 32.
+__device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t s) {
+    return __builtin_amdgcn_alignbit(hi, lo, s);
+}
+// The 16 bases of x in reverse order, complemented.
+__device__ __forceinline__ uint32_t revcomp16(uint32_t x) {
+    x = __builtin_bitreverse32(~x);
+    return ((x >> 1) & 0x55555555u) | ((x & 0x55555555u) << 1);
+}
+
+// The packed stream from base x0 on, 16 bases at a time (first base in the top
+// bits). The next word is requested one call ahead.
+struct Bases16 {
+    const uint32_t* P;
+    int64_t q, last;   // next half word to request; the last one that exists
+    uint32_t a, b, s;
+    __device__ __forceinline__ void open(const uint64_t* packed, int64_t x0, uint64_t n_bytes) {
+        // from the half word of base x0 - 1, so that the funnel shift is never by 32
+        P = (const uint32_t*)packed;
+        last = 2 * (int64_t)((n_bytes + 31) >> 5) + 3;   // two zero words follow the stream
+        q = (x0 - 1) >> 4;
+        s = 30u - 2u * (uint32_t)((x0 - 1) & 15);
+        a = get();
+        b = get();
+    }
+    __device__ __forceinline__ uint32_t get() {
+        const int64_t i = q < last ? q : last;
+        q++;
+        return P[i ^ 1];   // a word's first 16 bases are its high half
+    }
+    __device__ __forceinline__ uint32_t next() {
+        const uint32_t x = funnel(a, b, s);
+        a = b;
+        b = get();
+        return x;
+    }
+};
+
+// Super-mers to pieces. A lane takes up to n0 consecutive windows of one
+// super-mer and then the next free descriptor of the item, so lanes stay
+// busy whatever the lengths. The n + w2 - 1 middle m2-mers of n windows (n <= w2) fall in three parts: the first n - 1 (window i holds those
+// from i on: suffix minima), the w2 - n + 1 that every window holds, and the
+// last n - 1 (window i holds the first i: prefix minima). All lanes of a wave
+// run the steps of its longest lane, so every branch is uniform. Sixteen
+// m2-mers at a time are cut out of two words each of the forward and the
+// reverse-complement strand by constant shifts: about six instructions an
+// m2-mer. The suffix minima wait in LDS, one column per lane (no conflicts);
+// they are kept per block of 16 with the minima of the later blocks in rows
+// of their own.
+template <bool kFull>
+__global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
+    extern __shared__ uint32_t S[];                 // [n0 + 4][kSplitB]; then the sub-table counts
+    __shared__ uint64_t red[kSplitB / 64];
+    __shared__ uint64_t s_start;
+    __shared__ uint32_t s_item, s_n, s_cap, s_next;
+    const uint32_t tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
+    const uint32_t k = q.k, m2 = kFull ? 16u : q.m2, w2 = q.w2, n0 = q.n0;
+    const uint32_t lead = (k - m2 + 1 - w2) / 2;   // m2-mers before the middle ones
+    const uint32_t n_items = (uint32_t)q.scal[kScalItems], descs = (uint32_t)q.scal[kScalDescs];
+    const uint32_t cmask = 0xFFFFFFFFu << (32 - 2 * m2);   // codes are held left-aligned
+    const uint32_t hist_cap = q.split_lds / 8;
+    uint64_t* hist = (uint64_t*)S;
+    uint32_t* col = S + tid;
+    uint32_t* block = S + n0 * kSplitB + tid;       // minima of the first part's blocks of 16
+    for (;;) {
+        if (tid == 0) {
+            s_item = (uint32_t)add_dev(&q.scal[kScalItem], 1ull);
+            s_n = 0;
+            s_next = 0;
+        }
+        __syncthreads();
+        const uint32_t item = s_item;
+        if (item >= n_items) break;
+        const uint64_t t0 = q.stage_clocks ? wall_clock64() : 0;
+        const uint32_t b = item_bin(q.item_first, q.n_bins, item);
+        const uint64_t d0 = q.bin_off[b] + (uint64_t)(item - q.item_first[b]) * descs;
+        const uint64_t d1 = d0 + descs < q.bin_off[b + 1] ? d0 + descs : q.bin_off[b + 1];
+        const uint32_t cnt = (uint32_t)(d1 - d0);
+        // list slots for the pieces to expect
+        uint64_t est = 0;
+        for (uint32_t j = tid; j < cnt; j += kSplitB) {
+            const uint32_t n = (uint32_t)(q.desc[d0 + j] & 0xFFFFFFull);
+            est += (uint64_t)((n + n0 - 1) / n0) * 65536ull + (uint64_t)n * q.piece_fx;
+        }
+        for (int off = 32; off > 0; off >>= 1) est += __shfl_xor(est, off);
+        if (lane == 0) red[wave] = est;
+        __syncthreads();
+        if (tid == 0) {
+            uint64_t e = 0;
+            for (uint32_t i = 0; i < kSplitB / 64; i++) e += red[i];
+            e >>= 16;
+            e += e / 16 + kItemSlack;
+            const uint64_t at = add_dev(&q.scal[kScalList], e);
+            s_start = at;
+            s_cap = at + e <= q.cap && e < 0x7FFFFFFFull ? (uint32_t)e : 0u;
+        }
+        __syncthreads();
+        const uint32_t cap = s_cap;
+        uint64_t* out = q.list + s_start;
+        uint64_t x0 = 0;
+        uint32_t n = 0;   // windows of this lane's super-mer still to do, from base x0
+        while (cap) {
+            const uint64_t idle = __ballot(n == 0);
+            if (idle) {
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&s_next, (uint32_t)__popcll(idle));
+                at = __shfl(at, 0) + (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
+                if (n == 0 && at < cnt) {
+                    const uint64_t d = q.desc[d0 + at];
+                    x0 = d >> 24;
+                    n = (uint32_t)(d & 0xFFFFFFull);
+                    if (n && x0 + n - 1 + k > q.n_bytes) {   // a corrupt descriptor must not read out of range
+                        set_status(q.status, ST_SPIN);
+                        n = 0;
+                    }
+                }
+                if (__ballot(n > 0) == 0ull) {
+                    if (__shfl(at, 0) >= cnt) break;   // (lane 0 was idle: it asked first)
+                    continue;
+                }
+            }
+            const uint32_t ns = n < n0 ? n : n0;
+            uint32_t nm = ns;
+            for (int off = 32; off > 0; off >>= 1) {
+                const uint32_t y = __shfl_xor(nm, off);
+                nm = y > nm ? y : nm;
+            }
+            nm = __builtin_amdgcn_readfirstlane(nm);
+            Bases16 fs, rs;
+            fs.open(q.packed, (int64_t)(x0 + lead), q.n_bytes);
+            uint32_t A = fs.next(), R;
+            if (kFull) {
+                R = revcomp16(A);
+            } else {
+                rs.open(q.packed, (int64_t)(x0 + lead + m2) - 16, q.n_bytes);
+                R = revcomp16(rs.next());
+            }
+            col[(nm - 1) * kSplitB] = 0xFFFFFFFFu;   // the last window holds none of the first part
+            uint32_t mid = 0xFFFFFFFFu, pre = 0xFFFFFFFFu, carry = 0, prev = 0;
+            uint64_t cuts = 1;
+            bool begun = false;   // uniform: the first part and the shared one are done
+            for (uint32_t p0 = 0; p0 < nm + w2 - 1; p0 += 16) {
+                const uint32_t An = fs.next();
+                const uint32_t Rn = revcomp16(kFull ? An : rs.next());
+                uint32_t h[16];
+#pragma unroll
+                for (uint32_t j = 0; j < 16; j++) {
+                    uint32_t fw = j ? funnel(A, An, 32u - 2u * j) : A;
+                    uint32_t rc = j ? funnel(Rn, R, 2u * j) : R;
+                    if (!kFull) {
+                        fw &= cmask;
+                        rc &= cmask;
+                    }
+                    const uint32_t c = fw < rc ? fw : rc;
+                    h[j] = __umul24(c, 0x9E3779u) + (c ^ 0x5bd1e995u);
+                }
+                A = An;
+                R = Rn;
+                const uint32_t f = p0 + 1 >= nm ? 0u : nm - 1 - p0 < 16 ? nm - 1 - p0 : 16u;   // positions of the first part
+                const uint32_t t = p0 >= w2 ? 0u : w2 - p0 < 16 ? w2 - p0 : 16u;               // first of the last part
+                if (f) {
+                    uint32_t run = 0xFFFFFFFFu;
+#pragma unroll
+                    for (int j = 15; j >= 0; j--) {
+                        if ((uint32_t)j < f) {
+                            run = min(run, h[j]);
+                            col[(p0 + j) * kSplitB] = run;
+                        }
+                    }
+                    block[(p0 >> 4) * kSplitB] = run;
+                }
+                if (f == 0 && t == 16) {
+#pragma unroll
+                    for (uint32_t j = 0; j < 16; j++) mid = min(mid, h[j]);
+                } else {
+#pragma unroll
+                    for (uint32_t j = 0; j < 16; j++)
+                        if (j >= f && j < t) mid = min(mid, h[j]);
+                }
+                if (t == 16) continue;
+                if (!begun) {
+                    begun = true;
+                    // minima of everything after a block of the first part, the shared part included
+                    uint32_t run = mid;
+                    for (int c = (int)((nm - 1) >> 4); c >= 0; c--) {
+                        const uint32_t m = (uint32_t)c * 16 < nm - 1 ? block[c * kSplitB] : 0xFFFFFFFFu;
+                        block[c * kSplitB] = run;
+                        run = min(run, m);
+                    }
+                    prev = run;
+                    col[0] = run;   // window 0
+                    carry = block[0];
+                }
+                uint32_t bits = 0;
+#pragma unroll
+                for (uint32_t j = 0; j < 16; j++) {
+                    const uint32_t i = p0 + j + 1 - w2;   // (wraps below the last part)
+                    if (j >= t && i < nm) {
+                        if ((i & 15u) == 0) carry = block[(i >> 4) * kSplitB];
+                        pre = min(pre, h[j]);
+                        const uint32_t v = min(min(pre, carry), col[i * kSplitB]);
+                        col[i * kSplitB] = v;
+                        bits |= v != prev ? 1u << j : 0u;
+                        prev = v;
+                    }
+                }
+                const int32_t i0 = (int32_t)(p0 + 1) - (int32_t)w2;
+                cuts |= i0 >= 0 ? (uint64_t)bits << i0 : (uint64_t)(bits >> -i0);
+            }
+            if (!begun) col[0] = mid;   // one window only
+            // the lane's pieces
+            cuts = ns ? cuts & (~0ull >> (64 - ns)) : 0ull;
+            const uint32_t np = (uint32_t)__popcll(cuts);
+            uint32_t incl = np;
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t y = __shfl_up(incl, off);
+                if (lane >= (uint32_t)off) incl += y;
+            }
+            uint32_t at = 0;
+            if (lane == 63) at = atomicAdd(&s_n, incl);
+            at = __shfl(at, 63) + incl - np;
+            while (__ballot(cuts != 0ull) != 0ull) {
+                if (cuts) {
+                    const uint32_t i = (uint32_t)__builtin_ctzll(cuts);
+                    cuts &= cuts - 1;
+                    const uint32_t e = cuts ? (uint32_t)__builtin_ctzll(cuts) : ns;
+                    const uint32_t v = col[i * kSplitB];
+                    const uint32_t hh = ((v ^ (v >> 15)) * 0x85EBCA6Bu) >> (32 - kSubHashBits);
+                    if (at < cap) out[at] = ((x0 + i) << 24) | ((uint64_t)hh << 6) | (e - i - 1);
+                    at++;
+                }
+            }
+            x0 += ns;
+            n -= ns;
+        }
+        __syncthreads();
+        const uint32_t total = s_n;
+        const bool fits = cap && total <= cap;
+        if (tid == 0) {
+            q.item_start[item] = s_start;
+            q.item_n[item] = fits ? total : 0u;
+            if (!fits && cnt) __hip_atomic_store(&q.bin_fail[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const uint32_t P = q.nsub[b], sb = q.spbase[b];
+        if (fits && P <= hist_cap) {
+            for (uint32_t i = tid; i < P; i += kSplitB) hist[i] = 0;
+            __syncthreads();
+            for (uint32_t e = tid; e < total; e += kSplitB) {
+                const uint64_t p = out[e];
+                atomicAdd((unsigned long long*)&hist[sub_of_hash(piece_hash(p), P)],
+                          (1ull << 32) | (unsigned long long)piece_kmers(p));
+            }
+            __syncthreads();
+            for (uint32_t i = tid; i < P; i += kSplitB)
+                if (hist[i]) add_dev(&q.sub_cnt[sb + i], hist[i]);
+        } else if (fits) {
+            for (uint32_t e = tid; e < total; e += kSplitB) {
+                const uint64_t p = out[e];
+                add_dev(&q.sub_cnt[sb + sub_of_hash(piece_hash(p), P)], (1ull << 32) | (uint64_t)piece_kmers(p));
+            }
+        }
+        __syncthreads();
+        if (q.stage_clocks && tid == 0) {
+            add_dev(&q.stage_clocks[0], wall_clock64() - t0);
+            add_dev(&q.stage_clocks[4], 1ull);
+        }
+    }
+}
+
+// One workgroup per bin: runs of the light sub-tables from the bottom of
+// pieces, of the heavy ones from its top, and the bin's fallback descriptors.
+__global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
+    __shared__ uint32_t wsum[32];
+    __shared__ uint64_t s_light, s_heavy, s_hk;
+    const uint32_t tid = threadIdx.x, b = blockIdx.x;
+    const uint64_t t0 = q.stage_clocks ? wall_clock64() : 0;
+    const uint32_t P = q.nsub[b], sb = q.spbase[b];
+    const bool fail = q.bin_fail[b] != 0;
+    auto heavy = [&](uint64_t c) -> bool {
+        const uint32_t km = (uint32_t)c, np = (uint32_t)(c >> 32);
+        return km > q.heavy_kmers || piece_halves(km, np, q.k) > q.max_halves;
+    };
+    if (fail) {
+        for (uint32_t i = tid; i < P; i += kScanB) q.sub_cnt[sb + i] = 0;
+        if (tid == 0) {
+            const uint64_t d0 = q.bin_off[b], nd = q.bin_off[b + 1] - d0;
+            q.fb_ptr[b] = (uint64_t)(q.desc + d0);
+            q.fb_n[b] = nd;
+            q.fb_kmers[b] = q.bin_kmers[b];
+            if (nd) add_dev(&q.scal[kScalFallback], 1ull);
+        }
+        return;
+    }
+    if (tid == 0) s_hk = 0;
+    const uint32_t per = (P + kScanB - 1) / kScanB;
+    const uint32_t i0 = tid * per, i1 = i0 + per < P ? i0 + per : P;
+    uint32_t nl = 0, nh = 0;
+    uint64_t hk = 0;
+    for (uint32_t i = i0; i < i1; i++) {
+        const uint64_t c = q.sub_cnt[sb + i];
+        if (heavy(c)) {
+            nh += (uint32_t)(c >> 32);
+            hk += (uint32_t)c;
+        } else {
+            nl += (uint32_t)(c >> 32);
+        }
+    }
+    uint32_t tl, th;
+    const uint32_t pl = block_excl_scan(nl, wsum, tl), ph = block_excl_scan(nh, wsum, th);
+    if (hk) atomicAdd((unsigned long long*)&s_hk, (unsigned long long)hk);
+    if (tid == 0) {
+        s_light = tl ? add_dev(&q.scal[kScalLight], (uint64_t)tl) : 0ull;
+        s_heavy = th ? q.cap - add_dev(&q.scal[kScalHeavy], (uint64_t)th) - th : 0ull;
+    }
+    __syncthreads();
+    uint64_t rl = s_light + pl, rh = s_heavy + ph;
+    for (uint32_t i = i0; i < i1; i++) {
+        const uint64_t c = q.sub_cnt[sb + i];
+        const uint32_t np = (uint32_t)(c >> 32);
+        if (heavy(c)) {
+            q.sub_off[sb + i] = rh | (1ull << 63);
+            q.sub_cnt[sb + i] = 0;   // nothing for the table kernel
+            rh += np;
+        } else {
+            q.sub_off[sb + i] = rl;
+            rl += np;
+        }
+    }
+    if (tid == 0) {
+        q.fb_ptr[b] = (uint64_t)(q.pieces + s_heavy);
+        q.fb_n[b] = th;
+        q.fb_kmers[b] = s_hk;
+        if (th) add_dev(&q.scal[kScalFallback], 1ull);
+        if (q.stage_clocks) {
+            add_dev(&q.stage_clocks[1], wall_clock64() - t0);
+            add_dev(&q.stage_clocks[5], 1ull);
+        }
+    }
+}
+
+// Every item's pieces to their sub-tables' runs: counted per sub-table in
+// LDS, one reservation per sub-table and item, then placed. Bound by the
+// scattered 8-byte stores (an item leaves about 11 pieces per sub-table).
+__global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
+    __shared__ uint64_t pos[kScatSubs];
+    __shared__ uint32_t cnt[kScatSubs];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t n_items = (uint32_t)q.scal[kScalItems];
+    for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+        const uint32_t b = item_bin(q.item_first, q.n_bins, item);
+        const uint32_t total = q.item_n[item];
+        if (total == 0 || q.bin_fail[b]) continue;
+        const uint64_t t0 = q.stage_clocks ? wall_clock64() : 0;
+        const uint64_t* in = q.list + q.item_start[item];
+        const uint32_t P = q.nsub[b], sb = q.spbase[b];
+        if (P <= kScatSubs) {
+            for (uint32_t i = tid; i < P; i += kScatB) cnt[i] = 0;
+            __syncthreads();
+            for (uint32_t e = tid; e < total; e += kScatB) atomicAdd(&cnt[sub_of_hash(piece_hash(in[e]), P)], 1u);
+            __syncthreads();
+            for (uint32_t i = tid; i < P; i += kScatB)
+                if (cnt[i]) pos[i] = q.sub_off[sb + i] + add_dev(&q.sub_cur[sb + i], cnt[i]);
+            __syncthreads();
+            for (uint32_t e = tid; e < total; e += kScatB) {
+                const uint64_t p = in[e];
+                uint64_t at = atomicAdd((unsigned long long*)&pos[sub_of_hash(piece_hash(p), P)], 1ull);
+                const bool heavy = at >> 63;
+                at &= ~0ull >> 1;
+                if (at < q.cap) q.pieces[at] = heavy ? (piece_start(p) << 24) | piece_kmers(p) : p;
+            }
+            __syncthreads();
+        } else {
+            for (uint32_t e = tid; e < total; e += kScatB) {
+                const uint64_t p = in[e];
+                const uint32_t j = sb + sub_of_hash(piece_hash(p), P);
+                const uint64_t o = q.sub_off[j], at = (o & (~0ull >> 1)) + add_dev(&q.sub_cur[j], 1u);
+                if (at < q.cap) q.pieces[at] = (o >> 63) ? (piece_start(p) << 24) | piece_kmers(p) : p;
+            }
+        }
+        if (q.stage_clocks && tid == 0) {
+            add_dev(&q.stage_clocks[2], wall_clock64() - t0);
+            add_dev(&q.stage_clocks[6], 1ull);
+        }
+    }
+}
+
+hipError_t launch_piece_plan(const PieceArgs& q, uint64_t* zero_scalars, uint64_t* zero_hist, hipStream_t s) {
+    const uint64_t blocks = ((uint64_t)q.sp_cap + kPlanB - 1) / kPlanB;
+    const uint32_t g = 1 + (uint32_t)(blocks < 64 ? 64 : blocks > 512 ? 512 : blocks);
+    hipLaunchKernelGGL(k_piece_plan, dim3(g), dim3(kPlanB), 0, s, q, zero_scalars, zero_hist);
+    return hipGetLastError();
+}
+
+uint32_t split_lds_bytes(uint32_t n0) {
+    const uint32_t rows = (n0 + 4) * kSplitB * 4;
+    return rows < 16384u ? 16384u : rows;   // (also the counts of up to bytes / 8 sub-tables)
+}
+
+hipError_t launch_split(const PieceArgs& q, uint32_t cus, hipStream_t s) {
+    const void* f = q.m2 == 16 ? (const void*)k_split<true> : (const void*)k_split<false>;
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)q.split_lds);
+    if (e != hipSuccess) return e;
+    uint32_t per_cu = 160u * 1024u / (q.split_lds + 128u);   // items are popped: more workgroups than fit would only wait
+    per_cu = per_cu < 1 ? 1 : per_cu > 6 ? 6 : per_cu;
+    if (q.m2 == 16) hipLaunchKernelGGL(k_split<true>, dim3(cus * per_cu), dim3(kSplitB), q.split_lds, s, q);
+    else hipLaunchKernelGGL(k_split<false>, dim3(cus * per_cu), dim3(kSplitB), q.split_lds, s, q);
+    return hipGetLastError();
+}
+
+hipError_t launch_sub_scan(const PieceArgs& q, hipStream_t s) {
+    hipLaunchKernelGGL(k_sub_scan, dim3(q.n_bins), dim3(kScanB), 0, s, q);
+    return hipGetLastError();
+}
+
+hipError_t launch_piece_scatter(const PieceArgs& q, uint32_t cus, hipStream_t s) {
+    hipLaunchKernelGGL(k_piece_scatter, dim3(cus * 3), dim3(kScatB), 0, s, q);
+    return hipGetLastError();
+}
+
+}  // namespace gerbil

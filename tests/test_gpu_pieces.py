@@ -1,0 +1,117 @@
+"""The piece partition of the batched counter (bins cut by a second minimizer
+into LDS sub-tables) at the key lengths where its layout changes, and on reads
+that leave its ordinary path: sub-tables counted in hash slices, strongly
+repeated sub-minimizers and piece lists that are too small, both of which the
+fallback counts. Exact counts have no tolerance: pairs and histogram equal the
+oracle's, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import random_reads, reads_to_csr, to_device
+from paper_1607_06618_amd import gerbil as g
+
+pytestmark = pytest.mark.gpu
+
+B = g.GERBIL_BATCHED
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    g.load()
+
+
+def same(res, a, o, k, t, canonical=True):
+    ref = oracle.count(a, o, k, threshold=t, canonical=canonical)
+    keys, counts = res.sorted()
+    assert res.report.n_valid == ref.n_valid
+    assert np.array_equal(keys, ref.keys) and np.array_equal(counts, ref.counts)
+    assert np.array_equal(res.hist, ref.folded_hist(res.hist.size))
+
+
+def bases(rng, n):
+    return "".join(np.array(list("ACGT"))[rng.integers(0, 4, n)].tolist())
+
+
+def flip(r):
+    return r[::-1].translate(str.maketrans("ACGT", "TGCA"))
+
+
+def genome_reads(rng, k, glen=6000, n=300, extra=200):
+    gen = bases(rng, glen)
+    out = []
+    for _ in range(n):
+        L = int(rng.integers(max(1, k - 3), k + extra))
+        s = int(rng.integers(0, glen - L))
+        r = gen[s:s + L]
+        out.append(flip(r) if rng.random() < 0.5 else r)
+    return out + random_reads(rng, 20, 0, k + 60)
+
+
+# shortest keys; m2 from k/2 to 16; every remainder of the 16-base words; the
+# window of middle m2-mers full (k <= 111), then 97 and 96 of them; the longest keys
+@pytest.mark.parametrize("canonical", [True, False])
+@pytest.mark.parametrize("k", [20, 21, 31, 32, 33, 47, 48, 49, 63, 64, 65, 80, 81, 110, 111, 112, 113, 159, 160, 161,
+                               255, 256, 257, 272, 400, 479, 480])
+def test_key_lengths(k, canonical):
+    rng = np.random.default_rng(900 + 2 * k + canonical)
+    a, o = reads_to_csr(genome_reads(rng, k))
+    res = g.count_kmers(a, o, k, 9, 13, 1, 64, mode=B, canonical=canonical)
+    same(res, a, o, k, 1, canonical)
+
+
+@pytest.mark.parametrize("block", [512, 1024])
+@pytest.mark.parametrize("k,copies", [(31, 40), (65, 30), (65, 120), (65, 900), (200, 60), (200, 700), (300, 500)])
+def test_repeated_sub_minimizers(k, copies, block):
+    """Reads over one short sequence: few sub-minimizers carry everything, so
+    sub-tables are counted whole, in hash slices, or by the fallback."""
+    rng = np.random.default_rng(k + copies)
+    core = bases(rng, k + 160)
+    reads = []
+    for i in range(copies):
+        r = bases(rng, int(rng.integers(0, 30))) + core + bases(rng, int(rng.integers(0, 30)))
+        reads.append(flip(r) if i & 1 else r)
+    a, o = reads_to_csr(reads + genome_reads(rng, k, n=60))
+    res = g.count_kmers(a, o, k, 9, 4, 1, 2048, mode=B, block=block)
+    same(res, a, o, k, 1)
+
+
+def test_one_window_reads():
+    """Every piece is a single k-mer (reads of k and k + 1 bases)."""
+    k = 99
+    rng = np.random.default_rng(4)
+    gen = bases(rng, 5000)
+    a, o = reads_to_csr([gen[s:s + k + (s & 1)] for s in rng.integers(0, 4800, 6000).tolist()])
+    same(g.count_kmers(a, o, k, 9, 8, 1, 128, mode=B), a, o, k, 1)
+
+
+@pytest.mark.parametrize("share", [0.35, 0.7])
+def test_list_too_small_for_the_pieces(share):
+    """A workspace below the one asked for: bins whose pieces do not fit are
+    left whole to the fallback, and results stay exact."""
+    import torch
+    k = 55
+    rng = np.random.default_rng(8)
+    a, o = reads_to_csr(genome_reads(rng, k, glen=60000, n=6000))
+    ad, od = to_device(a, o)
+    p = g.make_params(k, 9, 32, 1, mode=B, pool=1, overflow_cap=1 << 12)
+    job = g.Job(ad, od, a.size, p, hist_len=128)
+    job.encode()
+    job.bin()
+    job.prepare_count()
+    need = job.ws_count.numel()
+    fixed = 0   # what a workspace holds besides the pieces: the smallest one that is accepted, to 64 KB
+    lo, hi = 0, need
+    while hi - lo > 65536:
+        mid = (lo + hi) // 2
+        st = g.gerbil_count(job.bins, p, job.ws_count.data_ptr(), mid, job.keys_d.data_ptr(), job.counts_d.data_ptr(),
+                            job.cap, job.state, g._stream_handle(None))
+        lo, hi = (mid, hi) if st == g.GERBIL_EINVAL else (lo, mid)
+    torch.cuda.synchronize()
+    fixed = hi
+    job.ws_count = job.ws_count[: fixed + int(share * (need - fixed)) // 256 * 256]
+    job.count()
+    same(job.result(), a, o, k, 1)
