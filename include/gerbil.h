@@ -101,16 +101,17 @@ typedef struct {
     uint32_t table;          /* GERBIL_TABLE_*                                                   */
     float load_factor;       /* k-mers per table slot when tables are sized: HBM tables (0, 0.95]
                                 (k-mers bound the distinct keys), default 0.5; LDS sub-tables
-                                (0, 4], default 0.68 (BATCHED, k >= 20) or 0.8 (occurrences
+                                (0, 4], default 0.7 (BATCHED, k >= 20) or 0.8 (occurrences
                                 repeat, so more than one per slot can fit; distinct keys beyond
-                                the slots take the emergency area)                                                             */
+                                the slots take the emergency area)                               */
     uint32_t max_probes;     /* theta of Alg. 1: trials before the emergency path; 0 = default
-                                (8 buckets of 8 slots in HBM tables, 64 slots in LDS tables)     */
+                                (8 buckets of 8 slots in HBM tables; LDS tables 32 buckets of two
+                                slots (BATCHED, k >= 20) or 64 slots)                            */
     uint32_t block;          /* threads per workgroup for counting, 64..1024 in steps of 64. HBM
-                                tables: 0 = 256. LDS tables, BATCHED, k >= 20: 1024 runs one
-                                1024-thread workgroup per CU with 160 KB of LDS, any other value
-                                two of 512 with 80 KB each (half-size tables whose stages overlap
-                                on the CU); k < 20: 512 runs two workgroups, any other value one.
+                                tables: 0 = 256. LDS tables, BATCHED: 512 (and k > 256, always)
+                                runs two workgroups of 512 threads per CU with 80 KB of LDS each
+                                (half-size tables whose stages overlap on the CU), any other
+                                value one of 1024 with 160 KB.
                                 LDS tables, PLAIN: always 1024                                    */
     uint32_t pool;           /* BATCHED: hash tables resident at once. LDS tables: key slots (ranks
                                 scattered by key hash and not yet counted), best a multiple of 8

@@ -325,13 +325,19 @@ uint64_t lds_fixed(const LdsSizing& z, void* ws, uint64_t start, LdsLayout* L) {
 // LDS tables are allowed, keys of any length included: its tables refer to
 // the bases instead of holding keys. Keys below kPieceMinK stay with the
 // key partition (LDS path).
-constexpr double kPieceFill = 0.68;  // k-mers per slot: a sub-table holds some ten sub-minimizers' k-mers, so
-                                     // its size spreads by about a third around this
+// K-mers per slot; sub-tables are cut to within a group's size of it. 0.6
+// costs 3 to 5 % (more sub-tables, each with its scan and dump); 0.8 gains
+// 1 % at k = 65 and 99 and loses 3 % at k = 28 (longer probes): 25.0 / 25.1 /
+// 26.4 ms for 0.8 / 0.7 / 0.6 at k = 65, 9.1 / 8.8 / 9.2 at k = 28.
+constexpr double kPieceFill = 0.7;
+// Sub-tables wanted at least: four per CU, so that their workgroups end about
+// together. Small inputs get smaller ones for it.
+constexpr uint32_t kTablesGoal = 1024;
 
 struct PieceSizing {
     uint32_t block, C, target, half_target, max_kmers, slice_kmers, heavy_kmers, max_halves;
-    uint32_t m2, n0, split_lds, piece_fx, group_log2, items_cap;
-    uint64_t sp_cap;
+    uint32_t m2, n0, split_lds, piece_fx, items_cap;
+    uint64_t grp_cap, tab_cap;
 };
 
 bool use_pieces(const gerbil_params* p, uint64_t n_bytes) {
@@ -340,30 +346,37 @@ bool use_pieces(const gerbil_params* p, uint64_t n_bytes) {
 
 PieceSizing piece_sizing(const gerbil_params* p, const gerbil_bins* bins) {
     PieceSizing z;
-    z.block = p->block == 1024 ? 1024u : 512u;
+    // One workgroup of 1024 threads per CU or two of 512: the single large
+    // table wastes less on the spread of group sizes and on dumps (count step
+    // of 107 M 65-mers 24.5 ms against 27.6 ms; 28-mers 8.9 / 9.7, 200-mers
+    // 8.5 / 9.1). Beyond k = 256 a thread of 1024 has too few registers for the
+    // key's two strands.
+    z.block = p->block == 512 || p->k > 256 ? 512u : 1024u;
     z.m2 = sub_minimizer_len(p->k);
     const uint32_t w2 = sub_window(p->k, z.m2), w = p->k - p->m + 1;
     // The LDS left by the fixed parts holds the staged bases and the slots. A
     // piece has about 0.8 / (2 / (w2 + 1) + 2 / (w + 1)) k-mers (cuts of either
-    // minimizer, and read ends); its bases get room for 2.2 times the mean
-    // sub-table (what does not fit goes to the fallback, and a fallback of HBM
-    // tables is slow enough for a wider margin), the slots 1 / kPieceFill.
+    // minimizer, and read ends). The bases get half as much again as that, so
+    // that the k-mers are what fills a sub-table, and 1.3 times their target
+    // fits: a sub-table is cut to within a group's size.
     const double per_kmer = (2.0 / (w2 + 1) + 2.0 / (w + 1)) / 0.8;
     const double halves = std::min(p->k / 16.0 + 2.0, (1.0 + per_kmer * (p->k + 29)) / 16.0);
-    const double margin = words_for(p->k) <= GERBIL_MAX_LDS_W ? 2.2 : 3.5;
     const double pool = z.block == 1024 ? SubShape<1024>::pool : SubShape<512>::pool;
-    const double n = pool / (8.0 / kPieceFill + 4.0 * margin * halves);
-    z.max_halves = 2 * (uint32_t)(margin * halves * n / 2.0);
-    z.half_target = std::max<uint32_t>(1u, (uint32_t)(z.max_halves / margin));
-    z.C = ((uint32_t)pool - 4 * z.max_halves) / 8;
-    for (;; z.C--) {   // a prime, so that double hashing has a full period
+    const double n = pool / (8.0 / kPieceFill + 4.0 * 1.5 * halves);
+    z.max_halves = 4 * (uint32_t)(1.5 * halves * n / 4.0);
+    // whole rounds of the workgroup's threads over the slots; what that leaves goes to the bases
+    uint32_t nb = ((uint32_t)pool - 4 * z.max_halves) / (8 * z.block) * z.block / 2;
+    z.max_halves = ((uint32_t)pool - 16 * nb) / 16 * 4;
+    for (;; nb--) {   // a prime number of buckets, so that double hashing has a full period
         bool prime = true;
-        for (uint32_t d = 2; prime && d * d <= z.C; d++) prime = z.C % d != 0;
+        for (uint32_t d = 2; prime && d * d <= nb; d++) prime = nb % d != 0;
         if (prime) break;
     }
+    z.C = 2 * nb;
+    z.half_target = std::max<uint32_t>(1u, (uint32_t)(z.max_halves / 1.3));
     const double fill = p->load_factor > 0 ? p->load_factor : kPieceFill;
     z.target = std::min<uint32_t>(40000u, std::max<uint32_t>(64u, (uint32_t)(z.C * fill)));
-    z.max_kmers = std::max<uint32_t>((uint32_t)(0.95 * z.C), z.target + z.target / 4);
+    z.max_kmers = std::max<uint32_t>((uint32_t)(0.93 * z.C), z.target + z.target / 4);
     z.slice_kmers = std::max<uint32_t>((uint32_t)(0.75 * z.C), z.target);
     // counts are 16 bits wide; more than four tables' worth goes to the fallback
     z.heavy_kmers = std::min<uint32_t>(60000u, std::max<uint32_t>(4 * z.C, z.target + z.target / 2));
@@ -373,36 +386,40 @@ PieceSizing piece_sizing(const gerbil_params* p, const gerbil_bins* bins) {
     z.split_lds = split_lds_bytes(z.n0);
     // random sub-minimizers change every (w2 + 1) / 2 windows
     z.piece_fx = (uint32_t)(65536.0 * 2.15 / (w2 + 1));
-    uint32_t g = 0;
-    while ((1u << g) < (p->k + 24) / 16 && g < 6) g++;   // half words of an ordinary piece
-    z.group_log2 = g;
     z.items_cap = piece_items_cap(bins->cap_superm, p->n_bins);
     // any bins of n_bytes bases: every base a k-mer, cap_superm super-mers; the
     // number of a large bin's sub-tables is rounded up to a power of two
     const uint64_t E = bins->cap_superm + ((bins->n_bytes * z.piece_fx) >> 16);
-    z.sp_cap = 2 * (bins->n_bytes / z.target + piece_halves(bins->n_bytes, E, p->k) / z.half_target) +
-               2ull * p->n_bins + 2;
+    const uint64_t tabs = bins->n_bytes / z.target + piece_halves(bins->n_bytes, E, p->k) / z.half_target + kTablesGoal;
+    z.grp_cap = 2 * kGroupsPerTable * tabs + 2ull * p->n_bins;
+    z.tab_cap = 2 * tabs + 2ull * p->n_bins;
     return z;
 }
 
 struct PieceLayout {
-    uint32_t *nsub, *spbase, *item_first, *bin_fail, *item_n, *sub_cur;
-    uint64_t *scal, *item_start, *sub_cnt, *sub_off, *fb_ptr, *fb_n, *fb_kmers;
+    uint32_t *ngrp, *grp_first, *item_first, *bin_fail, *item_n, *grp_tab, *tab_first, *ntab, *tab_cur, *heavy_cur;
+    uint64_t *scal, *item_start, *grp_cnt, *tab_cnt, *tab_off, *heavy_off, *fb_ptr, *fb_n, *fb_kmers;
 };
 
 uint64_t piece_fixed(const PieceSizing& z, uint32_t n_bins, void* ws, uint64_t start, PieceLayout* L) {
     Carve c(ws ? (uint8_t*)ws + start : nullptr);
     PieceLayout l;
-    l.nsub = c.take<uint32_t>(n_bins);
-    l.spbase = c.take<uint32_t>(n_bins + 1);
+    l.ngrp = c.take<uint32_t>(n_bins);
+    l.grp_first = c.take<uint32_t>(n_bins + 1);
     l.item_first = c.take<uint32_t>(n_bins + 1);
     l.bin_fail = c.take<uint32_t>(n_bins);
     l.scal = c.take<uint64_t>(kScalCount);
     l.item_start = c.take<uint64_t>(z.items_cap);
     l.item_n = c.take<uint32_t>(z.items_cap);
-    l.sub_cnt = c.take<uint64_t>(z.sp_cap);
-    l.sub_off = c.take<uint64_t>(z.sp_cap);
-    l.sub_cur = c.take<uint32_t>(z.sp_cap);
+    l.grp_cnt = c.take<uint64_t>(z.grp_cap);
+    l.grp_tab = c.take<uint32_t>(z.grp_cap);
+    l.tab_first = c.take<uint32_t>(n_bins);
+    l.ntab = c.take<uint32_t>(n_bins);
+    l.tab_cnt = c.take<uint64_t>(z.tab_cap);
+    l.tab_off = c.take<uint64_t>(z.tab_cap);
+    l.tab_cur = c.take<uint32_t>(z.tab_cap);
+    l.heavy_off = c.take<uint64_t>(n_bins);
+    l.heavy_cur = c.take<uint32_t>(n_bins);
     l.fb_ptr = c.take<uint64_t>(n_bins);
     l.fb_n = c.take<uint64_t>(n_bins);
     l.fb_kmers = c.take<uint64_t>(n_bins);
@@ -697,20 +714,28 @@ int32_t count_pieces(const gerbil_bins* bins, const gerbil_params* p, void* ws, 
     q.heavy_kmers = z.heavy_kmers;
     q.max_halves = z.max_halves;
     q.piece_fx = z.piece_fx;
-    q.sp_cap = (uint32_t)std::min<uint64_t>(z.sp_cap, 0xFFFFFFFFull);
+    q.tables_goal = p->load_factor > 0 ? 1 : kTablesGoal;   // (a load that is asked for stands)
+    q.grp_cap = (uint32_t)std::min<uint64_t>(z.grp_cap, 0xFFFFFFFFull);
+    q.tab_cap = (uint32_t)std::min<uint64_t>(z.tab_cap, 0xFFFFFFFFull);
     q.items_cap = z.items_cap;
     q.cap = r.cap;
-    q.nsub = PL.nsub;
-    q.spbase = PL.spbase;
+    q.ngrp = PL.ngrp;
+    q.grp_first = PL.grp_first;
     q.item_first = PL.item_first;
     q.scal = PL.scal;
     q.bin_fail = PL.bin_fail;
     q.item_start = PL.item_start;
     q.item_n = PL.item_n;
     q.list = r.second;
-    q.sub_cnt = PL.sub_cnt;
-    q.sub_off = PL.sub_off;
-    q.sub_cur = PL.sub_cur;
+    q.grp_cnt = PL.grp_cnt;
+    q.grp_tab = PL.grp_tab;
+    q.tab_first = PL.tab_first;
+    q.ntab = PL.ntab;
+    q.tab_cnt = PL.tab_cnt;
+    q.tab_off = PL.tab_off;
+    q.tab_cur = PL.tab_cur;
+    q.heavy_off = PL.heavy_off;
+    q.heavy_cur = PL.heavy_cur;
     q.pieces = r.pieces;
     q.fb_ptr = PL.fb_ptr;
     q.fb_n = PL.fb_n;
@@ -719,15 +744,14 @@ int32_t count_pieces(const gerbil_bins* bins, const gerbil_params* p, void* ws, 
 
     SubArgs t;
     t.pieces = r.pieces;
-    t.sub_cnt = PL.sub_cnt;
-    t.sub_off = PL.sub_off;
-    t.n_sub = PL.scal + kScalSubs;
-    t.slots = z.C;
+    t.tab_cnt = PL.tab_cnt;
+    t.tab_off = PL.tab_off;
+    t.n_tab = PL.scal + kScalTables;
+    t.buckets = z.C / 2;
     t.halves = z.max_halves;
-    t.theta = p->max_probes ? p->max_probes : kDefaultLdsTheta;
+    t.theta = p->max_probes ? p->max_probes : kDefaultLdsTheta / 2;   // buckets of two slots
     t.max_kmers = z.max_kmers;
     t.slice_kmers = z.slice_kmers;
-    t.group_log2 = z.group_log2;
     t.probe_hist = p->probe_hist;
     t.stage_clocks = p->stage_clocks;
 

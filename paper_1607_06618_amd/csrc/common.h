@@ -201,6 +201,18 @@ __device__ __forceinline__ void set_status(uint32_t* status, uint32_t bits) {
     __hip_atomic_fetch_or(status, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Inclusive sum over the 64 lanes of a wave, in registers (row shifts and row
+// broadcasts of the data-parallel primitives; lanes without a source add 0).
+__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);   // row_bcast 15, 31
+    v += __builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
 // Wave-aggregated reservation of `want` (0 or 1 per lane) slots on a global
 // cursor: one atomic per wave; returns this lane's index.
 __device__ __forceinline__ uint64_t wave_reserve(uint64_t* cursor, bool want) {

@@ -3,11 +3,18 @@
 // All occurrences of a canonical k-mer lie in one bin (Sec. 2.1). The same
 // argument, repeated with a second and longer minimizer, splits a bin further:
 // the sub-minimizer of a k-mer is the smallest of its middle canonical m2-mers
-// under a hashed order, a piece is a run of consecutive k-mers of one super-mer with equal
-// sub-minimizers, and a piece goes to the sub-table its sub-minimizer hashes
-// to. A sub-table then holds every occurrence of its k-mers, and what is
-// written to memory and read back is 8 bytes per piece (about 13 k-mers at
-// k = 65) where a partition by the hash of the k-mer writes every key.
+// under a hashed order, a piece is a run of consecutive k-mers of one super-mer
+// with equal sub-minimizers, and a piece goes to the group its sub-minimizer
+// hashes to. A run of groups makes a sub-table, which holds every occurrence
+// of its k-mers; what is written to memory and read back is 8 bytes per piece
+// (about 11 k-mers at k = 65) where a partition by the hash of the k-mer
+// writes every key.
+//
+// A sub-minimizer brings all the k-mers of its place in the genome (some 400
+// at 30x), so sub-tables of a fixed number of hash values differ widely in
+// size. Groups are an eighth of a sub-table, and sub-tables are cut from their
+// running total: they come out within a few per cent of what the LDS table
+// takes.
 #pragma once
 #include "internal.h"
 
@@ -16,16 +23,17 @@ namespace gerbil {
 // A piece: first base (40 bits) | 18 hash bits of the sub-minimizer | k-mers - 1 (6 bits).
 constexpr uint32_t kPieceMax = 64;     // k-mers of a piece at most
 constexpr uint32_t kSubHashBits = 18;
-// Sub-tables of a bin: their number is bounded by the hash bits; above
-// kExactSubs it is a power of two, so that every sub-table owns the same
-// number of hash values.
-constexpr uint32_t kMaxSubs = 1u << kSubHashBits;
-constexpr uint32_t kExactSubs = 4096;
+// Groups of a bin: their number is bounded by the hash bits; above
+// kExactGroups it is a power of two, so that every group owns the same number
+// of hash values.
+constexpr uint32_t kMaxGroups = 1u << kSubHashBits;
+constexpr uint32_t kExactGroups = 4096;
+constexpr uint32_t kGroupsPerTable = 8;
 
 __host__ __device__ inline uint64_t piece_start(uint64_t p) { return p >> 24; }
 __host__ __device__ inline uint32_t piece_kmers(uint64_t p) { return (uint32_t)(p & 63u) + 1u; }
-__host__ __device__ inline uint32_t piece_hash(uint64_t p) { return (uint32_t)(p >> 6) & (kMaxSubs - 1u); }
-__host__ __device__ inline uint32_t sub_of_hash(uint32_t h, uint32_t P) {
+__host__ __device__ inline uint32_t piece_hash(uint64_t p) { return (uint32_t)(p >> 6) & (kMaxGroups - 1u); }
+__host__ __device__ inline uint32_t group_of_hash(uint32_t h, uint32_t P) {
     return (uint32_t)(((uint64_t)h * P) >> kSubHashBits);
 }
 
@@ -53,13 +61,13 @@ struct SubShape {
     static constexpr uint32_t bytes = 160u * B;
     static constexpr uint32_t hist_at = 0;                                  // u32 [kLdsHist]
     static constexpr uint32_t probe_at = 4 * kLdsHist;                      // u32 [kProbeHist]
-    static constexpr uint32_t scan_at = probe_at + 4 * kProbeHist;          // u32 [32] scan scratch
-    static constexpr uint32_t base_at = scan_at + 128;                      // u64 output base
-    static constexpr uint32_t cls_at = base_at + 16;                        // u32 [8] segments by length
+    static constexpr uint32_t sum_at = probe_at + 4 * kProbeHist;           // u32 [16] pairs of every wave
+    static constexpr uint32_t base_at = sum_at + 64;                        // u64 output base
+    static constexpr uint32_t cls_at = base_at + 16;                        // u32 [8] segments by length; [0]: half words and full segments
     static constexpr uint32_t seg_at = cls_at + 32;                         // u32 [2B] segments of the round
-    static constexpr uint32_t piece_at = seg_at + 8 * B;                    // u64 [B] first half word of a piece, half words
-    static constexpr uint32_t pbase_at = piece_at + 8 * B;                  // u32 [B] its place in the staged bases
-    static constexpr uint32_t bases_at = pbase_at + 4 * B + 8;              // u32 [halves], 8 bytes of pad before
+    static constexpr uint32_t retry_at = seg_at + 8 * B;                    // u32 [B / 64][retry] k-mers whose first bucket failed
+    static constexpr uint32_t retry = 96;
+    static constexpr uint32_t bases_at = (retry_at + B / 16 * retry + 31) / 16 * 16;   // u32 [halves], a pad before it
     static constexpr uint32_t pool = bytes - bases_at;                      // bytes of staged bases and slots together
     static constexpr uint32_t segs = 2 * B;
 };
@@ -86,16 +94,17 @@ struct PieceArgs {
     uint32_t split_lds;       // dynamic LDS of the split kernel
     uint32_t target;          // k-mers per sub-table
     uint32_t half_target;     // staged half words (16 bases) per sub-table
+    uint32_t tables_goal;     // sub-tables wanted at least: small inputs get smaller ones
     uint32_t max_kmers;       // a sub-table of more is counted in hash slices
     uint32_t slice_kmers;     // k-mers per slice
     uint32_t heavy_kmers;     // a sub-table of more goes to the fallback
     uint32_t max_halves;      // staged half words a sub-table may need
     uint32_t piece_fx;        // expected pieces per k-mer, 16.16 (over the one per super-mer)
-    uint32_t sp_cap, items_cap;
+    uint32_t grp_cap, tab_cap, items_cap;
     uint64_t cap;             // pieces that fit in list and in pieces
     // plan
-    uint32_t* nsub;           // [n_bins]
-    uint32_t* spbase;         // [n_bins + 1] first sub-table
+    uint32_t* ngrp;           // [n_bins]
+    uint32_t* grp_first;      // [n_bins + 1] first group
     uint32_t* item_first;     // [n_bins + 1] first split item
     uint64_t* scal;           // kScal*
     uint32_t* bin_fail;       // [n_bins] 1: the bin's pieces did not fit, the fallback counts it whole
@@ -103,11 +112,17 @@ struct PieceArgs {
     uint64_t* item_start;     // [items_cap] the item's pieces in list
     uint32_t* item_n;         // [items_cap]
     uint64_t* list;           // [cap]
-    uint64_t* sub_cnt;        // [sp_cap] pieces << 32 | k-mers
+    uint64_t* grp_cnt;        // [grp_cap] pieces << 32 | k-mers
     // scan, scatter
-    uint64_t* sub_off;        // [sp_cap] first piece in pieces
-    uint32_t* sub_cur;        // [sp_cap]
-    uint64_t* pieces;         // [cap] by sub-table; the heavy ones from the top, as descriptors
+    uint32_t* grp_tab;        // [grp_cap] sub-table of the group, counted from the bin's first
+    uint32_t* tab_first;      // [n_bins] first sub-table of the bin
+    uint32_t* ntab;           // [n_bins] sub-tables; as a group's sub-table: the group is heavy
+    uint64_t* tab_cnt;        // [tab_cap] pieces << 32 | k-mers
+    uint64_t* tab_off;        // [tab_cap] first piece in pieces
+    uint32_t* tab_cur;        // [tab_cap]
+    uint64_t* heavy_off;      // [n_bins] first heavy piece in pieces
+    uint32_t* heavy_cur;      // [n_bins]
+    uint64_t* pieces;         // [cap] by sub-table; those of heavy groups from the top, as descriptors
     // fallback: descriptors of every bin (heavy pieces, or the whole bin)
     uint64_t* fb_ptr;         // [n_bins] device address of the first
     uint64_t* fb_n;           // [n_bins]
@@ -115,7 +130,8 @@ struct PieceArgs {
     uint64_t* stage_clocks;
 };
 // scalars
-enum { kScalItem = 0, kScalList, kScalLight, kScalHeavy, kScalSubs, kScalItems, kScalDescs, kScalFallback, kScalCount };
+enum { kScalItem = 0, kScalList, kScalLight, kScalHeavy, kScalTables, kScalItems, kScalDescs, kScalFallback,
+       kScalTarget, kScalCount };
 
 uint32_t piece_items_cap(uint64_t n_superm, uint32_t n_bins);
 // List slots for this many super-mers and k-mers.
@@ -130,11 +146,11 @@ hipError_t launch_piece_scatter(const PieceArgs& q, uint32_t cus, hipStream_t s)
 // Table kernel: sub-tables [0, n) of the plan, in LDS tables of `slots` slots.
 struct SubArgs {
     const uint64_t* pieces;
-    const uint64_t* sub_cnt;
-    const uint64_t* sub_off;
-    const uint64_t* n_sub;    // scalar
-    uint32_t slots, halves, theta, max_kmers, slice_kmers;
-    uint32_t group_log2;      // lanes that stage one piece's half words
+    const uint64_t* tab_cnt;
+    const uint64_t* tab_off;
+    const uint64_t* n_tab;    // scalar
+    uint32_t buckets;         // of two slots
+    uint32_t halves, theta, max_kmers, slice_kmers;
     uint64_t* probe_hist;
     uint64_t* stage_clocks;
 };

@@ -1,10 +1,11 @@
 // The partition of the bins into sub-tables by sub-minimizers (pieces.h), in
 // four launches with no host synchronisation:
-//   plan     sub-tables per bin, work items (runs of descriptors of one bin);
-//   split    super-mers cut into pieces, k-mers and pieces per sub-table;
-//   scan     a contiguous run of pieces for every sub-table; the heavy ones
-//            (more k-mers or bases than a workgroup's LDS takes even in slices:
-//            strongly repeated sub-minimizers) are set apart for the fallback;
+//   plan     groups per bin, work items (runs of descriptors of one bin);
+//   split    super-mers cut into pieces, k-mers and pieces per group;
+//   scan     groups to sub-tables, a contiguous run of pieces for each; heavy
+//            groups (more k-mers or bases than a workgroup's LDS takes even in
+//            slices: strongly repeated sub-minimizers) are set apart for the
+//            fallback;
 //   scatter  every piece to its sub-table's run.
 // A bin whose pieces do not fit the list (which is sized for random
 // sub-minimizers) is left to the fallback as a whole, so every input is
@@ -22,8 +23,11 @@ constexpr uint32_t kScanB = 256;
 constexpr uint32_t kScatB = 512;
 constexpr uint32_t kItemDescs = 8192;      // descriptors per item at most (at least 256)
 constexpr uint32_t kItemGoal = 2048;       // items wanted
+constexpr uint32_t kMinTarget = 1024;      // k-mers of a small input's sub-tables
 constexpr uint32_t kItemSlack = 64;        // list slots of an item over its expected pieces
-constexpr uint32_t kScatSubs = 4096;       // sub-tables of a bin privatised in LDS by the scatter
+constexpr uint32_t kScatGroups = 8192;     // groups and sub-tables of a bin that the scatter holds in LDS
+constexpr uint32_t kScatTabs = 2048;
+constexpr uint32_t kUnit = 4096;           // weight of a full sub-table
 
 }  // namespace
 
@@ -54,9 +58,11 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     const uint32_t tid = threadIdx.x;
     if (blockIdx.x > 0) {
         const uint64_t g = (uint64_t)(blockIdx.x - 1) * kPlanB + tid, G = (uint64_t)(gridDim.x - 1) * kPlanB;
-        for (uint64_t i = g; i < q.sp_cap; i += G) {
-            q.sub_cnt[i] = 0;
-            q.sub_cur[i] = 0;
+        for (uint64_t i = g; i < q.grp_cap; i += G) q.grp_cnt[i] = 0;
+        for (uint64_t i = g; i < q.tab_cap; i += G) {
+            q.tab_cnt[i] = 0;
+            q.tab_off[i] = ~0ull;
+            q.tab_cur[i] = 0;
         }
         for (uint64_t i = g; i < kHistInternal; i += G) zero_hist[i] = 0;
         return;
@@ -69,16 +75,27 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     const uint64_t S = overfull ? 0 : q.bin_off[n];
     uint32_t descs = (uint32_t)((S / kItemGoal + 63) & ~63ull);
     descs = descs < 256 ? 256 : descs > kItemDescs ? kItemDescs : descs;
-    auto subs = [&](uint32_t b) -> uint32_t {
+    // k-mers per sub-table: the target, or less where that leaves workgroups without one
+    uint64_t km = 0;
+    for (uint32_t e = 0; e < per; e++) {
+        const uint32_t b = tid * per + e;
+        if (b < n && !overfull) km += q.bin_kmers[b];
+    }
+    plan_scan(part, km);
+    uint64_t target = part[kPlanB - 1] / q.tables_goal;
+    target = target < kMinTarget ? kMinTarget : target;
+    target = target > q.target ? q.target : target;
+    __syncthreads();
+    auto groups = [&](uint32_t b) -> uint32_t {
         const uint64_t ns = q.bin_off[b + 1] - q.bin_off[b], K = q.bin_kmers[b];
         if (overfull || ns == 0) return 0;
         const uint64_t E = ns + ((K * q.piece_fx) >> 16);
-        uint64_t P = (K + q.target - 1) / q.target;
-        const uint64_t Pw = (piece_halves(K, E, q.k) + q.half_target - 1) / q.half_target;
-        if (Pw > P) P = Pw;
-        if (P > kExactSubs) {
-            uint64_t p2 = kExactSubs;
-            while (p2 < P && p2 < kMaxSubs) p2 *= 2;
+        uint64_t P = (K * kGroupsPerTable + target - 1) / target;
+        const uint64_t Ph = (piece_halves(K, E, q.k) * kGroupsPerTable + q.half_target - 1) / q.half_target;
+        if (Ph > P) P = Ph;
+        if (P > kExactGroups) {
+            uint64_t p2 = kExactGroups;
+            while (p2 < P && p2 < kMaxGroups) p2 *= 2;
             P = p2;
         }
         return (uint32_t)(P ? P : 1);
@@ -87,7 +104,7 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     for (uint32_t e = 0; e < per; e++) {
         const uint32_t b = tid * per + e;
         if (b >= n) break;
-        sp += subs(b);
+        sp += groups(b);
         it += overfull ? 0 : (q.bin_off[b + 1] - q.bin_off[b] + descs - 1) / descs;
     }
     plan_scan(part, it);
@@ -97,25 +114,25 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     plan_scan(part, sp);
     uint64_t sp0 = part[tid] - sp;
     const uint64_t n_sp = part[kPlanB - 1];
-    // sub-tables and items that do not fit their arrays (sized for any bins of
+    // groups and items that do not fit their arrays (sized for any bins of
     // this many bases, so only for parameters far from the default): nothing
     // is split, and the fallback counts every bin
-    const bool none = n_sp > q.sp_cap || n_items > q.items_cap;
+    const bool none = n_sp > q.grp_cap || n_items > q.items_cap;
     for (uint32_t e = 0; e < per; e++) {
         const uint32_t b = tid * per + e;
         if (b >= n) break;
-        const uint32_t P = none ? 0u : subs(b);
-        q.nsub[b] = P;
-        q.spbase[b] = none ? 0u : (uint32_t)sp0;
+        const uint32_t P = none ? 0u : groups(b);
+        q.ngrp[b] = P;
+        q.grp_first[b] = none ? 0u : (uint32_t)sp0;
         q.item_first[b] = none ? 0u : (uint32_t)it0;
         q.bin_fail[b] = none ? 1u : 0u;
         sp0 += P;
         it0 += overfull ? 0 : (q.bin_off[b + 1] - q.bin_off[b] + descs - 1) / descs;
     }
     if (tid == 0) {
-        q.spbase[n] = none ? 0u : (uint32_t)n_sp;
+        q.grp_first[n] = none ? 0u : (uint32_t)n_sp;
         q.item_first[n] = none ? 0u : (uint32_t)n_items;
-        q.scal[kScalSubs] = none ? 0 : n_sp;
+        q.scal[kScalTarget] = target;
         q.scal[kScalItems] = none ? 0 : n_items;
         q.scal[kScalDescs] = descs;
         if (overfull) set_status(q.status, ST_SUPERM_CAP);
@@ -183,7 +200,7 @@ struct Bases16 {
 // of their own.
 template <bool kFull>
 __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
-    extern __shared__ uint32_t S[];                 // [n0 + 4][kSplitB]; then the sub-table counts
+    extern __shared__ uint32_t S[];                 // [n0 + 4][kSplitB]; then the group counts
     __shared__ uint64_t red[kSplitB / 64];
     __shared__ uint64_t s_start;
     __shared__ uint32_t s_item, s_n, s_cap, s_next;
@@ -375,22 +392,22 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
             q.item_n[item] = fits ? total : 0u;
             if (!fits && cnt) __hip_atomic_store(&q.bin_fail[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        const uint32_t P = q.nsub[b], sb = q.spbase[b];
+        const uint32_t P = q.ngrp[b], gb = q.grp_first[b];
         if (fits && P <= hist_cap) {
             for (uint32_t i = tid; i < P; i += kSplitB) hist[i] = 0;
             __syncthreads();
             for (uint32_t e = tid; e < total; e += kSplitB) {
                 const uint64_t p = out[e];
-                atomicAdd((unsigned long long*)&hist[sub_of_hash(piece_hash(p), P)],
+                atomicAdd((unsigned long long*)&hist[group_of_hash(piece_hash(p), P)],
                           (1ull << 32) | (unsigned long long)piece_kmers(p));
             }
             __syncthreads();
             for (uint32_t i = tid; i < P; i += kSplitB)
-                if (hist[i]) add_dev(&q.sub_cnt[sb + i], hist[i]);
+                if (hist[i]) add_dev(&q.grp_cnt[gb + i], hist[i]);
         } else if (fits) {
             for (uint32_t e = tid; e < total; e += kSplitB) {
                 const uint64_t p = out[e];
-                add_dev(&q.sub_cnt[sb + sub_of_hash(piece_hash(p), P)], (1ull << 32) | (uint64_t)piece_kmers(p));
+                add_dev(&q.grp_cnt[gb + group_of_hash(piece_hash(p), P)], (1ull << 32) | (uint64_t)piece_kmers(p));
             }
         }
         __syncthreads();
@@ -401,21 +418,19 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
     }
 }
 
-// One workgroup per bin: runs of the light sub-tables from the bottom of
-// pieces, of the heavy ones from its top, and the bin's fallback descriptors.
+// One workgroup per bin: its groups to sub-tables, runs of pieces for the
+// sub-tables from the bottom of pieces and for the heavy groups from its top,
+// and the bin's fallback descriptors. A group's weight is the larger of its
+// shares of a sub-table's k-mers and bases; a group belongs to the sub-table
+// that the middle of its weight falls into.
 __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
     __shared__ uint32_t wsum[32];
     __shared__ uint64_t s_light, s_heavy, s_hk;
+    __shared__ uint32_t s_tab;
     const uint32_t tid = threadIdx.x, b = blockIdx.x;
     const uint64_t t0 = q.stage_clocks ? wall_clock64() : 0;
-    const uint32_t P = q.nsub[b], sb = q.spbase[b];
-    const bool fail = q.bin_fail[b] != 0;
-    auto heavy = [&](uint64_t c) -> bool {
-        const uint32_t km = (uint32_t)c, np = (uint32_t)(c >> 32);
-        return km > q.heavy_kmers || piece_halves(km, np, q.k) > q.max_halves;
-    };
-    if (fail) {
-        for (uint32_t i = tid; i < P; i += kScanB) q.sub_cnt[sb + i] = 0;
+    const uint32_t P = q.ngrp[b], gb = q.grp_first[b];
+    if (q.bin_fail[b]) {
         if (tid == 0) {
             const uint64_t d0 = q.bin_off[b], nd = q.bin_off[b + 1] - d0;
             q.fb_ptr[b] = (uint64_t)(q.desc + d0);
@@ -425,42 +440,83 @@ __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
         }
         return;
     }
+    const uint32_t target = (uint32_t)q.scal[kScalTarget];
+    auto heavy = [&](uint64_t c) -> bool {
+        return (uint32_t)c > q.heavy_kmers || piece_halves((uint32_t)c, c >> 32, q.k) > q.max_halves;
+    };
+    auto weight = [&](uint64_t c) -> uint32_t {   // of a group that is not heavy
+        const uint32_t wk = (uint32_t)((uint64_t)(uint32_t)c * kUnit / target);
+        const uint32_t wh = (uint32_t)(piece_halves((uint32_t)c, c >> 32, q.k) * kUnit / q.half_target);
+        return wk > wh ? wk : wh;
+    };
     if (tid == 0) s_hk = 0;
     const uint32_t per = (P + kScanB - 1) / kScanB;
     const uint32_t i0 = tid * per, i1 = i0 + per < P ? i0 + per : P;
-    uint32_t nl = 0, nh = 0;
+    uint32_t nl = 0, nh = 0, w = 0;
     uint64_t hk = 0;
     for (uint32_t i = i0; i < i1; i++) {
-        const uint64_t c = q.sub_cnt[sb + i];
+        const uint64_t c = q.grp_cnt[gb + i];
         if (heavy(c)) {
             nh += (uint32_t)(c >> 32);
             hk += (uint32_t)c;
         } else {
             nl += (uint32_t)(c >> 32);
+            w += weight(c);
         }
     }
-    uint32_t tl, th;
+    uint32_t tl, th, tw;
     const uint32_t pl = block_excl_scan(nl, wsum, tl), ph = block_excl_scan(nh, wsum, th);
+    (void)ph;
+    uint32_t wr = block_excl_scan(w, wsum, tw);
+    const uint32_t nt = tl ? tw / kUnit + 1 : 0u;
     if (hk) atomicAdd((unsigned long long*)&s_hk, (unsigned long long)hk);
     if (tid == 0) {
         s_light = tl ? add_dev(&q.scal[kScalLight], (uint64_t)tl) : 0ull;
         s_heavy = th ? q.cap - add_dev(&q.scal[kScalHeavy], (uint64_t)th) - th : 0ull;
+        s_tab = nt ? (uint32_t)add_dev(&q.scal[kScalTables], (uint64_t)nt) : 0u;
     }
     __syncthreads();
-    uint64_t rl = s_light + pl, rh = s_heavy + ph;
+    const uint32_t tab = s_tab;
+    uint64_t at = s_light + pl;
+    // the groups of one sub-table that this thread has seen
+    uint32_t cur = 0xFFFFFFFFu;
+    uint64_t cnt = 0, first = 0;
+    auto flush = [&]() {
+        if (cnt && tab + cur < q.tab_cap) {
+            add_dev(&q.tab_cnt[tab + cur], cnt);
+            __hip_atomic_fetch_min(&q.tab_off[tab + cur], first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        cnt = 0;
+    };
     for (uint32_t i = i0; i < i1; i++) {
-        const uint64_t c = q.sub_cnt[sb + i];
+        const uint64_t c = q.grp_cnt[gb + i];
         const uint32_t np = (uint32_t)(c >> 32);
         if (heavy(c)) {
-            q.sub_off[sb + i] = rh | (1ull << 63);
-            q.sub_cnt[sb + i] = 0;   // nothing for the table kernel
-            rh += np;
-        } else {
-            q.sub_off[sb + i] = rl;
-            rl += np;
+            q.grp_tab[gb + i] = nt;
+            continue;
         }
+        const uint32_t gw = weight(c);
+        uint32_t t = (wr + gw / 2) / kUnit;
+        t = t < nt ? t : nt - 1;
+        if (np == 0) t = 0;
+        q.grp_tab[gb + i] = t;
+        if (np) {
+            if (t != cur) {
+                flush();
+                cur = t;
+                first = at;
+            }
+            cnt += c;
+            at += np;
+        }
+        wr += gw;
     }
+    flush();
     if (tid == 0) {
+        q.tab_first[b] = tab;
+        q.ntab[b] = nt;
+        q.heavy_off[b] = s_heavy;
+        q.heavy_cur[b] = 0;
         q.fb_ptr[b] = (uint64_t)(q.pieces + s_heavy);
         q.fb_n[b] = th;
         q.fb_kmers[b] = s_hk;
@@ -474,10 +530,11 @@ __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
 
 // Every item's pieces to their sub-tables' runs: counted per sub-table in
 // LDS, one reservation per sub-table and item, then placed. Bound by the
-// scattered 8-byte stores (an item leaves about 11 pieces per sub-table).
+// scattered 8-byte stores.
 __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
-    __shared__ uint64_t pos[kScatSubs];
-    __shared__ uint32_t cnt[kScatSubs];
+    __shared__ uint64_t pos[kScatTabs + 1];       // the last one used: the bin's heavy pieces
+    __shared__ uint32_t cnt[kScatTabs + 1];
+    __shared__ uint16_t map[kScatGroups];
     const uint32_t tid = threadIdx.x;
     const uint32_t n_items = (uint32_t)q.scal[kScalItems];
     for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
@@ -486,18 +543,23 @@ __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
         if (total == 0 || q.bin_fail[b]) continue;
         const uint64_t t0 = q.stage_clocks ? wall_clock64() : 0;
         const uint64_t* in = q.list + q.item_start[item];
-        const uint32_t P = q.nsub[b], sb = q.spbase[b];
-        if (P <= kScatSubs) {
-            for (uint32_t i = tid; i < P; i += kScatB) cnt[i] = 0;
+        const uint32_t P = q.ngrp[b], gb = q.grp_first[b], tb = q.tab_first[b], nt = q.ntab[b];
+        if (P <= kScatGroups && nt <= kScatTabs) {
+            for (uint32_t i = tid; i < P; i += kScatB) map[i] = (uint16_t)q.grp_tab[gb + i];
+            for (uint32_t i = tid; i <= nt; i += kScatB) cnt[i] = 0;
             __syncthreads();
-            for (uint32_t e = tid; e < total; e += kScatB) atomicAdd(&cnt[sub_of_hash(piece_hash(in[e]), P)], 1u);
+            for (uint32_t e = tid; e < total; e += kScatB) atomicAdd(&cnt[map[group_of_hash(piece_hash(in[e]), P)]], 1u);
             __syncthreads();
-            for (uint32_t i = tid; i < P; i += kScatB)
-                if (cnt[i]) pos[i] = q.sub_off[sb + i] + add_dev(&q.sub_cur[sb + i], cnt[i]);
+            for (uint32_t i = tid; i <= nt; i += kScatB) {
+                const uint32_t n = cnt[i];
+                if (n == 0) continue;
+                pos[i] = i < nt ? q.tab_off[tb + i] + add_dev(&q.tab_cur[tb + i], n)
+                                : (q.heavy_off[b] + add_dev(&q.heavy_cur[b], n)) | (1ull << 63);
+            }
             __syncthreads();
             for (uint32_t e = tid; e < total; e += kScatB) {
                 const uint64_t p = in[e];
-                uint64_t at = atomicAdd((unsigned long long*)&pos[sub_of_hash(piece_hash(p), P)], 1ull);
+                uint64_t at = atomicAdd((unsigned long long*)&pos[map[group_of_hash(piece_hash(p), P)]], 1ull);
                 const bool heavy = at >> 63;
                 at &= ~0ull >> 1;
                 if (at < q.cap) q.pieces[at] = heavy ? (piece_start(p) << 24) | piece_kmers(p) : p;
@@ -506,9 +568,11 @@ __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
         } else {
             for (uint32_t e = tid; e < total; e += kScatB) {
                 const uint64_t p = in[e];
-                const uint32_t j = sb + sub_of_hash(piece_hash(p), P);
-                const uint64_t o = q.sub_off[j], at = (o & (~0ull >> 1)) + add_dev(&q.sub_cur[j], 1u);
-                if (at < q.cap) q.pieces[at] = (o >> 63) ? (piece_start(p) << 24) | piece_kmers(p) : p;
+                const uint32_t t = q.grp_tab[gb + group_of_hash(piece_hash(p), P)];
+                const bool heavy = t >= nt;
+                const uint64_t at = heavy ? q.heavy_off[b] + add_dev(&q.heavy_cur[b], 1u)
+                                          : q.tab_off[tb + t] + add_dev(&q.tab_cur[tb + t], 1u);
+                if (at < q.cap) q.pieces[at] = heavy ? (piece_start(p) << 24) | piece_kmers(p) : p;
             }
         }
         if (q.stage_clocks && tid == 0) {
@@ -519,7 +583,7 @@ __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
 }
 
 hipError_t launch_piece_plan(const PieceArgs& q, uint64_t* zero_scalars, uint64_t* zero_hist, hipStream_t s) {
-    const uint64_t blocks = ((uint64_t)q.sp_cap + kPlanB - 1) / kPlanB;
+    const uint64_t blocks = ((uint64_t)q.grp_cap + kPlanB - 1) / kPlanB;
     const uint32_t g = 1 + (uint32_t)(blocks < 64 ? 64 : blocks > 512 ? 512 : blocks);
     hipLaunchKernelGGL(k_piece_plan, dim3(g), dim3(kPlanB), 0, s, q, zero_scalars, zero_hist);
     return hipGetLastError();
@@ -547,7 +611,7 @@ hipError_t launch_sub_scan(const PieceArgs& q, hipStream_t s) {
 }
 
 hipError_t launch_piece_scatter(const PieceArgs& q, uint32_t cus, hipStream_t s) {
-    hipLaunchKernelGGL(k_piece_scatter, dim3(cus * 3), dim3(kScatB), 0, s, q);
+    hipLaunchKernelGGL(k_piece_scatter, dim3(cus * 4), dim3(kScatB), 0, s, q);
     return hipGetLastError();
 }
 

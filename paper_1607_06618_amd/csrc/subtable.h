@@ -4,7 +4,7 @@
 //
 // A workgroup copies the packed bases of its sub-table's pieces into LDS,
 // rolls every k-mer of them and inserts it. A slot does not hold the key: it
-// is one 64-bit word [tag 29 | reference 19 | count 16], where the tag is part
+// is one 64-bit word [reference 32 | tag 16 | count 16], where the tag is part
 // of the key's hash and the reference says where in the staged bases the key
 // was first seen and which strand is its canonical form. A key of any length
 // so takes 8 bytes (a 65-mer 24, a 200-mer 56 when it is stored), one CAS
@@ -15,6 +15,21 @@
 //
 // Keys are held left-aligned in D 32-bit words, D = ceil(k / 16): the forward
 // strand and the reverse complement both roll by one funnel shift per word.
+//
+// What bounds it: vector issue (60 % of the cycles at k = 65, some 3.3 wave
+// instructions per key and lane-64th) and the barriers between the stages of
+// the one workgroup a CU holds; memory takes under a fifth of its time
+// (the bases once, 28 bytes out per distinct key). So
+// - the first try of a key is straight-line code for a bucket of two slots read
+//   at once; the few that find it taken go to a queue per wave, and are probed
+//   on in full waves (as a loop, a wave ran on for its slowest lane);
+// - k-mers are cut into segments of 8, sorted by length, so that the lanes of a
+//   wave roll equally far;
+// - the pieces of the next round, and of the next sub-table, are requested
+//   before the current ones are processed;
+// - pairs are collected per wave and written 64 at a time.
+// 107 M 65-mers (30x): 15.2 ms, against 24.4 ms for a probe loop over single
+// slots, one round at a time; 41 M 99-mers of skewed coverage 10 ms of 17.
 #pragma once
 #include "pieces.h"
 #include "table.h"
@@ -23,10 +38,15 @@ namespace gerbil {
 namespace sub {
 
 constexpr uint32_t kSeg = 8;             // k-mers a lane rolls from one start
-constexpr uint32_t kRefBits = 19;        // base in the staged ones, strand
-constexpr uint32_t kSegBaseBits = 18;
+constexpr uint32_t kSegLenAt = 24;       // a segment: reference of its first k-mer, k-mers - 1
 
-// (hi:lo) >> s, low word, 0 <= s < 32.
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t uniform(uint64_t x) {
+    return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
+}
+
+// (hi:lo) >> (s mod 32), low word.
 __device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t s) {
     return __builtin_amdgcn_alignbit(hi, lo, s);
 }
@@ -36,21 +56,24 @@ __device__ __forceinline__ uint32_t revcomp16(uint32_t x) {
     return ((x >> 1) & 0x55555555u) | ((x & 0x55555555u) << 1);
 }
 
-// Bases o.. of the staged ones as D left-aligned words (the bits past k
-// bases cleared). b32 holds 16 bases a word, in order; word -1 exists.
+// The k bases of reference ref as D left-aligned words (the bits past them
+// cleared). A reference to base o is 2 (o + 15), plus one for a k-mer whose
+// canonical form is its reverse complement: ref / 32 is then the word that
+// holds base o - 1, counted from the word before the staged ones, and the
+// funnel shifts from there are by 30 - 2 ((o - 1) mod 16), never by 32. b32
+// points to the word before the staged ones, 16 bases a word.
 template <int D>
-__device__ __forceinline__ void window(const uint32_t* b32, uint32_t o, uint32_t tail_mask, uint32_t (&x)[D]) {
-    // shifts of 2..32 from the half that holds base o - 1, so that a funnel
-    // shift by 32 - 2..32 never needs the case of no shift
-    const int32_t h = ((int32_t)o - 1) >> 4;
-    const uint32_t s = 30u - 2u * ((o - 1u) & 15u);
+__device__ __forceinline__ void window(const uint32_t* b32, uint32_t ref, uint32_t tail_mask, uint32_t (&x)[D]) {
+    const uint32_t* p = b32 + (ref >> 5);
+    const uint32_t s = ~(ref | 1u);   // (the low five bits count)
     uint32_t w[D + 1];
 #pragma unroll
-    for (int i = 0; i <= D; i++) w[i] = b32[h + i];
+    for (int i = 0; i <= D; i++) w[i] = p[i];
 #pragma unroll
     for (int i = 0; i < D; i++) x[i] = funnel(w[i], w[i + 1], s);
     x[D - 1] &= tail_mask;
 }
+__device__ __forceinline__ uint32_t ref_of(uint32_t o) { return 2 * o + 30; }
 
 // Reverse complement of D left-aligned words of k bases (pad = 32 D - 2 k bits).
 template <int D>
@@ -78,50 +101,52 @@ __device__ __forceinline__ void to_words(const uint32_t (&x)[D], uint32_t k, uin
     w[W - 1] >>= 2 * (32u * W - k);
 }
 
-// Hash of a key: a multilinear sum of its words modulo 2^64 (any difference of
-// two words changes it). lo, whose top bits choose the slot, is mixed once
-// more; hi is the tag.
+// Hash of a key: its words rotated and added up, then mixed by one
+// multiplication. The top bits choose the bucket, the low ones are the tag.
+// (A multiply-add per word costs four issue slots here where this takes two.)
 template <int D>
-__device__ __forceinline__ void hash_key(const uint32_t (&x)[D], uint32_t& hi, uint32_t& lo) {
-    uint64_t s = 0x243F6A8885A308D3ull;
+__device__ __forceinline__ uint32_t hash_key(const uint32_t (&x)[D]) {
+    uint32_t h = x[0];
 #pragma unroll
-    for (int i = 0; i < D; i++) {
-        // odd constants from SplitMix64's increment, one per word
-        const uint32_t m = (uint32_t)((0x9E3779B97F4A7C15ull * (2 * i + 3)) >> 29) | 1u;
-        s += (uint64_t)x[i] * m;
-    }
-    hi = (uint32_t)(s >> 32);
-    lo = (uint32_t)s ^ hi;
-    lo = (lo ^ (lo >> 15)) * 0x2C1B3C6Du;
+    for (int i = 1; i < D; i++) h = funnel(h, h, 21) + x[i];
+    h = (h ^ (h >> 16)) * 0x9E3779B1u;
+    return h ^ (h >> 15);
 }
 
-template <int D, uint32_t B>
+template <uint32_t B>
 struct Wg {
     using Sh = SubShape<B>;
     uint8_t* lds;
     __device__ __forceinline__ uint32_t* hist() const { return (uint32_t*)(lds + Sh::hist_at); }
     __device__ __forceinline__ uint32_t* probes() const { return (uint32_t*)(lds + Sh::probe_at); }
-    __device__ __forceinline__ uint32_t* wsum() const { return (uint32_t*)(lds + Sh::scan_at); }
+    __device__ __forceinline__ uint32_t* sums() const { return (uint32_t*)(lds + Sh::sum_at); }
     __device__ __forceinline__ uint64_t* base() const { return (uint64_t*)(lds + Sh::base_at); }
     __device__ __forceinline__ uint32_t* cls() const { return (uint32_t*)(lds + Sh::cls_at); }
     __device__ __forceinline__ uint32_t* segs() const { return (uint32_t*)(lds + Sh::seg_at); }
-    __device__ __forceinline__ uint64_t* piece() const { return (uint64_t*)(lds + Sh::piece_at); }
-    __device__ __forceinline__ uint32_t* pbase() const { return (uint32_t*)(lds + Sh::pbase_at); }
     __device__ __forceinline__ uint32_t* bases() const { return (uint32_t*)(lds + Sh::bases_at); }
-    // emission queue of a wave, over the segments and the piece table: 128 slots each
+    __device__ __forceinline__ uint32_t* retries() const {
+        return (uint32_t*)(lds + Sh::retry_at) + Sh::retry * (threadIdx.x >> 6);
+    }
+    // emission queue of a wave, over the segments: 64 slots
     __device__ __forceinline__ uint64_t* queue() const {
-        return (uint64_t*)(lds + Sh::seg_at) + 128u * (threadIdx.x >> 6);
+        return (uint64_t*)(lds + Sh::seg_at) + 64u * (threadIdx.x >> 6);
     }
 };
 
-// Insert the key of a rolled k-mer (fw, its reverse complement rc, base o of
-// the staged words). One loop with one exit: a lane stays in it until its key
-// has a slot or theta probes have failed.
+// A key ready to be inserted: its hash, and the halves of the slot word that
+// claims a slot for it with a count of one.
+struct Probe {
+    uint32_t hash, ref, tag1;
+};
+
+// Key of a rolled k-mer (fw, its reverse complement rc, reference ref without
+// the strand). False if the key is not to be inserted: another slice's, or the
+// one first word that is never stored in a table in the `-d` mode (sent to the
+// emergency area).
 template <int D, uint32_t B>
-__device__ __forceinline__ void insert(const CountArgs& a, const SubArgs& t, const Wg<D, B>& g, uint64_t* slots,
-                                       const uint32_t* b32, const uint32_t (&fw)[D], const uint32_t (&rc)[D],
-                                       uint32_t o, uint32_t tail_mask, uint64_t kx, uint32_t V, uint32_t v) {
-    constexpr int W = (D + 1) / 2;
+__device__ __forceinline__ bool make_probe(const CountArgs& a, const SubArgs& t, const Wg<B>& g,
+                                           const uint32_t (&fw)[D], const uint32_t (&rc)[D], uint32_t ref, uint64_t kx,
+                                           uint32_t V, uint32_t v, Probe& p) {
     // canonical strand: the first 32 bases nearly always decide
     const uint64_t f0 = ((uint64_t)fw[0] << 32) | fw[1], r0 = ((uint64_t)rc[0] << 32) | rc[1];
     bool take = r0 < f0;
@@ -137,46 +162,84 @@ __device__ __forceinline__ void insert(const CountArgs& a, const SubArgs& t, con
     uint32_t key[D];
 #pragma unroll
     for (int i = 0; i < D; i++) key[i] = take ? rc[i] : fw[i];
-    uint32_t hi, lo;
-    hash_key<D>(key, hi, lo);
-    if (V > 1 && fastrange32(hi << 9, V) != v) return;   // another slice's key
-    // (its other half: the one first word that is never stored in a table)
-    bool pend = ((key[0] ^ (uint32_t)(kx >> 32)) & (key[1] ^ (uint32_t)kx)) == 0xFFFFFFFFu;
-    uint32_t tries = 0;
-    if (!pend) {
-        const uint32_t C = t.slots, f = take ? 1u : 0u;
-        uint32_t s = fastrange32(lo, C);
-        const uint32_t st = 1u + (hi & 1023u);
-        const uint32_t ref = (o << 1) | f;
-        const uint32_t mine_hi = ((hi >> 6) << 6) | ((lo & 7u) << 3) | (ref >> 16), mine_lo = (ref << 16) | 1u;
-        const uint64_t mine = ((uint64_t)mine_hi << 32) | mine_lo;
-        do {
-            uint64_t* p = slots + s;
-            uint64_t cur = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (cur == 0)   // claim it, with a count of one; cur stays 0 if that works
-                __hip_atomic_compare_exchange_strong(p, &cur, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-            pend = cur != 0;
-            if (pend && (((uint32_t)(cur >> 32)) ^ mine_hi) < 8u) {
-                // the tag agrees: compare with the first occurrence, base by base
-                const uint32_t r = (uint32_t)(cur >> 16) & ((1u << kRefBits) - 1u);
-                uint32_t x[D];
-                window<D>(b32, r >> 1, tail_mask, x);
-                const bool other = (r ^ f) & 1u;
-                uint32_t diff = 0;
-#pragma unroll
-                for (int i = 0; i < D; i++) diff |= x[i] ^ (other ? rc[i] : fw[i]);
-                if (diff == 0) {
-                    __hip_atomic_fetch_add((uint32_t*)p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    pend = false;
-                }
-            }
-            s += st;
-            s = min(s, s - C);   // s - C wraps to a large value below C
-            tries++;
-        } while (pend && tries < t.theta);
+    p.hash = hash_key<D>(key);
+    p.ref = ref + (take ? 1u : 0u);
+    p.tag1 = (p.hash << 16) | 1u;
+    if (V > 1 && fastrange32(p.hash * 0x85EBCA6Bu, V) != v) return false;
+    if (kx && (((fw[0] ^ (uint32_t)(kx >> 32)) & (fw[1] ^ (uint32_t)kx)) == 0xFFFFFFFFu)) {
+        constexpr int W = (D + 1) / 2;
+        uint64_t w[W];
+        to_words<D>(fw, a.k, w);
+        w[0] ^= kx;
+        overflow_push<W>(a, w);
+        if (t.probe_hist) atomicAdd(&g.probes()[kProbeHist - 1], 1u);
+        return false;
     }
-    if (pend) {
+    return true;
+}
+
+enum { kSettled = 0, kNext = 1, kAgain = 2 };
+
+// One bucket of Alg. 1: settled, on to the next bucket, or this one again. A
+// bucket's first slot fills before its second. A slot found free but lost to
+// another lane leaves the bucket to be read again; one whose tag agrees without
+// the bases agreeing sends every occurrence of the key on to the next bucket
+// (the slot keeps its content), so a key has one slot only.
+template <int D>
+__device__ __forceinline__ uint32_t probe_bucket(uint64_t* slots, const uint32_t* b32, const Probe& p, uint32_t bk,
+                                                 const uint32_t (&fw)[D], const uint32_t (&rc)[D],
+                                                 uint32_t tail_mask) {
+    uint64_t* s = slots + 2 * bk;
+    const uint64_t c0 = __hip_atomic_load(s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const uint64_t c1 = __hip_atomic_load(s + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const bool use0 = (uint32_t)c0 == 0 || ((uint32_t)c0 ^ p.tag1) < 0x10000u;
+    uint64_t cur = use0 ? c0 : c1;
+    s += use0 ? 0 : 1;
+    uint32_t r = kNext;
+    if ((uint32_t)cur == 0) {   // claim it; cur stays 0 if that works
+        cur = 0;
+        __hip_atomic_compare_exchange_strong(s, &cur, ((uint64_t)p.ref << 32) | p.tag1, __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        r = (uint32_t)cur == 0 ? kSettled : kAgain;
+    }
+    if (r != kSettled && ((uint32_t)cur ^ p.tag1) < 0x10000u) {
+        // the tag agrees: compare with the first occurrence, base by base
+        const uint32_t ref = (uint32_t)(cur >> 32);
+        uint32_t x[D];
+        window<D>(b32, ref, tail_mask, x);
+        const bool other = (ref ^ p.ref) & 1u;
+        uint32_t diff = 0;
+#pragma unroll
+        for (int i = 0; i < D; i++) diff |= x[i] ^ (other ? rc[i] : fw[i]);
+        r = kNext;
+        if (diff == 0) {
+            __hip_atomic_fetch_add((uint32_t*)s, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            r = kSettled;
+        }
+    }
+    return r;
+}
+
+// The whole of Alg. 1 for a key: theta buckets, then the emergency area.
+template <int D, uint32_t B>
+__device__ __forceinline__ void insert(const CountArgs& a, const SubArgs& t, const Wg<B>& g, uint64_t* slots,
+                                       const uint32_t* b32, const Probe& p, const uint32_t (&fw)[D],
+                                       const uint32_t (&rc)[D], uint32_t tail_mask, uint64_t kx) {
+    const uint32_t st = 1u + (p.hash & 1023u);
+    uint32_t bk = fastrange32(p.hash, t.buckets), tries = 0, r;
+    do {
+        r = probe_bucket<D>(slots, b32, p, bk, fw, rc, tail_mask);
+        if (r != kAgain) {
+            bk += st;
+            bk = min(bk, bk - t.buckets);   // (wraps to a large value below)
+            tries++;
+        }
+    } while (r != kSettled && tries < t.theta);
+    if (r != kSettled) {
+        constexpr int W = (D + 1) / 2;
+        uint32_t key[D];
+#pragma unroll
+        for (int i = 0; i < D; i++) key[i] = (p.ref & 1u) ? rc[i] : fw[i];
         uint64_t w[W];
         to_words<D>(key, a.k, w);
         w[0] ^= kx;
@@ -184,6 +247,21 @@ __device__ __forceinline__ void insert(const CountArgs& a, const SubArgs& t, con
         tries = kProbeHist;
     }
     if (t.probe_hist) atomicAdd(&g.probes()[tries < kProbeHist - 1 ? tries : kProbeHist - 1], 1u);
+}
+
+// Up to 64 queued k-mers, one per lane.
+template <int D, uint32_t B>
+__device__ __forceinline__ void retry(const CountArgs& a, const SubArgs& t, const Wg<B>& g, uint64_t* slots,
+                                      const uint32_t* b32, const uint32_t* queue, uint32_t m, uint32_t pad,
+                                      uint32_t tail_mask, uint64_t kx) {
+    if (__lane_id() >= m) return;
+    const uint32_t ref = queue[__lane_id()];
+    uint32_t fw[D], rc[D];
+    window<D>(b32, ref, tail_mask, fw);
+    revcomp<D>(fw, pad, tail_mask, rc);
+    Probe p;
+    make_probe<D, B>(a, t, g, fw, rc, ref, kx, 1, 0, p);   // (only keys to insert are queued)
+    insert<D, B>(a, t, g, slots, b32, p, fw, rc, tail_mask, kx);
 }
 
 // The pairs of up to 64 queued slots, one per lane, to output positions from pos0.
@@ -198,10 +276,10 @@ __device__ __forceinline__ void emit(const CountArgs& a, const uint32_t* b32, co
         set_status(a.status, ST_OUT_CAP);
         return;
     }
-    const uint32_t r = (uint32_t)(e >> 16) & ((1u << kRefBits) - 1u);
+    const uint32_t ref = (uint32_t)(e >> 32);
     uint32_t x[D];
-    window<D>(b32, r >> 1, tail_mask, x);
-    if (r & 1u) {
+    window<D>(b32, ref, tail_mask, x);
+    if (ref & 1u) {
         uint32_t y[D];
         revcomp<D>(x, pad, tail_mask, y);
 #pragma unroll
@@ -217,193 +295,272 @@ __device__ __forceinline__ void emit(const CountArgs& a, const uint32_t* b32, co
 template <int D, uint32_t B>
 __global__ void __launch_bounds__(B, (D <= 16 ? 4 : 2)) k_sub_tables(CountArgs a, SubArgs t) {
     using Sh = SubShape<B>;
+    constexpr uint32_t kQuads = D <= 6 ? 2 : D <= 10 ? 3 : 4;   // 16-byte loads that hold an ordinary piece
     extern __shared__ __align__(16) uint8_t lds_raw[];
-    const Wg<D, B> g{lds_raw};
+    const Wg<B> g{lds_raw};
     const uint32_t tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
-    const uint32_t k = a.k, C = t.slots;
+    const uint32_t k = a.k, CP = (2 * t.buckets + B - 1) / B * B;   // slots, in whole rounds of the workgroup
     const uint32_t pad = 32u * D - 2u * k;   // 0 .. 30 bits
     const uint32_t tail_mask = 0xFFFFFFFFu << pad;
     const uint64_t kx = stored_xor(a.canonical, k);
     uint32_t* hist = g.hist();
+    uint32_t* cls = g.cls();
     uint32_t* bases = g.bases();
-    const uint32_t* b32 = bases;
-    uint64_t* slots = (uint64_t*)(bases + t.halves);   // (an even number)
-    const uint32_t* packed = (const uint32_t*)a.packed;
+    const uint32_t* b32 = bases - 1;
+    uint64_t* slots = (uint64_t*)(bases + t.halves);   // (a multiple of 16 bytes)
     uint32_t* segs = g.segs();
     for (uint32_t i = tid; i < kLdsHist; i += B) hist[i] = 0;
     if (tid < kProbeHist) g.probes()[tid] = 0;
     if (tid == 0) bases[-1] = 0;
-    for (uint32_t i = tid; i < C; i += B) slots[i] = 0;
-    if (tid < 8) g.cls()[tid] = 0;
+    if (tid < 8) cls[tid] = 0;
+    for (uint32_t i = tid; i < CP; i += B) slots[i] = 0;
     __syncthreads();
     uint32_t wmax = 0;
-    const uint32_t n_sub = (uint32_t)*t.n_sub;
-    const uint32_t G = 1u << t.group_log2;
-    // a sub-table's size and place are read two of them ahead, its first pieces one ahead
-    uint32_t j = blockIdx.x;
-    uint64_t meta = j < n_sub ? t.sub_cnt[j] : 0ull, off = j < n_sub ? t.sub_off[j] : 0ull;
-    uint64_t first = tid < (uint32_t)(meta >> 32) ? t.pieces[off + tid] : 0ull;
-    for (; j < n_sub; ) {
-        const uint32_t N = (uint32_t)meta, np = (uint32_t)(meta >> 32), jn = j + gridDim.x;
-        const uint64_t* in = t.pieces + off;
-        const uint64_t meta_n = jn < n_sub ? t.sub_cnt[jn] : 0ull, off_n = jn < n_sub ? t.sub_off[jn] : 0ull;
-        uint64_t first_n = 0;
-        const uint64_t t0 = t.stage_clocks ? wall_clock64() : 0;
+    const uint32_t n_tab = uniform((uint32_t)*t.n_tab), G = gridDim.x;
+    // Work goes in batches of B pieces of one sub-table (and slice). While a
+    // batch is counted the bases of the next one's pieces are on their way to
+    // registers, the pieces of the one after that too, and the size and place
+    // of the sub-table after that.
+    struct Batch {
+        uint32_t j, v, p0;
+        uint64_t meta, off;
+        __device__ __forceinline__ uint32_t pieces() const { return (uint32_t)(meta >> 32); }
+    };
+    auto slices = [&](uint64_t meta) -> uint32_t {
         // more k-mers than the table takes for sure: one pass per slice of the keys' hashes
-        const uint32_t V = N == 0 ? 0u : N <= t.max_kmers ? 1u : (N + t.slice_kmers - 1) / t.slice_kmers;
-        if (V == 0 && tid < (uint32_t)(meta_n >> 32)) first_n = t.pieces[off_n + tid];
-        for (uint32_t v = 0; v < V; v++) {
-            uint32_t wbase = 0;   // half words staged so far
-            for (uint32_t p0 = 0; p0 < np; p0 += B) {
-                const uint32_t nb = np - p0 < B ? np - p0 : B;
-                uint64_t start = 0;
-                uint32_t n = 0, nw = 0, rank = 0;
-                if (tid < nb) {
-                    const uint64_t d = p0 ? in[p0 + tid] : first;
-                    start = piece_start(d);
-                    n = piece_kmers(d);
-                    nw = ((uint32_t)(start & 15) + n + k + 14) >> 4;
-                    // segments of kSeg k-mers, and one of the rest: ordered by length, so
-                    // that the lanes of a wave roll equally far
-                    if (n % kSeg) rank = atomicAdd(&g.cls()[n % kSeg], 1u);
+        const uint32_t N = (uint32_t)meta;
+        return N <= t.max_kmers ? 1u : (N + t.slice_kmers - 1) / t.slice_kmers;
+    };
+    auto meta_at = [&](uint32_t j) -> uint64_t { return j < n_tab ? t.tab_cnt[j] : 0ull; };
+    auto off_at = [&](uint32_t j) -> uint64_t { return j < n_tab ? t.tab_off[j] : 0ull; };
+    Batch cur{blockIdx.x, 0, 0, uniform(meta_at(blockIdx.x)), uniform(off_at(blockIdx.x))};
+    uint64_t meta_f = meta_at(blockIdx.x + G), off_f = off_at(blockIdx.x + G);   // of the sub-table after nxt's
+    auto advance = [&](Batch& x) {
+        if (x.p0 + B < x.pieces()) {
+            x.p0 += B;
+        } else if (x.v + 1 < slices(x.meta)) {
+            x.v++;
+            x.p0 = 0;
+        } else {
+            x = Batch{x.j + G, 0, 0, uniform(meta_f), uniform(off_f)};
+            meta_f = meta_at(x.j + G);
+            off_f = off_at(x.j + G);
+        }
+    };
+    auto piece_of = [&](const Batch& x) -> uint64_t {   // this thread's
+        return x.p0 + tid < x.pieces() ? t.pieces[x.off + x.p0 + tid] : 0ull;
+    };
+    uint64_t x[2 * kQuads];
+    auto request = [&](uint64_t d, bool have) {
+        const uint32_t h = have ? (uint32_t)((piece_start(d) & 31) + piece_kmers(d) + k + 14) >> 4 : 0u;   // half words from its first word
+        const uint64_t* src = a.packed + (piece_start(d) >> 5);
+#pragma unroll
+        for (uint32_t e = 0; e < kQuads; e++) {
+            x[2 * e] = 4 * e < h ? src[2 * e] : 0ull;
+            x[2 * e + 1] = 4 * e < h ? src[2 * e + 1] : 0ull;
+        }
+    };
+    uint64_t d = piece_of(cur);
+    request(d, cur.p0 + tid < cur.pieces());
+    Batch nxt = cur;
+    advance(nxt);
+    uint64_t d_nxt = piece_of(nxt);
+    uint32_t hbase = 0;   // half words staged so far
+    while (cur.j < n_tab) {
+        const uint64_t t0 = t.stage_clocks ? wall_clock64() : 0;
+        const uint32_t np = cur.pieces(), V = slices(cur.meta), v = cur.v;
+        const bool last = cur.p0 + B >= np;   // of the sub-table's pieces
+        // one piece per thread
+        const uint64_t start = piece_start(d);
+        const uint32_t n = cur.p0 + tid < np ? piece_kmers(d) : 0u;
+        const uint32_t nh = n ? ((uint32_t)(start & 15) + n + k + 14) >> 4 : 0u;
+        const uint32_t odd = (uint32_t)(start >> 4) & 1u, nq = (nh + odd + 3) >> 2;   // its bases: whole words, 16 bytes at a time
+        const uint64_t* src = a.packed + (start >> 5);
+        // segments of kSeg k-mers, and one of the rest: ordered by length, so that
+        // the lanes of a wave roll equally far
+        const uint32_t rest = n % kSeg;
+        const uint32_t mine = nh | ((n / kSeg) << 16);
+        const uint32_t incl = wave_incl_sum(mine);
+        uint32_t rank = 0, add = 0;   // lane c: the wave's segments of c k-mers; lane 0: the sums
+#pragma unroll
+        for (uint32_t c = 1; c < kSeg; c++) {
+            const uint64_t m = __ballot(rest == c);
+            if (rest == c) rank = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+            if (lane == c) add = (uint32_t)__popcll(m);
+        }
+        if (lane == 0) add = __builtin_amdgcn_readlane(incl, 63);
+        uint32_t from = 0;
+        if (lane < kSeg) from = atomicAdd(&cls[lane], add);
+        const uint32_t pre = __builtin_amdgcn_readlane(from, 0) + incl - mine;
+        rank += __shfl(from, (int)rest);
+        const uint32_t hpre = hbase + (pre & 0xFFFFu), spre = pre >> 16;
+        __syncthreads();
+        const uint32_t total = cls[0];
+        uint32_t S = total >> 16, at = 0;
+#pragma unroll
+        for (uint32_t c = kSeg - 1; c > 0; c--) {
+            if (c == rest) at = S + rank;
+            S += cls[c];
+        }
+        for (uint32_t q = 0; q < nq; q += kQuads) {
+            if (q) {   // a longer piece than most
+#pragma unroll
+                for (uint32_t e = 0; e < kQuads; e++) {
+                    x[2 * e] = q + e < nq ? src[2 * (q + e)] : 0ull;
+                    x[2 * e + 1] = q + e < nq ? src[2 * (q + e) + 1] : 0ull;
                 }
-                uint32_t total;
-                const uint32_t pre = block_excl_scan(nw | ((n / kSeg) << 16), g.wsum(), total);
-                const uint32_t wpre = wbase + (pre & 0xFFFFu), spre = pre >> 16, F = total >> 16;
-                uint32_t S = F, at = 0;
-                for (uint32_t c = kSeg - 1; c > 0; c--) {
-                    const uint32_t x = g.cls()[c];
-                    if (c == n % kSeg) at = S + rank;
-                    S += x;
-                }
-                if (tid < nb) {
-                    g.piece()[tid] = ((start >> 4) << 16) | nw;
-                    g.pbase()[tid] = wpre;
-                }
-                for (uint32_t s0 = 0; s0 < S; s0 += Sh::segs) {
-                    if (s0) __syncthreads();
-                    const uint32_t o = 16u * wpre + (uint32_t)(start & 15);
-                    for (uint32_t i = 0; i < n / kSeg; i++) {
-                        const uint32_t x = spre + i - s0;
-                        if (x < Sh::segs) segs[x] = (o + i * kSeg) | ((kSeg - 1u) << kSegBaseBits);
-                    }
-                    if (n % kSeg && at - s0 < Sh::segs)
-                        segs[at - s0] = (o + (n & ~(kSeg - 1u))) | ((n % kSeg - 1u) << kSegBaseBits);
-                    if (s0 == 0) {
-                        __syncthreads();
-                        if (tid < 8) g.cls()[tid] = 0;   // (read by every thread before the barrier)
-                        // G lanes copy a piece's half words, four pieces of a group in flight
-                        const uint32_t sub = tid & (G - 1), stride = B >> t.group_log2;
-                        for (uint32_t p = tid >> t.group_log2; p < nb; p += 4 * stride) {
-                            uint64_t info[4];
-                            uint32_t to[4], x[4];
-#pragma unroll
-                            for (uint32_t e = 0; e < 4; e++) {
-                                const uint32_t pp = p + e * stride;
-                                info[e] = pp < nb ? g.piece()[pp] : 0ull;
-                                to[e] = pp < nb ? g.pbase()[pp] : 0u;
-                            }
-#pragma unroll
-                            for (uint32_t e = 0; e < 4; e++)   // a word's first 16 bases are its high half
-                                x[e] = sub < (uint32_t)(info[e] & 0xFFFFu) ? packed[((info[e] >> 16) + sub) ^ 1] : 0u;
-#pragma unroll
-                            for (uint32_t e = 0; e < 4; e++) {
-                                const uint32_t m = (uint32_t)(info[e] & 0xFFFFu);
-                                if (sub < m) bases[to[e] + sub] = x[e];
-                                for (uint32_t i = sub + G; i < m; i += G)
-                                    bases[to[e] + i] = packed[((info[e] >> 16) + i) ^ 1];
-                            }
-                        }
-                        // the next sub-table's pieces arrive while this one is counted
-                        if (v + 1 == V && p0 + B >= np && tid < (uint32_t)(meta_n >> 32)) first_n = t.pieces[off_n + tid];
-                    }
-                    __syncthreads();
-                    const uint32_t sn = S - s0 < Sh::segs ? S - s0 : Sh::segs;
-                    for (uint32_t x = tid; x < sn; x += B) {
-                        const uint32_t sg = segs[x];
-                        const uint32_t o0 = sg & ((1u << kSegBaseBits) - 1u), len = (sg >> kSegBaseBits) + 1u;
-                        uint32_t fw[D], rc[D];
-                        window<D>(b32, o0, tail_mask, fw);
-                        revcomp<D>(fw, pad, tail_mask, rc);
-                        // the bases that follow the first k-mer (at most kSeg - 1)
-                        uint32_t nx[1];
-                        window<1>(b32, o0 + k, 0xFFFFFFFFu, nx);
-                        for (uint32_t i = 0;;) {
-                            insert<D, B>(a, t, g, slots, b32, fw, rc, o0 + i, tail_mask, kx, V, v);
-                            if (++i >= len) break;
-                            const uint32_t bb = nx[0] >> 30;
-                            nx[0] <<= 2;
-#pragma unroll
-                            for (int q = 0; q + 1 < D; q++) fw[q] = funnel(fw[q], fw[q + 1], 30);
-                            fw[D - 1] = (fw[D - 1] << 2) | (bb << pad);
-#pragma unroll
-                            for (int q = D - 1; q > 0; q--) rc[q] = funnel(rc[q - 1], rc[q], 2);
-                            rc[0] = (rc[0] >> 2) | ((3u - bb) << 30);
-                            rc[D - 1] &= tail_mask;
-                        }
-                    }
-                }
-                wbase += total & 0xFFFFu;
-                if (p0 + B < np) __syncthreads();   // the batch's segments and piece table are done with
             }
+#pragma unroll
+            for (uint32_t e = 0; e < 4 * kQuads; e++) {
+                const uint32_t i = 4 * q + e - odd;   // (wraps for the half word before the piece)
+                if (i < nh) bases[hpre + i] = (uint32_t)(x[e >> 1] >> (e & 1 ? 0 : 32));
+            }
+        }
+        d = d_nxt;
+        request(d, nxt.p0 + tid < nxt.pieces());
+        cur = nxt;
+        advance(nxt);
+        d_nxt = piece_of(nxt);
+        const uint32_t ref = ref_of(16u * hpre + (uint32_t)(start & 15));
+        uint32_t s0 = 0;
+        do {
+            if (s0) __syncthreads();
+            for (uint32_t i = 0; i < n / kSeg; i++) {
+                const uint32_t y = spre + i - s0;
+                if (y < Sh::segs) segs[y] = (ref + 2 * i * kSeg) | ((kSeg - 1u) << kSegLenAt);
+            }
+            if (rest && at - s0 < Sh::segs) segs[at - s0] = (ref + 2 * (n - rest)) | ((rest - 1u) << kSegLenAt);
             __syncthreads();
-            // dump: count the pairs and the histogram, reserve, then write and clear
-            uint32_t mine = 0;   // the wave's pairs (uniform)
-            for (uint32_t s0 = 0; s0 < C; s0 += B) {
-                const uint32_t s = s0 + tid;
-                const uint32_t c = s < C ? ((const uint32_t*)(slots + s))[0] & 0xFFFFu : 0u;
-                const uint64_t ones = __ballot(c == 1u);
-                if (ones && lane == (uint32_t)__builtin_ctzll(ones)) atomicAdd(&hist[1], (uint32_t)__popcll(ones));
+            if (s0 == 0 && tid < 8) cls[tid] = 0;   // (every thread has read them)
+            const uint32_t sn = S - s0 < Sh::segs ? S - s0 : Sh::segs;
+            uint32_t* queue = g.retries();
+            uint32_t qn = 0;   // queued k-mers of the wave
+            for (uint32_t y0 = wave * 64; y0 < sn; y0 += B) {
+                const uint32_t sg = segs[y0 + lane < sn ? y0 + lane : sn - 1];
+                const uint32_t ref0 = sg & ((1u << kSegLenAt) - 1u);
+                const uint32_t len = y0 + lane < sn ? (sg >> kSegLenAt) + 1u : 0u;
+                const uint32_t most = __builtin_amdgcn_readfirstlane(len);   // (they never increase)
+                uint32_t fw[D], rc[D];
+                window<D>(b32, ref0, tail_mask, fw);
+                revcomp<D>(fw, pad, tail_mask, rc);
+                // the bases that follow the first k-mer (at most kSeg - 1)
+                uint32_t nx[1];
+                window<1>(b32, ref0 + 2 * k, 0xFFFFFFFFu, nx);
+                for (uint32_t i = 0;;) {
+                    Probe p;
+                    bool left = false;
+                    if (i < len && make_probe<D, B>(a, t, g, fw, rc, ref0 + 2 * i, kx, V, v, p)) {
+                        left = probe_bucket<D>(slots, b32, p, fastrange32(p.hash, t.buckets), fw, rc, tail_mask) != kSettled;
+                        if (t.probe_hist && !left) atomicAdd(&g.probes()[1], 1u);
+                    }
+                    const uint64_t m = __ballot(left);
+                    if (left) {
+                        const uint32_t q = qn + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                        if (q < Sh::retry) queue[q] = ref0 + 2 * i;
+                        else insert<D, B>(a, t, g, slots, b32, p, fw, rc, tail_mask, kx);
+                    }
+                    qn += (uint32_t)__popcll(m);
+                    qn = qn < Sh::retry ? qn : Sh::retry;
+                    if (++i >= most) break;
+                    const uint32_t bb = nx[0] >> 30;
+                    nx[0] <<= 2;
+#pragma unroll
+                    for (int q = 0; q + 1 < D; q++) fw[q] = funnel(fw[q], fw[q + 1], 30);
+                    fw[D - 1] = (fw[D - 1] << 2) | (bb << pad);
+#pragma unroll
+                    for (int q = D - 1; q > 0; q--) rc[q] = funnel(rc[q - 1], rc[q], 2);
+                    rc[0] = (rc[0] >> 2) | ((3u - bb) << 30);
+                    rc[D - 1] &= tail_mask;
+                }
+                if (qn >= 64) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    qn -= 64;
+                    retry<D, B>(a, t, g, slots, b32, queue + qn, 64, pad, tail_mask, kx);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (qn) retry<D, B>(a, t, g, slots, b32, queue, qn, pad, tail_mask, kx);
+            s0 += Sh::segs;
+        } while (s0 < S);
+        hbase += total & 0xFFFFu;
+        __syncthreads();   // the segments are done with; after the last batch, the slots are final
+        if (!last) continue;
+        hbase = 0;
+        // (what was requested ahead has arrived: nothing that follows waits for the stores of the dump)
+#pragma unroll
+        for (uint32_t e = 0; e < 2 * kQuads; e++) asm volatile("" : "+v"(x[e]));
+        asm volatile("" : "+v"(d_nxt), "+v"(meta_f), "+v"(off_f));
+        // dump: the pairs are counted and places for them reserved; while that is on
+        // its way the histogram is raised; then full waves of pairs are
+        // written from a queue and the slots cleared
+        uint32_t ones = 0, pairs = 0;   // of the wave (uniform)
+        for (uint32_t s = tid; s < CP; s += 4 * B) {
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++) {
+                const uint32_t c = s + i * B < CP ? ((const uint32_t*)(slots + s + i * B))[0] & 0xFFFFu : 0u;
+                ones += (uint32_t)__popcll(__ballot(c == 1u));
+                pairs += (uint32_t)__popcll(__ballot(c >= a.threshold));   // (a threshold is at least 1)
+            }
+        }
+        if (lane == 0) {
+            g.sums()[wave] = pairs;
+            if (ones) atomicAdd(&hist[1], ones);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            uint32_t all = 0;
+            for (uint32_t i = 0; i < B / 64; i++) all += g.sums()[i];
+            *g.base() = all ? add_dev(a.n_out, (uint64_t)all) : 0ull;
+        }
+        for (uint32_t s = tid; s < CP; s += 4 * B) {
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++) {
+                const uint32_t c = s + i * B < CP ? ((const uint32_t*)(slots + s + i * B))[0] & 0xFFFFu : 0u;
+                wmax = c > wmax ? c : wmax;
                 if (c > 1u) {
                     if (c < kLdsHist) atomicAdd(&hist[c], 1u);
                     else add_dev(&a.hist[c], 1ull);   // at most 65535, the last bucket
                 }
-                wmax = c > wmax ? c : wmax;
-                mine += (uint32_t)__popcll(__ballot(c != 0u && c >= a.threshold));
             }
-            if (lane == 0) g.wsum()[wave] = mine;
-            __syncthreads();
-            if (tid == 0) {
-                uint32_t all = 0;
-                for (uint32_t i = 0; i < B / 64; i++) all += g.wsum()[i];
-                *g.base() = all ? add_dev(a.n_out, (uint64_t)all) : 0ull;
+        }
+        __syncthreads();
+        uint64_t pos = *g.base();
+        for (uint32_t i = 0; i < wave; i++) pos += g.sums()[i];
+        uint64_t* queue = g.queue();
+        uint32_t qn = 0;
+        for (uint32_t s = tid; s < CP; s += 4 * B) {
+            uint64_t e[4];
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++) {
+                e[i] = s + i * B < CP ? slots[s + i * B] : 0ull;
+                if (s + i * B < CP) slots[s + i * B] = 0;
             }
-            __syncthreads();
-            uint64_t pos = *g.base();
-            for (uint32_t i = 0; i < wave; i++) pos += g.wsum()[i];
-            uint64_t* queue = g.queue();
-            uint32_t qn = 0;
-            for (uint32_t s0 = 0; s0 < C; s0 += B) {
-                const uint32_t s = s0 + tid;
-                const uint64_t e = s < C ? slots[s] : 0ull;
-                if (e) slots[s] = 0;
-                const uint32_t c = (uint32_t)e & 0xFFFFu;
-                const bool want = c != 0u && c >= a.threshold;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++) {
+                const bool want = ((uint32_t)e[i] & 0xFFFFu) >= a.threshold;
                 const uint64_t m = __ballot(want);
-                if (want) queue[qn + __popcll(m & ((1ull << lane) - 1ull))] = e;
+                if (m == 0) continue;
+                const uint32_t at = qn + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                if (want && at < 64) queue[at] = e[i];
                 qn += (uint32_t)__popcll(m);
                 if (qn >= 64) {
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                     emit<D, B>(a, b32, queue, 64, pos, pad, tail_mask);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                     pos += 64;
                     qn -= 64;
-                    const uint64_t rest = queue[64 + lane];
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                    queue[lane] = rest;
+                    if (want && at >= 64) queue[at - 64] = e[i];
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if (qn) emit<D, B>(a, b32, queue, qn, pos, pad, tail_mask);
-            __syncthreads();
         }
-        if (t.stage_clocks && tid == 0 && V) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (qn) emit<D, B>(a, b32, queue, qn, pos, pad, tail_mask);
+        __syncthreads();
+        if (t.stage_clocks && tid == 0) {
             add_dev(&t.stage_clocks[3], wall_clock64() - t0);
             add_dev(&t.stage_clocks[7], 1ull);
         }
-        j = jn;
-        meta = meta_n;
-        off = off_n;
-        first = first_n;
     }
     flush_max(a.max_count, wmax);
     __syncthreads();
