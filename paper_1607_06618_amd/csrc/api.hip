@@ -112,11 +112,13 @@ uint64_t bin_layout(uint64_t cap, uint32_t n_bins, void* ws, BinLayout* L) {
     l.list_desc = c.take<uint64_t>(cap + kListSlack);
     l.list_bin = c.take<uint32_t>(cap + kListSlack);
     l.desc = c.take<uint64_t>(cap);
-    l.bin_count = c.take<uint32_t>(n_bins);
     l.bin_fill = c.take<uint32_t>(n_bins);
     l.bin_off = c.take<uint64_t>(n_bins + 1);
     l.bin_kmers = c.take<uint64_t>(n_bins);
-    l.scalars = c.take<uint64_t>(4);   // [0] n_superm [1] list slots handed out
+    // [0] n_superm [1] list slots handed out; then the counts, to be cleared with them
+    static_assert(kBinCopies % 2 == 0, "whole 64-bit words");
+    l.scalars = c.take<uint64_t>(4 + kBinCopies / 2 * (uint64_t)n_bins);
+    l.bin_count = (uint32_t*)(l.scalars + 4);
     if (L) *L = l;
     return c.used;
 }
@@ -348,7 +350,7 @@ PieceSizing piece_sizing(const gerbil_params* p, const gerbil_bins* bins) {
     PieceSizing z;
     // One workgroup of 1024 threads per CU or two of 512: the single large
     // table wastes less on the spread of group sizes and on dumps (count step
-    // of 107 M 65-mers 24.5 ms against 27.6 ms; 28-mers 8.9 / 9.7, 200-mers
+    // of 1.7 G 65-mer windows 24.5 ms against 27.6 ms; 28-mers 8.9 / 9.7, 200-mers
     // 8.5 / 9.1). Beyond k = 256 a thread of 1024 has too few registers for the
     // key's two strands.
     z.block = p->block == 512 || p->k > 256 ? 512u : 1024u;
@@ -898,8 +900,7 @@ int32_t gerbil_bin(const gerbil_encoded* enc, const gerbil_params* p, void* ws, 
     a.bin_kmers = L.bin_kmers;
     a.desc = L.desc;
     a.status = enc->status;
-    hipError_t e = launch_fill_u64(L.scalars, 4, 0, stream);
-    if (e == hipSuccess) e = launch_fill_u32(L.bin_count, p->n_bins, 0, stream);
+    hipError_t e = launch_fill_u64(L.scalars, 4 + kBinCopies / 2 * (uint64_t)p->n_bins, 0, stream);
     uint64_t n_tiles = (enc->n_bytes + kTile - 1) / kTile;
     uint64_t g = std::max<uint64_t>(n_tiles, 1);
     if (g > kMaxTileGrid) g = kMaxTileGrid;   // bounds the list's slack (one partial chunk per workgroup)

@@ -10,16 +10,22 @@
 // that minimizer, so every occurrence of a canonical k-mer lands in one bin
 // (the partition property of Sec. 2.1).
 //
-// GPU design: the read stream is cut into tiles of kTile k-mer start
-// positions. A workgroup computes the m-mer ranks of its tile plus a halo of
-// w = k-m+1 positions (each thread rolls the canonical m-mer over a run of
-// positions), takes the minimum of every window of w ranks (each thread
-// covers a run of windows as suffix minimum + shared middle + prefix
-// minimum), finds super-mer starts with wave ballots, and writes
-// one descriptor per super-mer piece (super-mers are also cut at tile
-// boundaries; both pieces keep the same bin). Per-bin super-mer counts are
-// privatised in LDS. A scan and an LDS-privatised scatter then group the
-// descriptors by bin.
+// The read stream is cut into tiles of kTile k-mer start positions; super-mers
+// are also cut at tile boundaries (both pieces keep the same bin). A workgroup
+// takes runs of consecutive tiles. A thread owns 8 positions of each: it
+// computes the ranks of their m-mers for the next tile while it takes the
+// minima of this one's windows of w = k-m+1 ranks, each as the suffix minimum
+// of its own ranks (registers), the shared middle (minima of the threads'
+// blocks) and the prefix minimum of the ranks where the windows end. Then
+// one descriptor per super-mer piece is written into the workgroup's chunk of
+// the list. Per-bin super-mer counts are privatised
+// in LDS. A scan and an LDS-privatised scatter then group the descriptors by
+// bin.
+//
+// The tile kernel is bound by vector issue (28 instructions a position, 75 %
+// of the cycles): 3.0 G bases at k = 65 take 3.0 ms, against 6.8 ms when ranks
+// were rolled one by one, windows read their ends rank by rank and one lane in
+// two wrote descriptors. The descriptors are 1.0 GB of that, 0.2 ms.
 #include "../../include/gerbil.h"
 #include "common.h"
 #include "internal.h"
@@ -27,26 +33,14 @@
 namespace gerbil {
 
 constexpr uint32_t kBinBlock = 256;
-// Longest window w = k - m + 1 a tile kernel serves: one instantiation for
-// w <= 256, one for the longest keys (the halo of ranks grows with w).
-constexpr uint32_t kMaxWShort = 256;
-constexpr uint32_t kMaxWLong = 32 * GERBIL_MAX_W;
-// ranks for positions P0-1 .. P0+kTile-1+w-1
-template <uint32_t MW> constexpr uint32_t rank_len() { return kTile + MW; }
-constexpr uint32_t kWordsPerTile = kTile / 64;
-
-// The same rank for m-mers held in 32 bits (m <= 15: 30 bits; the moved codes
-// c + 4^m stay below 2^31).
-__device__ __forceinline__ uint32_t rank_of32(uint32_t fw, uint32_t rc, uint32_t m, uint32_t order,
-                                              const uint32_t* __restrict__ table) {
-    uint32_t c = fw < rc ? fw : rc;
-    if (order == GERBIL_ORDER_TABLE) return table[c];
-    if (order == 0 && m >= 3) {
-        const uint32_t head = c >> (2 * m - 6);
-        if (head == 0 /* AAA */ || head == 4 /* ACA */) c += 1u << (2 * m);
-    }
-    return c;
-}
+constexpr uint32_t kPer = 8;                                       // positions per thread
+static_assert(kTile == kBinBlock * kPer, "one run of positions per thread");
+// Ranks past the tile that its last windows reach (w <= 32 GERBIL_MAX_W, and
+// the whole run of a thread).
+constexpr uint32_t kHalo = 64;                                     // threads' runs
+constexpr uint32_t kRow = kBinBlock + kHalo;
+static_assert(kPer * kHalo >= 32 * GERBIL_MAX_W + 2 * kPer, "the longest window ends in the halo");
+constexpr uint32_t kTileRun = 16;                                  // consecutive tiles of a workgroup at most
 
 __device__ __forceinline__ uint32_t rank_of(uint64_t fw, uint64_t rc, uint32_t m, uint32_t order,
                                             const uint32_t* __restrict__ table) {
@@ -59,281 +53,253 @@ __device__ __forceinline__ uint32_t rank_of(uint64_t fw, uint64_t rc, uint32_t m
     return (uint32_t)c;
 }
 
-template <uint32_t MW> constexpr uint32_t rank_per() { return (rank_len<MW>() + kBinBlock - 1) / kBinBlock; }
-constexpr uint32_t kMinPer = (kTile + 1 + kBinBlock - 1) / kBinBlock;      // minimizers per thread
-// The bases a thread's ranks need (kRankPer m-mers, m <= 15) start at most 31
-// bases into a packed word, so they lie in that word and the next.
-static_assert(31 + rank_per<kMaxWLong>() - 1 + 15 <= 64, "a rank run must fit in two packed words");
-static_assert(15 + rank_per<kMaxWLong>() - 1 <= 32, "a rank run must fit in the 32 bases from its start");
-static_assert(kWordsPerTile <= kBinBlock, "one bitmap word per thread");
-
-// Position of the n-th (from 0) set bit of x; x has more than n set bits.
-__device__ __forceinline__ uint32_t select_bit(uint64_t x, uint32_t n) {
-    uint32_t pos = 0;
-#pragma unroll
-    for (uint32_t s = 32; s >= 1; s >>= 1) {
-        const uint32_t c = (uint32_t)__popcll(x & ((1ull << s) - 1ull));
-        if (n >= c) {
-            n -= c;
-            x >>= s;
-            pos += s;
-        }
-    }
-    return pos;
-}
-
-// Global data one tile needs, loaded one tile ahead into registers.
+// Global data a thread needs for its 8 positions of a tile, loaded ahead.
 struct TileFetch {
-    uint64_t w0, w1;   // the two packed words of this thread's rank run
-    uint64_t ok;       // threads < kWordsPerTile: one word of the valid-window bitmap
+    uint32_t a, b;     // the 32 bases from the 16-base half that holds the first position
+    uint32_t ok, ok0;  // valid-window bits of the positions (8), and of the 8 before them
 };
 
-template <uint32_t MW>
-__device__ __forceinline__ TileFetch tile_fetch(const BinArgs& a, uint64_t tile, uint64_t n_tiles, uint64_t n_mask) {
-    TileFetch f{0ull, 0ull, 0ull};
-    if (tile >= n_tiles) return f;
-    const int64_t P0 = (int64_t)(tile * kTile);
-    const int64_t j0 = P0 - 1 + (int64_t)(threadIdx.x * rank_per<MW>());
-    if (j0 < (int64_t)a.n_bytes) {   // j0 >= -1: word -1 is the zero pad; q + 1 <= n_words
-        const int64_t q = j0 >> 5;
-        f.w0 = a.packed[q];
-        f.w1 = a.packed[q + 1];
-    }
-    if (threadIdx.x < kWordsPerTile) {
-        const uint64_t qq = (uint64_t)(P0 >> 6) + threadIdx.x;
-        f.ok = qq < n_mask ? a.kmer_ok[qq] : 0ull;
-    }
+__device__ __forceinline__ TileFetch tile_fetch(const BinArgs& a, uint64_t tile, bool wanted) {
+    TileFetch f{0, 0, 0, 0};
+    const uint64_t p = tile * kTile + threadIdx.x * kPer;
+    if (!wanted || p >= a.n_bytes) return f;
+    const uint32_t* P = (const uint32_t*)a.packed;   // a word's first 16 bases are its high half
+    const uint8_t* ok = (const uint8_t*)a.kmer_ok;
+    const uint64_t h = p >> 4;                       // (h + 1) / 2 is at most one word past the last
+    f.a = P[h ^ 1];
+    f.b = P[(h + 1) ^ 1];
+    f.ok = ok[p >> 3];
+    if (p) f.ok0 = ok[(p >> 3) - 1];
     return f;
 }
 
-// Base at offset o (0..63) of the 64-base pair (w0, w1).
-__device__ __forceinline__ uint64_t pair_base(uint64_t w0, uint64_t w1, uint32_t o) {
-    const uint64_t w = o < 32 ? w0 : w1;
-    return (w >> (62 - 2 * (o & 31))) & 3ull;
+// Ranks of the m-mers at a thread's 8 positions. Forward and reverse-complement
+// codes are cut out of 32 bases of either strand by constant shifts, left-
+// aligned with whatever follows them below: the smaller one is the same, and
+// the last shift drops the rest. Six instructions a position.
+__device__ __forceinline__ void ranks8(const BinArgs& a, const TileFetch& f, uint32_t (&r)[kPer]) {
+    const bool mid = threadIdx.x & 1u;   // the first position is the 9th base of its half word
+    const uint32_t hi = mid ? funnel(f.a, f.b, 16) : f.a;
+    const uint32_t lo = mid ? f.b << 16 : f.b;
+    // reverse complement; the m-mer at position 7 in the top bits
+    const uint64_t y = (((uint64_t)revcomp16(lo) << 32) | revcomp16(hi)) << (2 * (32 - a.m) - 14);
+    const uint32_t yhi = (uint32_t)(y >> 32), ylo = (uint32_t)y;
+    const uint32_t down = 32 - 2 * a.m;
+    // KMC2 order: AAA and ACA (first bits 000000 and 000100) come behind all
+    // others; nothing is left of the saturated difference for the rest
+    const uint32_t head = a.order == 0 && a.m >= 3 ? 0xEC000000u : 0u, one = head ? 1u : 0u;
+#pragma unroll
+    for (uint32_t e = 0; e < kPer; e++) {
+        const uint32_t fw = e ? funnel(hi, lo, 32 - 2 * e) : hi;
+        const uint32_t rc = e < 7 ? funnel(yhi, ylo, 18 + 2 * e) : yhi;
+        const uint32_t c = fw < rc ? fw : rc;
+        const uint32_t moved = __builtin_elementwise_sub_sat(one, c & head);
+        r[e] = funnel(moved, c, down);   // moved 4^m + code
+    }
+    if (a.order == GERBIL_ORDER_TABLE) {
+#pragma unroll
+        for (uint32_t e = 0; e < kPer; e++) r[e] = a.rank_table[r[e]];
+    }
 }
 
-template <uint32_t MW>
-__global__ void __launch_bounds__(kBinBlock, 7) k_bin_tiles(BinArgs a) {
-    constexpr uint32_t kRankPer = rank_per<MW>();
-    // When a thread's run of ranks is one block of kMinPer positions, it also
-    // writes the block's minimum, and a window's middle part is read as block
-    // minima plus the ranks at its two ends.
-    constexpr bool kBlockMin = kRankPer == kMinPer;
-    constexpr uint32_t kBlocks = kBlockMin ? rank_len<MW>() / kMinPer : 1;
-    __shared__ uint32_t R[rank_len<MW>()];
-    __shared__ uint32_t BM[kBlocks];   // BM[j] = min R[j*kMinPer .. (j+1)*kMinPer), whole blocks below len
-    __shared__ uint32_t M[kTile + 1];
-    __shared__ uint64_t brk[kWordsPerTile];
-    __shared__ uint64_t stw[kWordsPerTile];
-    __shared__ uint64_t okS[kWordsPerTile];
-    __shared__ uint32_t wpre[kWordsPerTile + 1];
-    __shared__ uint64_t tile_base, tile_split, tile_base2;
-    extern __shared__ uint32_t bin_cnt[];   // [n_bins]
+// Minima of a thread's 8 windows, to M, and which of them differ from the one
+// before (the first window's bit on top). kR: (w - 1) mod 8, so that every
+// address is a constant away from the thread's column.
+template <uint32_t kR>
+__device__ __forceinline__ uint32_t window_minima(const uint32_t* R, const uint32_t* BM, uint32_t* M,
+                                                  const uint32_t (&cur)[kPer], uint32_t before, uint32_t q) {
+    const uint32_t tid = threadIdx.x;
+    const uint32_t* Rq = R + tid + q;
+    // [8 tid + 8, 8 tid + w - 1): in every one of these windows
+    uint32_t mid = 0xFFFFFFFFu;
+#pragma unroll
+    for (uint32_t e = 0; e < kR; e++) mid = min(mid, Rq[e * kRow]);
+    const uint32_t* B = BM + tid + 1;
+    uint32_t j = q - 1;
+    for (; j >= 6; j -= 6, B += 6)
+        mid = min(min(min(mid, min(B[0], B[1])), min(B[2], B[3])), min(B[4], B[5]));
+    if (j & 4) {
+        mid = min(min(mid, min(B[0], B[1])), min(B[2], B[3]));
+        B += 4;
+    }
+    if (j & 2) {
+        mid = min(mid, min(B[0], B[1]));
+        B += 2;
+    }
+    if (j & 1) mid = min(mid, B[0]);
+    uint32_t suf[kPer];
+    suf[7] = cur[7];
+#pragma unroll
+    for (int e = 6; e >= 0; e--) suf[e] = min(cur[e], suf[e + 1]);
+    uint32_t mn = min(min(before, suf[0]), mid), diff = 0;
+#pragma unroll
+    for (uint32_t e = 0; e < kPer; e++) {
+        constexpr uint32_t P = kPer;
+        mid = min(mid, Rq[((kR + e) % P) * kRow + (kR + e) / P]);   // the rank that this window ends with
+        const uint32_t v = min(suf[e], mid);
+        diff = diff + diff + (v != mn ? 1u : 0u);
+        M[e * kBinBlock + tid] = v;
+        mn = v;
+    }
+    return diff;
+}
 
-    const uint32_t tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
+__global__ void __launch_bounds__(kBinBlock, 6) k_bin_tiles(BinArgs a, uint32_t run) {
+    // Rank of position 8 j + e of the tile at row e, column j (the halo
+    // included): every access is to consecutive words across the lanes.
+    __shared__ uint32_t R[kPer * kRow];
+    __shared__ uint32_t BM[kRow];                     // minima of the columns
+    __shared__ uint32_t M[kPer * kBinBlock];          // minimizer of the window at position 8 j + e: row e, column j
+    __shared__ uint16_t Q[kBinBlock / 64][kPer * 64]; // starts of every wave
+    __shared__ uint64_t brk[kTile / 64];              // starts and positions without a window
+    __shared__ uint32_t cnt[kTileWaves];              // starts of every wave
+    __shared__ uint64_t s_chunk;
+    extern __shared__ uint32_t bin_cnt[];             // [n_bins]
+
+    const uint32_t tid = threadIdx.x, lane = __lane_id(), wave = uniform(tid >> 6);
     const uint32_t w = a.k - a.m + 1;
-    const uint64_t n_pos = a.n_bytes;
-    const uint64_t n_tiles = (n_pos + kTile - 1) / kTile;
-    const uint64_t n_mask = (n_pos + 63) >> 6;
+    const uint64_t n_tiles = (a.n_bytes + kTile - 1) / kTile;
     const uint32_t code_mask = (uint32_t)((1ull << (2 * a.m)) - 1ull);
-    const uint64_t mmask = (1ull << (2 * a.m)) - 1ull;
-    // list slots of this workgroup's current chunk [ch_cur, ch_end) (used by wave 0's last word lane)
-    uint64_t ch_cur = 0, ch_end = 0;
-    uint64_t n_mine = 0;   // pieces found by this workgroup, added to n_superm once at the end
+    const bool in_halo = tid * kPer < w + kPer;       // columns of the next tile that this one reads
+    // list slots of this workgroup's current chunk [ch_cur, ch_end): every wave
+    // keeps the same account. The first chunk is its own; more are reserved.
+    uint64_t ch_cur = (uint64_t)blockIdx.x * a.list_chunk, ch_end = ch_cur + a.list_chunk;
 
     for (uint32_t b = tid; b < a.n_bins; b += kBinBlock) bin_cnt[b] = 0;
 
-    TileFetch f = tile_fetch<MW>(a, blockIdx.x, n_tiles, n_mask);
-    for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const int64_t P0 = (int64_t)(tile * kTile);
-        const uint32_t len = kTile + w;   // ranks R[i] for positions P0-1+i
-        // 1. ranks: every thread rolls the canonical m-mer over its own run of
-        //    positions, from the two packed words fetched for it
-        {
-            const uint32_t i0 = tid * kRankPer;
-            const uint32_t i1 = i0 + kRankPer < len ? i0 + kRankPer : len;
-            const int64_t j0 = P0 - 1 + (int64_t)i0;
-            const uint32_t s0 = (uint32_t)(j0 & 31);
-            // the run's first m-mer and the bases rolled in after it all lie in the
-            // 32 bases from s0 (m + kRankPer - 1 <= 32); 32-bit arithmetic throughout
-            uint32_t fw = 0, rc = 0;
-            uint64_t nb = 0;   // the bases still to roll in, first one in the top two bits
-            if (i0 < i1) {
-                const uint64_t win = s0 ? ((f.w0 << (2 * s0)) | (f.w1 >> (64 - 2 * s0))) : f.w0;
-                fw = (uint32_t)(win >> (64 - 2 * a.m));
-                rc = (uint32_t)(revcomp32(win) & mmask);
-                nb = win << (2 * a.m);
-            }
-            // positions of this run inside the read stream, at most kRankPer
-            const int64_t n_left = (int64_t)n_pos - (P0 - 1 + (int64_t)i0);
-            const uint32_t n_in = n_left <= 0 ? 0u : n_left >= (int64_t)kRankPer ? kRankPer : (uint32_t)n_left;
-            uint32_t bmin = 0xFFFFFFFFu;
+    for (uint64_t t0 = (uint64_t)blockIdx.x * run; t0 < n_tiles; t0 += (uint64_t)gridDim.x * run) {
+        const uint64_t t1 = t0 + run < n_tiles ? t0 + run : n_tiles;
+        TileFetch f = tile_fetch(a, t0, true);
+        uint32_t cur[kPer];
+        ranks8(a, f, cur);
+        uint32_t ok = f.ok, ok0 = f.ok0;
+        f = tile_fetch(a, t0 + 1, t0 + 1 < t1 || in_halo);
+        for (uint64_t tile = t0; tile < t1; tile++) {
+            // 1. this tile's ranks to LDS (nothing reads the last tile's any
+            //    more), and the next one's: of the last tile of a run only
+            //    what the windows of this one reach
+            uint32_t nxt[kPer];
+            {
+                uint32_t bm = cur[0];
 #pragma unroll
-            for (uint32_t e = 0; e < kRankPer; e++) {
-                if (i0 + e < i1) {
-                    if (e > 0) {
-                        const uint32_t b2 = (uint32_t)(nb >> 62);
-                        nb <<= 2;
-                        fw = ((fw << 2) | b2) & code_mask;
-                        rc = (rc >> 2) | ((3u - b2) << (2 * a.m - 2));
+                for (uint32_t e = 0; e < kPer; e++) {
+                    R[e * kRow + tid] = cur[e];
+                    bm = min(bm, cur[e]);
+                }
+                BM[tid] = bm;
+            }
+            if (tile + 1 < t1 || wave * 64 * kPer < w + kPer) {
+                ranks8(a, f, nxt);
+                if (wave == 0) {
+                    uint32_t bm = nxt[0];
+#pragma unroll
+                    for (uint32_t e = 0; e < kPer; e++) {
+                        R[e * kRow + kBinBlock + lane] = nxt[e];
+                        bm = min(bm, nxt[e]);
                     }
-                    const uint32_t rk = e < n_in ? rank_of32(fw, rc, a.m, a.order, a.rank_table) : 0xFFFFFFFFu;
-                    R[i0 + e] = rk;
-                    bmin = min(bmin, rk);
+                    BM[kBinBlock + lane] = bm;
                 }
             }
-            if constexpr (kBlockMin) {
-                if (i0 + kMinPer <= len) BM[tid] = bmin;   // a whole block: i0 = tid * kMinPer
-            }
-            if (tid < kWordsPerTile) okS[tid] = f.ok;
-        }
-        // the next tile's loads are in flight while this one is processed
-        f = tile_fetch<MW>(a, tile + gridDim.x, n_tiles, n_mask);
-        __syncthreads();
-        // 2. minimizer of the k-mer at P0-1+i = min R[i .. i+w): each thread takes
-        //    a run of kMinPer positions; their windows share the middle part.
-        {
-            const uint32_t i0 = tid * kMinPer;
-            const uint32_t i1 = i0 + kMinPer < kTile + 1 ? i0 + kMinPer : kTile + 1;
-            if (i0 < i1) {
-                if (w <= 2 * kMinPer) {
-                    for (uint32_t i = i0; i < i1; i++) {
-                        uint32_t mn = 0xFFFFFFFFu;
-                        for (uint32_t t = 0; t < w; t++) mn = min(mn, R[i + t]);
-                        M[i] = mn;
-                    }
-                } else {
-                    // window [i, i+w) = [i, i1-1) + [i1-1, i0+w) + [i0+w, i+w)
-                    uint32_t mid = 0xFFFFFFFFu;
-                    const uint32_t lo = i1 - 1, hi = i0 + w;   // hi <= kTile + w = len
-                    const uint32_t jb = (lo + kMinPer - 1) / kMinPer, je = hi / kMinPer;
-                    if (kBlockMin && jb < je) {
-                        // whole blocks jb .. je-1 lie in [lo, hi) and below len
-                        for (uint32_t t = lo; t < jb * kMinPer; t++) mid = min(mid, R[t]);
-                        for (uint32_t j = jb; j < je; j++) mid = min(mid, BM[j]);
-                        for (uint32_t t = je * kMinPer; t < hi; t++) mid = min(mid, R[t]);
-                    } else {
-#pragma unroll 8
-                        for (uint32_t t = lo; t < hi; t++) mid = min(mid, R[t]);
-                    }
-                    uint32_t suf[kMinPer], pre[kMinPer];
-                    uint32_t run = 0xFFFFFFFFu;
-#pragma unroll
-                    for (int e = kMinPer - 1; e >= 0; e--) {   // suffix minima of [i, i1-1)
-                        const uint32_t i = i0 + e;
-                        if (i + 1 < i1) run = min(run, R[i]);
-                        suf[e] = run;
-                    }
-                    run = 0xFFFFFFFFu;
-#pragma unroll
-                    for (int e = 0; e < (int)kMinPer; e++) {   // prefix minima of [i0+w, i+w)
-                        pre[e] = run;
-                        const uint32_t t = i0 + w + e;
-                        if (i0 + e + 1 < i1) run = min(run, R[t]);
-                    }
-#pragma unroll
-                    for (int e = 0; e < (int)kMinPer; e++) {
-                        const uint32_t i = i0 + e;
-                        if (i < i1) M[i] = min(min(suf[e], mid), pre[e]);
-                    }
+            const uint32_t ok_nxt = f.ok, ok0_nxt = f.ok0;
+            f = tile_fetch(a, tile + 2, tile + 2 < t1 || (tile + 2 == t1 && in_halo));
+            __syncthreads();
+            // 2. minimizers: window e of the thread is ranks [8 tid + e, 8 tid + e + w).
+            const uint32_t before = R[7 * kRow + (tid ? tid - 1 : 0)];   // (any value for the tile's first)
+            uint32_t diff = 0;
+            if (w > kPer) {
+                const uint32_t q = (w - 1) / kPer;
+                switch ((w - 1) % kPer) {
+                    case 0: diff = window_minima<0>(R, BM, M, cur, before, q); break;
+                    case 1: diff = window_minima<1>(R, BM, M, cur, before, q); break;
+                    case 2: diff = window_minima<2>(R, BM, M, cur, before, q); break;
+                    case 3: diff = window_minima<3>(R, BM, M, cur, before, q); break;
+                    case 4: diff = window_minima<4>(R, BM, M, cur, before, q); break;
+                    case 5: diff = window_minima<5>(R, BM, M, cur, before, q); break;
+                    case 6: diff = window_minima<6>(R, BM, M, cur, before, q); break;
+                    default: diff = window_minima<7>(R, BM, M, cur, before, q); break;
                 }
-            }
-        }
-        __syncthreads();
-        // 3. super-mer starts and ends (ballot per 64 positions); the first
-        //    position of a tile always starts a piece (the tile cut)
-        for (uint32_t c = wave; c < kWordsPerTile; c += kBinBlock / 64) {
-            const uint64_t okw = okS[c];
-            const uint64_t okprev = c ? okS[c - 1] : 0ull;
-            bool ok = (okw >> lane) & 1ull;
-            bool ok_before = lane ? ((okw >> (lane - 1)) & 1ull) : ((okprev >> 63) & 1ull);
-            uint32_t t = c * 64 + lane;   // position P0 + t, minimizer M[t+1]
-            bool start = ok && (t == 0 || !ok_before || M[t + 1] != M[t]);
-            uint64_t sb = __ballot(start);
-            uint64_t bb = __ballot(!ok || start);
-            if (lane == 0) { stw[c] = sb; brk[c] = bb; }
-        }
-        __syncthreads();
-        // list slots for this tile's pieces: the rest of the workgroup's
-        // chunk first, then a new chunk (reserved only when the current one
-        // runs out), so only the unused end of a workgroup's last chunk is
-        // left as a hole
-        if (wave == 0) {
-            uint32_t n = lane < kWordsPerTile ? (uint32_t)__popcll(stw[lane]) : 0u;
-            uint32_t incl = n;
-            for (int off = 1; off < 64; off <<= 1) {
-                uint32_t y = __shfl_up(incl, off);
-                if (lane >= (uint32_t)off) incl += y;
-            }
-            if (lane < kWordsPerTile) wpre[lane] = incl - n;
-            if (lane == kWordsPerTile - 1) {
-                wpre[kWordsPerTile] = incl;
-                const uint64_t rem = ch_end - ch_cur;
-                uint64_t b1 = ch_cur, sp = incl, b2 = 0;
-                if (incl > rem) {
-                    const uint64_t need = incl - rem;
-                    const uint64_t take = need > kListChunk ? need : kListChunk;
-                    b2 = add_dev(a.list_used, take);
-                    sp = rem;
-                    ch_cur = b2 + need;
-                    ch_end = b2 + take;
-                } else {
-                    ch_cur += incl;
-                }
-                n_mine += incl;
-                tile_base = b1;
-                tile_split = sp;
-                tile_base2 = b2;
-            }
-        }
-        __syncthreads();
-        // 4. one descriptor per start: thread i takes starts i, i + kBinBlock, ...
-        //    of the tile, so the lanes stay busy however sparse the starts are
-        const uint32_t n_st = wpre[kWordsPerTile];
-        for (uint32_t q = tid; q < n_st; q += kBinBlock) {
-            uint32_t lo = 0, hi = kWordsPerTile;   // word of start q: last c with wpre[c] <= q
-            while (hi - lo > 1) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (wpre[mid] <= q) lo = mid; else hi = mid;
-            }
-            const uint32_t c = lo;
-            const uint32_t bit = select_bit(stw[c], q - wpre[c]);
-            const uint32_t t = c * 64 + bit;
-            const uint64_t above = (bit == 63) ? 0ull : (brk[c] & ~((2ull << bit) - 1ull));
-            uint32_t end = kTile;
-            if (above) {
-                end = c * 64 + (uint32_t)__builtin_ctzll(above);
             } else {
-                for (uint32_t d = c + 1; d < kWordsPerTile; d++) {
-                    if (brk[d]) { end = d * 64 + (uint32_t)__builtin_ctzll(brk[d]); break; }
+                uint32_t mn = before;
+                for (uint32_t i = 0; i + 1 < w; i++) mn = min(mn, R[i * kRow + tid]);
+#pragma unroll
+                for (uint32_t e = 0; e < kPer; e++) {
+                    uint32_t v = 0xFFFFFFFFu;
+                    for (uint32_t i = e; i < e + w; i++) v = min(v, R[(i % kPer) * kRow + i / kPer + tid]);
+                    diff = diff + diff + (v != mn ? 1u : 0u);
+                    M[e * kBinBlock + tid] = v;
+                    mn = v;
                 }
             }
-            const uint32_t nk = end - t;
-            const uint32_t mr = M[t + 1];
-            const uint32_t code = mr & code_mask;
-            uint32_t bin = a.bin_map ? a.bin_map[code] : (mr % a.n_bins);
-            if (bin >= a.n_bins) bin = a.n_bins - 1;   // defensive: a bad map must not index out of range
-            const uint64_t idx = q < tile_split ? tile_base + q : tile_base2 + (q - tile_split);
-            if (idx < a.list_cap) {
-                a.list_desc[idx] = ((uint64_t)(P0 + t) << 24) | nk;
-                a.list_bin[idx] = bin;
+            diff = __builtin_bitreverse32(diff) >> 24;
+            // 3. super-mer starts; the first position of a tile always starts a piece (the tile cut)
+            uint32_t st = ok & (diff | ~((ok << 1) | (ok0 >> 7)) | (tid == 0 ? 1u : 0u));
+            ((uint8_t*)brk)[tid] = (uint8_t)(st | ~ok);
+            const uint32_t mine = (uint32_t)__popc(st), incl = wave_incl_sum(mine);
+            const uint32_t n_st = __builtin_amdgcn_readlane(incl, 63);
+            for (uint32_t at = incl - mine; st; at++, st &= st - 1) Q[wave][at] = (uint16_t)(tid * kPer + __builtin_ctz(st));
+            if (lane == 0) cnt[wave] = n_st;
+            __syncthreads();
+            // 4. one descriptor per start. List slots: the rest of the chunk first,
+            //    then a new chunk (reserved only when the current one runs
+            //    out), so only the unused end of a workgroup's last chunk is
+            //    left as a hole. One address takes an atomic every 10 ns or
+            //    so: a chunk per wave and tile, of 512 slots, would bound the
+            //    kernel.
+            const uint32_t n0 = uniform(cnt[0]), n1 = n0 + uniform(cnt[1]), n2 = n1 + uniform(cnt[2]);
+            const uint32_t all = n2 + uniform(cnt[3]);
+            const uint64_t b1 = ch_cur;
+            uint64_t b2 = 0;
+            const uint32_t rest = (uint32_t)(ch_end - ch_cur), split = rest < all ? rest : all;
+            if (all > split) {
+                const uint32_t need = all - split, take = need > a.list_chunk ? need : a.list_chunk;
+                if (tid == 0) s_chunk = (uint64_t)gridDim.x * a.list_chunk + add_dev(a.list_used, (uint64_t)take);
+                __syncthreads();
+                b2 = uniform(s_chunk);
+                ch_cur = b2 + need;
+                ch_end = b2 + take;
+            } else {
+                ch_cur += all;
+            }
+            // (some 110 starts at k = 65: the waves take turns at them 64 at a
+            // time, rather than each its own in a third of its lanes)
+            for (uint32_t i = ((tid + (uint32_t)tile * 64) % kBinBlock); i < all; i += kBinBlock) {
+                const uint32_t v = (i >= n0 ? 1u : 0u) + (i >= n1 ? 1u : 0u) + (i >= n2 ? 1u : 0u);
+                const uint32_t t = Q[v][i - (v == 0 ? 0u : v == 1 ? n0 : v == 2 ? n1 : n2)], c = t >> 6, bit = t & 63;
+                uint64_t above = (brk[c] >> bit) >> 1;
+                uint32_t end = t + 1;
+                if (above) {
+                    end += (uint32_t)__builtin_ctzll(above);
+                } else {
+                    end = kTile;
+                    for (uint32_t d = c + 1; d < kTile / 64; d++) {
+                        if (brk[d]) { end = d * 64 + (uint32_t)__builtin_ctzll(brk[d]); break; }
+                    }
+                }
+                const uint32_t mr = M[(t % kPer) * kBinBlock + t / kPer];
+                uint32_t bin = a.bin_map ? a.bin_map[mr & code_mask] : (mr % a.n_bins);
+                if (bin >= a.n_bins) bin = a.n_bins - 1;   // defensive: a bad map must not index out of range
                 atomicAdd(&bin_cnt[bin], 1u);
-            } else {
-                set_status(a.status, ST_SUPERM_CAP);
+                const uint64_t idx = i < split ? b1 + i : b2 + (i - split);
+                if (idx < a.list_cap) {
+                    a.list_desc[idx] = ((tile * kTile + t) << 24) | (end - t);
+                    a.list_bin[idx] = bin;
+                } else {
+                    set_status(a.status, ST_SUPERM_CAP);
+                }
             }
+#pragma unroll
+            for (uint32_t e = 0; e < kPer; e++) cur[e] = nxt[e];
+            ok = ok_nxt;
+            ok0 = ok0_nxt;
         }
-        __syncthreads();
     }
     // the unused end of the last chunk is a hole
-    if (wave == 0) {
-        const uint64_t lo = __shfl(ch_cur, (int)kWordsPerTile - 1), hi = __shfl(ch_end, (int)kWordsPerTile - 1);
-        for (uint64_t i = lo + lane; i < hi; i += 64)
-            if (i < a.list_cap) a.list_bin[i] = kHole;
-        if (lane == kWordsPerTile - 1 && n_mine) add_dev(a.n_superm, n_mine);
-    }
+    for (uint64_t i = ch_cur + tid; i < ch_end; i += kBinBlock)
+        if (i < a.list_cap) a.list_bin[i] = kHole;
     __syncthreads();
+    uint32_t* total = a.bin_count + (blockIdx.x % kBinCopies) * a.n_bins;
     for (uint32_t b = tid; b < a.n_bins; b += kBinBlock)
-        if (bin_cnt[b]) atomicAdd(&a.bin_count[b], bin_cnt[b]);
+        if (bin_cnt[b]) atomicAdd(&total[b], bin_cnt[b]);
 }
 
 // Exclusive prefix of the per-bin super-mer counts (single workgroup).
@@ -345,7 +311,9 @@ __global__ void __launch_bounds__(1024) k_bin_scan(BinArgs a) {
     uint64_t s = 0;
     for (uint32_t e = 0; e < per; e++) {
         uint32_t b = tid * per + e;
-        uint64_t v = b < a.n_bins ? (uint64_t)a.bin_count[b] : 0ull;
+        uint64_t v = 0;
+        if (b < a.n_bins)
+            for (uint32_t c = 0; c < kBinCopies; c++) v += a.bin_count[c * a.n_bins + b];
         local[e] = s;
         s += v;
     }
@@ -366,48 +334,59 @@ __global__ void __launch_bounds__(1024) k_bin_scan(BinArgs a) {
             a.bin_kmers[b] = 0;
         }
     }
-    if (tid == 1023) a.bin_off[a.n_bins] = part[1023];
+    if (tid == 1023) {
+        a.bin_off[a.n_bins] = part[1023];
+        *a.n_superm = part[1023];
+    }
 }
 
 constexpr uint32_t kScatterPer = 16;   // descriptors per thread per chunk
+// Chunks of 16384 descriptors, so that a bin's share of one (32 of 512 bins)
+// is a few whole lines in the one L2 its workgroup writes through; shares of 8
+// from chunks of 4096 took 1.28 ms for 80 M descriptors, these 0.57 ms.
+// Lists that would not fill the chip with those take the small chunks.
+constexpr uint32_t kScatterBig = 1024;
+constexpr uint64_t kScatterBigFrom = 1ull << 23;   // list slots: two chunks per CU
 
-__global__ void __launch_bounds__(kBinBlock) k_bin_scatter(BinArgs a) {
-    extern __shared__ uint32_t sh[];
-    uint32_t* lh = sh;                  // [n_bins] counts in this chunk
-    uint32_t* lk = sh + a.n_bins;       // [n_bins] k-mers in this chunk
-    uint32_t* gb = sh + 2 * a.n_bins;   // [n_bins] global base of this chunk in the bin
-    // [n_bins] k-mers of this workgroup's chunks, added to the bins' totals once at the end
-    uint64_t* tk = (uint64_t*)(sh + 3 * a.n_bins + (a.n_bins & 1u));
+template <uint32_t B>
+__global__ void __launch_bounds__(B) k_bin_scatter(BinArgs a) {
+    extern __shared__ uint64_t sh[];
+    uint64_t* lh = sh;                              // [n_bins] count << 32 | k-mers in this chunk
+    uint64_t* tk = sh + a.n_bins;                   // [n_bins] k-mers of this workgroup's chunks, added to the bins' totals once at the end
+    uint32_t* gb = (uint32_t*)(sh + 2 * a.n_bins);  // [n_bins] place of this chunk's share in the list of bins
     const uint32_t tid = threadIdx.x;
-    uint64_t n = ld_dev(a.list_used);   // list slots handed out, holes included
+    uint64_t n = a.list_first + ld_dev(a.list_used);   // list slots handed out, holes included
     if (n > a.list_cap) n = a.list_cap;
-    const uint64_t chunk = (uint64_t)kBinBlock * kScatterPer;
-    for (uint32_t b = tid; b < a.n_bins; b += kBinBlock) tk[b] = 0;   // read back only by thread b % kBinBlock
+    const uint64_t chunk = (uint64_t)B * kScatterPer;
+    for (uint32_t b = tid; b < a.n_bins; b += B) tk[b] = 0;   // read back only by thread b % B
     for (uint64_t c0 = blockIdx.x * chunk; c0 < n; c0 += (uint64_t)gridDim.x * chunk) {
-        for (uint32_t b = tid; b < a.n_bins; b += kBinBlock) { lh[b] = 0; lk[b] = 0; }
-        __syncthreads();
+        for (uint32_t b = tid; b < a.n_bins; b += B) lh[b] = 0;
         uint64_t d[kScatterPer];
         uint32_t bn[kScatterPer], lr[kScatterPer];
 #pragma unroll
         for (uint32_t e = 0; e < kScatterPer; e++) {
-            uint64_t i = c0 + tid + (uint64_t)e * kBinBlock;
+            uint64_t i = c0 + tid + (uint64_t)e * B;
             bn[e] = 0xFFFFFFFFu;
+            d[e] = 0;
             if (i < n) {
                 bn[e] = a.list_bin[i];
-                if (bn[e] < a.n_bins) {
-                    d[e] = a.list_desc[i];
-                    lr[e] = atomicAdd(&lh[bn[e]], 1u);
-                    atomicAdd(&lk[bn[e]], (uint32_t)(d[e] & 0xFFFFFFu));
-                } else {
-                    bn[e] = 0xFFFFFFFFu;   // a hole
-                }
+                d[e] = a.list_desc[i];
             }
         }
         __syncthreads();
-        for (uint32_t b = tid; b < a.n_bins; b += kBinBlock) {
-            if (lh[b]) {
-                gb[b] = atomicAdd(&a.bin_fill[b], lh[b]);
-                tk[b] += lk[b];
+#pragma unroll
+        for (uint32_t e = 0; e < kScatterPer; e++) {
+            if (bn[e] < a.n_bins)
+                lr[e] = (uint32_t)(atomicAdd((unsigned long long*)&lh[bn[e]], (1ull << 32) | (d[e] & 0xFFFFFFull)) >> 32);
+            else
+                bn[e] = 0xFFFFFFFFu;   // a hole
+        }
+        __syncthreads();
+        for (uint32_t b = tid; b < a.n_bins; b += B) {
+            const uint64_t c = lh[b];
+            if (c) {
+                gb[b] = atomicAdd(&a.bin_fill[b], (uint32_t)(c >> 32));
+                tk[b] += (uint32_t)c;
             }
         }
         __syncthreads();
@@ -419,8 +398,21 @@ __global__ void __launch_bounds__(kBinBlock) k_bin_scatter(BinArgs a) {
         }
         __syncthreads();
     }
-    for (uint32_t b = tid; b < a.n_bins; b += kBinBlock)
+    for (uint32_t b = tid; b < a.n_bins; b += B)
         if (tk[b]) add_dev(&a.bin_kmers[b], tk[b]);
+}
+
+template <uint32_t B>
+hipError_t run_bin_scatter(const BinArgs& a, hipStream_t s) {
+    const size_t sh = 20 * (size_t)a.n_bins;
+    if (sh > 65536) {   // above the default limit of dynamic LDS per workgroup (n_bins > 3276)
+        const hipError_t e = hipFuncSetAttribute((const void*)k_bin_scatter<B>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+        if (e != hipSuccess) return e;
+    }
+    const uint64_t chunks = (a.list_cap + (uint64_t)B * kScatterPer - 1) / ((uint64_t)B * kScatterPer);
+    const uint32_t most = 2048 * 256 / B, g = (uint32_t)(chunks < most ? (chunks ? chunks : 1) : most);
+    hipLaunchKernelGGL(k_bin_scatter<B>, dim3(g), dim3(B), sh, s, a);
+    return hipGetLastError();
 }
 
 // Bin of each key, as the tile kernel assigns it: the smallest rank over the
@@ -461,40 +453,36 @@ hipError_t launch_key_bins(const uint64_t* keys, uint64_t n, const BinArgs& a, u
     return hipGetLastError();
 }
 
-hipError_t launch_bin(const BinArgs& a, uint32_t max_grid, uint32_t cus, hipStream_t s) {
+hipError_t launch_bin(BinArgs a, uint32_t max_grid, uint32_t cus, hipStream_t s) {
     size_t sh_tiles = (size_t)a.n_bins * sizeof(uint32_t);
     // as many workgroups as are resident at once (a second, partial wave of
     // workgroups would double the time of a grid-stride kernel)
-    const uint32_t w = a.k - a.m + 1;
-    if (w > kMaxWLong) return hipErrorInvalidValue;
-    const bool shrt = w <= kMaxWShort;
+    if (a.k - a.m + 1 > 32 * GERBIL_MAX_W) return hipErrorInvalidValue;
     int per_cu = 0;
-    const hipError_t oe = shrt ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_bin_tiles<kMaxWShort>,
-                                                                              kBinBlock, sh_tiles)
-                               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_bin_tiles<kMaxWLong>,
-                                                                              kBinBlock, sh_tiles);
+    const hipError_t oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_bin_tiles, kBinBlock, sh_tiles);
     if (oe != hipSuccess || per_cu < 1) per_cu = 1;
     uint64_t grid = (uint64_t)cus * (uint32_t)per_cu;
     if (grid > max_grid) grid = max_grid;
     if (grid < 1) grid = 1;
-    if (shrt)
-        hipLaunchKernelGGL(k_bin_tiles<kMaxWShort>, dim3((uint32_t)grid), dim3(kBinBlock), sh_tiles, s, a);
-    else
-        hipLaunchKernelGGL(k_bin_tiles<kMaxWLong>, dim3((uint32_t)grid), dim3(kBinBlock), sh_tiles, s, a);
+    // Consecutive tiles share the ranks at their boundary; at least four runs
+    // per workgroup even out parts of the stream with more or fewer starts.
+    const uint64_t n_tiles = (a.n_bytes + kTile - 1) / kTile;
+    uint64_t run = n_tiles / (4 * grid);
+    if (run < 1) run = (n_tiles + grid - 1) / grid;
+    if (run < 1) run = 1;
+    if (run > kTileRun) run = kTileRun;
+    // a chunk holds about what a workgroup finds, so that a small input leaves few holes
+    const uint64_t tiles = (n_tiles + grid - 1) / grid;
+    const uint64_t est = tiles * kTile * 5 / (2 * (a.k - a.m + 2)) / 64 * 64 + 64;
+    a.list_chunk = (uint32_t)(est < kListChunk ? est : kListChunk);
+    a.list_first = grid * a.list_chunk;
+    hipLaunchKernelGGL(k_bin_tiles, dim3((uint32_t)grid), dim3(kBinBlock), sh_tiles, s, a, (uint32_t)run);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(1024), 0, s, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    size_t sh_sc = (3 * (size_t)a.n_bins + (a.n_bins & 1u)) * sizeof(uint32_t) + (size_t)a.n_bins * sizeof(uint64_t);
-    if (sh_sc > 65536) {   // above the default limit of dynamic LDS per workgroup (n_bins > 3276)
-        e = hipFuncSetAttribute((const void*)k_bin_scatter, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh_sc);
-        if (e != hipSuccess) return e;
-    }
-    uint64_t chunks = (a.list_cap + (uint64_t)kBinBlock * kScatterPer - 1) / ((uint64_t)kBinBlock * kScatterPer);
-    uint32_t g = (uint32_t)(chunks < 2048 ? (chunks ? chunks : 1) : 2048);
-    hipLaunchKernelGGL(k_bin_scatter, dim3(g), dim3(kBinBlock), sh_sc, s, a);
-    return hipGetLastError();
+    return a.list_cap >= kScatterBigFrom + kListSlack ? run_bin_scatter<kScatterBig>(a, s) : run_bin_scatter<kBinBlock>(a, s);
 }
 
 }  // namespace gerbil

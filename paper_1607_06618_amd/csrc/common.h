@@ -201,6 +201,22 @@ __device__ __forceinline__ void set_status(uint32_t* status, uint32_t bits) {
     __hip_atomic_fetch_or(status, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t uniform(uint64_t x) {
+    return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
+}
+
+// (hi:lo) >> (s mod 32), low word.
+__device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t s) {
+    return __builtin_amdgcn_alignbit(hi, lo, s);
+}
+// The 16 bases of x in reverse order, complemented.
+__device__ __forceinline__ uint32_t revcomp16(uint32_t x) {
+    x = __builtin_bitreverse32(~x);
+    return ((x >> 1) & 0x55555555u) | ((x & 0x55555555u) << 1);
+}
+
 // Inclusive sum over the 64 lanes of a wave, in registers (row shifts and row
 // broadcasts of the data-parallel primitives; lanes without a source add 0).
 __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {

@@ -33,28 +33,34 @@ struct BinArgs {
     uint64_t list_cap;      // cap + kListSlack: slots of the tile-order list, holes included
     uint64_t* list_desc;    // [list_cap] tile order
     uint32_t* list_bin;     // [list_cap] bin, or kHole for a slot left unused
-    uint64_t* list_used;    // scalar: list slots handed out
+    uint32_t list_chunk;    // list slots of a chunk
+    uint64_t list_first;    // slots of the workgroups' first chunks
+    uint64_t* list_used;    // scalar: list slots handed out beyond those
     uint64_t* n_superm;     // scalar
-    uint32_t* bin_count;    // [n_bins] super-mers per bin
+    uint32_t* bin_count;    // [kBinCopies][n_bins] super-mers per bin, zero at the start
     uint32_t* bin_fill;     // [n_bins] scatter cursors
     uint64_t* bin_off;      // [n_bins+1]
     uint64_t* bin_kmers;    // [n_bins]
     uint64_t* desc;         // [cap] bin order
     uint32_t* status;
 };
-hipError_t launch_bin(const BinArgs& a, uint32_t max_grid, uint32_t cus, hipStream_t s);
+hipError_t launch_bin(BinArgs a, uint32_t max_grid, uint32_t cus, hipStream_t s);
 // bins[i] = the bin gerbil_bin gives key i (uses a.k, a.m, a.order, a.rank_table, a.bin_map, a.n_bins)
 hipError_t launch_key_bins(const uint64_t* keys, uint64_t n, const BinArgs& a, uint32_t* bins, hipStream_t s);
 // HyperLogLog registers [n_bins << p] of every bin's canonical (or, canonical = 0, as read) k-mers
 hipError_t launch_hll(const uint64_t* packed, uint64_t n_bytes, const uint64_t* desc, const uint64_t* bin_off,
                       uint32_t n_bins, uint32_t k, uint32_t canonical, uint32_t p, uint32_t* regs, hipStream_t s);
-// The tile kernel hands out list slots to each workgroup in chunks of at
-// least kListChunk and fills them without gaps; only the unused end of each
-// workgroup's last chunk (under kListChunk slots) is a hole. At most
-// kMaxTileGrid workgroups, hence the slack.
-constexpr uint32_t kListChunk = 2048;
+// The tile kernel hands out list slots to each workgroup in chunks of at most
+// kListChunk (or what one tile needs) and fills them without gaps; only the
+// unused end of each workgroup's last chunk is a hole. At most kMaxTileGrid
+// workgroups, hence the slack.
+constexpr uint32_t kTileWaves = 4;
+constexpr uint32_t kListChunk = kTile;
 constexpr uint32_t kMaxTileGrid = 2048;
 constexpr uint64_t kListSlack = (uint64_t)kListChunk * kMaxTileGrid;
+// Copies of the per-bin counts that workgroups add to in turn: all of them
+// end at about the same time, and adds to one address take their turn.
+constexpr uint32_t kBinCopies = 8;
 constexpr uint32_t kHole = 0xFFFFFFFFu;
 
 // ------------------------------------------------------------ count

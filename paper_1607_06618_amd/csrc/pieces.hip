@@ -149,16 +149,6 @@ __device__ __forceinline__ uint32_t item_bin(const uint32_t* first, uint32_t n, 
     return lo;
 }
 
-// (hi:lo) >> s, low word, 0 <= s < 32.
-__device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t s) {
-    return __builtin_amdgcn_alignbit(hi, lo, s);
-}
-// The 16 bases of x in reverse order, complemented.
-__device__ __forceinline__ uint32_t revcomp16(uint32_t x) {
-    x = __builtin_bitreverse32(~x);
-    return ((x >> 1) & 0x55555555u) | ((x & 0x55555555u) << 1);
-}
-
 // The packed stream from base x0 on, 16 bases at a time (first base in the top
 // bits). The next word is requested one call ahead.
 struct Bases16 {

@@ -28,8 +28,8 @@
 // - the pieces of the next round, and of the next sub-table, are requested
 //   before the current ones are processed;
 // - pairs are collected per wave and written 64 at a time.
-// 107 M 65-mers (30x): 15.2 ms, against 24.4 ms for a probe loop over single
-// slots, one round at a time; 41 M 99-mers of skewed coverage 10 ms of 17.
+// 1.7 G 65-mer windows (3.0 G bases, 30x): 15.2 ms, against 24.4 ms for a probe loop over single
+// slots, one round at a time.
 #pragma once
 #include "pieces.h"
 #include "table.h"
@@ -39,22 +39,6 @@ namespace sub {
 
 constexpr uint32_t kSeg = 8;             // k-mers a lane rolls from one start
 constexpr uint32_t kSegLenAt = 24;       // a segment: reference of its first k-mer, k-mers - 1
-
-// A value that is the same in every lane, in scalar registers.
-__device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ uint64_t uniform(uint64_t x) {
-    return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
-}
-
-// (hi:lo) >> (s mod 32), low word.
-__device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t s) {
-    return __builtin_amdgcn_alignbit(hi, lo, s);
-}
-// The 16 bases of x in reverse order, complemented.
-__device__ __forceinline__ uint32_t revcomp16(uint32_t x) {
-    x = __builtin_bitreverse32(~x);
-    return ((x >> 1) & 0x55555555u) | ((x & 0x55555555u) << 1);
-}
 
 // The k bases of reference ref as D left-aligned words (the bits past them
 // cleared). A reference to base o is 2 (o + 15), plus one for a k-mer whose
