@@ -384,7 +384,11 @@ PieceSizing piece_sizing(const gerbil_params* p, const gerbil_bins* bins) {
     z.heavy_kmers = std::min<uint32_t>(60000u, std::max<uint32_t>(4 * z.C, z.target + z.target / 2));
     // a turn of n windows costs n + w2 - 1 m2-mers: wide windows take the longest turns, at two
     // workgroups per CU; 48 windows leave LDS for a third, and super-mers are seldom longer
-    z.n0 = std::min(w2 >= kPieceMax ? kPieceMax : 48u, w2);
+    // the most windows per step of 16 m2-mers
+    const uint32_t n_most = std::min(w2 >= kPieceMax ? kPieceMax : 48u, w2);
+    z.n0 = n_most;
+    for (uint32_t n = n_most > 15 ? n_most - 15 : 1; n < n_most; n++)
+        if (n * ((z.n0 + w2 + 14) / 16) > z.n0 * ((n + w2 + 14) / 16)) z.n0 = n;
     z.split_lds = split_lds_bytes(z.n0);
     // random sub-minimizers change every (w2 + 1) / 2 windows
     z.piece_fx = (uint32_t)(65536.0 * 2.15 / (w2 + 1));

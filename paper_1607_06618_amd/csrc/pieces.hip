@@ -24,6 +24,7 @@ constexpr uint32_t kScatB = 512;
 constexpr uint32_t kItemDescs = 8192;      // descriptors per item at most (at least 256)
 constexpr uint32_t kItemGoal = 2048;       // items wanted
 constexpr uint32_t kMinTarget = 1024;      // k-mers of a small input's sub-tables
+constexpr uint32_t kBatch = 256;          // descriptors a wave takes at a time
 constexpr uint32_t kItemSlack = 64;        // list slots of an item over its expected pieces
 constexpr uint32_t kScatGroups = 8192;     // groups and sub-tables of a bin that the scatter holds in LDS
 constexpr uint32_t kScatTabs = 2048;
@@ -149,57 +150,82 @@ __device__ __forceinline__ uint32_t item_bin(const uint32_t* first, uint32_t n, 
     return lo;
 }
 
-// The packed stream from base x0 on, 16 bases at a time (first base in the top
-// bits). The next word is requested one call ahead.
-struct Bases16 {
-    const uint32_t* P;
-    int64_t q, last;   // next half word to request; the last one that exists
-    uint32_t a, b, s;
-    __device__ __forceinline__ void open(const uint64_t* packed, int64_t x0, uint64_t n_bytes) {
-        // from the half word of base x0 - 1, so that the funnel shift is never by 32
-        P = (const uint32_t*)packed;
-        last = 2 * (int64_t)((n_bytes + 31) >> 5) + 3;   // two zero words follow the stream
-        q = (x0 - 1) >> 4;
-        s = 30u - 2u * (uint32_t)((x0 - 1) & 15);
-        a = get();
-        b = get();
+// The packed stream from base x on: requested in whole 128-bit loads, later cut
+// into words of 16 bases (first base in the top bits).
+typedef uint32_t Words __attribute__((ext_vector_type(16)));
+struct BasesAhead {
+    uint64_t w[8];
+    uint32_t at;   // base before the first one, mod 32
+    __device__ __forceinline__ void request(const uint64_t* packed, int64_t x, uint64_t n_bytes, uint32_t quads) {
+        // from the word of base x - 1, so that no funnel shift is by 32
+        const int64_t last = (int64_t)((n_bytes + 31) >> 5);   // two zero words follow the stream
+        const int64_t e = (x - 1) >> 5;
+        at = (uint32_t)(x - 1) & 31u;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; j++) {
+            if (j < quads) {   // (uniform)
+                const int64_t i = e + 2 * (int64_t)j < last ? e + 2 * (int64_t)j : last;
+                __builtin_memcpy(&w[2 * j], packed + i, 16);
+            }
+        }
     }
-    __device__ __forceinline__ uint32_t get() {
-        const int64_t i = q < last ? q : last;
-        q++;
-        return P[i ^ 1];   // a word's first 16 bases are its high half
-    }
-    __device__ __forceinline__ uint32_t next() {
-        const uint32_t x = funnel(a, b, s);
-        a = b;
-        b = get();
-        return x;
+    __device__ __forceinline__ void cut(Words& v, uint32_t quads) const {
+        const bool odd = at >= 16;
+        const uint32_t s = 30u - 2u * (at & 15u);
+        uint32_t h[16];
+#pragma unroll
+        for (uint32_t j = 0; j < 8; j++) {   // a word's first 16 bases are its high half
+            h[2 * j] = (uint32_t)(w[j] >> 32);
+            h[2 * j + 1] = (uint32_t)w[j];
+        }
+        uint32_t a = odd ? h[1] : h[0];
+#pragma unroll
+        for (uint32_t j = 0; j < 14; j++) {
+            if (j % 4 == 2 && j / 4 + 1 >= quads) break;   // (uniform) nothing beyond was requested
+            const uint32_t b = odd ? h[j + 2 < 16 ? j + 2 : 15] : h[j + 1];
+            v[j] = funnel(a, b, s);
+            a = b;
+        }
     }
 };
 
 // Super-mers to pieces. A lane takes up to n0 consecutive windows of one
-// super-mer and then the next free descriptor of the item, so lanes stay
-// busy whatever the lengths. The n + w2 - 1 middle m2-mers of n windows (n <= w2) fall in three parts: the first n - 1 (window i holds those
+// super-mer and then the next descriptor of its wave's batch. All lanes of a
+// wave run the steps of its longest lane, so a batch of 256 descriptors is
+// taken longest first, and every branch is uniform. The descriptors are
+// requested a batch ahead and the first bases a turn ahead: both come from
+// places all over the stream. The n + w2 - 1 middle m2-mers of n windows (n <= w2) fall in three parts: the first n - 1 (window i holds those
 // from i on: suffix minima), the w2 - n + 1 that every window holds, and the
-// last n - 1 (window i holds the first i: prefix minima). All lanes of a wave
-// run the steps of its longest lane, so every branch is uniform. Sixteen
+// last n - 1 (window i holds the first i: prefix minima). Sixteen
 // m2-mers at a time are cut out of two words each of the forward and the
 // reverse-complement strand by constant shifts: about six instructions an
 // m2-mer. The suffix minima wait in LDS, one column per lane (no conflicts);
 // they are kept per block of 16 with the minima of the later blocks in rows
 // of their own.
+//
+// Bound by vector issue (60 % of the cycles; some 1000 lane instructions a
+// super-mer) and what is left of the latency of the scattered requests: 80 M
+// super-mers of 1.7 G windows at k = 65 take 4.8 ms. Descriptors in stream
+// order took 7.3 ms (each wave ran 48 windows for an average of 21), and
+// requesting the bases word by word 6.6 ms: the waits of the ordinary words
+// also waited for the next turn's.
 template <bool kFull>
 __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
     extern __shared__ uint32_t S[];                 // [n0 + 4][kSplitB]; then the group counts
     __shared__ uint64_t red[kSplitB / 64];
     __shared__ uint64_t s_start;
     __shared__ uint32_t s_item, s_n, s_cap, s_next;
+    __shared__ uint8_t s_order[kSplitB / 64][kBatch];
+    __shared__ uint32_t s_cls[kSplitB / 64][16];
     const uint32_t tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
     const uint32_t k = q.k, m2 = kFull ? 16u : q.m2, w2 = q.w2, n0 = q.n0;
     const uint32_t lead = (k - m2 + 1 - w2) / 2;   // m2-mers before the middle ones
     const uint32_t n_items = (uint32_t)q.scal[kScalItems], descs = (uint32_t)q.scal[kScalDescs];
     const uint32_t cmask = 0xFFFFFFFFu << (32 - 2 * m2);   // codes are held left-aligned
     const uint32_t hist_cap = q.split_lds / 8;
+    // 128-bit loads of a turn: words of 16 bases for all its steps and one more
+    // (and one before), one for the funnel and one for the odd half
+    const uint32_t quads = ((n0 + w2 + 14) / 16 + (kFull ? 1 : 2) + 2 + 3) / 4;
     uint64_t* hist = (uint64_t*)S;
     uint32_t* col = S + tid;
     uint32_t* block = S + n0 * kSplitB + tid;       // minima of the first part's blocks of 16
@@ -219,6 +245,7 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
         const uint32_t cnt = (uint32_t)(d1 - d0);
         // list slots for the pieces to expect
         uint64_t est = 0;
+#pragma unroll 8
         for (uint32_t j = tid; j < cnt; j += kSplitB) {
             const uint32_t n = (uint32_t)(q.desc[d0 + j] & 0xFFFFFFull);
             est += (uint64_t)((n + n0 - 1) / n0) * 65536ull + (uint64_t)n * q.piece_fx;
@@ -238,51 +265,111 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
         __syncthreads();
         const uint32_t cap = s_cap;
         uint64_t* out = q.list + s_start;
+        // The wave's batch of descriptors and the one after it, one register a
+        // lane for each 64; pos: how many of the batch are taken, in s_order's order
+        const uint32_t batch = cnt >= kSplitB / 64 * kBatch ? kBatch : (cnt / (kSplitB / 64) / 64 + 1) * 64;   // every wave its share of a small item
+        uint64_t d[kBatch / 64], d2[kBatch / 64];
+        uint32_t pos = batch, left2 = 0;   // left2: descriptors in d2 (0: none left)
+        auto request = [&]() {
+            uint32_t c0 = 0;
+            if (lane == 0) c0 = atomicAdd(&s_next, batch);
+            c0 = uniform(c0);
+            left2 = c0 < cnt ? cnt - c0 : 0u;
+#pragma unroll
+            for (uint32_t r = 0; r < kBatch / 64; r++) {
+                const uint32_t i = c0 + 64 * r + lane;
+                d2[r] = i < cnt && 64 * r < batch ? q.desc[d0 + i] : 0ull;
+            }
+        };
+        // the next batch becomes the current one, longest super-mers first
+        auto next_batch = [&]() {
+            uint32_t* cls = s_cls[wave];
+            if (lane < 16) cls[lane] = 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            uint32_t c[kBatch / 64], rank[kBatch / 64];
+#pragma unroll
+            for (uint32_t r = 0; r < kBatch / 64; r++) {
+                d[r] = d2[r];
+                const uint32_t n = (uint32_t)(d[r] & 0xFFFFFFull);
+                const uint32_t len = n <= n0 ? n >> 3 : 7 + n / n0 < 15 ? 7 + n / n0 : 15;
+                c[r] = 15 - len;
+                rank[r] = atomicAdd(&cls[c[r]], 1u);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const uint32_t m = lane < 16 ? cls[lane] : 0u, first = wave_incl_sum(m) - m;
+#pragma unroll
+            for (uint32_t r = 0; r < kBatch / 64; r++) {
+                const uint32_t at = __builtin_amdgcn_ds_bpermute((int)(4 * c[r]), (int)first) + rank[r];
+                s_order[wave][at] = (uint8_t)(64 * r + lane);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            pos = 0;
+        };
+        // A lane's next windows: nx windows from base x of the same super-mer,
+        // or if there are none the batch's next one; the first bases are requested
         uint64_t x0 = 0;
-        uint32_t n = 0;   // windows of this lane's super-mer still to do, from base x0
-        while (cap) {
-            const uint64_t idle = __ballot(n == 0);
-            if (idle) {
-                uint32_t at = 0;
-                if (lane == 0) at = atomicAdd(&s_next, (uint32_t)__popcll(idle));
-                at = __shfl(at, 0) + (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
-                if (n == 0 && at < cnt) {
-                    const uint64_t d = q.desc[d0 + at];
-                    x0 = d >> 24;
-                    n = (uint32_t)(d & 0xFFFFFFull);
-                    if (n && x0 + n - 1 + k > q.n_bytes) {   // a corrupt descriptor must not read out of range
+        uint32_t n = 0;
+        BasesAhead ahead{};
+        Words words;   // from base x0 + lead on, or for a shorter m2-mer 16 bases before it
+        auto take = [&](uint64_t x, uint32_t nx, uint64_t& to_x, uint32_t& to_n, BasesAhead& f) {
+            const uint64_t idle = __ballot(nx == 0);
+            if (idle == ~0ull && pos >= batch && left2) {
+                next_batch();
+                request();
+            }
+            if (idle && pos < batch) {
+                uint32_t at = pos + (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
+                const bool got = nx == 0 && at < batch;
+                const uint32_t e = s_order[wave][at < batch ? at : 0];
+                uint32_t lo = 0, hi = 0;
+#pragma unroll
+                for (uint32_t s = 0; s < kBatch / 64; s++) {
+                    const uint32_t l = __builtin_amdgcn_ds_bpermute((int)(4 * e), (int)(uint32_t)d[s]);
+                    const uint32_t h = __builtin_amdgcn_ds_bpermute((int)(4 * e), (int)(uint32_t)(d[s] >> 32));
+                    lo = e >> 6 == s ? l : lo;
+                    hi = e >> 6 == s ? h : hi;
+                }
+                if (got) {
+                    x = ((uint64_t)hi << 8) | (lo >> 24);
+                    nx = lo & 0xFFFFFFu;
+                    if (nx && x + nx - 1 + k > q.n_bytes) {   // a corrupt descriptor must not read out of range
                         set_status(q.status, ST_SPIN);
-                        n = 0;
+                        nx = 0;
                     }
+                    x = nx ? x : 0ull;
                 }
-                if (__ballot(n > 0) == 0ull) {
-                    if (__shfl(at, 0) >= cnt) break;   // (lane 0 was idle: it asked first)
-                    continue;
-                }
+                pos += (uint32_t)__popcll(idle);
             }
-            const uint32_t ns = n < n0 ? n : n0;
-            uint32_t nm = ns;
-            for (int off = 32; off > 0; off >>= 1) {
-                const uint32_t y = __shfl_xor(nm, off);
-                nm = y > nm ? y : nm;
+            to_x = x;
+            to_n = nx;
+            f.request(q.packed, (int64_t)(x + lead) - (kFull ? 0 : 16), q.n_bytes, quads);
+        };
+        if (cap) {
+            request();
+            take(0, 0, x0, n, ahead);
+            ahead.cut(words, quads);
+        }
+        while (cap) {
+            if (__ballot(n > 0) == 0ull) {   // only empty descriptors were taken, or nothing is left
+                if (pos >= batch && left2 == 0) break;
+                take(0, 0, x0, n, ahead);
+                ahead.cut(words, quads);
+                continue;
             }
-            nm = __builtin_amdgcn_readfirstlane(nm);
-            Bases16 fs, rs;
-            fs.open(q.packed, (int64_t)(x0 + lead), q.n_bytes);
-            uint32_t A = fs.next(), R;
-            if (kFull) {
-                R = revcomp16(A);
-            } else {
-                rs.open(q.packed, (int64_t)(x0 + lead + m2) - 16, q.n_bytes);
-                R = revcomp16(rs.next());
-            }
+            uint64_t x_nxt = 0;
+            uint32_t n_nxt = 0;
+            const uint32_t ns = n <= n0 ? n : n <= 2 * n0 ? (n + 1) / 2 : n0;
+            const uint32_t nm = wave_max(ns);
+            // the m2 bases of a reverse complement end where the code's begin: 16 - m2 bases earlier
+            uint32_t A = words[kFull ? 0 : 1];
+            uint32_t R = revcomp16(kFull ? A : funnel(words[0], A, 32 - 2 * m2));
             col[(nm - 1) * kSplitB] = 0xFFFFFFFFu;   // the last window holds none of the first part
             uint32_t mid = 0xFFFFFFFFu, pre = 0xFFFFFFFFu, carry = 0, prev = 0;
             uint64_t cuts = 1;
             bool begun = false;   // uniform: the first part and the shared one are done
             for (uint32_t p0 = 0; p0 < nm + w2 - 1; p0 += 16) {
-                const uint32_t An = fs.next();
-                const uint32_t Rn = revcomp16(kFull ? An : rs.next());
+                const uint32_t An = words[(p0 >> 4) + (kFull ? 1 : 2)];
+                const uint32_t Rn = revcomp16(kFull ? An : funnel(A, An, 32 - 2 * m2));
                 uint32_t h[16];
 #pragma unroll
                 for (uint32_t j = 0; j < 16; j++) {
@@ -297,6 +384,8 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
                 }
                 A = An;
                 R = Rn;
+                // the next turn's first bases travel while this one goes on
+                if (p0 == 0) take(x0 + ns, n - ns, x_nxt, n_nxt, ahead);
                 const uint32_t f = p0 + 1 >= nm ? 0u : nm - 1 - p0 < 16 ? nm - 1 - p0 : 16u;   // positions of the first part
                 const uint32_t t = p0 >= w2 ? 0u : w2 - p0 < 16 ? w2 - p0 : 16u;               // first of the last part
                 if (f) {
@@ -349,17 +438,14 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
                 cuts |= i0 >= 0 ? (uint64_t)bits << i0 : (uint64_t)(bits >> -i0);
             }
             if (!begun) col[0] = mid;   // one window only
+            ahead.cut(words, quads);   // (before the stores, which nothing has to wait for)
             // the lane's pieces
             cuts = ns ? cuts & (~0ull >> (64 - ns)) : 0ull;
             const uint32_t np = (uint32_t)__popcll(cuts);
-            uint32_t incl = np;
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t y = __shfl_up(incl, off);
-                if (lane >= (uint32_t)off) incl += y;
-            }
+            const uint32_t incl = wave_incl_sum(np);
             uint32_t at = 0;
             if (lane == 63) at = atomicAdd(&s_n, incl);
-            at = __shfl(at, 63) + incl - np;
+            at = (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + incl - np;
             while (__ballot(cuts != 0ull) != 0ull) {
                 if (cuts) {
                     const uint32_t i = (uint32_t)__builtin_ctzll(cuts);
@@ -371,8 +457,8 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
                     at++;
                 }
             }
-            x0 += ns;
-            n -= ns;
+            x0 = x_nxt;
+            n = n_nxt;
         }
         __syncthreads();
         const uint32_t total = s_n;
@@ -386,10 +472,15 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
         if (fits && P <= hist_cap) {
             for (uint32_t i = tid; i < P; i += kSplitB) hist[i] = 0;
             __syncthreads();
-            for (uint32_t e = tid; e < total; e += kSplitB) {
-                const uint64_t p = out[e];
-                atomicAdd((unsigned long long*)&hist[group_of_hash(piece_hash(p), P)],
-                          (1ull << 32) | (unsigned long long)piece_kmers(p));
+            for (uint32_t e0 = tid; e0 < total; e0 += 8 * kSplitB) {
+                uint64_t p[8];
+#pragma unroll
+                for (uint32_t j = 0; j < 8; j++) p[j] = e0 + j * kSplitB < total ? out[e0 + j * kSplitB] : 0ull;
+#pragma unroll
+                for (uint32_t j = 0; j < 8; j++)
+                    if (e0 + j * kSplitB < total)
+                        atomicAdd((unsigned long long*)&hist[group_of_hash(piece_hash(p[j]), P)],
+                                  (1ull << 32) | (unsigned long long)piece_kmers(p[j]));
             }
             __syncthreads();
             for (uint32_t i = tid; i < P; i += kSplitB)
@@ -520,7 +611,8 @@ __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
 
 // Every item's pieces to their sub-tables' runs: counted per sub-table in
 // LDS, one reservation per sub-table and item, then placed. Bound by the
-// scattered 8-byte stores.
+// scattered 8-byte stores: 150 M pieces at k = 65 take 1.6 ms, with eight
+// pieces requested at a time (one at a time: 2.1 ms).
 __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
     __shared__ uint64_t pos[kScatTabs + 1];       // the last one used: the bin's heavy pieces
     __shared__ uint32_t cnt[kScatTabs + 1];
@@ -538,7 +630,14 @@ __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
             for (uint32_t i = tid; i < P; i += kScatB) map[i] = (uint16_t)q.grp_tab[gb + i];
             for (uint32_t i = tid; i <= nt; i += kScatB) cnt[i] = 0;
             __syncthreads();
-            for (uint32_t e = tid; e < total; e += kScatB) atomicAdd(&cnt[map[group_of_hash(piece_hash(in[e]), P)]], 1u);
+            for (uint32_t e0 = tid; e0 < total; e0 += 8 * kScatB) {
+                uint64_t p[8];
+#pragma unroll
+                for (uint32_t j = 0; j < 8; j++) p[j] = e0 + j * kScatB < total ? in[e0 + j * kScatB] : 0ull;
+#pragma unroll
+                for (uint32_t j = 0; j < 8; j++)
+                    if (e0 + j * kScatB < total) atomicAdd(&cnt[map[group_of_hash(piece_hash(p[j]), P)]], 1u);
+            }
             __syncthreads();
             for (uint32_t i = tid; i <= nt; i += kScatB) {
                 const uint32_t n = cnt[i];
@@ -547,12 +646,18 @@ __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
                                 : (q.heavy_off[b] + add_dev(&q.heavy_cur[b], n)) | (1ull << 63);
             }
             __syncthreads();
-            for (uint32_t e = tid; e < total; e += kScatB) {
-                const uint64_t p = in[e];
-                uint64_t at = atomicAdd((unsigned long long*)&pos[map[group_of_hash(piece_hash(p), P)]], 1ull);
-                const bool heavy = at >> 63;
-                at &= ~0ull >> 1;
-                if (at < q.cap) q.pieces[at] = heavy ? (piece_start(p) << 24) | piece_kmers(p) : p;
+            for (uint32_t e0 = tid; e0 < total; e0 += 8 * kScatB) {
+                uint64_t p[8];
+#pragma unroll
+                for (uint32_t j = 0; j < 8; j++) p[j] = e0 + j * kScatB < total ? in[e0 + j * kScatB] : 0ull;
+#pragma unroll
+                for (uint32_t j = 0; j < 8; j++) {
+                    if (e0 + j * kScatB >= total) break;
+                    uint64_t at = atomicAdd((unsigned long long*)&pos[map[group_of_hash(piece_hash(p[j]), P)]], 1ull);
+                    const bool heavy = at >> 63;
+                    at &= ~0ull >> 1;
+                    if (at < q.cap) q.pieces[at] = heavy ? (piece_start(p[j]) << 24) | piece_kmers(p[j]) : p[j];
+                }
             }
             __syncthreads();
         } else {
@@ -579,6 +684,7 @@ hipError_t launch_piece_plan(const PieceArgs& q, uint64_t* zero_scalars, uint64_
     return hipGetLastError();
 }
 
+constexpr uint32_t kSplitStatic = kSplitB / 64 * (kBatch + 64) + 256;   // static LDS of the split kernel, rounded up
 uint32_t split_lds_bytes(uint32_t n0) {
     const uint32_t rows = (n0 + 4) * kSplitB * 4;
     return rows < 16384u ? 16384u : rows;   // (also the counts of up to bytes / 8 sub-tables)
@@ -588,7 +694,7 @@ hipError_t launch_split(const PieceArgs& q, uint32_t cus, hipStream_t s) {
     const void* f = q.m2 == 16 ? (const void*)k_split<true> : (const void*)k_split<false>;
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)q.split_lds);
     if (e != hipSuccess) return e;
-    uint32_t per_cu = 160u * 1024u / (q.split_lds + 128u);   // items are popped: more workgroups than fit would only wait
+    uint32_t per_cu = 160u * 1024u / (q.split_lds + kSplitStatic);   // items are popped: more workgroups than fit would only wait
     per_cu = per_cu < 1 ? 1 : per_cu > 6 ? 6 : per_cu;
     if (q.m2 == 16) hipLaunchKernelGGL(k_split<true>, dim3(cus * per_cu), dim3(kSplitB), q.split_lds, s, q);
     else hipLaunchKernelGGL(k_split<false>, dim3(cus * per_cu), dim3(kSplitB), q.split_lds, s, q);

@@ -115,3 +115,13 @@ def test_list_too_small_for_the_pieces(share):
     job.ws_count = job.ws_count[: fixed + int(share * (need - fixed)) // 256 * 256]
     job.count()
     same(job.result(), a, o, k, 1)
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 255, 257, 1023, 1025, 8200])
+@pytest.mark.parametrize("k", [21, 33, 65, 150])
+def test_batches_of_super_mers(n, k):
+    """One bin whose super-mers end inside, at and past the splitter's batches and items; runs longer than a turn."""
+    rng = np.random.default_rng(n * k)
+    reads = [bases(rng, k + int(rng.integers(0, 6))) for _ in range(n)] + [bases(rng, 40) + "A" * 400 + bases(rng, 40)]
+    a, o = reads_to_csr(reads)
+    same(g.count_kmers(a, o, k, 7, 1, 1, 256, mode=B), a, o, k, 1)
