@@ -187,7 +187,7 @@ static hipError_t compact_w(const CountArgs& a, const Table& t, uint32_t nb, hip
 // each returns at once when the area is empty.
 static uint32_t ovf_grid(const CountArgs& a) {
     const uint64_t blocks = (2 * a.ovf_cap + kOvfBlock - 1) / kOvfBlock;
-    return (uint32_t)(blocks < 2048 ? blocks : 2048);
+    return (uint32_t)(blocks < 1024 ? blocks : 1024);   // (an empty area costs the dispatch of these)
 }
 template <int W>
 static hipError_t overflow_w(const CountArgs& a, hipStream_t s) {

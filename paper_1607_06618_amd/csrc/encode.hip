@@ -4,9 +4,11 @@
 // ignored; windows never span two reads).
 //
 // Three streaming passes, all coalesced:
-//   read_starts  scatter one bit per read start into a bitmap;
 //   pack         16 ASCII bytes per lane -> 32 bits of packed codes and 16
-//                validity bits (SWAR over 4 bytes per 32-bit word);
+//                validity bits (SWAR over 4 bytes per 32-bit word); clears what
+//                the others need cleared (six launches of fills before: 15 us
+//                of a small call);
+//   read_starts  scatter one bit per read start into a bitmap;
 //   kmer_ok      bit p = window [p, p+k) is valid, from the "position i and
 //                i+1 belong to one read and are both valid" bitmap: each
 //                (rare) zero of that bitmap clears the windows that span it.
@@ -87,10 +89,25 @@ __device__ __forceinline__ void encode4(uint32_t x, uint32_t& codes8, uint32_t& 
 
 // Lane h encodes bytes [16h, 16h+16): 32 bits of packed codes (half of a
 // 64-bit word; the first 16 bases of a word are its high half, hence dword
-// index h^1 on a little-endian device) and 16 validity bits.
+// index h^1 on a little-endian device) and 16 validity bits. The kernel also
+// clears what the ones after it expect to be zero: the read starts (a word per
+// 64 bytes), the words around the stream, and the scalars.
 __global__ void k_pack(const uint8_t* __restrict__ ascii, uint64_t n_bytes, uint32_t* __restrict__ packed32,
-                       uint16_t* __restrict__ valid16, int aligned) {
+                       uint16_t* __restrict__ valid16, uint64_t* __restrict__ read_start,
+                       uint64_t* __restrict__ kmer_ok, uint64_t* __restrict__ scalars, int aligned) {
     uint64_t n16 = (n_bytes + 15) >> 4;
+    if (blockIdx.x == 0 && threadIdx.x < 16) {
+        const uint32_t t = threadIdx.x;
+        const uint64_t n_words = (n_bytes + 31) / 32, n_mask = (n_bytes + 63) / 64;
+        if (t < 4) scalars[t] = 0;
+        else if (t < 6) packed32[(int)t - 6] = 0;                    // the word before the stream
+        else if (t < 10) packed32[2 * n_words + (t - 6)] = 0;        // the two after it
+        else if (t == 10) read_start[n_mask] = 0;
+        else if (t == 11) kmer_ok[n_mask] = 0;
+        else if (4 * n_mask + (t - 12) >= n16) valid16[4 * n_mask + (t - 12)] = 0;
+        if (t < 4 && 4 * n_mask >= t + 1 && 4 * n_mask - 1 - t >= n16) valid16[4 * n_mask - 1 - t] = 0;   // halves of the last word
+        if (t == 4 && (n16 & 1)) packed32[n16 ^ 1] = 0;
+    }
     for (uint64_t h = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; h < n16; h += (uint64_t)gridDim.x * blockDim.x) {
         uint64_t b0 = h << 4;
         uint32_t x[4];
@@ -120,14 +137,17 @@ __global__ void k_pack(const uint8_t* __restrict__ ascii, uint64_t n_bytes, uint
         }
         packed32[h ^ 1] = out;
         valid16[h] = (uint16_t)vbits;
+        if ((h & 3) == 0) read_start[h >> 2] = 0;
     }
 }
 
-hipError_t launch_pack(const uint8_t* ascii, uint64_t n_bytes, uint64_t* packed, uint64_t* valid, hipStream_t s) {
+hipError_t launch_pack(const uint8_t* ascii, uint64_t n_bytes, uint64_t* packed, uint64_t* valid,
+                       uint64_t* read_start, uint64_t* kmer_ok, uint64_t* scalars, hipStream_t s) {
     uint64_t n16 = (n_bytes + 15) >> 4;
     int aligned = (((uintptr_t)ascii) & 15) == 0;
     hipLaunchKernelGGL(k_pack, dim3(grid_for(n16, 256, 1 << 20)), dim3(256), 0, s, ascii, n_bytes,
-                       reinterpret_cast<uint32_t*>(packed), reinterpret_cast<uint16_t*>(valid), aligned);
+                       reinterpret_cast<uint32_t*>(packed), reinterpret_cast<uint16_t*>(valid), read_start, kmer_ok,
+                       scalars, aligned);
     return hipGetLastError();
 }
 

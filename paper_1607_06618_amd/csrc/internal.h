@@ -17,7 +17,9 @@ hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t value, hipStream_t 
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t value, hipStream_t s);
 hipError_t launch_read_starts(const uint64_t* offsets, uint64_t n_reads, uint64_t n_bytes, uint64_t* read_start,
                               uint32_t* status, hipStream_t s);
-hipError_t launch_pack(const uint8_t* ascii, uint64_t n_bytes, uint64_t* packed, uint64_t* valid, hipStream_t s);
+// also clears the words around the stream, the read starts and the scalars
+hipError_t launch_pack(const uint8_t* ascii, uint64_t n_bytes, uint64_t* packed, uint64_t* valid,
+                       uint64_t* read_start, uint64_t* kmer_ok, uint64_t* scalars, hipStream_t s);
 hipError_t launch_kmer_ok(const uint64_t* valid, const uint64_t* read_start, uint64_t n_mask, uint32_t k,
                           uint64_t* kmer_ok, uint64_t* n_valid, hipStream_t s);
 
