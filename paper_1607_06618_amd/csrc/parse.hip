@@ -91,6 +91,13 @@ __device__ __forceinline__ void load_chunk(const uint8_t* __restrict__ text, uin
     }
 }
 
+// Newlines of a chunk, one bit a byte.
+__device__ __forceinline__ uint32_t chunk_mask(const uint32_t (&w)[4]) {
+    const uint32_t lo = __builtin_amdgcn_udot4(nl_bytes(w[1]) >> 7, 0x80402010u, __builtin_amdgcn_udot4(nl_bytes(w[0]) >> 7, 0x08040201u, 0u, false), false);
+    const uint32_t hi = __builtin_amdgcn_udot4(nl_bytes(w[3]) >> 7, 0x80402010u, __builtin_amdgcn_udot4(nl_bytes(w[2]) >> 7, 0x08040201u, 0u, false), false);
+    return lo | hi << 8;
+}
+
 __device__ __forceinline__ uint32_t chunk_newlines(const uint32_t (&w)[4]) {
     uint32_t c = 0;
 #pragma unroll
@@ -130,21 +137,29 @@ __device__ __forceinline__ uint64_t block_scan64(uint64_t v, uint64_t* wsum, uin
 }
 
 // In-place exclusive scan of v[0..n) by one workgroup of kScanBlock threads;
-// returns the total to every thread.
+// returns the total to every thread. Eight consecutive values a thread at a
+// time, all in flight (29 000 tile counts: 28 us; a run of 29 per thread, one
+// load after the other, took 66).
 __device__ uint64_t wg_scan_inplace(uint64_t* v, uint64_t n, uint64_t* wsum) {
-    const uint32_t tid = threadIdx.x;
-    const uint64_t per = (n + kScanBlock - 1) / kScanBlock;
-    const uint64_t lo = tid * per, hi = lo + per < n ? lo + per : n;
-    uint64_t s = 0;
-    for (uint64_t i = lo; i < hi; i++) s += v[i];
-    uint64_t total;
-    uint64_t run = block_scan64(s, wsum, total);
-    for (uint64_t i = lo; i < hi; i++) {
-        const uint64_t x = v[i];
-        v[i] = run;
-        run += x;
+    constexpr uint32_t kPer = 8;
+    uint64_t before = 0;
+    for (uint64_t i0 = 0; i0 < n; i0 += kPer * kScanBlock) {
+        const uint64_t i = i0 + kPer * threadIdx.x;
+        uint64_t x[kPer], s = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < kPer; j++) x[j] = i + j < n ? v[i + j] : 0ull;
+#pragma unroll
+        for (uint32_t j = 0; j < kPer; j++) s += x[j];
+        uint64_t total;
+        uint64_t run = before + block_scan64(s, wsum, total);
+#pragma unroll
+        for (uint32_t j = 0; j < kPer; j++) {
+            if (i + j < n) v[i + j] = run;
+            run += x[j];
+        }
+        before += total;
     }
-    return total;
+    return before;
 }
 
 // --------------------------------------------------------------- kernels
@@ -203,60 +218,90 @@ __global__ void __launch_bounds__(kScanBlock) k_nl_scan(const uint8_t* __restric
 
 // 3. the line words. Four rounds share one block scan: their newline counts
 // (at most 16 per lane and round, at most 4096 per round) ride in 16-bit
-// fields of one 64-bit value.
+// fields of two words. The bytes around a newline come from the lane's chunk
+// or its neighbours'; those of the wave's first and last lane are loaded with
+// the chunks, so that nothing is loaded while newlines are written. 1.9 GB of
+// text in 0.49 ms (a load per newline at a chunk's edge and a loop per word
+// of four bytes: 1.04 ms).
 __device__ __forceinline__ uint32_t chunk_byte(const uint32_t (&w)[4], uint32_t idx) {
-    const uint32_t x = idx < 4 ? w[0] : idx < 8 ? w[1] : idx < 12 ? w[2] : w[3];
-    return (x >> (8 * (idx & 3))) & 0xFFu;
+    const uint32_t a = idx & 4 ? w[1] : w[0], b = idx & 4 ? w[3] : w[2];
+    return ((idx & 8 ? b : a) >> (8 * (idx & 3))) & 0xFFu;
 }
 
 __global__ void __launch_bounds__(kPB) k_nl_write(const uint8_t* __restrict__ text, uint64_t n, bool aligned,
                                                   const uint64_t* __restrict__ tile_nl, uint64_t* __restrict__ line,
                                                   uint64_t lines_cap) {
-    __shared__ uint64_t wsum[kPB / 64 + 1];
+    __shared__ uint2 wsum[2][kPB / 64];
     const uint64_t nt = n_btiles_of(n);
+    const uint32_t lane = __lane_id(), wave = threadIdx.x >> 6;
+    // byte before the first lane's chunk, after the last lane's
+    auto edge_of = [&](uint64_t c) -> uint32_t {
+        const uint64_t p = lane == 0 ? c * kChunk - 1 : c * kChunk + kChunk;   // (wraps before the text: not loaded)
+        return (lane == 0 || lane == 63) && p < n ? (uint32_t)text[p] : 0u;
+    };
     for (uint64_t t = blockIdx.x; t < nt; t += gridDim.x) {
         uint64_t base = tile_nl[t];
         uint32_t w[4][4], nx[4][4];   // this group's chunks, the next group's (loaded ahead)
+        uint32_t edge[4], edge_nx[4];
 #pragma unroll
-        for (uint32_t rr = 0; rr < 4; rr++) load_chunk(text, n, (t * kRounds + rr) * kPB + threadIdx.x, aligned, nx[rr]);
+        for (uint32_t rr = 0; rr < 4; rr++) {
+            const uint64_t c = (t * kRounds + rr) * kPB + threadIdx.x;
+            load_chunk(text, n, c, aligned, nx[rr]);
+            edge_nx[rr] = edge_of(c);
+        }
 #pragma unroll 1
         for (uint32_t g = 0; g < kRounds; g += 4) {
-            uint64_t packed = 0;
+            uint32_t m[4];
 #pragma unroll
             for (uint32_t rr = 0; rr < 4; rr++) {
 #pragma unroll
                 for (int i = 0; i < 4; i++) w[rr][i] = nx[rr][i];
-                packed |= (uint64_t)chunk_newlines(w[rr]) << (16 * rr);
+                edge[rr] = edge_nx[rr];
+                m[rr] = chunk_mask(w[rr]);
             }
             if (g + 4 < kRounds) {
 #pragma unroll
-                for (uint32_t rr = 0; rr < 4; rr++)
-                    load_chunk(text, n, (t * kRounds + g + 4 + rr) * kPB + threadIdx.x, aligned, nx[rr]);
+                for (uint32_t rr = 0; rr < 4; rr++) {
+                    const uint64_t c = (t * kRounds + g + 4 + rr) * kPB + threadIdx.x;
+                    load_chunk(text, n, c, aligned, nx[rr]);
+                    edge_nx[rr] = edge_of(c);
+                }
             }
-            uint64_t total;
-            const uint64_t excl = block_scan64(packed, wsum, total);
+            const uint2 own = make_uint2((uint32_t)__popc(m[0]) | (uint32_t)__popc(m[1]) << 16,
+                                         (uint32_t)__popc(m[2]) | (uint32_t)__popc(m[3]) << 16);
+            const uint2 incl = make_uint2(wave_incl_sum(own.x), wave_incl_sum(own.y));
+            uint2* ws = wsum[(g >> 2) & 1];   // (two in turn: one barrier a group)
+            if (lane == 63) ws[wave] = incl;
+            __syncthreads();
+            uint2 excl = make_uint2(incl.x - own.x, incl.y - own.y), total = make_uint2(0, 0);
+#pragma unroll
+            for (uint32_t i = 0; i < kPB / 64; i++) {
+                const uint2 s = ws[i];
+                excl.x += i < wave ? s.x : 0u;
+                excl.y += i < wave ? s.y : 0u;
+                total.x += s.x;
+                total.y += s.y;
+            }
 #pragma unroll
             for (uint32_t rr = 0; rr < 4; rr++) {
                 const uint64_t c = (t * kRounds + g + rr) * kPB + threadIdx.x;
-                uint64_t idx = base + ((excl >> (16 * rr)) & 0xFFFFull);
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    uint32_t m = nl_bytes(w[rr][i]);
-                    while (m) {
-                        const uint32_t j = 4 * i + ((uint32_t)__builtin_ctz(m) >> 3);   // byte of the chunk
-                        m &= m - 1;
-                        const uint64_t p = c * kChunk + j;   // < n: bytes past n read as 0
-                        const uint32_t before = j ? chunk_byte(w[rr], j - 1) : (p ? (uint32_t)text[p - 1] : 0u);
-                        const uint32_t after = j < kChunk - 1 ? chunk_byte(w[rr], j + 1)
-                                                              : (p + 1 < n ? (uint32_t)text[p + 1] : 0u);
-                        if (idx < lines_cap)
-                            line[idx] = p | ((uint64_t)(before == '\r') << 40) | ((uint64_t)after << 48);
-                        idx++;
-                    }
+                uint64_t idx = base + (((rr & 2 ? excl.y : excl.x) >> (16 * (rr & 1))) & 0xFFFFu);
+                // (by every lane: a lane that is not running gives nothing)
+                const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[rr][3], 0x138, 0xf, 0xf, false);   // wave shifts by one lane
+                const uint32_t above = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[rr][0], 0x130, 0xf, 0xf, false);
+                const uint32_t prev = lane == 0 ? edge[rr] : below >> 24, next = lane == 63 ? edge[rr] : above & 0xFFu;
+                for (uint32_t left = m[rr]; left; left &= left - 1) {
+                    const uint32_t j = (uint32_t)__builtin_ctz(left);   // byte of the chunk
+                    const uint64_t p = c * kChunk + j;                  // < n: bytes past n read as 0
+                    const uint32_t before = j ? chunk_byte(w[rr], j - 1) : prev;
+                    const uint32_t after = j < kChunk - 1 ? chunk_byte(w[rr], j + 1) : next;
+                    if (idx < lines_cap) line[idx] = p | ((uint64_t)(before == '\r') << 40) | ((uint64_t)after << 48);
+                    idx++;
                 }
-                base += (total >> (16 * rr)) & 0xFFFFull;
+                base += ((rr & 2 ? total.y : total.x) >> (16 * (rr & 1))) & 0xFFFFu;
             }
         }
+        __syncthreads();   // the sums of the last group are read
     }
 }
 
@@ -411,13 +456,16 @@ __global__ void __launch_bounds__(kPB) k_line_apply(const uint8_t* __restrict__ 
 // 7. per line tile: the tile's lines own the output range [O0, O1); each
 // lane fills aligned 16-byte chunks of it (two at a time, so that their loads
 // overlap). The line holding a chunk's first byte is found by binary search
-// in the tile's offsets, which sit in LDS with the line starts. A chunk that
-// lies inside one line is two aligned 16-byte loads and a byte funnel shift;
-// one that spans lines, or is cut by the range ends or seq_cap, is gathered
-// and written byte by byte (its bytes outside the range belong to
-// neighbouring tiles).
+// in the tile's offsets, which sit in LDS with the line starts. A chunk's part
+// of a line is two aligned 16-byte loads and a byte funnel shift; one that
+// spans two lines that have bytes is put together from both (a chunk in nine at 150
+// bytes a line, so that nearly every wave has some). One of more lines, or at
+// the ends of the text, of the range or of seq_cap is gathered and written
+// byte by byte (its bytes outside the range belong to neighbouring tiles).
+// 0.9 GB of 150-byte reads in 0.75 ms, where gathering every chunk of two
+// lines byte by byte took 1.36 ms.
 constexpr uint32_t kCopyBatch = 2;
-constexpr uint32_t kCopyTile = 2 * kPB;   // lines per copy tile: 8 KB of LDS, many workgroups per CU
+constexpr uint32_t kCopyTile = 4 * kPB;   // lines per copy tile: 20 KB of LDS, seven workgroups per CU
 
 // bytes [o, o + 16) of the 32 bytes a, b (o < 16)
 __device__ __forceinline__ uint4 funnel16(const uint4 a, const uint4 b, uint32_t o) {
@@ -433,12 +481,24 @@ __device__ __forceinline__ uint4 funnel16(const uint4 a, const uint4 b, uint32_t
                       __builtin_amdgcn_alignbyte(e3, e2, r), __builtin_amdgcn_alignbyte(e4, e3, r));
 }
 
+// First line whose offset in s exceeds q, less one (s[0] <= q).
+template <typename T>
+__device__ __forceinline__ uint32_t line_of(const T* s, uint32_t cnt, T q) {
+    uint32_t lo = 0, hi = cnt;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (s[mid] <= q) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
 __global__ void __launch_bounds__(kPB) k_line_copy(const uint8_t* __restrict__ text, uint64_t n,
                                                    const uint64_t* __restrict__ line,
                                                    const uint64_t* __restrict__ line_off, uint8_t* __restrict__ seq,
                                                    uint64_t seq_cap, gerbil_parsed* out) {
     __shared__ uint64_t s_off[kCopyTile + 1];
     __shared__ uint64_t s_start[kCopyTile];
+    __shared__ uint32_t s_rel[kCopyTile + 1];   // offsets from the tile's first
     uint64_t lines;
     uint32_t fmt;
     if (!lines_usable(out, lines, fmt)) return;
@@ -466,6 +526,13 @@ __global__ void __launch_bounds__(kPB) k_line_copy(const uint8_t* __restrict__ t
         }
         __syncthreads();
         const uint64_t O0 = s_off[0], O1 = s_off[cnt];
+        const bool narrow = O1 - O0 < 1ull << 32;
+#pragma unroll
+        for (uint32_t r = 0; r <= kCopyTile / kPB; r++) {
+            const uint32_t j = threadIdx.x + r * kPB;
+            if (j <= cnt) s_rel[j] = (uint32_t)(o_v[r] - O0);
+        }
+        __syncthreads();
         if (O1 > O0) {
             const uint64_t c0 = (O0 + ms) / kChunk, c1 = (O1 + ms + kChunk - 1) / kChunk;
             for (uint64_t cb = c0 + threadIdx.x; cb < c1; cb += (uint64_t)kPB * kCopyBatch) {
@@ -482,21 +549,37 @@ __global__ void __launch_bounds__(kPB) k_line_copy(const uint8_t* __restrict__ t
                     const uint64_t a0 = c * kChunk;
                     const uint64_t qs = (a0 > O0 + ms ? a0 : O0 + ms) - ms;
                     // last line whose offset is <= qs: the line holding byte qs
-                    uint32_t lo = 0, hi = cnt;
-                    while (hi - lo > 1) {
-                        const uint32_t mid = (lo + hi) >> 1;
-                        if (s_off[mid] <= qs) lo = mid; else hi = mid;
-                    }
-                    uint32_t j = lo;
+                    uint32_t j = narrow ? line_of<uint32_t>(s_rel, cnt, (uint32_t)(qs - O0)) : line_of<uint64_t>(s_off, cnt, qs);
                     uint64_t lend = s_off[j + 1];
                     const bool whole = a0 >= O0 + ms && a0 + kChunk <= O1 + ms && a0 + kChunk <= seq_cap + ms;
-                    const uint64_t q0 = whole ? a0 - ms : 0;
-                    if (whole && q0 + kChunk <= lend) {
-                        const uintptr_t src = (uintptr_t)(text + s_start[j] + (q0 - s_off[j]));
-                        const uintptr_t A = src & ~(uintptr_t)15;
-                        if (A >= t_lo && A + 32 <= t_hi) {
+                    if (whole) {
+                        const uint64_t q0 = a0 - ms;
+                        // the 16 bytes from the one that output byte q0 would be in line j
+                        const uintptr_t src = (uintptr_t)text + s_start[j] + (q0 - s_off[j]), A = src & ~(uintptr_t)15;
+                        bool ok = A >= t_lo && A + 32 <= t_hi;
+                        uintptr_t src2 = src, A2 = A;
+                        const bool two = q0 + kChunk > lend;
+                        if (two) {   // the next line that has bytes
+                            uint32_t j2 = j + 1;
+                            while (s_off[j2 + 1] == lend) j2++;   // (byte lend is in the range: one has it)
+                            ok = ok && q0 + kChunk <= s_off[j2 + 1];
+                            src2 = (uintptr_t)text + s_start[j2] - (uintptr_t)(lend - q0);
+                            A2 = src2 & ~(uintptr_t)15;
+                            ok = ok && A2 >= t_lo && A2 + 32 <= t_hi;
+                        }
+                        if (ok) {
                             const uint4 x = *(const uint4*)A, y = *(const uint4*)(A + 16);
                             v[b] = funnel16(x, y, (uint32_t)(src & 15));
+                            if (two) {
+                                const uint4 x2 = *(const uint4*)A2, y2 = *(const uint4*)(A2 + 16);
+                                const uint4 z = funnel16(x2, y2, (uint32_t)(src2 & 15));
+                                const uint32_t cut = (uint32_t)(lend - q0);   // bytes of the first line, 1 .. 15
+                                auto join = [&](uint32_t e, uint32_t f, uint32_t at) {
+                                    const uint32_t keep = cut >= at + 4 ? 0xFFFFFFFFu : cut <= at ? 0u : 0xFFFFFFFFu >> (32 - 8 * (cut - at));
+                                    return (e & keep) | (f & ~keep);
+                                };
+                                v[b] = make_uint4(join(v[b].x, z.x, 0), join(v[b].y, z.y, 4), join(v[b].z, z.z, 8), join(v[b].w, z.w, 12));
+                            }
                             fast[b] = true;
                             continue;
                         }
