@@ -7,8 +7,8 @@
 // the offset of record i is i (1 + kb) + 4 x (large counters before i): an
 // exclusive scan of one flag per pair. Three launches: flags per tile, a
 // scan of the tile totals, then per tile and round the records are built in
-// LDS and the round's byte range is copied out with consecutive lanes on
-// consecutive bytes.
+// LDS, a word of the key at a time, and the round's byte range is copied out
+// in aligned 16-byte words.
 #include <mutex>
 
 #include "../../include/gerbil.h"
@@ -34,6 +34,7 @@ __global__ void __launch_bounds__(kRecBlock) k_rec_flags(const uint32_t* __restr
     const uint64_t n_tiles = (n + kRecTile - 1) / kRecTile;
     for (uint64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         uint32_t big = 0;
+#pragma unroll
         for (uint32_t r = 0; r < kRecRounds; r++) {
             const uint64_t i = t * kRecTile + (uint64_t)r * kRecBlock + threadIdx.x;
             big += (i < n && counts[i] >= 255u) ? 1u : 0u;
@@ -75,65 +76,110 @@ __global__ void __launch_bounds__(kRecBlock) k_rec_scan(const uint32_t* __restri
     if (tid == kRecBlock - 1) *out_bytes = n * (1ull + kb) + 4ull * part[kRecBlock - 1];
 }
 
-// The k-mer bytes of a key: byte j holds bases 4j..4j+3.
-__device__ __forceinline__ uint32_t kmer_byte(const uint64_t* key, uint32_t W, uint32_t k, uint32_t j) {
-    const uint32_t w = j / 8, b = j % 8;
-    uint64_t x = key[w];
-    if (w == W - 1) {
-        const uint32_t r = k - 32 * (W - 1);   // bases in the last word, right-aligned
-        if (r < 32) x <<= 2 * (32 - r);        // left-align: the padding bits become zero
-    }
-    return (uint32_t)(x >> (56 - 8 * b)) & 0xFFu;
+// A word's bytes to p, the most significant first.
+__device__ __forceinline__ void put64(uint8_t* p, uint64_t x) {
+    x = __builtin_bswap64(x);
+    __builtin_memcpy(p, &x, 8);
 }
 
+// The stage holds a round's records at their place modulo 16 in the output, so
+// that it is copied out in aligned 16-byte words. The next round's pairs are
+// requested before this one's are staged. Bound by memory: 20 M pairs of k =
+// 65 (560 MB in, 360 MB out) in 0.19 ms; byte by byte it was bound by the LDS
+// and store instructions, 0.39 ms.
+template <int W>
 __global__ void __launch_bounds__(kRecBlock) k_rec_write(const uint64_t* __restrict__ keys,
                                                          const uint32_t* __restrict__ counts, uint64_t n, uint32_t k,
-                                                         uint32_t W, const uint64_t* __restrict__ tile_base,
+                                                         const uint64_t* __restrict__ tile_base,
                                                          uint8_t* __restrict__ out, uint64_t out_cap) {
     extern __shared__ __align__(16) uint8_t stage[];   // one round of records
     __shared__ uint32_t wsum[32];
     const uint32_t tid = threadIdx.x;
     const uint32_t kb = (k + 3) / 4;
+    const uint32_t left = 2 * (32 * W - k);            // the last word is right-aligned
+    const uint32_t end = kb - 8 * (W - 1);             // bytes of the last word, 1 .. 8
     const uint64_t n_tiles = (n + kRecTile - 1) / kRecTile;
     for (uint64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         uint64_t big_before = tile_base[t];   // large counters before this round
+        uint32_t c_nxt = 0;
+        uint64_t key_nxt[W];
+        auto request = [&](uint64_t i) {
+            c_nxt = i < n ? counts[i] : 0u;
+#pragma unroll
+            for (int w = 0; w < W; w++) key_nxt[w] = i < n ? keys[i * W + w] : 0ull;
+        };
+        request(t * kRecTile + tid);
         for (uint32_t r = 0; r < kRecRounds; r++) {
             const uint64_t i0 = t * kRecTile + (uint64_t)r * kRecBlock;
             if (i0 >= n) break;
-            const uint64_t i = i0 + tid;
-            const bool have = i < n;
-            const uint32_t c = have ? counts[i] : 0u;
+            const bool have = i0 + tid < n;
+            const uint32_t c = c_nxt;
+            uint64_t key[W];
+#pragma unroll
+            for (int w = 0; w < W; w++) key[w] = key_nxt[w];
+            if (r + 1 < kRecRounds) request(i0 + kRecBlock + tid);
             const uint32_t big = (have && c >= 255u) ? 1u : 0u;
             uint32_t big_round;
             const uint32_t big_pre = block_excl_scan(big, wsum, big_round);
             // the round's bytes start at the record offset of pair i0
             const uint64_t base = i0 * (1ull + kb) + 4ull * big_before;
-            const uint32_t loc = tid * (1u + kb) + 4u * big_pre;   // this record inside the round
+            const uint32_t sh = (uint32_t)((uintptr_t)out + base) & 15u;
             const uint32_t n_here = (uint32_t)((n - i0) < kRecBlock ? (n - i0) : kRecBlock);
             const uint32_t round_bytes = n_here * (1u + kb) + 4u * big_round;
             if (have) {
-                uint32_t o = loc;
-                if (c < 255u) {
-                    stage[o++] = (uint8_t)c;
-                } else {
-                    stage[o++] = 0xFF;
-                    stage[o++] = (uint8_t)(c >> 24);
-                    stage[o++] = (uint8_t)(c >> 16);
-                    stage[o++] = (uint8_t)(c >> 8);
-                    stage[o++] = (uint8_t)c;
+                uint8_t* p = stage + sh + tid * (1u + kb) + 4u * big_pre;
+                *p++ = big ? 0xFF : (uint8_t)c;
+                if (big) {
+                    const uint32_t x = __builtin_bswap32(c);
+                    __builtin_memcpy(p, &x, 4);
+                    p += 4;
                 }
-                const uint64_t* key = keys + i * W;
-                for (uint32_t j = 0; j < kb; j++) stage[o++] = (uint8_t)kmer_byte(key, W, k, j);
+#pragma unroll
+                for (int w = 0; w + 1 < W; w++, p += 8) put64(p, key[w]);
+                uint64_t x = key[W - 1] << left;   // (zero bits after the last base)
+                if (end == 8) {
+                    put64(p, x);
+                } else {
+                    if (end & 4) {
+                        const uint32_t y = __builtin_bswap32((uint32_t)(x >> 32));
+                        __builtin_memcpy(p, &y, 4);
+                        p += 4;
+                        x <<= 32;
+                    }
+                    if (end & 2) {
+                        const uint16_t y = __builtin_bswap16((uint16_t)(x >> 48));
+                        __builtin_memcpy(p, &y, 2);
+                        p += 2;
+                        x <<= 16;
+                    }
+                    if (end & 1) *p = (uint8_t)(x >> 56);
+                }
             }
             __syncthreads();
-            for (uint32_t b = tid; b < round_bytes; b += kRecBlock) {
-                const uint64_t g = base + b;
-                if (g < out_cap) out[g] = stage[b];
+            for (uint32_t b = 16 * tid; b < sh + round_bytes; b += 16 * kRecBlock) {
+                const uint64_t g = base + b - sh;   // (wraps for bytes before the round's first: not written)
+                if (b >= sh && b + 16 <= sh + round_bytes && g + 16 <= out_cap) {
+                    *(uint4*)(out + g) = *(const uint4*)(stage + b);
+                } else {
+                    for (uint32_t e = 0; e < 16; e++)
+                        if (b + e >= sh && b + e < sh + round_bytes && g + e < out_cap) out[g + e] = stage[b + e];
+                }
             }
             big_before += big_round;
             __syncthreads();   // the stage is reused by the next round
         }
     }
+}
+
+template <int W>
+hipError_t rec_write(const uint64_t* keys, const uint32_t* counts, uint64_t n, uint32_t k, const uint64_t* tile_base,
+                     uint8_t* out, uint64_t out_cap, uint32_t grid, hipStream_t s) {
+    const uint32_t lds = kRecBlock * (5 + (k + 3) / 4) + 16;   // up to 128 KB: above the default dynamic LDS limit
+    // set on every call: the attribute belongs to the current device's module
+    const hipError_t e = hipFuncSetAttribute((const void*)k_rec_write<W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_rec_write<W>, dim3(grid), dim3(kRecBlock), lds, s, keys, counts, n, k, tile_base, out, out_cap);
+    return hipGetLastError();
 }
 
 // Workspace bytes for n_tiles tiles: the large-counter count per tile, then
@@ -142,7 +188,7 @@ constexpr uint64_t rec_ws_bytes(uint64_t n_tiles) { return 256 + ((4 * n_tiles +
 
 hipError_t enqueue_records(const uint64_t* keys, const uint32_t* counts, uint64_t n, uint32_t k, uint8_t* ws,
                            uint8_t* out, uint64_t out_cap, uint64_t* out_bytes, hipStream_t stream) {
-    const uint32_t W = (k + 31) / 32, kb = (k + 3) / 4;
+    const uint32_t kb = (k + 3) / 4;
     if (n == 0) return launch_fill_u64(out_bytes, 1, 0ull, stream);
     const uint64_t n_tiles = (n + kRecTile - 1) / kRecTile;
     uint32_t* tile_big = (uint32_t*)(ws + 256);
@@ -150,13 +196,24 @@ hipError_t enqueue_records(const uint64_t* keys, const uint32_t* counts, uint64_
     const uint32_t grid = (uint32_t)(n_tiles < 4096 ? n_tiles : 4096);
     hipLaunchKernelGGL(k_rec_flags, dim3(grid), dim3(kRecBlock), 0, stream, counts, n, tile_big);
     hipLaunchKernelGGL(k_rec_scan, dim3(1), dim3(kRecBlock), 0, stream, tile_big, n_tiles, tile_base, n, kb, out_bytes);
-    const uint32_t lds = kRecBlock * (5 + kb);   // up to 69 KB: above the default dynamic LDS limit
-    // set on every call: the attribute belongs to the current device's module
-    hipError_t e = hipFuncSetAttribute((const void*)k_rec_write, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rec_write, dim3(grid), dim3(kRecBlock), lds, stream, keys, counts, n, k, W, tile_base, out,
-                       out_cap);
-    return hipGetLastError();
+    switch ((k + 31) / 32) {
+        case 1: return rec_write<1>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 2: return rec_write<2>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 3: return rec_write<3>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 4: return rec_write<4>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 5: return rec_write<5>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 6: return rec_write<6>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 7: return rec_write<7>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 8: return rec_write<8>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 9: return rec_write<9>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 10: return rec_write<10>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 11: return rec_write<11>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 12: return rec_write<12>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 13: return rec_write<13>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 14: return rec_write<14>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+        case 15: return rec_write<15>(keys, counts, n, k, tile_base, out, out_cap, grid, stream);
+    }
+    return hipErrorInvalidValue;
 }
 
 // The allocation-free variant keeps the workspace in a static device array
