@@ -63,9 +63,10 @@ typedef enum {
     GERBIL_EDEVICE = -4       /* launch failure or a device wait gave up      */
 } gerbil_status;
 
-/* Counting schedule. PLAIN: one launch sequence per bin, bins in order, the
- * host reads the bin sizes once. BATCHED: every bin of the run in one
- * persistent launch with work stealing over bins (no host synchronisation). */
+/* Counting schedule. PLAIN: one launch sequence per bin, or per group of bins
+ * whose pieces fit in the workspace (see GERBIL_TABLE_*), bins in order, the
+ * host reads the bin sizes once. BATCHED: all bins of the run in one launch
+ * sequence with work stealing over bins (no host synchronisation). */
 enum { GERBIL_PLAIN = 0, GERBIL_BATCHED = 1 };
 
 /* Total order on minimizers (Sec. 3.1). KMC2: canonical m-mers in A<C<G<T
@@ -77,9 +78,10 @@ enum { GERBIL_ORDER_KMC2 = 0, GERBIL_ORDER_LEX = 1, GERBIL_ORDER_TABLE = 2 };
 
 /* Where hash tables live. LDS (and AUTO): every bin is split into sub-tables
  * that one workgroup counts in LDS (the hasher threads of Sec. 2.3.2 with
- * their own tables): BATCHED, k >= 20, by a second minimizer, so that runs of
- * k-mers move as one descriptor; PLAIN, shorter keys and what the second
- * minimizer repeats too often, by key hash. HBM: one open-addressing table per
+ * their own tables): k >= 20 by a second minimizer, so that runs of k-mers move
+ * as one descriptor (BATCHED; PLAIN with AUTO, k <= 256 and no size_sample); in
+ * the other cases, and what the second minimizer repeats too often, by key
+ * hash. HBM: one open-addressing table per
  * bin in device memory, probed by every workgroup. */
 enum { GERBIL_TABLE_AUTO = 0, GERBIL_TABLE_HBM = 1, GERBIL_TABLE_LDS = 2 };
 
@@ -112,7 +114,7 @@ typedef struct {
                                 runs two workgroups of 512 threads per CU with 80 KB of LDS each
                                 (half-size tables whose stages overlap on the CU), any other
                                 value one of 1024 with 160 KB.
-                                LDS tables, PLAIN: always 1024                                    */
+                                LDS tables, PLAIN by key hash: always 1024                        */
     uint32_t pool;           /* BATCHED: hash tables resident at once. LDS tables: key slots (ranks
                                 scattered by key hash and not yet counted), best a multiple of 8
                                 (one work queue per XCD), 0 = 16, or 8 where they only serve what

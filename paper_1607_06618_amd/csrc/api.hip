@@ -342,11 +342,22 @@ struct PieceSizing {
     uint64_t grp_cap, tab_cap;
 };
 
+// PLAIN takes the pieces too where AUTO leaves the partition to the library
+// and nothing asks for the key partition's sampled run sizes: a group of bins
+// at a time, as many as their pieces fit in the workspace. Four launches per
+// bin left most of the chip idle: 256 bins of 0.3 M 55-mers took 23.2 ms, in
+// groups 2.8 ms.
 bool use_pieces(const gerbil_params* p, uint64_t n_bytes) {
-    return p->mode == GERBIL_BATCHED && p->table != GERBIL_TABLE_HBM && p->k >= kPieceMinK && n_bytes < (1ull << 38);
+    if (p->k < kPieceMinK || n_bytes >= (1ull << 38)) return false;
+    if (p->mode == GERBIL_BATCHED) return p->table != GERBIL_TABLE_HBM;
+    return p->table == GERBIL_TABLE_AUTO && words_for(p->k) <= GERBIL_MAX_LDS_W && p->size_sample == 0;
 }
+// k-mers of a group of PLAIN bins at most (or the largest bin's): some 900
+// sub-tables, enough for every CU to count several.
+constexpr uint64_t kPlainGroup = 1ull << 23;
 
-PieceSizing piece_sizing(const gerbil_params* p, const gerbil_bins* bins) {
+// For groups of bins with up to n_kmers k-mers in up to n_superm super-mers.
+PieceSizing piece_sizing(const gerbil_params* p, uint64_t n_kmers, uint64_t n_superm) {
     PieceSizing z;
     // One workgroup of 1024 threads per CU or two of 512: the single large
     // table wastes less on the spread of group sizes and on dumps (count step
@@ -392,14 +403,22 @@ PieceSizing piece_sizing(const gerbil_params* p, const gerbil_bins* bins) {
     z.split_lds = split_lds_bytes(z.n0);
     // random sub-minimizers change every (w2 + 1) / 2 windows
     z.piece_fx = (uint32_t)(65536.0 * 2.15 / (w2 + 1));
-    z.items_cap = piece_items_cap(bins->cap_superm, p->n_bins);
-    // any bins of n_bytes bases: every base a k-mer, cap_superm super-mers; the
-    // number of a large bin's sub-tables is rounded up to a power of two
-    const uint64_t E = bins->cap_superm + ((bins->n_bytes * z.piece_fx) >> 16);
-    const uint64_t tabs = bins->n_bytes / z.target + piece_halves(bins->n_bytes, E, p->k) / z.half_target + kTablesGoal;
+    z.items_cap = piece_items_cap(n_superm, p->n_bins);
+    // the number of a large bin's groups is rounded up to a power of two
+    const uint64_t E = n_superm + ((n_kmers * z.piece_fx) >> 16);
+    const uint64_t tabs = n_kmers / z.target + piece_halves(n_kmers, E, p->k) / z.half_target + kTablesGoal;
     z.grp_cap = 2 * kGroupsPerTable * tabs + 2ull * p->n_bins;
     z.tab_cap = 2 * tabs + 2ull * p->n_bins;
     return z;
+}
+
+// BATCHED: any bins of n_bytes bases, every base a k-mer. PLAIN: groups.
+PieceSizing piece_sizing(const gerbil_params* p, const gerbil_bins* bins, uint64_t group) {
+    return p->mode == GERBIL_BATCHED ? piece_sizing(p, bins->n_bytes, bins->cap_superm)
+                                     : piece_sizing(p, group, std::min(group, bins->cap_superm));
+}
+uint64_t list_slots(const gerbil_params* p, const PieceSizing& z, uint64_t n_superm, uint64_t kmers, uint32_t n_bins) {
+    return piece_list_slots(n_superm, kmers, z.piece_fx, z.n0, p->k - p->m + 1 > z.n0, n_bins);
 }
 
 struct PieceLayout {
@@ -690,15 +709,34 @@ uint64_t pool_slots_in(uint64_t bytes, uint32_t Q, uint32_t W) {
 
 uint32_t fallback_pool(const gerbil_params* p) { return std::min(p->pool ? p->pool : kFallbackPool, p->n_bins); }
 
-// BATCHED with LDS tables: the piece partition, its table kernel, then the
-// key partition (or, above GERBIL_MAX_LDS_W words, HBM tables) for the heavy
-// rest, which is usually empty.
+// The piece partition (all bins of BATCHED at once, PLAIN's by groups), its
+// table kernel, then the key partition (or, above GERBIL_MAX_LDS_W words, HBM
+// tables) for the heavy rest, which is usually empty.
 int32_t count_pieces(const gerbil_bins* bins, const gerbil_params* p, void* ws, uint64_t ws_bytes, uint64_t* keys,
                      uint32_t* counts, uint64_t cap, gerbil_counted* state, hipStream_t stream) {
     const uint32_t W = words_for(p->k);
     const bool lds_fb = W <= GERBIL_MAX_LDS_W;
     const uint64_t ovf_cap = ovf_capacity(p);
-    const PieceSizing z = piece_sizing(p, bins);
+    const bool batched = p->mode == GERBIL_BATCHED;
+    // PLAIN reads the bin sizes once, to group the bins
+    std::vector<uint64_t> off, kmers;
+    uint64_t n_superm = 0, group = 0;
+    if (!batched) {
+        off.resize(p->n_bins + 1);
+        kmers.resize(p->n_bins);
+        if (hipMemcpyAsync(off.data(), bins->bin_off, 8 * off.size(), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+            hipMemcpyAsync(kmers.data(), bins->bin_kmers, 8 * kmers.size(), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+            hipMemcpyAsync(&n_superm, bins->n_superm, 8, hipMemcpyDeviceToHost, stream) != hipSuccess ||
+            hipStreamSynchronize(stream) != hipSuccess)
+            return GERBIL_EDEVICE;
+        uint64_t mx = 1, total = 0;
+        for (uint64_t v : kmers) {
+            mx = std::max(mx, v);
+            total += v;
+        }
+        group = std::max(mx, std::min(total, kPlainGroup));
+    }
+    const PieceSizing z = piece_sizing(p, bins, group);
     const LdsSizing zl = lds_sizing(p, bins->n_bytes, kFallbackKeySlots);
     CountLayout L;
     uint64_t used = count_fixed(W, ovf_cap, p->n_bins, !lds_fb, ws, &L);
@@ -774,33 +812,51 @@ int32_t count_pieces(const gerbil_bins* bins, const gerbil_params* p, void* ws, 
     t.theta = p->max_probes ? p->max_probes : kDefaultLdsTheta / 2;   // buckets of two slots
     t.max_kmers = z.max_kmers;
     t.slice_kmers = z.slice_kmers;
-    t.probe_hist = p->probe_hist;
+    t.probe_hist = batched ? p->probe_hist : nullptr;
     t.stage_clocks = p->stage_clocks;
 
     const uint32_t cus = (uint32_t)device_cus();
     const FallbackBins fb{PL.fb_ptr, PL.fb_n, PL.scal + kScalFallback};
-    hipError_t e = launch_piece_plan(q, L.scalars, L.hist, stream);
-    if (e == hipSuccess && p->timing_events) e = hipEventRecord(p->timing_events[0], stream);
-    if (e == hipSuccess) e = launch_split(q, cus, stream);
-    if (e == hipSuccess) e = launch_sub_scan(q, stream);
-    if (e == hipSuccess) e = launch_piece_scatter(q, cus, stream);
-    if (e == hipSuccess) e = launch_sub_tables(a, t, z.block, cus, stream);
-    if (lds_fb) {
-        LdsArgs l = lds_args(bins, p, zl, LL, fb_size, state);
-        l.keys = r.second;
-        l.bin_kmers = PL.fb_kmers;
-        l.fb = fb;
-        if (e == hipSuccess) e = launch_lds_plan(l, stream);
-        if (e == hipSuccess) e = launch_lds_persistent(a, l, lds_grid(zl), stream);
-    } else {
-        PersistArgs h = persist_args(bins, p, L, (uint8_t*)r.second, fb_size, Q, state);
-        h.bin_kmers = PL.fb_kmers;
-        h.fb = fb;
-        a.theta = kDefaultTheta;   // buckets, where max_probes counts slots
-        if (e == hipSuccess) e = launch_pool_clear(h.pool, h.slots, W, Q, fb.any, stream);
-        if (e == hipSuccess) e = launch_plan(h, stream);
-        if (e == hipSuccess)
-            e = launch_count_persistent(a, h, cus * persistent_blocks_per_cu(W, h.ins_chunk), h.ins_chunk, stream);
+    hipError_t e = hipSuccess;
+    for (uint32_t b0 = 0, b1; b0 < p->n_bins && e == hipSuccess; b0 = b1) {
+        b1 = p->n_bins;
+        if (!batched && n_superm <= bins->cap_superm) {   // (else nothing is counted: the plan says so)
+            uint64_t ns = 0, nk = 0;
+            for (b1 = b0; b1 < p->n_bins; b1++) {
+                const uint64_t s = ns + off[b1 + 1] - off[b1], k = nk + kmers[b1];
+                if (b1 > b0 && (k > group || list_slots(p, z, s, k, b1 + 1 - b0) > r.cap)) break;
+                ns = s;
+                nk = k;
+            }
+        }
+        q.bin_off = bins->bin_off + b0;
+        q.bin_kmers = bins->bin_kmers + b0;
+        q.n_bins = b1 - b0;
+        e = launch_piece_plan(q, b0 ? nullptr : L.scalars, b0 ? nullptr : L.hist, stream);
+        if (e == hipSuccess && p->timing_events && b0 == 0) e = hipEventRecord(p->timing_events[0], stream);
+        if (e == hipSuccess) e = launch_split(q, cus, stream);
+        if (e == hipSuccess) e = launch_sub_scan(q, stream);
+        if (e == hipSuccess) e = launch_piece_scatter(q, cus, stream);
+        if (e == hipSuccess) e = launch_sub_tables(a, t, z.block, cus, stream);
+        if (lds_fb) {
+            LdsArgs l = lds_args(bins, p, zl, LL, fb_size, state);
+            l.keys = r.second;
+            l.n_bins = q.n_bins;
+            l.bin_kmers = PL.fb_kmers;
+            l.fb = fb;
+            if (e == hipSuccess) e = launch_lds_plan(l, stream);
+            if (e == hipSuccess) e = launch_lds_persistent(a, l, lds_grid(zl), stream);
+        } else {
+            PersistArgs h = persist_args(bins, p, L, (uint8_t*)r.second, fb_size, Q, state);
+            h.bin_kmers = PL.fb_kmers;
+            h.fb = fb;
+            CountArgs ah = a;
+            ah.theta = kDefaultTheta;   // buckets, where max_probes counts slots
+            if (e == hipSuccess) e = launch_pool_clear(h.pool, h.slots, W, Q, fb.any, stream);
+            if (e == hipSuccess) e = launch_plan(h, stream);
+            if (e == hipSuccess)
+                e = launch_count_persistent(ah, h, cus * persistent_blocks_per_cu(W, h.ins_chunk), h.ins_chunk, stream);
+        }
     }
     if (e == hipSuccess && p->timing_events) e = hipEventRecord(p->timing_events[1], stream);
     if (e == hipSuccess) e = launch_overflow(a, stream);
@@ -943,12 +999,17 @@ int32_t gerbil_count_workspace(const gerbil_bins* bins, const gerbil_params* p, 
             return GERBIL_EDEVICE;
         n_superm = std::min(n_superm, bins->cap_superm);
         const bool lds_fb = W <= GERBIL_MAX_LDS_W;
-        const PieceSizing z = piece_sizing(p, bins);
+        const uint64_t group = std::max(mx, std::min(total, kPlainGroup));
+        const PieceSizing z = piece_sizing(p, bins, group);
         const LdsSizing zl = lds_sizing(p, bins->n_bytes, kFallbackKeySlots);
         uint64_t fixed = count_fixed(W, ovf_capacity(p), p->n_bins, !lds_fb, nullptr, nullptr);
         fixed += piece_fixed(z, p->n_bins, nullptr, 0, nullptr);
         if (lds_fb) fixed += lds_fixed(zl, nullptr, 0, nullptr);
-        const uint64_t slots = piece_list_slots(n_superm, total, z.piece_fx, z.n0, p->k - p->m + 1 > z.n0, p->n_bins);
+        // (a group's super-mers: its share of all, which grouping goes by)
+        const uint64_t slots = p->mode == GERBIL_BATCHED
+                                   ? list_slots(p, z, n_superm, total, p->n_bins)
+                                   : list_slots(p, z, (uint64_t)((double)n_superm * ((double)group / (double)std::max<uint64_t>(total, 1))) + 1,
+                                                group, p->n_bins);
         const uint64_t fb = lds_fb ? (uint64_t)zl.Q * slot_words_for(lds_slot_keys(mx, zl), p->k) * 8ull + kAlign
                                    : (uint64_t)fallback_pool(p) *
                                          pool_table_bytes(slots_for(mx, std::min(load_of(p), 0.95f)), W);

@@ -54,7 +54,8 @@ __device__ __forceinline__ void plan_scan(uint64_t* part, uint64_t v) {
     }
 }
 
-// Workgroup 0 plans; the others clear what the later launches add to.
+// Workgroup 0 plans; the others clear what the later launches add to (and with
+// the first bins of a run the run's scalars and histogram).
 __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* zero_scalars, uint64_t* zero_hist) {
     const uint32_t tid = threadIdx.x;
     if (blockIdx.x > 0) {
@@ -65,11 +66,12 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
             q.tab_off[i] = ~0ull;
             q.tab_cur[i] = 0;
         }
-        for (uint64_t i = g; i < kHistInternal; i += G) zero_hist[i] = 0;
+        if (zero_hist)
+            for (uint64_t i = g; i < kHistInternal; i += G) zero_hist[i] = 0;
         return;
     }
     __shared__ uint64_t part[kPlanB];
-    if (tid < 8) zero_scalars[tid] = 0;
+    if (zero_scalars && tid < 8) zero_scalars[tid] = 0;
     if (tid < kScalCount) q.scal[tid] = 0;
     const uint32_t n = q.n_bins, per = (n + kPlanB - 1) / kPlanB;
     const bool overfull = *q.n_superm > q.superm_cap;   // descriptors past the capacity were never stored

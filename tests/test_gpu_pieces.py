@@ -125,3 +125,30 @@ def test_batches_of_super_mers(n, k):
     reads = [bases(rng, k + int(rng.integers(0, 6))) for _ in range(n)] + [bases(rng, 40) + "A" * 400 + bases(rng, 40)]
     a, o = reads_to_csr(reads)
     same(g.count_kmers(a, o, k, 7, 1, 1, 256, mode=B), a, o, k, 1)
+
+
+@pytest.mark.parametrize("k", [20, 31, 55, 100, 256])
+def test_plain_groups(k):
+    """PLAIN counts as many bins at a time as the workspace holds: all of them, a few, and one."""
+    rng = np.random.default_rng(k)
+    a, o = reads_to_csr(genome_reads(rng, k, glen=30000, n=3000))
+    ad, od = to_device(a, o)
+    p = g.make_params(k, 9, 24, 1, mode=g.GERBIL_PLAIN, overflow_cap=1 << 14)
+    job = g.Job(ad, od, a.size, p, hist_len=128)
+    job.encode()
+    job.bin()
+    job.prepare_count()
+    need = job.ws_count.numel()
+
+    def count(size):
+        return g.gerbil_count(job.bins, p, job.ws_count.data_ptr(), size, job.keys_d.data_ptr(), job.counts_d.data_ptr(),
+                              job.cap, job.state, g._stream_handle(None))
+
+    lo, hi = 0, need
+    while hi - lo > 4096:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if count(mid) == g.GERBIL_EINVAL else (lo, mid)
+    for size in (need, (hi + 3 * need) // 4, (hi + need) // 2, (3 * hi + need) // 4, (15 * hi + need) // 16):
+        assert count(size // 256 * 256) == g.GERBIL_OK
+        assert g.gerbil_histogram(job.state, job.hist_d.data_ptr(), 128, g._stream_handle(None)) == g.GERBIL_OK
+        same(job.result(), a, o, k, 1)
