@@ -332,9 +332,10 @@ uint64_t lds_fixed(const LdsSizing& z, void* ws, uint64_t start, LdsLayout* L) {
 // 1 % at k = 65 and 99 and loses 3 % at k = 28 (longer probes): 25.0 / 25.1 /
 // 26.4 ms for 0.8 / 0.7 / 0.6 at k = 65, 9.1 / 8.8 / 9.2 at k = 28.
 constexpr double kPieceFill = 0.7;
-// Sub-tables wanted at least: four per CU, so that their workgroups end about
-// together. Small inputs get smaller ones for it.
-constexpr uint32_t kTablesGoal = 1024;
+// Sub-tables wanted at least: one per CU. Small inputs get smaller ones for
+// it. Two or more per CU even out their ends, but cost more fixed time each: 2 M
+// bases at k = 55 take 191 us with one, 204 with two and 229 with four.
+constexpr uint32_t kTablesGoal = 256;
 
 struct PieceSizing {
     uint32_t block, C, target, half_target, max_kmers, slice_kmers, heavy_kmers, max_halves;
