@@ -465,7 +465,16 @@ __global__ void __launch_bounds__(kPB) k_line_apply(const uint8_t* __restrict__ 
 // 0.9 GB of 150-byte reads in 0.75 ms, where gathering every chunk of two
 // lines byte by byte took 1.36 ms.
 constexpr uint32_t kCopyBatch = 2;
-constexpr uint32_t kCopyTile = 4 * kPB;   // lines per copy tile: 20 KB of LDS, seven workgroups per CU
+// Lines per copy tile: 1024 (20 KB of LDS, seven workgroups per CU), or 256
+// where those would be fewer than two per CU (14 000 lines of a 0.5 MB text:
+// 128 us a call with the large tiles, 90 us with the small ones).
+constexpr uint32_t kCopyTileBig = 4 * kPB, kCopyTileSmall = kPB;
+constexpr uint64_t kCopyBigFrom = 512ull * kCopyTileBig;
+// Output bytes of a tile that one workgroup copies at a time, about: lines
+// longer than 128 bytes on average are shared out over several, or few long
+// lines would leave the chip idle (500 MB in lines of 10 KB: 1.2 ms with a
+// workgroup per 512 lines, 0.51 ms with slices).
+constexpr uint64_t kCopySlice = 128 * 1024;
 
 // bytes [o, o + 16) of the 32 bytes a, b (o < 16)
 __device__ __forceinline__ uint4 funnel16(const uint4 a, const uint4 b, uint32_t o) {
@@ -492,7 +501,8 @@ __device__ __forceinline__ uint32_t line_of(const T* s, uint32_t cnt, T q) {
     return lo;
 }
 
-__global__ void __launch_bounds__(kPB) k_line_copy(const uint8_t* __restrict__ text, uint64_t n,
+template <uint32_t kCopyTile>
+__global__ void __launch_bounds__(kPB, 7) k_line_copy(const uint8_t* __restrict__ text, uint64_t n,
                                                    const uint64_t* __restrict__ line,
                                                    const uint64_t* __restrict__ line_off, uint8_t* __restrict__ seq,
                                                    uint64_t seq_cap, gerbil_parsed* out) {
@@ -506,7 +516,10 @@ __global__ void __launch_bounds__(kPB) k_line_copy(const uint8_t* __restrict__ t
     const uint64_t ms = ((uintptr_t)seq) & 15;   // chunks are aligned in the address space
     const uintptr_t t_lo = (uintptr_t)text, t_hi = (uintptr_t)text + n;
     const uint64_t nt = (lines + kCopyTile - 1) / kCopyTile;
-    for (uint64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+    const uint32_t S = nt ? (uint32_t)(total / nt / kCopySlice) + 1u : 1u;   // slices of a tile
+    for (uint64_t unit = blockIdx.x; unit < nt * S; unit += gridDim.x) {
+        const uint64_t t = S == 1 ? unit : unit / S;
+        const uint32_t slice = (uint32_t)(unit - t * S), step = S * kPB * kCopyBatch;
         const uint64_t i0 = t * kCopyTile;
         const uint32_t cnt = (uint32_t)(lines - i0 < kCopyTile ? lines - i0 : kCopyTile);
         // the tables: every load issued before any is used
@@ -535,7 +548,7 @@ __global__ void __launch_bounds__(kPB) k_line_copy(const uint8_t* __restrict__ t
         __syncthreads();
         if (O1 > O0) {
             const uint64_t c0 = (O0 + ms) / kChunk, c1 = (O1 + ms + kChunk - 1) / kChunk;
-            for (uint64_t cb = c0 + threadIdx.x; cb < c1; cb += (uint64_t)kPB * kCopyBatch) {
+            for (uint64_t cb = c0 + (slice * kPB * kCopyBatch + threadIdx.x); cb < c1; cb += step) {
                 uint4 v[kCopyBatch];
                 bool fast[kCopyBatch];
 #pragma unroll
@@ -654,8 +667,12 @@ int32_t gerbil_parse(const uint8_t* text, uint64_t n, uint32_t format, void* ws,
                        reads_cap, out);
     hipLaunchKernelGGL(k_line_apply, dim3(grid_of(lt)), dim3(kPB), 0, stream, text, w.line, w.lt_kept, w.lt_reads,
                        w.line_off, offsets, reads_cap, out);
-    hipLaunchKernelGGL(k_line_copy, dim3(grid_of((lines_cap + kCopyTile - 1) / kCopyTile)), dim3(kPB), 0, stream, text,
-                       n, w.line, w.line_off, seq, seq_cap, out);
+    if (lines_cap >= kCopyBigFrom)
+        hipLaunchKernelGGL(k_line_copy<kCopyTileBig>, dim3(grid_of((lines_cap + kCopyTileBig - 1) / kCopyTileBig + n / kCopySlice)),
+                           dim3(kPB), 0, stream, text, n, w.line, w.line_off, seq, seq_cap, out);
+    else
+        hipLaunchKernelGGL(k_line_copy<kCopyTileSmall>, dim3(grid_of((lines_cap + kCopyTileSmall - 1) / kCopyTileSmall + n / kCopySlice)),
+                           dim3(kPB), 0, stream, text, n, w.line, w.line_off, seq, seq_cap, out);
     return hipGetLastError() == hipSuccess ? GERBIL_OK : GERBIL_EDEVICE;
 }
 

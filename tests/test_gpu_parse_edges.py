@@ -50,3 +50,13 @@ def test_fastq_read_lengths(longest, shift):
 @pytest.mark.parametrize("gap", [15, 16, 17, 1023, 1024, 1025, 4095, 4096])
 def test_newlines_at_lane_and_wave_edges(gap):
     compare(b">a\n" + b"\n".join(b"A" * gap for _ in range(100)) + b"\n>b\nC")
+
+
+@pytest.mark.parametrize("lines", [1, 3, 300, 2100])
+def test_long_lines_are_shared_out(lines):
+    """Lines of more than a slice of a copy tile, among empty and short ones."""
+    rng = np.random.default_rng(lines)
+    out = []
+    for i in range(lines):
+        out += [b">", b"", line(rng, 3_000_000 // lines + int(rng.integers(0, 40))), b"AC"]
+    compare(b"\n".join(out))
