@@ -4,7 +4,7 @@
 // The text is cut into lines by a newline compaction; every later step works
 // on lines, never on the text again, except for the copy of the sequence
 // bytes:
-//   1. newlines per byte tile (64 KB: sixteen rounds of 4 KB, 16 B per lane);
+//   1. newlines per byte tile (64 or 16 KB in rounds of 4 KB, 16 B per lane);
 //   2. one workgroup scans the tile counts (line count, final line);
 //   3. each newline writes a line word: its position (40 bits), whether the
 //      byte before it is '\r' (bit 40), and the first byte of the next line
@@ -25,8 +25,13 @@ namespace {
 
 constexpr uint32_t kPB = 256;                        // threads of the tile kernels
 constexpr uint32_t kChunk = 16;                      // text bytes per lane and round
-constexpr uint32_t kRounds = 16;                     // a multiple of 4: four rounds share one scan
-constexpr uint64_t kByteTile = (uint64_t)kPB * kChunk * kRounds;   // 64 KB
+// Rounds of a byte tile, a multiple of 4 (four share one scan): tiles of 64 KB,
+// or of 16 KB for texts of fewer than eight of those per CU (23 MB: newlines
+// written in 31 us from large tiles, 23 from small ones).
+constexpr uint32_t kRoundsBig = 16, kRoundsSmall = 4;
+constexpr uint64_t tile_bytes(uint32_t rounds) { return (uint64_t)kPB * kChunk * rounds; }
+constexpr uint64_t kByteBigFrom = 2048 * tile_bytes(kRoundsBig);
+__host__ __device__ inline uint32_t rounds_of(uint64_t n) { return n >= kByteBigFrom ? kRoundsBig : kRoundsSmall; }
 constexpr uint32_t kLinesPer = 8;                    // lines per lane
 constexpr uint64_t kLineTile = (uint64_t)kPB * kLinesPer;          // 2048 lines
 constexpr uint32_t kScanBlock = 1024;                // threads of the one-workgroup scans
@@ -42,7 +47,7 @@ struct Ws {
     uint64_t* lt_reads;    // [n_ltiles + 1]
 };
 
-__host__ __device__ inline uint64_t n_btiles_of(uint64_t n) { return (n + kByteTile - 1) / kByteTile; }
+__host__ __device__ inline uint64_t n_btiles_of(uint64_t n) { return (n + tile_bytes(rounds_of(n)) - 1) / tile_bytes(rounds_of(n)); }
 __host__ __device__ inline uint64_t n_ltiles_of(uint64_t lines) { return (lines + kLineTile - 1) / kLineTile; }
 
 inline uint64_t ws_layout(uint64_t n, uint64_t lines_cap, uint8_t* base, Ws* w) {
@@ -180,6 +185,7 @@ __global__ void k_parse_init(const uint8_t* __restrict__ text, uint64_t n, uint3
 }
 
 // 1. newlines per byte tile
+template <uint32_t kRounds>
 __global__ void __launch_bounds__(kPB) k_nl_count(const uint8_t* __restrict__ text, uint64_t n, bool aligned,
                                                   uint64_t* __restrict__ tile_nl) {
     __shared__ uint64_t wsum[kPB / 64 + 1];
@@ -228,6 +234,7 @@ __device__ __forceinline__ uint32_t chunk_byte(const uint32_t (&w)[4], uint32_t 
     return ((idx & 8 ? b : a) >> (8 * (idx & 3))) & 0xFFu;
 }
 
+template <uint32_t kRounds>
 __global__ void __launch_bounds__(kPB) k_nl_write(const uint8_t* __restrict__ text, uint64_t n, bool aligned,
                                                   const uint64_t* __restrict__ tile_nl, uint64_t* __restrict__ line,
                                                   uint64_t lines_cap) {
@@ -466,10 +473,10 @@ __global__ void __launch_bounds__(kPB) k_line_apply(const uint8_t* __restrict__ 
 // lines byte by byte took 1.36 ms.
 constexpr uint32_t kCopyBatch = 2;
 // Lines per copy tile: 1024 (20 KB of LDS, seven workgroups per CU), or 256
-// where those would be fewer than two per CU (14 000 lines of a 0.5 MB text:
+// where those would be fewer than some ten per CU (14 000 lines of a 0.5 MB text:
 // 128 us a call with the large tiles, 90 us with the small ones).
 constexpr uint32_t kCopyTileBig = 4 * kPB, kCopyTileSmall = kPB;
-constexpr uint64_t kCopyBigFrom = 512ull * kCopyTileBig;
+constexpr uint64_t kCopyBigFrom = 8192ull * kCopyTileBig;   // of the capacity for lines, some three times their number
 // Output bytes of a tile that one workgroup copies at a time, about: lines
 // longer than 128 bytes on average are shared out over several, or few long
 // lines would leave the chip idle (500 MB in lines of 10 KB: 1.2 ms with a
@@ -658,10 +665,12 @@ int32_t gerbil_parse(const uint8_t* text, uint64_t n, uint32_t format, void* ws,
     const bool aligned = (((uintptr_t)text) & 15) == 0;
     const uint64_t bt = n_btiles_of(n), lt = n_ltiles_of(lines_cap);
     hipLaunchKernelGGL(k_parse_init, dim3(1), dim3(64), 0, stream, text, n, format, out);
-    hipLaunchKernelGGL(k_nl_count, dim3(grid_of(bt)), dim3(kPB), 0, stream, text, n, aligned, w.tile_nl);
+    const bool big = rounds_of(n) == kRoundsBig;
+    hipLaunchKernelGGL(big ? k_nl_count<kRoundsBig> : k_nl_count<kRoundsSmall>, dim3(grid_of(bt)), dim3(kPB), 0, stream, text,
+                       n, aligned, w.tile_nl);
     hipLaunchKernelGGL(k_nl_scan, dim3(1), dim3(kScanBlock), 0, stream, text, n, w.tile_nl, w.line, lines_cap, out);
-    hipLaunchKernelGGL(k_nl_write, dim3(grid_of(bt)), dim3(kPB), 0, stream, text, n, aligned, w.tile_nl, w.line,
-                       lines_cap);
+    hipLaunchKernelGGL(big ? k_nl_write<kRoundsBig> : k_nl_write<kRoundsSmall>, dim3(grid_of(bt)), dim3(kPB), 0, stream, text,
+                       n, aligned, w.tile_nl, w.line, lines_cap);
     hipLaunchKernelGGL(k_line_sums, dim3(grid_of(lt)), dim3(kPB), 0, stream, text, w.line, w.lt_kept, w.lt_reads, out);
     hipLaunchKernelGGL(k_line_scan, dim3(1), dim3(kScanBlock), 0, stream, w.lt_kept, w.lt_reads, offsets, seq_cap,
                        reads_cap, out);

@@ -39,3 +39,34 @@ def test_output_address(k, shift, short):
     host = out.cpu().numpy().tobytes()
     assert host[shift: shift + cap] == ref[:cap]
     assert host[:shift] == b"\xa5" * shift and host[shift + cap:] == b"\xa5" * (len(host) - shift - cap)
+
+
+def stream_of(keys, counts, k):
+    """oracle_stream for many pairs: counter bytes and key bytes placed by offset."""
+    kb, W = (k + 3) // 4, keys.shape[1]
+    x = keys.copy()
+    x[:, -1] <<= np.uint64(2 * (32 * W - k))
+    body = x.astype(">u8").view(np.uint8).reshape(-1, 8 * W)[:, :kb]
+    big = counts >= 255
+    size = 1 + kb + 4 * big.astype(np.int64)
+    at = np.cumsum(size) - size
+    out = np.zeros(int(size.sum()), dtype=np.uint8)
+    out[at] = np.where(big, 255, counts).astype(np.uint8)
+    head = counts.astype(">u4").view(np.uint8).reshape(-1, 4)
+    for j in range(4):
+        out[at[big] + 1 + j] = head[big, j]
+    for j in range(kb):
+        out[at + size - kb + j] = body[:, j]
+    return out.tobytes()
+
+
+@pytest.mark.parametrize("k", [3, 28, 32, 33, 61, 64, 65])
+def test_large_tiles(k):
+    """From 2 M pairs on a tile takes several rounds, of two pairs a thread up to k = 64."""
+    rng = np.random.default_rng(k)
+    few = random_pairs(rng, 500, k)
+    assert stream_of(*few, k) == oracle_stream(*few, k)
+    n = 256 * 8192 + 1024 * 9 + 77
+    keys, counts = random_pairs(rng, n, k)
+    kd, cd = device_pairs(keys, counts)
+    assert g.records(kd, cd, n, k).cpu().numpy().tobytes() == stream_of(keys, counts, k)
