@@ -394,10 +394,13 @@ PieceSizing piece_sizing(const gerbil_params* p, uint64_t n_kmers, uint64_t n_su
     z.slice_kmers = std::max<uint32_t>((uint32_t)(0.75 * z.C), z.target);
     // counts are 16 bits wide; more than four tables' worth goes to the fallback
     z.heavy_kmers = std::min<uint32_t>(60000u, std::max<uint32_t>(4 * z.C, z.target + z.target / 2));
-    // a turn of n windows costs n + w2 - 1 m2-mers: wide windows take the longest turns, at two
-    // workgroups per CU; 48 windows leave LDS for a third, and super-mers are seldom longer
-    // the most windows per step of 16 m2-mers
-    const uint32_t n_most = std::min(w2 >= kPieceMax ? kPieceMax : 48u, w2);
+    // A turn of n windows costs n + w2 - 1 m2-mers, so long turns do less work a
+    // window, but their minima take the LDS that more workgroups would need.
+    // Whole passes with 32 / 40 / 48 / 64 windows at most: k = 99 19.6 / 19.5 /
+    // 19.3 / 20.1 ms, k = 200 9.44 / 9.50 / 9.69 / 9.68 ms, k = 479 3.07 / 3.03 /
+    // 3.02 / 3.02 ms. (Narrow windows: super-mers are seldom longer than 48.)
+    // Of the last 16, the number with the most windows per step of 16 m2-mers.
+    const uint32_t n_most = std::min(w2 >= kPieceMax ? 40u : 48u, w2);
     z.n0 = n_most;
     for (uint32_t n = n_most > 15 ? n_most - 15 : 1; n < n_most; n++)
         if (n * ((z.n0 + w2 + 14) / 16) > z.n0 * ((n + w2 + 14) / 16)) z.n0 = n;

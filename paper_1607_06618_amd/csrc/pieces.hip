@@ -21,7 +21,7 @@ constexpr uint32_t kPlanB = 1024;
 constexpr uint32_t kSplitB = 256;
 constexpr uint32_t kScanB = 256;
 constexpr uint32_t kScatB = 512;
-constexpr uint32_t kItemDescs = 8192;      // descriptors per item at most (at least 256)
+constexpr uint32_t kItemDescs = 4096;      // descriptors per item at most (at least 256); 8192 and 2048 are 1 % slower
 constexpr uint32_t kItemGoal = 2048;       // items wanted
 constexpr uint32_t kMinTarget = 1024;      // k-mers of a small input's sub-tables
 constexpr uint32_t kBatch = 256;          // descriptors a wave takes at a time
