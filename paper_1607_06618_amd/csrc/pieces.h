@@ -64,12 +64,12 @@ struct SubShape {
     static constexpr uint32_t sum_at = probe_at + 4 * kProbeHist;           // u32 [16] pairs of every wave
     static constexpr uint32_t base_at = sum_at + 64;                        // u64 output base
     static constexpr uint32_t cls_at = base_at + 16;                        // u32 [8] segments by length; [0]: half words and full segments
-    static constexpr uint32_t seg_at = cls_at + 32;                         // u32 [2B] segments of the round
-    static constexpr uint32_t retry_at = seg_at + 8 * B;                    // u32 [B / 64][retry] k-mers whose first bucket failed
+    static constexpr uint32_t segs = 5 * B / 2;
+    static constexpr uint32_t seg_at = cls_at + 32;                         // u32 [segs] segments of the round
+    static constexpr uint32_t retry_at = seg_at + 4 * segs;                    // u32 [B / 64][retry] k-mers whose first bucket failed
     static constexpr uint32_t retry = 96;
     static constexpr uint32_t bases_at = (retry_at + B / 16 * retry + 31) / 16 * 16;   // u32 [halves], a pad before it
     static constexpr uint32_t pool = bytes - bases_at;                      // bytes of staged bases and slots together
-    static constexpr uint32_t segs = 2 * B;
 };
 
 // Half words (16 bases) that pieces of `kmers` k-mers in all need at most when

@@ -23,7 +23,7 @@
 // - the first try of a key is straight-line code for a bucket of two slots read
 //   at once; the few that find it taken go to a queue per wave, and are probed
 //   on in full waves (as a loop, a wave ran on for its slowest lane);
-// - k-mers are cut into segments of 8, sorted by length, so that the lanes of a
+// - k-mers are cut into segments of 6, sorted by length, so that the lanes of a
 //   wave roll equally far;
 // - the pieces of the next round, and of the next sub-table, are requested
 //   before the current ones are processed;
@@ -37,7 +37,11 @@
 namespace gerbil {
 namespace sub {
 
-constexpr uint32_t kSeg = 8;             // k-mers a lane rolls from one start
+// k-mers a lane rolls from one start. Six make about two rounds of segments for
+// every wave of a full sub-table; with eight half of the waves had a second
+// round and the others waited (k = 200 9.55 -> 9.00 ms a pass, k = 28 9.51 ->
+// 9.09, k = 65 27.3 -> 27.1); with five the starts cost more than that at k >= 99.
+constexpr uint32_t kSeg = 6;
 constexpr uint32_t kSegLenAt = 24;       // a segment: reference of its first k-mer, k-mers - 1
 
 // The k bases of reference ref as D left-aligned words (the bits past them
