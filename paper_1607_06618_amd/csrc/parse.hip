@@ -50,6 +50,12 @@ struct Ws {
 __host__ __device__ inline uint64_t n_btiles_of(uint64_t n) { return (n + tile_bytes(rounds_of(n)) - 1) / tile_bytes(rounds_of(n)); }
 __host__ __device__ inline uint64_t n_ltiles_of(uint64_t lines) { return (lines + kLineTile - 1) / kLineTile; }
 
+// Byte tiles a workspace for n bytes has room for: never fewer for a longer text.
+inline uint64_t btiles_room(uint64_t n) {
+    const uint64_t t = n_btiles_of(n), most_small = n_btiles_of(kByteBigFrom - 1);
+    return n < kByteBigFrom || t > most_small ? t : most_small;
+}
+
 inline uint64_t ws_layout(uint64_t n, uint64_t lines_cap, uint8_t* base, Ws* w) {
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) {
@@ -58,7 +64,7 @@ inline uint64_t ws_layout(uint64_t n, uint64_t lines_cap, uint8_t* base, Ws* w) 
         return (uint64_t*)p;
     };
     Ws x;
-    x.tile_nl = take(8 * (n_btiles_of(n) + 1));
+    x.tile_nl = take(8 * (btiles_room(n) + 1));
     x.line = take(8 * (lines_cap + 1));
     x.line_off = take(8 * (lines_cap + 1));
     x.lt_kept = take(8 * (n_ltiles_of(lines_cap) + 1));
