@@ -1,4 +1,6 @@
-// LDS sub-table counting (the default table placement).
+// LDS sub-table counting by key hash: keys below 20 bases, the PLAIN schedule
+// with explicit LDS tables or sampled run sizes, and the rest that the piece
+// partition leaves (bins and groups too heavy for its tables).
 //
 // Phase two of the paper splits the k-mers of a temporary file over several
 // hasher threads by a hash of the k-mer, each with its own table

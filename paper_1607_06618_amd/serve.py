@@ -103,6 +103,10 @@ def footprint(n_bytes: int, n_reads: int, k: int, m: int, n_bins: int, threshold
     superm = min(n_bytes, n_bytes * 4 // (w + 1) + n_bytes // 2048 + 4096)
     bins = superm * 20 + n_bins * 32
     keys = SERVING_KEY_SLOTS * 2 * n_bytes * 8 * W // max(1, n_bins) + (1 << 24)   # key slots, bins up to 2x the mean
+    if k >= 20:   # pieces twice, 8 bytes each; their second place is also where the fallback's key slots lie
+        m2 = 16 if k >= 32 else k // 2
+        w2 = min(k - m2 + 1, 97)
+        keys = max(2 * keys, int(17 * n_bytes * (2.15 / (w2 + 1) + 2.5 / (w + 1)))) + n_bytes // 32
     out = (n_bytes // (2 * threshold) + 1) * (8 * W + 4)               # first output guess
     return ascii_b + enc + bins + keys + out + (1 << 22)
 
