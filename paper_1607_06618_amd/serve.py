@@ -91,7 +91,10 @@ class Result:
         return self.keys[order], self.counts[order]
 
 
-SERVING_KEY_SLOTS = 8
+def key_slots(k: int) -> int:
+    """Key slots of a job's partition by key hash: one per XCD queue, or two
+    where it only counts the heavy rest of the pieces."""
+    return 2 if k >= 20 else 8
 
 
 def footprint(n_bytes: int, n_reads: int, k: int, m: int, n_bins: int, threshold: int) -> int:
@@ -102,7 +105,7 @@ def footprint(n_bytes: int, n_reads: int, k: int, m: int, n_bins: int, threshold
     enc = n_bytes // 4 + 3 * (n_bytes // 8) + 4096
     superm = min(n_bytes, n_bytes * 4 // (w + 1) + n_bytes // 2048 + 4096)
     bins = superm * 20 + n_bins * 32
-    keys = SERVING_KEY_SLOTS * 2 * n_bytes * 8 * W // max(1, n_bins) + (1 << 24)   # key slots, bins up to 2x the mean
+    keys = key_slots(k) * 2 * n_bytes * 8 * W // max(1, n_bins) + (1 << 24)   # key slots, bins up to 2x the mean
     if k >= 20:   # pieces twice, 8 bytes each; their second place is also where the fallback's key slots lie
         m2 = 16 if k >= 32 else k // 2
         w2 = min(k - m2 + 1, 97)
@@ -166,12 +169,12 @@ class _PinnedPool:
 
 
 class _Job:
-    def __init__(self, req: Request, t_admit: float, device, torch, pool: "_PinnedPool", params_hook=None):
+    def __init__(self, req: Request, t_admit: float, device, torch, pool: "_PinnedPool", stream, params_hook=None):
         self.req = req
         self.t_admit = t_admit
         self.torch = torch
         self.pool = pool
-        self.stream = torch.cuda.Stream(device=device)   # default priority
+        self.stream = stream
         self.state = "ADMITTED"
         self.retries = 0
         self.error = ""
@@ -185,10 +188,10 @@ class _Job:
             self.ascii_d = torch.as_tensor(req.ascii).to(device, non_blocking=True)
             self.offsets_d = torch.as_tensor(req.offsets).to(device, non_blocking=True)
             n_bytes = int(self.ascii_d.numel())
-            # 8 key slots (one per XCD queue) instead of the library's 16: the jobs in
-            # flight already overlap on the GPU, and a smaller count workspace per job
-            # keeps the allocator's cache of freed workspaces small
-            p = g.make_params(req.k, req.m, req.n_bins, req.threshold, mode=g.GERBIL_BATCHED, pool=SERVING_KEY_SLOTS)
+            # fewer key slots than the library's: the jobs in flight already overlap
+            # on the GPU, and a smaller count workspace per job keeps the allocator's
+            # cache of freed workspaces small
+            p = g.make_params(req.k, req.m, req.n_bins, req.threshold, mode=g.GERBIL_BATCHED, pool=key_slots(req.k))
             if params_hook is not None:
                 params_hook(p)
             import ctypes
@@ -315,6 +318,9 @@ class CountingServer:
         self.max_inflight = int(max_inflight)
         self.params_hook = params_hook   # optional: adjusts each job's gerbil_params (tests force capacities)
         self.pool = _PinnedPool(torch)
+        # the streams of finished jobs serve the next ones: the allocator keeps freed
+        # memory by stream, and a stream per job kept many times the memory in use
+        self.streams: List = []
         g.load()
 
     def serve(self, requests: List[Request], realtime: bool = True, poll_s: float = 2e-4,
@@ -342,7 +348,8 @@ class CountingServer:
                 if inflight and used + fp > self.budget:
                     break
                 pending.popleft()
-                inflight.append((_Job(r, time.perf_counter() - t0, self.device, self.torch, self.pool,
+                stream = self.streams.pop() if self.streams else self.torch.cuda.Stream(device=self.device)   # default priority
+                inflight.append((_Job(r, time.perf_counter() - t0, self.device, self.torch, self.pool, stream,
                                       self.params_hook), fp))
                 used += fp
             progressed = False
@@ -355,6 +362,7 @@ class CountingServer:
                     else:
                         done.append(res)
                     used -= fp
+                    self.streams.append(job.stream)
                     progressed = True
                 else:
                     still.append((job, fp))
