@@ -3,7 +3,7 @@
 
 A step is one pass of the whole path over the workload's reads, already
 resident in HBM: encode -> bin -> count -> histogram. The headline is the
-BATCHED schedule (all bins in one persistent launch); the PLAIN schedule (one
+BATCHED schedule (all bins in one launch sequence); the PLAIN schedule (one
 launch sequence per bin) is timed beside it on the same inputs. The unit of
 work is a valid (N-free) k-mer window.
 
@@ -59,7 +59,7 @@ def parse_args(argv=None):
                     help="distinct job payloads the serving stream cycles through")
     ap.add_argument("--size-sample", type=int, default=0,
                     help="LDS run sizing: every n-th segment is counted (0 = library default, 1 = exact)")
-    ap.add_argument("--k", type=int, default=0, help="override the workload's k (keys above 256 bases use HBM tables)")
+    ap.add_argument("--k", type=int, default=0, help="override the workload's k (above 256 bases PLAIN uses HBM tables)")
     ap.add_argument("--non-canonical", action="store_true",
                     help="count k-mers as read, without reverse-complement normalisation (-d)")
     ap.add_argument("--records", action="store_true",
@@ -107,9 +107,10 @@ class HipEvents:
 
 
 # Kernel sources whose change invalidates the measured HBM traffic of the counting kernel.
-TRAFFIC_SOURCES = ["paper_1607_06618_amd/csrc/lds.hip", "paper_1607_06618_amd/csrc/common.h",
-                   "paper_1607_06618_amd/csrc/internal.h", "paper_1607_06618_amd/csrc/table.h",
-                   "paper_1607_06618_amd/csrc/api.hip"]
+TRAFFIC_SOURCES = ["paper_1607_06618_amd/csrc/pieces.hip", "paper_1607_06618_amd/csrc/pieces.h",
+                   "paper_1607_06618_amd/csrc/subtable.h", "paper_1607_06618_amd/csrc/common.h",
+                   "paper_1607_06618_amd/csrc/internal.h", "paper_1607_06618_amd/csrc/api.hip"]
+PIECES = "k_split+k_sub_scan+k_piece_scatter+k_sub_tables"   # the counting step, k >= 20
 
 
 def sources_digest(paths) -> str:
@@ -124,7 +125,7 @@ def sources_digest(paths) -> str:
 def measured_traffic(kernel: str, workload: str):
     """HBM bytes per launch from the committed counter summary of `kernel` on
     `workload`, or None if there is none or the kernel changed since."""
-    path = os.path.join(ROOT, "profiles", f"{kernel}_{workload}_pmc.txt")
+    path = os.path.join(ROOT, "profiles", f"{'pieces' if kernel == PIECES else kernel}_{workload}_pmc.txt")
     if not os.path.exists(path):
         return None
     vals = {}
@@ -364,7 +365,8 @@ def main(argv=None):
         ev = evs.pair()
         table = g.GERBIL_TABLE_LDS if args.table == "lds" else g.GERBIL_TABLE_HBM
         if w.k > 256 and args.table == "lds":
-            table = g.GERBIL_TABLE_HBM   # LDS tables hold keys of up to 256 bases
+            # LDS tables of keys take up to 256 bases; BATCHED counts longer ones in LDS too (PLAIN in HBM tables)
+            table = g.GERBIL_TABLE_HBM if mode == g.GERBIL_PLAIN else g.GERBIL_TABLE_AUTO
         p = g.make_params(w.k, w.m, w.n_bins, w.threshold, mode=mode, pool=args.pool, load_factor=args.load, table=table,
                           block=args.block, max_probes=args.theta, overflow_cap=args.overflow_cap,
                           canonical=not args.non_canonical, size_sample=args.size_sample,
@@ -473,22 +475,24 @@ def main(argv=None):
             bool(results[m]["res"].report.n_out == rep.n_out and np.array_equal(results[m]["res"].hist, R["res"].hist))
             for m in results if m != head)
 
-    # Algorithmic bytes of one counting launch: the super-mer bases read
-    # (2 bits per base, n_kmers + k - 1 bases per super-mer), every distinct
-    # entry (key + 32-bit counter, E = 8W + 4 bytes) written once and read
-    # once, and every output pair written once.
+    # Algorithmic bytes of one counting step: the super-mer bases read (2 bits
+    # per base, n_kmers + k - 1 bases per super-mer) and every output pair
+    # (key + 32-bit counter, E = 8W + 4 bytes) written once. Where keys are
+    # distributed (PLAIN, HBM tables, k < 20), also every distinct entry written
+    # once and read once.
+    pieces = head == "batched" and head_table == "lds" and w.k >= 20
     W = (w.k + 31) // 32
     E = 8 * W + 4
     b_in = 0.25 * (n_valid + rep.n_superm * (w.k - 1))
-    alg_bytes = b_in + 2.0 * E * n_distinct + E * rep.n_out
+    alg_bytes = b_in + (0.0 if pieces else 2.0 * E * n_distinct) + E * rep.n_out
     achieved = alg_bytes / (R["kernel_ms"] / 1000.0) / 1e9
-    kname = {("batched", "lds"): "k_lds_persistent", ("plain", "lds"): "k_lds_stage",
+    kname = {("batched", "lds"): PIECES if pieces else "k_lds_persistent", ("plain", "lds"): "k_lds_stage",
              ("batched", "hbm"): "k_count_persistent", ("plain", "hbm"): "k_count_bin+k_compact"}[(head, head_table)]
     traffic = None
     default_schedule = (not args.tune and args.load == 0.0 and args.pool == 0 and args.scale == 1.0 and args.block == 0
                         and args.theta == 0 and args.overflow_cap == 0
                         and not args.non_canonical and args.size_sample == 0)
-    if default_schedule and "+" not in kname:
+    if default_schedule and (kname == PIECES or "+" not in kname):
         traffic = measured_traffic(kname, w.name)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": kname,

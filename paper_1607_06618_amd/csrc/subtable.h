@@ -16,10 +16,10 @@
 // Keys are held left-aligned in D 32-bit words, D = ceil(k / 16): the forward
 // strand and the reverse complement both roll by one funnel shift per word.
 //
-// What bounds it: vector issue (60 % of the cycles at k = 65, some 3.3 wave
-// instructions per key and lane-64th) and the barriers between the stages of
-// the one workgroup a CU holds; memory takes under a fifth of its time
-// (the bases once, 28 bytes out per distinct key). So
+// What bounds it: vector issue (60 % of the cycles at k = 65, some 3.4 wave-wide
+// instructions per key) and the barriers between the stages of the one
+// workgroup a CU holds; memory would take a third of its time (21 GB of whole
+// 128-byte lines that hold the pieces' bases, 3 GB of pairs). So
 // - the first try of a key is straight-line code for a bucket of two slots read
 //   at once; the few that find it taken go to a queue per wave, and are probed
 //   on in full waves (as a loop, a wave ran on for its slowest lane);
@@ -28,8 +28,8 @@
 // - the pieces of the next round, and of the next sub-table, are requested
 //   before the current ones are processed;
 // - pairs are collected per wave and written 64 at a time.
-// 1.7 G 65-mer windows (3.0 G bases, 30x): 15.2 ms, against 24.4 ms for a probe loop over single
-// slots, one round at a time.
+// 1.7 G 65-mer windows (3.0 G bases, 30x): 15.6 ms, against 24.4 ms for a probe
+// loop over single slots, one round at a time.
 #pragma once
 #include "pieces.h"
 #include "table.h"
