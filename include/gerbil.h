@@ -79,7 +79,8 @@ enum { GERBIL_ORDER_KMC2 = 0, GERBIL_ORDER_LEX = 1, GERBIL_ORDER_TABLE = 2 };
 /* Where hash tables live. LDS (and AUTO): every bin is split into sub-tables
  * that one workgroup counts in LDS (the hasher threads of Sec. 2.3.2 with
  * their own tables): k >= 20 by a second minimizer, so that runs of k-mers move
- * as one descriptor (BATCHED; PLAIN with AUTO, k <= 256 and no size_sample); in
+ * as one descriptor (BATCHED; PLAIN with AUTO, k <= 256 and no size_sample;
+ * below k = 24 up to 16 M bases per bin); in
  * the other cases, and what the second minimizer repeats too often, by key
  * hash. HBM: one open-addressing table per
  * bin in device memory, probed by every workgroup. */

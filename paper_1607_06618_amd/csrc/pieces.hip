@@ -22,12 +22,17 @@ constexpr uint32_t kSplitB = 256;
 constexpr uint32_t kScanB = 256;
 constexpr uint32_t kScatB = 512;
 constexpr uint32_t kItemDescs = 4096;      // descriptors per item at most (at least 256); 8192 and 2048 are 1 % slower
+// Where the bins have more than kManyGroups groups on average, an item of 4096
+// descriptors has about one piece for each, and every piece is an atomic of its
+// own: 0.6 G bases at k = 28 in 32 bins took 17.7 ms, now 10.3 ms (14.2 by key hash).
+constexpr uint32_t kItemDescsMany = 16384;
+constexpr uint32_t kManyGroups = 3500;
 constexpr uint32_t kItemGoal = 2048;       // items wanted
 constexpr uint32_t kMinTarget = 1024;      // k-mers of a small input's sub-tables
 constexpr uint32_t kBatch = 256;          // descriptors a wave takes at a time
 constexpr uint32_t kItemSlack = 64;        // list slots of an item over its expected pieces
-constexpr uint32_t kScatGroups = 8192;     // groups and sub-tables of a bin that the scatter holds in LDS
-constexpr uint32_t kScatTabs = 2048;
+constexpr uint32_t kScatGroups = 4096;     // groups and sub-tables of a bin that the scatter holds in LDS
+constexpr uint32_t kScatTabs = 4096;
 constexpr uint32_t kUnit = 4096;           // weight of a full sub-table
 
 }  // namespace
@@ -77,7 +82,6 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     const bool overfull = *q.n_superm > q.superm_cap;   // descriptors past the capacity were never stored
     const uint64_t S = overfull ? 0 : q.bin_off[n];
     uint32_t descs = (uint32_t)((S / kItemGoal + 63) & ~63ull);
-    descs = descs < 256 ? 256 : descs > kItemDescs ? kItemDescs : descs;
     // k-mers per sub-table: the target, or less where that leaves workgroups without one
     uint64_t km = 0;
     for (uint32_t e = 0; e < per; e++) {
@@ -88,13 +92,22 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     uint64_t target = part[kPlanB - 1] / q.tables_goal;
     target = target < kMinTarget ? kMinTarget : target;
     target = target > q.target ? q.target : target;
+    // (large bins: an item has several pieces for each of their groups)
+    const uint32_t most = part[kPlanB - 1] * kGroupsPerTable / target > (uint64_t)n * kManyGroups ? kItemDescsMany : kItemDescs;
+    descs = descs < 256 ? 256 : descs > most ? most : descs;
     __syncthreads();
     auto groups = [&](uint32_t b) -> uint32_t {
         const uint64_t ns = q.bin_off[b + 1] - q.bin_off[b], K = q.bin_kmers[b];
         if (overfull || ns == 0) return 0;
         const uint64_t E = ns + ((K * q.piece_fx) >> 16);
-        uint64_t P = (K * kGroupsPerTable + target - 1) / target;
-        const uint64_t Ph = (piece_halves(K, E, q.k) * kGroupsPerTable + q.half_target - 1) / q.half_target;
+        // an eighth of a sub-table each; of large bins more, so that an item's
+        // counts of groups and sub-tables fit in LDS
+        const uint64_t halves = piece_halves(K, E, q.k);
+        const uint64_t Tk = (K + target - 1) / target, Th = (halves + q.half_target - 1) / q.half_target, T = Tk > Th ? Tk : Th;
+        uint64_t per = kGroupsPerTable;
+        if (T * per > kExactGroups) per = T < kExactGroups ? kExactGroups / T : 1;
+        uint64_t P = (K * per + target - 1) / target;
+        const uint64_t Ph = (halves * per + q.half_target - 1) / q.half_target;
         if (Ph > P) P = Ph;
         if (P > kExactGroups) {
             uint64_t p2 = kExactGroups;
@@ -616,8 +629,7 @@ __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
 // scattered 8-byte stores: 150 M pieces at k = 65 take 1.6 ms, with eight
 // pieces requested at a time (one at a time: 2.1 ms).
 __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
-    __shared__ uint64_t pos[kScatTabs + 1];       // the last one used: the bin's heavy pieces
-    __shared__ uint32_t cnt[kScatTabs + 1];
+    __shared__ uint32_t pos[kScatTabs + 1];       // counts, then places; the last one used: the bin's heavy pieces
     __shared__ uint16_t map[kScatGroups];
     const uint32_t tid = threadIdx.x;
     const uint32_t n_items = (uint32_t)q.scal[kScalItems];
@@ -628,9 +640,9 @@ __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
         const uint64_t t0 = q.stage_clocks ? wall_clock64() : 0;
         const uint64_t* in = q.list + q.item_start[item];
         const uint32_t P = q.ngrp[b], gb = q.grp_first[b], tb = q.tab_first[b], nt = q.ntab[b];
-        if (P <= kScatGroups && nt <= kScatTabs) {
+        if (P <= kScatGroups && nt <= kScatTabs && q.cap < 1ull << 32) {
             for (uint32_t i = tid; i < P; i += kScatB) map[i] = (uint16_t)q.grp_tab[gb + i];
-            for (uint32_t i = tid; i <= nt; i += kScatB) cnt[i] = 0;
+            for (uint32_t i = tid; i <= nt; i += kScatB) pos[i] = 0;
             __syncthreads();
             for (uint32_t e0 = tid; e0 < total; e0 += 8 * kScatB) {
                 uint64_t p[8];
@@ -638,14 +650,14 @@ __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
                 for (uint32_t j = 0; j < 8; j++) p[j] = e0 + j * kScatB < total ? in[e0 + j * kScatB] : 0ull;
 #pragma unroll
                 for (uint32_t j = 0; j < 8; j++)
-                    if (e0 + j * kScatB < total) atomicAdd(&cnt[map[group_of_hash(piece_hash(p[j]), P)]], 1u);
+                    if (e0 + j * kScatB < total) atomicAdd(&pos[map[group_of_hash(piece_hash(p[j]), P)]], 1u);
             }
             __syncthreads();
             for (uint32_t i = tid; i <= nt; i += kScatB) {
-                const uint32_t n = cnt[i];
+                const uint32_t n = pos[i];
                 if (n == 0) continue;
-                pos[i] = i < nt ? q.tab_off[tb + i] + add_dev(&q.tab_cur[tb + i], n)
-                                : (q.heavy_off[b] + add_dev(&q.heavy_cur[b], n)) | (1ull << 63);
+                pos[i] = i < nt ? (uint32_t)q.tab_off[tb + i] + add_dev(&q.tab_cur[tb + i], n)
+                                : (uint32_t)q.heavy_off[b] + add_dev(&q.heavy_cur[b], n);
             }
             __syncthreads();
             for (uint32_t e0 = tid; e0 < total; e0 += 8 * kScatB) {
@@ -655,9 +667,8 @@ __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
 #pragma unroll
                 for (uint32_t j = 0; j < 8; j++) {
                     if (e0 + j * kScatB >= total) break;
-                    uint64_t at = atomicAdd((unsigned long long*)&pos[map[group_of_hash(piece_hash(p[j]), P)]], 1ull);
-                    const bool heavy = at >> 63;
-                    at &= ~0ull >> 1;
+                    const uint32_t t = map[group_of_hash(piece_hash(p[j]), P)], at = atomicAdd(&pos[t], 1u);
+                    const bool heavy = t >= nt;
                     if (at < q.cap) q.pieces[at] = heavy ? (piece_start(p[j]) << 24) | piece_kmers(p[j]) : p[j];
                 }
             }
@@ -667,8 +678,15 @@ __global__ void __launch_bounds__(kScatB) k_piece_scatter(PieceArgs q) {
                 const uint64_t p = in[e];
                 const uint32_t t = q.grp_tab[gb + group_of_hash(piece_hash(p), P)];
                 const bool heavy = t >= nt;
-                const uint64_t at = heavy ? q.heavy_off[b] + add_dev(&q.heavy_cur[b], 1u)
-                                          : q.tab_off[tb + t] + add_dev(&q.tab_cur[tb + t], 1u);
+                // (heavy pieces all go to one place: one add for those of a wave)
+                const uint64_t hm = __ballot(heavy);
+                uint32_t h = 0;
+                if (hm) {
+                    const int first = __builtin_ctzll(hm);
+                    if ((int)__lane_id() == first) h = add_dev(&q.heavy_cur[b], (uint32_t)__popcll(hm));
+                    h = __shfl(h, first) + (uint32_t)__popcll(hm & ((1ull << __lane_id()) - 1ull));
+                }
+                const uint64_t at = heavy ? q.heavy_off[b] + h : q.tab_off[tb + t] + add_dev(&q.tab_cur[tb + t], 1u);
                 if (at < q.cap) q.pieces[at] = heavy ? (piece_start(p) << 24) | piece_kmers(p) : p;
             }
         }
@@ -689,7 +707,7 @@ hipError_t launch_piece_plan(const PieceArgs& q, uint64_t* zero_scalars, uint64_
 constexpr uint32_t kSplitStatic = kSplitB / 64 * (kBatch + 64) + 256;   // static LDS of the split kernel, rounded up
 uint32_t split_lds_bytes(uint32_t n0) {
     const uint32_t rows = (n0 + 4) * kSplitB * 4;
-    return rows < 16384u ? 16384u : rows;   // (also the counts of up to bytes / 8 sub-tables)
+    return rows < 36864u ? 36864u : rows;   // (also the counts of up to bytes / 8 groups: at least kExactGroups)
 }
 
 hipError_t launch_split(const PieceArgs& q, uint32_t cus, hipStream_t s) {

@@ -152,3 +152,12 @@ def test_plain_groups(k):
         assert count(size // 256 * 256) == g.GERBIL_OK
         assert g.gerbil_histogram(job.state, job.hist_d.data_ptr(), 128, g._stream_handle(None)) == g.GERBIL_OK
         same(job.result(), a, o, k, 1)
+
+
+@pytest.mark.parametrize("k,load", [(24, 0.2), (24, 0.06), (24, 0.012), (65, 0.04), (65, 0.01)])
+def test_large_bins(k, load):
+    """Bins of 500 to 5000 sub-tables: groups of an eighth, a half and a whole
+    sub-table, and more of them than the LDS counts take."""
+    rng = np.random.default_rng(k)
+    a, o = reads_to_csr(genome_reads(rng, k, glen=300000, n=24000))
+    same(g.count_kmers(a, o, k, 9, 1, 1, 128, mode=B, load_factor=load), a, o, k, 1)
