@@ -34,6 +34,7 @@ constexpr uint32_t kItemSlack = 64;        // list slots of an item over its exp
 constexpr uint32_t kScatGroups = 4096;     // groups and sub-tables of a bin that the scatter holds in LDS
 constexpr uint32_t kScatTabs = 4096;
 constexpr uint32_t kUnit = 4096;           // weight of a full sub-table
+constexpr uint32_t kLargeGroup = kUnit * 26 / 100;
 
 }  // namespace
 
@@ -541,8 +542,15 @@ __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
         return (uint32_t)c > q.heavy_kmers || piece_halves((uint32_t)c, c >> 32, q.k) > q.max_halves;
     };
     auto weight = [&](uint64_t c) -> uint32_t {   // of a group that is not heavy
-        const uint32_t wk = (uint32_t)((uint64_t)(uint32_t)c * kUnit / target);
-        const uint32_t wh = (uint32_t)(piece_halves((uint32_t)c, c >> 32, q.k) * kUnit / q.half_target);
+        // Rounded up, and a large group's bases doubled: the groups whose middles
+        // fall into one unit then have at most 1 + kLargeGroup units of bases
+        // (1.26, where the table holds 1.3): the extents between the first and the
+        // last middle add up to a unit, half of the first and half of the last lie
+        // outside it, and a large group's bases are at most half of its extent.
+        const uint32_t wk = (uint32_t)(((uint64_t)(uint32_t)c * kUnit + target - 1) / target);
+        uint32_t wh = (uint32_t)(((piece_halves((uint32_t)c, c >> 32, q.k) + 1) * kUnit + q.half_target - 1) / q.half_target);
+        if (c == 0) wh = 0;
+        if (wh > kLargeGroup) wh *= 2;
         return wk > wh ? wk : wh;
     };
     if (tid == 0) s_hk = 0;
