@@ -12,7 +12,7 @@
 #include "../../include/gerbil.h"
 #include "common.h"
 #include "internal.h"
-#include "pieces.h"
+#include "piece_plan.h"
 
 using namespace gerbil;
 
@@ -327,22 +327,6 @@ uint64_t lds_fixed(const LdsSizing& z, void* ws, uint64_t start, LdsLayout* L) {
 // LDS tables are allowed, keys of any length included: its tables refer to
 // the bases instead of holding keys. Keys below kPieceMinK stay with the
 // key partition (LDS path).
-// K-mers per slot; sub-tables are cut to within a group's size of it. 0.6
-// costs 3 to 5 % (more sub-tables, each with its scan and dump); 0.8 gains
-// 1 % at k = 65 and 99 and loses 3 % at k = 28 (longer probes): 25.0 / 25.1 /
-// 26.4 ms for 0.8 / 0.7 / 0.6 at k = 65, 9.1 / 8.8 / 9.2 at k = 28.
-constexpr double kPieceFill = 0.7;
-// Sub-tables wanted at least: one per CU. Small inputs get smaller ones for
-// it. Two or more per CU even out their ends, but cost more fixed time each: 2 M
-// bases at k = 55 take 191 us with one, 204 with two and 229 with four.
-constexpr uint32_t kTablesGoal = 256;
-
-struct PieceSizing {
-    uint32_t block, C, target, half_target, max_kmers, slice_kmers, heavy_kmers, max_halves;
-    uint32_t m2, n0, split_lds, piece_fx, items_cap;
-    uint64_t grp_cap, tab_cap;
-};
-
 constexpr uint64_t kShortKeyBin = 16ull << 20;   // bases per bin
 
 // PLAIN takes the pieces too where AUTO leaves the partition to the library
@@ -364,67 +348,8 @@ bool use_pieces(const gerbil_params* p, uint64_t n_bytes) {
 // sub-tables, enough for every CU to count several.
 constexpr uint64_t kPlainGroup = 1ull << 23;
 
-// For groups of bins with up to n_kmers k-mers in up to n_superm super-mers.
-PieceSizing piece_sizing(const gerbil_params* p, uint64_t n_kmers, uint64_t n_superm) {
-    PieceSizing z;
-    // One workgroup of 1024 threads per CU or two of 512: the single large
-    // table wastes less on the spread of group sizes and on dumps (count step
-    // of 1.7 G 65-mer windows 24.5 ms against 27.6 ms; 28-mers 8.9 / 9.7, 200-mers
-    // 8.5 / 9.1). Beyond k = 256 a thread of 1024 has too few registers for the
-    // key's two strands.
-    z.block = p->block == 512 || p->k > 256 ? 512u : 1024u;
-    z.m2 = sub_minimizer_len(p->k);
-    const uint32_t w2 = sub_window(p->k, z.m2), w = p->k - p->m + 1;
-    // The LDS left by the fixed parts holds the staged bases and the slots. A
-    // piece has about 0.8 / (2 / (w2 + 1) + 2 / (w + 1)) k-mers (cuts of either
-    // minimizer, and read ends). The bases get half as much again as that, so
-    // that the k-mers are what fills a sub-table, and 1.3 times their target
-    // fits: a sub-table is cut to within a group's size.
-    const double per_kmer = (2.0 / (w2 + 1) + 2.0 / (w + 1)) / 0.8;
-    const double halves = std::min(p->k / 16.0 + 2.0, (1.0 + per_kmer * (p->k + 29)) / 16.0);
-    const double pool = z.block == 1024 ? SubShape<1024>::pool : SubShape<512>::pool;
-    const double n = pool / (8.0 / kPieceFill + 4.0 * 1.5 * halves);
-    z.max_halves = 4 * (uint32_t)(1.5 * halves * n / 4.0);
-    // whole rounds of the workgroup's threads over the slots; what that leaves goes to the bases
-    uint32_t nb = ((uint32_t)pool - 4 * z.max_halves) / (8 * z.block) * z.block / 2;
-    z.max_halves = ((uint32_t)pool - 16 * nb) / 16 * 4;
-    for (;; nb--) {   // a prime number of buckets, so that double hashing has a full period
-        bool prime = true;
-        for (uint32_t d = 2; prime && d * d <= nb; d++) prime = nb % d != 0;
-        if (prime) break;
-    }
-    z.C = 2 * nb;
-    z.half_target = std::max<uint32_t>(1u, (uint32_t)(z.max_halves / 1.3));
-    const double fill = p->load_factor > 0 ? p->load_factor : kPieceFill;
-    z.target = std::min<uint32_t>(40000u, std::max<uint32_t>(64u, (uint32_t)(z.C * fill)));
-    z.max_kmers = std::max<uint32_t>((uint32_t)(0.93 * z.C), z.target + z.target / 4);
-    z.slice_kmers = std::max<uint32_t>((uint32_t)(0.75 * z.C), z.target);
-    // counts are 16 bits wide; more than four tables' worth goes to the fallback
-    z.heavy_kmers = std::min<uint32_t>(60000u, std::max<uint32_t>(4 * z.C, z.target + z.target / 2));
-    // A turn of n windows costs n + w2 - 1 m2-mers, so long turns do less work a
-    // window, but their minima take the LDS that more workgroups would need.
-    // Whole passes with 32 / 40 / 48 / 64 windows at most: k = 99 19.6 / 19.5 /
-    // 19.3 / 20.1 ms, k = 200 9.44 / 9.50 / 9.69 / 9.68 ms, k = 479 3.07 / 3.03 /
-    // 3.02 / 3.02 ms. (Narrow windows: super-mers are seldom longer than 48.)
-    // Of the last 16, the number with the most windows per step of 16 m2-mers.
-    const uint32_t n_most = std::min(w2 >= kPieceMax ? 40u : 48u, w2);
-    z.n0 = n_most;
-    for (uint32_t n = n_most > 15 ? n_most - 15 : 1; n < n_most; n++)
-        if (n * ((z.n0 + w2 + 14) / 16) > z.n0 * ((n + w2 + 14) / 16)) z.n0 = n;
-    z.split_lds = split_lds_bytes(z.n0);
-    // random sub-minimizers change every (w2 + 1) / 2 windows
-    z.piece_fx = (uint32_t)(65536.0 * 2.15 / (w2 + 1));
-    z.items_cap = piece_items_cap(n_superm, p->n_bins);
-    // the number of a large bin's groups is rounded up to a power of two
-    const uint64_t E = n_superm + ((n_kmers * z.piece_fx) >> 16);
-    const uint64_t tabs = n_kmers / z.target + piece_halves(n_kmers, E, p->k) / z.half_target + kTablesGoal;
-    z.grp_cap = 2 * kGroupsPerTable * tabs + 2ull * p->n_bins;
-    z.tab_cap = 2 * tabs + 2ull * p->n_bins;
-    return z;
-}
-
 // BATCHED: any bins of n_bytes bases, every base a k-mer. PLAIN: groups.
-PieceSizing piece_sizing(const gerbil_params* p, const gerbil_bins* bins, uint64_t group) {
+PieceSizing bins_sizing(const gerbil_params* p, const gerbil_bins* bins, uint64_t group) {
     return p->mode == GERBIL_BATCHED ? piece_sizing(p, bins->n_bytes, bins->cap_superm)
                                      : piece_sizing(p, group, std::min(group, bins->cap_superm));
 }
@@ -747,7 +672,7 @@ int32_t count_pieces(const gerbil_bins* bins, const gerbil_params* p, void* ws, 
         }
         group = std::max(mx, std::min(total, kPlainGroup));
     }
-    const PieceSizing z = piece_sizing(p, bins, group);
+    const PieceSizing z = bins_sizing(p, bins, group);
     const LdsSizing zl = lds_sizing(p, bins->n_bytes, kFallbackKeySlots);
     CountLayout L;
     uint64_t used = count_fixed(W, ovf_cap, p->n_bins, !lds_fb, ws, &L);
@@ -771,24 +696,9 @@ int32_t count_pieces(const gerbil_bins* bins, const gerbil_params* p, void* ws, 
     q.bin_kmers = bins->bin_kmers;
     q.n_superm = bins->n_superm;
     q.superm_cap = bins->cap_superm;
-    q.k = p->k;
-    q.m2 = z.m2;
-    q.w2 = sub_window(p->k, z.m2);
+    set_rules(q, p, z);
     q.n_bins = p->n_bins;
     q.status = state->status;
-    q.n0 = z.n0;
-    q.split_lds = z.split_lds;
-    q.target = z.target;
-    q.half_target = z.half_target;
-    q.max_kmers = z.max_kmers;
-    q.slice_kmers = z.slice_kmers;
-    q.heavy_kmers = z.heavy_kmers;
-    q.max_halves = z.max_halves;
-    q.piece_fx = z.piece_fx;
-    q.tables_goal = p->load_factor > 0 ? 1 : kTablesGoal;   // (a load that is asked for stands)
-    q.grp_cap = (uint32_t)std::min<uint64_t>(z.grp_cap, 0xFFFFFFFFull);
-    q.tab_cap = (uint32_t)std::min<uint64_t>(z.tab_cap, 0xFFFFFFFFull);
-    q.items_cap = z.items_cap;
     q.cap = r.cap;
     q.ngrp = PL.ngrp;
     q.grp_first = PL.grp_first;
@@ -818,6 +728,7 @@ int32_t count_pieces(const gerbil_bins* bins, const gerbil_params* p, void* ws, 
     t.tab_cnt = PL.tab_cnt;
     t.tab_off = PL.tab_off;
     t.n_tab = PL.scal + kScalTables;
+    t.tab_cap = q.tab_cap;
     t.buckets = z.C / 2;
     t.halves = z.max_halves;
     t.theta = p->max_probes ? p->max_probes : kDefaultLdsTheta / 2;   // buckets of two slots
@@ -1011,7 +922,7 @@ int32_t gerbil_count_workspace(const gerbil_bins* bins, const gerbil_params* p, 
         n_superm = std::min(n_superm, bins->cap_superm);
         const bool lds_fb = W <= GERBIL_MAX_LDS_W;
         const uint64_t group = std::max(mx, std::min(total, kPlainGroup));
-        const PieceSizing z = piece_sizing(p, bins, group);
+        const PieceSizing z = bins_sizing(p, bins, group);
         const LdsSizing zl = lds_sizing(p, bins->n_bytes, kFallbackKeySlots);
         uint64_t fixed = count_fixed(W, ovf_capacity(p), p->n_bins, !lds_fb, nullptr, nullptr);
         fixed += piece_fixed(z, p->n_bins, nullptr, 0, nullptr);

@@ -107,7 +107,7 @@ struct PieceArgs {
     uint32_t* grp_first;      // [n_bins + 1] first group
     uint32_t* item_first;     // [n_bins + 1] first split item
     uint64_t* scal;           // kScal*
-    uint32_t* bin_fail;       // [n_bins] 1: the bin's pieces did not fit, the fallback counts it whole
+    uint32_t* bin_fail;       // [n_bins] 1: the bin's pieces or sub-tables did not fit, the fallback counts it whole
     // split
     uint64_t* item_start;     // [items_cap] the item's pieces in list
     uint32_t* item_n;         // [items_cap]
@@ -133,11 +133,6 @@ struct PieceArgs {
 enum { kScalItem = 0, kScalList, kScalLight, kScalHeavy, kScalTables, kScalItems, kScalDescs, kScalFallback,
        kScalTarget, kScalCount };
 
-uint32_t piece_items_cap(uint64_t n_superm, uint32_t n_bins);
-// List slots for this many super-mers and k-mers.
-// `cut`: super-mers of more than n0 k-mers are to be expected.
-uint64_t piece_list_slots(uint64_t n_superm, uint64_t kmers, uint32_t piece_fx, uint32_t n0, bool cut, uint32_t n_bins);
-uint32_t split_lds_bytes(uint32_t n0);   // dynamic LDS of the split kernel
 hipError_t launch_piece_plan(const PieceArgs& q, uint64_t* zero_scalars, uint64_t* zero_hist, hipStream_t s);
 hipError_t launch_split(const PieceArgs& q, uint32_t cus, hipStream_t s);
 hipError_t launch_sub_scan(const PieceArgs& q, hipStream_t s);
@@ -148,7 +143,8 @@ struct SubArgs {
     const uint64_t* pieces;
     const uint64_t* tab_cnt;
     const uint64_t* tab_off;
-    const uint64_t* n_tab;    // scalar
+    const uint64_t* n_tab;    // scalar: sub-tables handed out, of which tab_cap are there
+    uint32_t tab_cap;
     uint32_t buckets;         // of two slots
     uint32_t halves, theta, max_kmers, slice_kmers;
     uint64_t* probe_hist;

@@ -10,7 +10,7 @@
 // A bin whose pieces do not fit the list (which is sized for random
 // sub-minimizers) is left to the fallback as a whole, so every input is
 // counted exactly whatever its sub-minimizers look like.
-#include "pieces.h"
+#include "piece_plan.h"
 #include "table.h"
 
 namespace gerbil {
@@ -18,34 +18,13 @@ namespace gerbil {
 namespace {
 
 constexpr uint32_t kPlanB = 1024;
-constexpr uint32_t kSplitB = 256;
 constexpr uint32_t kScanB = 256;
 constexpr uint32_t kScatB = 512;
-constexpr uint32_t kItemDescs = 4096;      // descriptors per item at most (at least 256); 8192 and 2048 are 1 % slower
-// Where the bins have more than kManyGroups groups on average, an item of 4096
-// descriptors has about one piece for each, and every piece is an atomic of its
-// own: 0.6 G bases at k = 28 in 32 bins took 17.7 ms, now 10.3 ms (14.2 by key hash).
-constexpr uint32_t kItemDescsMany = 16384;
-constexpr uint32_t kManyGroups = 3500;
-constexpr uint32_t kItemGoal = 2048;       // items wanted
-constexpr uint32_t kMinTarget = 1024;      // k-mers of a small input's sub-tables
 constexpr uint32_t kBatch = 256;          // descriptors a wave takes at a time
-constexpr uint32_t kItemSlack = 64;        // list slots of an item over its expected pieces
 constexpr uint32_t kScatGroups = 4096;     // groups and sub-tables of a bin that the scatter holds in LDS
 constexpr uint32_t kScatTabs = 4096;
-constexpr uint32_t kUnit = 4096;           // weight of a full sub-table
-constexpr uint32_t kLargeGroup = kUnit * 26 / 100;
 
 }  // namespace
-
-uint64_t piece_list_slots(uint64_t n_superm, uint64_t kmers, uint32_t piece_fx, uint32_t n0, bool cut, uint32_t n_bins) {
-    // a super-mer of n k-mers takes ceil(n / n0) lanes' turns: at most one more for every n0 k-mers
-    const uint64_t e = n_superm + ((kmers * piece_fx) >> 16) + (cut ? kmers / n0 : 0);
-    return e + e / 16 + (uint64_t)kItemSlack * piece_items_cap(n_superm, n_bins);
-}
-uint32_t piece_items_cap(uint64_t n_superm, uint32_t n_bins) {
-    return (uint32_t)(n_superm / kItemDescs + 2 * kItemGoal + n_bins + 8);
-}
 
 // Inclusive sums of one value per thread in part[kPlanB] (all threads call it).
 __device__ __forceinline__ void plan_scan(uint64_t* part, uint64_t v) {
@@ -90,32 +69,13 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
         if (b < n && !overfull) km += q.bin_kmers[b];
     }
     plan_scan(part, km);
-    uint64_t target = part[kPlanB - 1] / q.tables_goal;
-    target = target < kMinTarget ? kMinTarget : target;
-    target = target > q.target ? q.target : target;
+    const uint64_t target = plan_target(q, part[kPlanB - 1]);
     // (large bins: an item has several pieces for each of their groups)
     const uint32_t most = part[kPlanB - 1] * kGroupsPerTable / target > (uint64_t)n * kManyGroups ? kItemDescsMany : kItemDescs;
     descs = descs < 256 ? 256 : descs > most ? most : descs;
     __syncthreads();
     auto groups = [&](uint32_t b) -> uint32_t {
-        const uint64_t ns = q.bin_off[b + 1] - q.bin_off[b], K = q.bin_kmers[b];
-        if (overfull || ns == 0) return 0;
-        const uint64_t E = ns + ((K * q.piece_fx) >> 16);
-        // an eighth of a sub-table each; of large bins more, so that an item's
-        // counts of groups and sub-tables fit in LDS
-        const uint64_t halves = piece_halves(K, E, q.k);
-        const uint64_t Tk = (K + target - 1) / target, Th = (halves + q.half_target - 1) / q.half_target, T = Tk > Th ? Tk : Th;
-        uint64_t per = kGroupsPerTable;
-        if (T * per > kExactGroups) per = T < kExactGroups ? kExactGroups / T : 1;
-        uint64_t P = (K * per + target - 1) / target;
-        const uint64_t Ph = (halves * per + q.half_target - 1) / q.half_target;
-        if (Ph > P) P = Ph;
-        if (P > kExactGroups) {
-            uint64_t p2 = kExactGroups;
-            while (p2 < P && p2 < kMaxGroups) p2 *= 2;
-            P = p2;
-        }
-        return (uint32_t)(P ? P : 1);
+        return overfull ? 0u : bin_groups(q, target, q.bin_off[b + 1] - q.bin_off[b], q.bin_kmers[b]);
     };
     uint64_t sp = 0, it = 0;
     for (uint32_t e = 0; e < per; e++) {
@@ -523,36 +483,24 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
 __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
     __shared__ uint32_t wsum[32];
     __shared__ uint64_t s_light, s_heavy, s_hk;
-    __shared__ uint32_t s_tab;
+    __shared__ uint32_t s_tab, s_fail;
     const uint32_t tid = threadIdx.x, b = blockIdx.x;
     const uint64_t t0 = q.stage_clocks ? wall_clock64() : 0;
     const uint32_t P = q.ngrp[b], gb = q.grp_first[b];
+    auto leave_whole = [&]() {   // (one thread) the bin to the fallback
+        const uint64_t d0 = q.bin_off[b], nd = q.bin_off[b + 1] - d0;
+        q.fb_ptr[b] = (uint64_t)(q.desc + d0);
+        q.fb_n[b] = nd;
+        q.fb_kmers[b] = q.bin_kmers[b];
+        if (nd) add_dev(&q.scal[kScalFallback], 1ull);
+    };
     if (q.bin_fail[b]) {
-        if (tid == 0) {
-            const uint64_t d0 = q.bin_off[b], nd = q.bin_off[b + 1] - d0;
-            q.fb_ptr[b] = (uint64_t)(q.desc + d0);
-            q.fb_n[b] = nd;
-            q.fb_kmers[b] = q.bin_kmers[b];
-            if (nd) add_dev(&q.scal[kScalFallback], 1ull);
-        }
+        if (tid == 0) leave_whole();
         return;
     }
     const uint32_t target = (uint32_t)q.scal[kScalTarget];
-    auto heavy = [&](uint64_t c) -> bool {
-        return (uint32_t)c > q.heavy_kmers || piece_halves((uint32_t)c, c >> 32, q.k) > q.max_halves;
-    };
-    auto weight = [&](uint64_t c) -> uint32_t {   // of a group that is not heavy
-        // Rounded up, and a large group's bases doubled: the groups whose middles
-        // fall into one unit then have at most 1 + kLargeGroup units of bases
-        // (1.26, where the table holds 1.3): the extents between the first and the
-        // last middle add up to a unit, half of the first and half of the last lie
-        // outside it, and a large group's bases are at most half of its extent.
-        const uint32_t wk = (uint32_t)(((uint64_t)(uint32_t)c * kUnit + target - 1) / target);
-        uint32_t wh = (uint32_t)(((piece_halves((uint32_t)c, c >> 32, q.k) + 1) * kUnit + q.half_target - 1) / q.half_target);
-        if (c == 0) wh = 0;
-        if (wh > kLargeGroup) wh *= 2;
-        return wk > wh ? wk : wh;
-    };
+    auto heavy = [&](uint64_t c) { return group_heavy(q, c); };
+    auto weight = [&](uint64_t c) { return group_weight(q, target, c); };
     if (tid == 0) s_hk = 0;
     const uint32_t per = (P + kScanB - 1) / kScanB;
     const uint32_t i0 = tid * per, i1 = i0 + per < P ? i0 + per : P;
@@ -572,21 +520,29 @@ __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
     const uint32_t pl = block_excl_scan(nl, wsum, tl), ph = block_excl_scan(nh, wsum, th);
     (void)ph;
     uint32_t wr = block_excl_scan(w, wsum, tw);
-    const uint32_t nt = tl ? tw / kUnit + 1 : 0u;
+    const uint32_t nt = tl ? bin_tables(tw) : 0u;
     if (hk) atomicAdd((unsigned long long*)&s_hk, (unsigned long long)hk);
     if (tid == 0) {
-        s_light = tl ? add_dev(&q.scal[kScalLight], (uint64_t)tl) : 0ull;
-        s_heavy = th ? q.cap - add_dev(&q.scal[kScalHeavy], (uint64_t)th) - th : 0ull;
-        s_tab = nt ? (uint32_t)add_dev(&q.scal[kScalTables], (uint64_t)nt) : 0u;
+        const uint64_t tab = nt ? add_dev(&q.scal[kScalTables], (uint64_t)nt) : 0ull;
+        s_tab = (uint32_t)tab;
+        s_fail = tab + nt > q.tab_cap;
+        if (s_fail) {
+            q.bin_fail[b] = 1;
+            leave_whole();
+        } else {
+            s_light = tl ? add_dev(&q.scal[kScalLight], (uint64_t)tl) : 0ull;
+            s_heavy = th ? q.cap - add_dev(&q.scal[kScalHeavy], (uint64_t)th) - th : 0ull;
+        }
     }
     __syncthreads();
+    if (s_fail) return;
     const uint32_t tab = s_tab;
     uint64_t at = s_light + pl;
     // the groups of one sub-table that this thread has seen
     uint32_t cur = 0xFFFFFFFFu;
     uint64_t cnt = 0, first = 0;
     auto flush = [&]() {
-        if (cnt && tab + cur < q.tab_cap) {
+        if (cnt) {
             add_dev(&q.tab_cnt[tab + cur], cnt);
             __hip_atomic_fetch_min(&q.tab_off[tab + cur], first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -600,9 +556,7 @@ __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
             continue;
         }
         const uint32_t gw = weight(c);
-        uint32_t t = (wr + gw / 2) / kUnit;
-        t = t < nt ? t : nt - 1;
-        if (np == 0) t = 0;
+        const uint32_t t = np ? table_of_group(wr, gw, nt) : 0u;
         q.grp_tab[gb + i] = t;
         if (np) {
             if (t != cur) {
@@ -713,10 +667,6 @@ hipError_t launch_piece_plan(const PieceArgs& q, uint64_t* zero_scalars, uint64_
 }
 
 constexpr uint32_t kSplitStatic = kSplitB / 64 * (kBatch + 64) + 256;   // static LDS of the split kernel, rounded up
-uint32_t split_lds_bytes(uint32_t n0) {
-    const uint32_t rows = (n0 + 4) * kSplitB * 4;
-    return rows < 36864u ? 36864u : rows;   // (also the counts of up to bytes / 8 groups: at least kExactGroups)
-}
 
 hipError_t launch_split(const PieceArgs& q, uint32_t cus, hipStream_t s) {
     const void* f = q.m2 == 16 ? (const void*)k_split<true> : (const void*)k_split<false>;

@@ -304,7 +304,8 @@ __global__ void __launch_bounds__(B, (D <= 16 ? 4 : 2)) k_sub_tables(CountArgs a
     for (uint32_t i = tid; i < CP; i += B) slots[i] = 0;
     __syncthreads();
     uint32_t wmax = 0;
-    const uint32_t n_tab = uniform((uint32_t)*t.n_tab), G = gridDim.x;
+    const uint64_t tabs = *t.n_tab;   // (a bin that the last ones did not suffice for went to the fallback)
+    const uint32_t n_tab = uniform(tabs < t.tab_cap ? (uint32_t)tabs : t.tab_cap), G = gridDim.x;
     // Work goes in batches of B pieces of one sub-table (and slice). While a
     // batch is counted the bases of the next one's pieces are on their way to
     // registers, the pieces of the one after that too, and the size and place

@@ -161,3 +161,12 @@ def test_large_bins(k, load):
     rng = np.random.default_rng(k)
     a, o = reads_to_csr(genome_reads(rng, k, glen=300000, n=24000))
     same(g.count_kmers(a, o, k, 9, 1, 1, 128, mode=B, load_factor=load), a, o, k, 1)
+
+
+@pytest.mark.parametrize("k,load,n", [(479, 4.0, 6_000_000), (300, 4.0, 3_000_000), (200, 4.0, 3_000_000)])
+def test_sub_tables_cut_by_their_bases(k, load, n):
+    """One bin of one long sequence with room for many more k-mers in a sub-table than for their bases: over a
+    thousand sub-tables, several times as many as the k-mers would make."""
+    rng = np.random.default_rng(k)
+    a, o = reads_to_csr([bases(rng, n)])
+    same(g.count_kmers(a, o, k, 11, 1, 1, 128, mode=B, load_factor=load), a, o, k, 1)

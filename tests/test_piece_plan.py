@@ -1,0 +1,47 @@
+"""The plan and scan arithmetic of the piece partition, run on the host
+(tests/piece_plan_driver.cpp over csrc/piece_plan.h): the array sizes and LDS
+limits that the kernels rely on hold for the groups that sequences make, at the
+key lengths and load factors where they are closest. Whole numbers: there is no
+tolerance."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from conftest import ROOT
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if not (os.path.exists(HIPCC) or shutil.which(HIPCC)):
+        pytest.skip("needs hipcc")
+    exe = str(tmp_path_factory.mktemp("plan") / "driver")
+    subprocess.run([HIPCC, "-x", "hip", "--offload-host-only", "--offload-arch=gfx950", "-O2", "-std=c++17",
+                    os.path.join(ROOT, "tests", "piece_plan_driver.cpp"), "-o", exe], check=True, capture_output=True)
+
+    def run(*args):
+        out = subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True, timeout=300).stdout
+        words = out.split()[1:]
+        return dict(zip(words[::2], map(int, words[1::2])))
+
+    return run
+
+
+# One sequence (the most pieces for its k-mers) and reads at 30x; long keys with
+# many k-mers per slot are cut by their bases, into several times the sub-tables
+# that their k-mers would make.
+@pytest.mark.parametrize("k,m,load,block,n_bins,G,cov,read", [
+    (479, 11, 4.0, 0, 1, 11_500_000, 0, 0), (479, 11, 4.0, 0, 1, 6_000_000, 0, 0), (479, 11, 0.0, 0, 1, 11_500_000, 0, 0),
+    (300, 9, 4.0, 0, 3, 6_000_000, 0, 0), (256, 11, 4.0, 1024, 1, 8_000_000, 0, 0), (200, 11, 4.0, 512, 2, 8_000_000, 0, 0),
+    (200, 11, 0.0, 0, 1, 1_000_000, 30, 1000), (99, 9, 4.0, 0, 1, 500_000, 30, 250), (65, 9, 0.0, 512, 1, 500_000, 30, 150),
+    (65, 9, 0.05, 0, 4, 1_000_000, 10, 150), (28, 9, 4.0, 0, 1, 500_000, 30, 100), (20, 7, 0.0, 0, 2, 500_000, 30, 100)])
+def test_sub_tables_fit_their_arrays(driver, k, m, load, block, n_bins, G, cov, read):
+    r = driver("genome", k, m, load, block, n_bins, G, cov, read, k + n_bins)
+    assert r["groups"] <= r["grp_cap"]
+    assert r["tables"] <= r["tab_cap"] and r["failed"] == 0
+    assert r["pieces"] <= r["list"]
+    assert r["most_halves"] <= r["max_halves"]
+    assert r["lost"] == 0
