@@ -198,9 +198,10 @@ __host__ __device__ inline uint32_t group_weight(const PieceArgs& q, uint32_t ta
 // Sub-tables of a bin whose groups weigh `weight` together, and the one that a
 // group of weight w, w0 of weight before it, belongs to: the middle of its
 // weight falls into it.
-__host__ __device__ inline uint32_t bin_tables(uint32_t weight) { return weight / kUnit + 1; }
-__host__ __device__ inline uint32_t table_of_group(uint32_t w0, uint32_t w, uint32_t n_tables) {
-    const uint32_t t = (w0 + w / 2) / kUnit;
+// (A bin can weigh 2^32 and more: 94 M k-mers at a load factor of 0.01.)
+__host__ __device__ inline uint32_t bin_tables(uint64_t weight) { return (uint32_t)(weight / kUnit) + 1; }
+__host__ __device__ inline uint32_t table_of_group(uint64_t w0, uint32_t w, uint32_t n_tables) {
+    const uint32_t t = (uint32_t)((w0 + w / 2) / kUnit);
     return t < n_tables ? t : n_tables - 1;
 }
 

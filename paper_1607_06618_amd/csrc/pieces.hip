@@ -483,7 +483,7 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
 __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
     __shared__ uint32_t wsum[32];
     __shared__ uint64_t s_light, s_heavy, s_hk;
-    __shared__ uint32_t s_tab, s_fail;
+    __shared__ uint32_t s_nh, s_tab, s_fail;
     const uint32_t tid = threadIdx.x, b = blockIdx.x;
     const uint64_t t0 = q.stage_clocks ? wall_clock64() : 0;
     const uint32_t P = q.ngrp[b], gb = q.grp_first[b];
@@ -501,11 +501,11 @@ __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
     const uint32_t target = (uint32_t)q.scal[kScalTarget];
     auto heavy = [&](uint64_t c) { return group_heavy(q, c); };
     auto weight = [&](uint64_t c) { return group_weight(q, target, c); };
-    if (tid == 0) s_hk = 0;
+    if (tid == 0) s_hk = 0, s_nh = 0;
     const uint32_t per = (P + kScanB - 1) / kScanB;
     const uint32_t i0 = tid * per, i1 = i0 + per < P ? i0 + per : P;
-    uint32_t nl = 0, nh = 0, w = 0;
-    uint64_t hk = 0;
+    uint32_t nl = 0, nh = 0;
+    uint64_t w = 0, hk = 0;
     for (uint32_t i = i0; i < i1; i++) {
         const uint64_t c = q.grp_cnt[gb + i];
         if (heavy(c)) {
@@ -516,10 +516,14 @@ __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
             w += weight(c);
         }
     }
-    uint32_t tl, th, tw;
-    const uint32_t pl = block_excl_scan(nl, wsum, tl), ph = block_excl_scan(nh, wsum, th);
-    (void)ph;
-    uint32_t wr = block_excl_scan(w, wsum, tw);
+    uint32_t tl, tw0, tw1;
+    const uint32_t pl = block_excl_scan(nl, wsum, tl);
+    if (nh) atomicAdd(&s_nh, nh);
+    // weights add up in 64 bits: 20 of them, and the ones above, at a time
+    uint64_t wr = block_excl_scan((uint32_t)w & 0xFFFFFu, wsum, tw0);
+    wr += (uint64_t)block_excl_scan((uint32_t)(w >> 20), wsum, tw1) << 20;
+    const uint64_t tw = ((uint64_t)tw1 << 20) + tw0;
+    const uint32_t th = s_nh;
     const uint32_t nt = tl ? bin_tables(tw) : 0u;
     if (hk) atomicAdd((unsigned long long*)&s_hk, (unsigned long long)hk);
     if (tid == 0) {

@@ -138,6 +138,27 @@ static void print(const char* what, const PieceArgs& q, const PieceSizing& z, co
            (unsigned long long)T.lost);
 }
 
+// groups <k> <m> <load> <block> <groups> <k-mers> <pieces>: one bin of equal groups
+static void groups(char** a) {
+    gerbil_params p;
+    memset(&p, 0, sizeof(p));
+    p.k = atoi(a[0]);
+    p.m = atoi(a[1]);
+    p.load_factor = (float)atof(a[2]);
+    p.block = atoi(a[3]);
+    p.n_bins = 1;
+    p.mode = GERBIL_BATCHED;
+    const uint64_t n = strtoull(a[4], 0, 10), kmers = strtoull(a[5], 0, 10), pieces = strtoull(a[6], 0, 10);
+    const PieceSizing z = piece_sizing(&p, n * kmers, n * pieces);
+    PieceArgs q;
+    memset(&q, 0, sizeof(q));
+    set_rules(q, &p, z);
+    Totals T;
+    T.kmers = n * kmers;
+    scan(q, (uint32_t)plan_target(q, T.kmers), std::vector<uint64_t>(n, pieces << 32 | kmers), T);
+    print("groups", q, z, T, 0);
+}
+
 // genome <k> <m> <load> <block> <n_bins> <genome bases> <coverage, 0: one sequence> <read> <seed>
 static void genome(char** a) {
     gerbil_params p;
@@ -184,6 +205,7 @@ static void genome(char** a) {
 
 int main(int argc, char** argv) {
     if (argc == 11 && !strcmp(argv[1], "genome")) genome(argv + 2);
+    else if (argc == 9 && !strcmp(argv[1], "groups")) groups(argv + 2);
     else return 2;
     return 0;
 }

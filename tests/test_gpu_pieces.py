@@ -170,3 +170,27 @@ def test_sub_tables_cut_by_their_bases(k, load, n):
     rng = np.random.default_rng(k)
     a, o = reads_to_csr([bases(rng, n)])
     same(g.count_kmers(a, o, k, 11, 1, 1, 128, mode=B, load_factor=load), a, o, k, 1)
+
+
+def test_more_than_a_million_sub_tables_in_a_bin():
+    """Weights of a bin's groups that add up to more than 2^32: pairs and histogram as from HBM tables."""
+    import torch
+    k, n = 65, 72_000_000
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    letters = torch.tensor(list(b"ACGT"), dtype=torch.uint8, device="cuda")
+    half = letters[torch.randint(0, 4, (n // 2,), generator=gen, device="cuda")]
+    ad = torch.cat([half, half])   # every k-mer but those of the seam twice
+    od = torch.tensor([0, n], dtype=torch.int64, device="cuda")
+    out = []
+    for kw in (dict(table=g.GERBIL_TABLE_HBM), dict(load_factor=0.005)):
+        p = g.make_params(k, 9, 1, 2, mode=B, pool=1, **kw)
+        job = g.Job(ad, od, n, p, hist_len=16)
+        job.run()
+        st, rep = g.gerbil_result(job.enc, job.bins, job.state, g._stream_handle(None))
+        assert st == g.GERBIL_OK
+        keys = job.keys_d[: rep.n_out * job.W].view(-1, job.W)
+        out.append((rep.n_out, job.hist_d.cpu().tolist(), keys.sum(0).tolist(), int(job.counts_d[: rep.n_out].sum())))
+        del job, keys
+    assert out[0] == out[1]
+    assert out[0][0] > n // 2 - 2 * k

@@ -45,3 +45,16 @@ def test_sub_tables_fit_their_arrays(driver, k, m, load, block, n_bins, G, cov, 
     assert r["pieces"] <= r["list"]
     assert r["most_halves"] <= r["max_halves"]
     assert r["lost"] == 0
+
+
+# 2^18 groups, the most a bin has: their weights add up to under and over 2^32
+@pytest.mark.parametrize("k,load,kmers,pieces", [(65, 0.005, 200, 20), (65, 0.005, 300, 30), (28, 0.005, 2_000, 500),
+                                                 (479, 0.01, 250, 12), (65, 0.0, 6_000, 300)])
+def test_weights_of_a_very_large_bin(driver, k, load, kmers, pieces):
+    """Every sub-table is one run of groups, of no more k-mers than a unit of weight and half a group to either side."""
+    r = driver("groups", k, 9, load, 0, 1 << 18, kmers, pieces)
+    assert r["heavy"] == 0 and r["failed"] == 0
+    assert r["lost"] == 0
+    assert r["tables"] <= r["tab_cap"]
+    assert r["most_halves"] <= r["max_halves"]
+    assert r["most_kmers"] <= max(2 * kmers, 2 * r["kmers"] // r["tables"] + kmers)
