@@ -153,6 +153,11 @@ __host__ __device__ inline uint64_t plan_target(const PieceArgs& q, uint64_t tot
     return target > q.target ? q.target : target;
 }
 
+// A group's count has 32 bits for its k-mers, and one sub-minimizer can bring all
+// of a bin's (tandem repeats): bins of more go to the fallback as a whole. (By
+// then their 2^18 groups are too large for LDS tables anyway.)
+__host__ __device__ inline bool bin_left_whole(uint64_t K) { return K >> 32 != 0; }
+
 // Groups of a bin of K k-mers in ns super-mers.
 __host__ __device__ inline uint32_t bin_groups(const PieceArgs& q, uint64_t target, uint64_t ns, uint64_t K) {
     if (ns == 0) return 0;

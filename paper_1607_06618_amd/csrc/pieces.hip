@@ -75,14 +75,18 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     descs = descs < 256 ? 256 : descs > most ? most : descs;
     __syncthreads();
     auto groups = [&](uint32_t b) -> uint32_t {
-        return overfull ? 0u : bin_groups(q, target, q.bin_off[b + 1] - q.bin_off[b], q.bin_kmers[b]);
+        return overfull || bin_left_whole(q.bin_kmers[b])
+                   ? 0u : bin_groups(q, target, q.bin_off[b + 1] - q.bin_off[b], q.bin_kmers[b]);
+    };
+    auto items = [&](uint32_t b) -> uint64_t {
+        return overfull || bin_left_whole(q.bin_kmers[b]) ? 0ull : (q.bin_off[b + 1] - q.bin_off[b] + descs - 1) / descs;
     };
     uint64_t sp = 0, it = 0;
     for (uint32_t e = 0; e < per; e++) {
         const uint32_t b = tid * per + e;
         if (b >= n) break;
         sp += groups(b);
-        it += overfull ? 0 : (q.bin_off[b + 1] - q.bin_off[b] + descs - 1) / descs;
+        it += items(b);
     }
     plan_scan(part, it);
     uint64_t it0 = part[tid] - it;
@@ -102,9 +106,9 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
         q.ngrp[b] = P;
         q.grp_first[b] = none ? 0u : (uint32_t)sp0;
         q.item_first[b] = none ? 0u : (uint32_t)it0;
-        q.bin_fail[b] = none ? 1u : 0u;
+        q.bin_fail[b] = none || (!overfull && bin_left_whole(q.bin_kmers[b])) ? 1u : 0u;
         sp0 += P;
-        it0 += overfull ? 0 : (q.bin_off[b + 1] - q.bin_off[b] + descs - 1) / descs;
+        it0 += items(b);
     }
     if (tid == 0) {
         q.grp_first[n] = none ? 0u : (uint32_t)n_sp;

@@ -155,7 +155,8 @@ static void groups(char** a) {
     set_rules(q, &p, z);
     Totals T;
     T.kmers = n * kmers;
-    scan(q, (uint32_t)plan_target(q, T.kmers), std::vector<uint64_t>(n, pieces << 32 | kmers), T);
+    if (bin_left_whole(T.kmers)) T.failed++;
+    else scan(q, (uint32_t)plan_target(q, T.kmers), std::vector<uint64_t>(n, (pieces << 32) + kmers), T);   // (as the split adds up)
     print("groups", q, z, T, 0);
 }
 

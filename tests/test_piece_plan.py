@@ -58,3 +58,13 @@ def test_weights_of_a_very_large_bin(driver, k, load, kmers, pieces):
     assert r["tables"] <= r["tab_cap"]
     assert r["most_halves"] <= r["max_halves"]
     assert r["most_kmers"] <= max(2 * kmers, 2 * r["kmers"] // r["tables"] + kmers)
+
+
+@pytest.mark.parametrize("kmers", [(1 << 32) - 1, 1 << 32, (1 << 32) + 5, 9_000_000_000])
+@pytest.mark.parametrize("groups", [1, 3])
+def test_k_mers_of_a_group_stay_in_their_half_word(driver, kmers, groups):
+    """One sub-minimizer can bring all of a bin's k-mers: either the groups' counts hold them, or the bin is left whole."""
+    r = driver("groups", 65, 9, 0.0, 0, groups, kmers, kmers // 48)
+    if r["failed"] == 0:
+        assert r["pieces"] == groups * (kmers // 48)
+        assert r["heavy"] == groups and r["heavy_kmers"] == groups * kmers
