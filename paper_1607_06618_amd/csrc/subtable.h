@@ -361,13 +361,14 @@ __global__ void __launch_bounds__(B, (D <= 16 ? 4 : 2)) k_sub_tables(CountArgs a
         const bool last = cur.p0 + B >= np;   // of the sub-table's pieces
         // one piece per thread
         const uint64_t start = piece_start(d);
-        const uint32_t n = cur.p0 + tid < np ? piece_kmers(d) : 0u;
+        uint32_t n = cur.p0 + tid < np ? piece_kmers(d) : 0u;
         const uint32_t nh = n ? ((uint32_t)(start & 15) + n + k + 14) >> 4 : 0u;
-        const uint32_t odd = (uint32_t)(start >> 4) & 1u, nq = (nh + odd + 3) >> 2;   // its bases: whole words, 16 bytes at a time
+        const uint32_t odd = (uint32_t)(start >> 4) & 1u;
+        uint32_t nq = (nh + odd + 3) >> 2;   // its bases: whole words, 16 bytes at a time
         const uint64_t* src = a.packed + (start >> 5);
         // segments of kSeg k-mers, and one of the rest: ordered by length, so that
         // the lanes of a wave roll equally far
-        const uint32_t rest = n % kSeg;
+        uint32_t rest = n % kSeg;
         const uint32_t mine = nh | ((n / kSeg) << 16);
         const uint32_t incl = wave_incl_sum(mine);
         uint32_t rank = 0, add = 0;   // lane c: the wave's segments of c k-mers; lane 0: the sums
@@ -384,12 +385,18 @@ __global__ void __launch_bounds__(B, (D <= 16 ? 4 : 2)) k_sub_tables(CountArgs a
         rank += __shfl(from, (int)rest);
         const uint32_t hpre = hbase + (pre & 0xFFFFu), spre = pre >> 16;
         __syncthreads();
-        const uint32_t total = cls[0];
+        uint32_t total = uniform(cls[0]);
         uint32_t S = total >> 16, at = 0;
 #pragma unroll
         for (uint32_t c = kSeg - 1; c > 0; c--) {
             if (c == rest) at = S + rank;
             S += cls[c];
+        }
+        if (hbase + (total & 0xFFFFu) > t.halves) {
+            // The scan's weights rule this out. Bases past the stage would
+            // overwrite slots: an error instead, and none of the batch counted.
+            if (tid == 0) set_status(a.status, ST_SPIN);
+            n = rest = nq = S = total = 0;
         }
         for (uint32_t q = 0; q < nq; q += kQuads) {
             if (q) {   // a longer piece than most

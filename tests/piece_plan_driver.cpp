@@ -160,6 +160,39 @@ static void groups(char** a) {
     print("groups", q, z, T, 0);
 }
 
+// random <k> <load> <block> <seed>: bins of groups of all sizes up to the heavy ones'
+static void random_groups(char** a) {
+    gerbil_params p;
+    memset(&p, 0, sizeof(p));
+    p.k = atoi(a[0]);
+    p.m = 9;
+    p.load_factor = (float)atof(a[1]);
+    p.block = atoi(a[2]);
+    p.n_bins = 1;
+    p.mode = GERBIL_BATCHED;
+    rng_state = strtoull(a[3], 0, 10);
+    const PieceSizing z = piece_sizing(&p, 1ull << 30, 1ull << 28);
+    PieceArgs q;
+    memset(&q, 0, sizeof(q));
+    set_rules(q, &p, z);
+    Totals T;
+    auto unit = []() { return (double)(rnd() >> 11) / (double)(1ull << 53); };
+    for (int trial = 0; trial < 3000; trial++) {
+        const uint32_t target = trial % 3 ? q.target : std::min(q.target, kMinTarget);
+        // a bin's own largest group, share of large ones, and k-mers a piece
+        const double top = q.max_halves * (trial % 2 ? 1.0 : unit()), large = unit() * unit();
+        std::vector<uint64_t> cnt(30 + rnd() % 300);
+        for (auto& c : cnt) {
+            const double len = 1 + 63 * unit() * unit(), halves = top * (unit() < large ? 0.2 + 0.8 * unit() : 0.15 * unit());
+            const uint64_t pieces = (uint64_t)(halves * 16 / (len + q.k + 29)), kmers = (uint64_t)(pieces * len);
+            c = pieces << 32 | (kmers < pieces ? pieces : kmers);
+        }
+        scan(q, target, cnt, T);
+        T.tables = 0;   // (a bin each)
+    }
+    print("random", q, z, T, 0);
+}
+
 // genome <k> <m> <load> <block> <n_bins> <genome bases> <coverage, 0: one sequence> <read> <seed>
 static void genome(char** a) {
     gerbil_params p;
@@ -207,6 +240,7 @@ static void genome(char** a) {
 int main(int argc, char** argv) {
     if (argc == 11 && !strcmp(argv[1], "genome")) genome(argv + 2);
     else if (argc == 9 && !strcmp(argv[1], "groups")) groups(argv + 2);
+    else if (argc == 6 && !strcmp(argv[1], "random")) random_groups(argv + 2);
     else return 2;
     return 0;
 }

@@ -194,3 +194,15 @@ def test_more_than_a_million_sub_tables_in_a_bin():
         del job, keys
     assert out[0] == out[1]
     assert out[0][0] > n // 2 - 2 * k
+
+
+@pytest.mark.parametrize("k,load", [(65, 4.0), (99, 4.0), (99, 0.0), (200, 0.0)])
+def test_large_groups_side_by_side(k, load):
+    """One bin whose stretches occur once to 120 times: sub-tables are cut by their bases, from groups of very different sizes."""
+    rng = np.random.default_rng(k)
+    reads = []
+    for _ in range(900):
+        s = bases(rng, k + int(rng.integers(20, 300)))
+        reads += [s if rng.random() < 0.5 else flip(s) for _ in range(int(120 ** rng.random()))]
+    a, o = reads_to_csr([reads[i] for i in rng.permutation(len(reads))])
+    same(g.count_kmers(a, o, k, 9, 1, 1, 256, mode=B, load_factor=load), a, o, k, 1)

@@ -68,3 +68,12 @@ def test_k_mers_of_a_group_stay_in_their_half_word(driver, kmers, groups):
     if r["failed"] == 0:
         assert r["pieces"] == groups * (kmers // 48)
         assert r["heavy"] == groups and r["heavy_kmers"] == groups * kmers
+
+
+@pytest.mark.parametrize("load", [0.0, 0.3, 4.0])
+@pytest.mark.parametrize("k,block", [(20, 0), (28, 512), (65, 0), (99, 0), (200, 512), (256, 0), (479, 0)])
+def test_bases_of_a_sub_table_fit_the_stage(driver, k, block, load):
+    """Whatever the sizes of a bin's groups, large ones side by side among them, a sub-table's bases fit its LDS stage."""
+    r = driver("random", k, load, block, k)
+    assert r["failed"] == 0 and r["lost"] == 0
+    assert 0.8 * r["max_halves"] < r["most_halves"] <= r["max_halves"]
