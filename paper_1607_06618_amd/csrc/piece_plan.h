@@ -19,7 +19,12 @@ constexpr uint32_t kItemDescs = 4096;      // descriptors per item at most (at l
 // own: 0.6 G bases at k = 28 in 32 bins took 17.7 ms, now 10.3 ms (14.2 by key hash).
 constexpr uint32_t kItemDescsMany = 16384;
 constexpr uint32_t kManyGroups = 3500;
-constexpr uint32_t kItemGoal = 2048;       // items wanted
+// Items wanted (a PLAIN group's, or all bins'). An item adds its counts to its
+// bin's groups and reserves places in its sub-tables one by one, so small items
+// pay for each; 256 leave the chip idle: per-bin schedule of 125 M bases at k =
+// 55 2.81 / 2.54 / 2.61 / 2.82 ms with 256 / 512 / 1024 / 2048 items, 10 M bases
+// at k = 32 185 / 186 / 195 / 212 us.
+constexpr uint32_t kItemGoal = 512;
 constexpr uint32_t kItemSlack = 64;        // list slots of an item over its expected pieces
 constexpr uint32_t kMinTarget = 1024;      // k-mers of a small input's sub-tables
 constexpr uint32_t kUnit = 4096;           // weight of a full sub-table

@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     if (tid < kScalCount) q.scal[tid] = 0;
     const uint32_t n = q.n_bins, per = (n + kPlanB - 1) / kPlanB;
     const bool overfull = *q.n_superm > q.superm_cap;   // descriptors past the capacity were never stored
-    const uint64_t S = overfull ? 0 : q.bin_off[n];
+    const uint64_t S = overfull ? 0 : q.bin_off[n] - q.bin_off[0];   // (the bins of a PLAIN group are not the first)
     uint32_t descs = (uint32_t)((S / kItemGoal + 63) & ~63ull);
     // k-mers per sub-table: the target, or less where that leaves workgroups without one
     uint64_t km = 0;

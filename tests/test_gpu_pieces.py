@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import random_reads, reads_to_csr, to_device
+from gpu_util import bin_arrays, random_reads, reads_to_csr, to_device
 from paper_1607_06618_amd import gerbil as g
 
 pytestmark = pytest.mark.gpu
@@ -206,3 +206,32 @@ def test_large_groups_side_by_side(k, load):
         reads += [s if rng.random() < 0.5 else flip(s) for _ in range(int(120 ** rng.random()))]
     a, o = reads_to_csr([reads[i] for i in rng.permutation(len(reads))])
     same(g.count_kmers(a, o, k, 9, 1, 1, 256, mode=B, load_factor=load), a, o, k, 1)
+
+
+def test_items_of_a_plain_group_are_of_its_own_super_mers():
+    """The split's work items grow with the super-mers of the group (a 512th of them, 256 to 4096), not with those of
+    the bins before it."""
+    import torch
+    k, n_bins = 41, 64
+    rng = np.random.default_rng(5)
+    gen = np.array(list(b"ACGT"), np.uint8)[rng.integers(0, 4, 20_000_000)]   # one sequence: about a super-mer for every 17 bases
+    o = np.array([0, gen.size], np.uint64)
+    ad, od = to_device(gen, o)
+    clocks = torch.zeros(8, dtype=torch.int64, device="cuda")
+    p = g.make_params(k, 9, n_bins, 1, mode=g.GERBIL_PLAIN, stage_clocks=clocks.data_ptr())
+    job = g.Job(ad, od, gen.size, p, hist_len=128)
+    job.run()
+    job.result()
+    _, off, kmers = bin_arrays(job)
+    ns, items, groups = np.diff(off.astype(np.int64)), 0, 0
+    b = 0
+    while b < n_bins:   # groups: bins in order, up to 2^23 k-mers
+        e = b + 1
+        while e < n_bins and int(kmers[b:e + 1].sum()) <= 1 << 23:
+            e += 1
+        descs = min(max((int(ns[b:e].sum()) // 512 + 63) // 64 * 64, 256), 4096)
+        items += int((-(-ns[b:e] // descs)).sum())
+        groups += 1
+        b = e
+    assert groups >= 3
+    assert int(clocks[4]) == items
