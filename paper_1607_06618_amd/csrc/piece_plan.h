@@ -19,17 +19,27 @@ constexpr uint32_t kItemDescs = 4096;      // descriptors per item at most (at l
 // own: 0.6 G bases at k = 28 in 32 bins took 17.7 ms, now 10.3 ms (14.2 by key hash).
 constexpr uint32_t kItemDescsMany = 16384;
 constexpr uint32_t kManyGroups = 3500;
-// Items wanted (a PLAIN group's, or all bins'). An item adds its counts to its
-// bin's groups and reserves places in its sub-tables one by one, so small items
-// pay for each; 256 leave the chip idle: per-bin schedule of 125 M bases at k =
-// 55 2.81 / 2.54 / 2.61 / 2.82 ms with 256 / 512 / 1024 / 2048 items, 10 M bases
-// at k = 32 185 / 186 / 195 / 212 us.
-constexpr uint32_t kItemGoal = 512;
+// Items of a PLAIN group, or of all bins: 2048, which even out their lengths.
+// An item adds its counts to its bin's groups and reserves places in its
+// sub-tables one by one, so of few super-mers each item gets 1024, as long as
+// that leaves one for each of the split kernel's three workgroups a CU: a PLAIN
+// pass over 125 M bases at k = 55 takes 2.54 ms with 512 items a group, 2.51
+// with 768, 2.60 with 1024 and 2.82 with 2048; 100 M bases at k = 28, where the
+// rule makes no difference to 768, 3.29 / 2.97 / 3.23 / 3.50 ms.
+constexpr uint32_t kItemGoal = 2048;
+constexpr uint32_t kItemFew = 768, kItemFewDescs = 1024;
 constexpr uint32_t kItemSlack = 64;        // list slots of an item over its expected pieces
 constexpr uint32_t kMinTarget = 1024;      // k-mers of a small input's sub-tables
 constexpr uint32_t kUnit = 4096;           // weight of a full sub-table
 constexpr uint32_t kLargeGroup = kUnit * 26 / 100;
 
+// Descriptors per item, for S super-mers in all.
+__host__ __device__ inline uint32_t item_descs(uint64_t S, bool many) {
+    const uint64_t few = S / kItemFew < kItemFewDescs ? S / kItemFew : kItemFewDescs, most = many ? kItemDescsMany : kItemDescs;
+    uint64_t d = S / kItemGoal > few ? S / kItemGoal : few;
+    d = (d + 63) & ~63ull;
+    return (uint32_t)(d < 256 ? 256 : d > most ? most : d);
+}
 inline uint32_t piece_items_cap(uint64_t n_superm, uint32_t n_bins) {
     return (uint32_t)(n_superm / kItemDescs + 2 * kItemGoal + n_bins + 8);
 }

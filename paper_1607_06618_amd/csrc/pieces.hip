@@ -61,7 +61,6 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     const uint32_t n = q.n_bins, per = (n + kPlanB - 1) / kPlanB;
     const bool overfull = *q.n_superm > q.superm_cap;   // descriptors past the capacity were never stored
     const uint64_t S = overfull ? 0 : q.bin_off[n] - q.bin_off[0];   // (the bins of a PLAIN group are not the first)
-    uint32_t descs = (uint32_t)((S / kItemGoal + 63) & ~63ull);
     // k-mers per sub-table: the target, or less where that leaves workgroups without one
     uint64_t km = 0;
     for (uint32_t e = 0; e < per; e++) {
@@ -70,23 +69,25 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     }
     plan_scan(part, km);
     const uint64_t target = plan_target(q, part[kPlanB - 1]);
-    // (large bins: an item has several pieces for each of their groups)
-    const uint32_t most = part[kPlanB - 1] * kGroupsPerTable / target > (uint64_t)n * kManyGroups ? kItemDescsMany : kItemDescs;
-    descs = descs < 256 ? 256 : descs > most ? most : descs;
+    const bool many = part[kPlanB - 1] * kGroupsPerTable / target > (uint64_t)n * kManyGroups;
+    const uint32_t descs = item_descs(S, many);
     __syncthreads();
-    auto groups = [&](uint32_t b) -> uint32_t {
-        return overfull || bin_left_whole(q.bin_kmers[b])
-                   ? 0u : bin_groups(q, target, q.bin_off[b + 1] - q.bin_off[b], q.bin_kmers[b]);
+    struct Planned {
+        uint32_t groups, whole;
+        uint64_t items;
     };
-    auto items = [&](uint32_t b) -> uint64_t {
-        return overfull || bin_left_whole(q.bin_kmers[b]) ? 0ull : (q.bin_off[b + 1] - q.bin_off[b] + descs - 1) / descs;
+    auto planned = [&](uint32_t b) -> Planned {   // (everything is loaded before the caller stores)
+        const uint64_t ns = q.bin_off[b + 1] - q.bin_off[b], K = q.bin_kmers[b];
+        if (overfull || bin_left_whole(K)) return Planned{0, overfull ? 0u : 1u, 0};
+        return Planned{bin_groups(q, target, ns, K), 0, (ns + descs - 1) / descs};
     };
     uint64_t sp = 0, it = 0;
     for (uint32_t e = 0; e < per; e++) {
         const uint32_t b = tid * per + e;
         if (b >= n) break;
-        sp += groups(b);
-        it += items(b);
+        const Planned p = planned(b);
+        sp += p.groups;
+        it += p.items;
     }
     plan_scan(part, it);
     uint64_t it0 = part[tid] - it;
@@ -102,13 +103,13 @@ __global__ void __launch_bounds__(kPlanB) k_piece_plan(PieceArgs q, uint64_t* ze
     for (uint32_t e = 0; e < per; e++) {
         const uint32_t b = tid * per + e;
         if (b >= n) break;
-        const uint32_t P = none ? 0u : groups(b);
-        q.ngrp[b] = P;
+        const Planned p = planned(b);
+        q.ngrp[b] = none ? 0u : p.groups;
         q.grp_first[b] = none ? 0u : (uint32_t)sp0;
         q.item_first[b] = none ? 0u : (uint32_t)it0;
-        q.bin_fail[b] = none || (!overfull && bin_left_whole(q.bin_kmers[b])) ? 1u : 0u;
-        sp0 += P;
-        it0 += items(b);
+        q.bin_fail[b] = none ? 1u : p.whole;
+        sp0 += p.groups;
+        it0 += p.items;
     }
     if (tid == 0) {
         q.grp_first[n] = none ? 0u : (uint32_t)n_sp;

@@ -64,7 +64,7 @@ static void cut_read(const PieceArgs& q, uint32_t m, uint32_t n_bins, uint64_t p
     for (size_t i = 0; i < mn.size();) {
         size_t e = i + 1;
         while (e < mn.size() && mn[e] == mn[i] && (pos + e) % 2048 != 0) e++;
-        Bin& b = bins[mn[i] % n_bins];
+        Bin& b = bins[(mn[i] >> (32 - 2 * m)) % n_bins];
         b.ns++;
         b.kmers += e - i;
         while (i < e) {   // turns

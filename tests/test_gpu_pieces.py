@@ -209,7 +209,7 @@ def test_large_groups_side_by_side(k, load):
 
 
 def test_items_of_a_plain_group_are_of_its_own_super_mers():
-    """The split's work items grow with the super-mers of the group (a 512th of them, 256 to 4096), not with those of
+    """The split's work items grow with the super-mers of the group (a 2048th of them, or 1024 if a 768th is more than that; 256 to 4096), not with those of
     the bins before it."""
     import torch
     k, n_bins = 41, 64
@@ -229,7 +229,8 @@ def test_items_of_a_plain_group_are_of_its_own_super_mers():
         e = b + 1
         while e < n_bins and int(kmers[b:e + 1].sum()) <= 1 << 23:
             e += 1
-        descs = min(max((int(ns[b:e].sum()) // 512 + 63) // 64 * 64, 256), 4096)
+        S = int(ns[b:e].sum())
+        descs = min(max((max(S // 2048, min(S // 768, 1024)) + 63) // 64 * 64, 256), 4096)
         items += int((-(-ns[b:e] // descs)).sum())
         groups += 1
         b = e
