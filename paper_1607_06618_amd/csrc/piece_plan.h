@@ -126,7 +126,7 @@ inline PieceSizing piece_sizing(const gerbil_params* p, uint64_t n_kmers, uint64
     z.piece_fx = (uint32_t)(65536.0 * 2.15 / (w2 + 1));
     z.items_cap = piece_items_cap(n_superm, p->n_bins);
     // the number of a large bin's groups is rounded up to a power of two
-    const uint64_t E = n_superm + ((n_kmers * z.piece_fx) >> 16);
+    const uint64_t E = n_superm + n_kmers / z.n0 + ((n_kmers * z.piece_fx) >> 16);   // (never less than the plan's bins add up to)
     const uint64_t tabs = n_kmers / z.target + piece_halves(n_kmers, E, p->k) / z.half_target + kTablesGoal;
     z.grp_cap = 2 * kGroupsPerTable * tabs + 2ull * p->n_bins;
     // Sub-tables: no more than the groups' weights add up to (group_weight), for
@@ -154,6 +154,7 @@ inline void set_rules(PieceArgs& q, const gerbil_params* p, const PieceSizing& z
     q.heavy_kmers = z.heavy_kmers;
     q.max_halves = z.max_halves;
     q.piece_fx = z.piece_fx;
+    q.turn_fx = 65536 / z.n0;
     q.tables_goal = p->load_factor > 0 ? 1 : kTablesGoal;   // (a load that is asked for stands)
     q.grp_cap = (uint32_t)std::min<uint64_t>(z.grp_cap, 0xFFFFFFFFull);
     q.tab_cap = (uint32_t)std::min<uint64_t>(z.tab_cap, 0xFFFFFFFFull);
@@ -173,10 +174,18 @@ __host__ __device__ inline uint64_t plan_target(const PieceArgs& q, uint64_t tot
 // then their 2^18 groups are too large for LDS tables anyway.)
 __host__ __device__ inline bool bin_left_whole(uint64_t K) { return K >> 32 != 0; }
 
+// Pieces to expect from K k-mers in ns super-mers: their sub-minimizers change,
+// and a super-mer is split in turns of n0 windows at most: K / n0 of them and
+// half a turn more for each where they are long (half of all pieces at k = 479).
+__host__ __device__ inline uint64_t expected_pieces(const PieceArgs& q, uint64_t ns, uint64_t K) {
+    const uint64_t turns = ns / 2 + ((K * q.turn_fx) >> 16);
+    return (turns > ns ? turns : ns) + ((K * q.piece_fx) >> 16);
+}
+
 // Groups of a bin of K k-mers in ns super-mers.
 __host__ __device__ inline uint32_t bin_groups(const PieceArgs& q, uint64_t target, uint64_t ns, uint64_t K) {
     if (ns == 0) return 0;
-    const uint64_t E = ns + ((K * q.piece_fx) >> 16);
+    const uint64_t E = expected_pieces(q, ns, K);
     // an eighth of a sub-table each; of large bins more, so that an item's
     // counts of groups and sub-tables fit in LDS
     const uint64_t halves = piece_halves(K, E, q.k);
@@ -186,6 +195,12 @@ __host__ __device__ inline uint32_t bin_groups(const PieceArgs& q, uint64_t targ
     uint64_t P = (K * per + target - 1) / target;
     const uint64_t Ph = (halves * per + q.half_target - 1) / q.half_target;
     if (Ph > P) P = Ph;
+    // Where bases are what fills the sub-tables (k above some 130), groups of about
+    // one would often be heavy, and keys above 256 bases are then counted in HBM
+    // tables: as many groups as LDS counts, and three for two sub-tables at
+    // least. 20 M bases at k = 479 in one bin 6.07 -> 1.61 ms, 60 M at k = 300 in
+    // four 11.3 -> 2.83 ms, 600 M at k = 200 in 32 10.6 -> 10.5 ms.
+    if (Th > Tk && per < kGroupsPerTable) P = 3 * Th / 2 > kExactGroups ? 3 * Th / 2 : kExactGroups;
     if (P > kExactGroups) {
         uint64_t p2 = kExactGroups;
         while (p2 < P && p2 < kMaxGroups) p2 *= 2;

@@ -100,6 +100,7 @@ struct PieceArgs {
     uint32_t heavy_kmers;     // a sub-table of more goes to the fallback
     uint32_t max_halves;      // staged half words a sub-table may need
     uint32_t piece_fx;        // expected pieces per k-mer, 16.16 (over the one per super-mer)
+    uint32_t turn_fx;         // turns per k-mer of a long super-mer: 65536 / n0
     uint32_t grp_cap, tab_cap, items_cap;
     uint64_t cap;             // pieces that fit in list and in pieces
     // plan

@@ -82,7 +82,7 @@ static void cut_read(const PieceArgs& q, uint32_t m, uint32_t n_bins, uint64_t p
 }
 
 struct Totals {
-    uint64_t groups = 0, heavy = 0, tables = 0, failed = 0, kmers = 0, heavy_kmers = 0, pieces = 0, lost = 0;
+    uint64_t groups = 0, heavy = 0, tables = 0, failed = 0, kmers = 0, heavy_kmers = 0, pieces = 0, expected = 0, lost = 0;
     uint64_t most_halves = 0, most_kmers = 0;
 };
 
@@ -130,11 +130,11 @@ static void scan(const PieceArgs& q, uint32_t target, const std::vector<uint64_t
 
 static void print(const char* what, const PieceArgs& q, const PieceSizing& z, const Totals& T, uint64_t list) {
     printf("%s tables %llu tab_cap %llu failed %llu groups %llu grp_cap %llu heavy %llu kmers %llu heavy_kmers %llu "
-           "pieces %llu list %llu most_halves %llu max_halves %u most_kmers %llu lost %llu\n",
+           "pieces %llu expected %llu list %llu most_halves %llu max_halves %u most_kmers %llu lost %llu\n",
            what, (unsigned long long)T.tables, (unsigned long long)z.tab_cap, (unsigned long long)T.failed,
            (unsigned long long)T.groups, (unsigned long long)z.grp_cap, (unsigned long long)T.heavy,
            (unsigned long long)T.kmers, (unsigned long long)T.heavy_kmers, (unsigned long long)T.pieces,
-           (unsigned long long)list, (unsigned long long)T.most_halves, q.max_halves, (unsigned long long)T.most_kmers,
+           (unsigned long long)T.expected, (unsigned long long)list, (unsigned long long)T.most_halves, q.max_halves, (unsigned long long)T.most_kmers,
            (unsigned long long)T.lost);
 }
 
@@ -230,6 +230,7 @@ static void genome(char** a) {
     for (const Bin& b : bins) {
         const uint32_t P = bin_groups(q, target, b.ns, b.kmers);
         if (P == 0) continue;
+        T.expected += expected_pieces(q, b.ns, b.kmers);
         std::vector<uint64_t> cnt(P);
         for (uint64_t x : b.pieces) cnt[group_of_hash((uint32_t)(x >> 8), P)] += (1ull << 32) | (x & 255);
         scan(q, (uint32_t)target, cnt, T);

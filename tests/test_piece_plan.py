@@ -77,3 +77,21 @@ def test_bases_of_a_sub_table_fit_the_stage(driver, k, block, load):
     r = driver("random", k, load, block, k)
     assert r["failed"] == 0 and r["lost"] == 0
     assert 0.8 * r["max_halves"] < r["most_halves"] <= r["max_halves"]
+
+
+@pytest.mark.parametrize("k,m,n_bins,G,cov,read", [
+    (20, 7, 2, 2_000_000, 0, 0), (28, 9, 4, 2_000_000, 0, 0), (55, 9, 2, 500_000, 10, 150), (65, 9, 1, 2_000_000, 0, 0),
+    (99, 9, 4, 500_000, 10, 250), (111, 9, 1, 2_000_000, 0, 0), (200, 11, 1, 2_000_000, 0, 0), (300, 7, 2, 2_000_000, 0, 0),
+    (479, 11, 1, 4_000_000, 0, 0), (480, 15, 1, 2_000_000, 0, 0)])
+def test_expected_pieces(driver, k, m, n_bins, G, cov, read):
+    """The plan's estimate counts every kind of cut. It is an upper one: a tenth is added for change of sub-minimizers
+    and ends, and turns shared out evenly are a few less; it is never short by more than 5 %."""
+    r = driver("genome", k, m, 0.0, 0, n_bins, G, cov, read, k)
+    assert r["pieces"] / 1.05 <= r["expected"] <= 1.3 * r["pieces"]
+
+
+@pytest.mark.parametrize("load,n_bins,G", [(0.0, 1, 11_500_000), (0.0, 1, 7_000_000), (4.0, 1, 18_000_000), (0.0, 4, 18_000_000)])
+def test_groups_of_long_keys_are_seldom_heavy(driver, load, n_bins, G):
+    """Keys above 256 bases whose groups are heavy are counted in HBM tables: a random sequence leaves next to none."""
+    r = driver("genome", 479, 11, load, 0, n_bins, G, 0, 0, 1)
+    assert r["heavy_kmers"] <= 0.01 * r["kmers"]
