@@ -391,7 +391,7 @@ def main(argv=None):
             tune = None
             if args.tune and mode == g.GERBIL_BATCHED:
                 info = job.autotune()
-                tune = {"table": {g.GERBIL_TABLE_LDS: "lds", g.GERBIL_TABLE_HBM: "hbm"}[info.table],
+                tune = {"table": {g.GERBIL_TABLE_AUTO: "auto", g.GERBIL_TABLE_LDS: "lds", g.GERBIL_TABLE_HBM: "hbm"}[info.table],
                         "load_factor": round(info.load_factor, 3), "pool": info.pool, "block": info.block,
                         "candidates": info.candidates, "cached": bool(info.cached),
                         "best_count_ms": round(info.best_ms, 3)}

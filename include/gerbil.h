@@ -345,14 +345,15 @@ int32_t gerbil_graph_destroy(gerbil_graph* g);
 
 /* What gerbil_autotune chose. */
 typedef struct {
-    uint32_t table;          /* GERBIL_TABLE_LDS or GERBIL_TABLE_HBM                     */
-    float load_factor;       /* chosen gerbil_params.load_factor                         */
+    uint32_t table;          /* GERBIL_TABLE_LDS or GERBIL_TABLE_HBM; GERBIL_TABLE_AUTO where that alone
+                                takes the second minimizer (PLAIN, or k > 256)           */
+    float load_factor;       /* chosen gerbil_params.load_factor (0: the default)        */
     uint32_t pool;           /* chosen gerbil_params.pool (0 in PLAIN mode)              */
     uint32_t candidates;     /* candidates timed (0 when the choice came from the cache) */
     uint32_t cached;         /* 1 if the choice came from the cache                      */
     float best_ms;           /* time of one gerbil_count with the choice                 */
-    uint32_t block;          /* chosen gerbil_params.block (LDS: 1024 or 512 threads per
-                                workgroup; HBM: 256, 512 or 1024)                            */
+    uint32_t block;          /* chosen gerbil_params.block (LDS: 1024 or 512 threads per workgroup; HBM: 256,
+                                512 or 1024; the caller's own, or 0 with AUTO, if that is the choice) */
 } gerbil_tune_result;
 
 /* Workspace bytes that fit every candidate of gerbil_autotune for these
@@ -360,17 +361,19 @@ typedef struct {
 int32_t gerbil_autotune_workspace(const gerbil_bins* bins, const gerbil_params* p, uint64_t* bytes,
                                   hipStream_t stream);
 
-/* Time gerbil_count on `bins` for each candidate of the grid (LDS tables:
+/* Time gerbil_count on `bins` for the caller's own parameters and for each
+ * candidate of the grid (bins split by the second minimizer: load_factor
+ * default/0.6/0.8/1.0 x block 1024/512, p->pool; LDS tables by key hash:
  * load_factor 0.6/0.8/1.0/1.2 x pool 8/16/24 x block 1024/512; HBM tables:
  * load_factor 0.4/0.6 x pool 8/32 x block 256/512/1024; p->table = LDS or
  * HBM restricts the grid to that placement; PLAIN mode has no pool and LDS
- * tables only block 1024) and write into *best a copy of *p with table,
+ * tables by key hash only block 1024) and write into *best a copy of *p with table,
  * load_factor, pool and block of the fastest candidate that finished without
  * a capacity error (one warm-up run, then one timed run per candidate). Candidates whose workspace exceeds ws_bytes are skipped.
  * keys/counts/cap serve as the output of the trial runs (their contents are
- * overwritten). The choice is cached per (device, ceil(k/32), m, n_bins,
- * mode, p->table, and the total, largest and median bin size in quarter
- * octaves); a later call with the same profile returns the cached choice
+ * overwritten). The choice is cached per (device, k, m, n_bins, mode, table,
+ * load_factor, pool, block and size_sample of *p, and the total, largest and
+ * median bin size in quarter octaves); a later call with the same profile returns the cached choice
  * without running anything (info->cached = 1). SYNCHRONISES `stream`.
  * Errors: GERBIL_EINVAL (bad arguments, or no candidate fits ws_bytes),
  * GERBIL_ECAPACITY (cap too small, or every candidate ran out of a

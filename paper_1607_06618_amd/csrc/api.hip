@@ -327,23 +327,6 @@ uint64_t lds_fixed(const LdsSizing& z, void* ws, uint64_t start, LdsLayout* L) {
 // LDS tables are allowed, keys of any length included: its tables refer to
 // the bases instead of holding keys. Keys below kPieceMinK stay with the
 // key partition (LDS path).
-constexpr uint64_t kShortKeyBin = 16ull << 20;   // bases per bin
-
-// PLAIN takes the pieces too where AUTO leaves the partition to the library
-// and nothing asks for the key partition's sampled run sizes: a group of bins
-// at a time, as many as their pieces fit in the workspace. Four launches per
-// bin left most of the chip idle: 256 bins of 0.3 M 55-mers took 23.2 ms, in
-// groups 2.8 ms.
-bool use_pieces(const gerbil_params* p, uint64_t n_bytes) {
-    if (p->k < kPieceMinK || n_bytes >= (1ull << 38)) return false;
-    // Short keys have few sub-minimizers (4^10 or 4^11 at k < 24, and the smallest
-    // dozenth of those takes most k-mers): in a large bin each brings more than a
-    // sub-table's. 1.2 G bases at k = 21 in 32 bins: 65 ms by pieces, 41 by key
-    // hash; 0.3 G in 32 bins 7.7 and 9.2 ms, 1.2 G in 512 bins 28.8 and 36.1 ms.
-    if (p->k < 24 && n_bytes / p->n_bins > kShortKeyBin) return false;
-    if (p->mode == GERBIL_BATCHED) return p->table != GERBIL_TABLE_HBM;
-    return p->table == GERBIL_TABLE_AUTO && words_for(p->k) <= GERBIL_MAX_LDS_W && p->size_sample == 0;
-}
 // k-mers of a group of PLAIN bins at most (or the largest bin's): some 900
 // sub-tables, enough for every CU to count several.
 constexpr uint64_t kPlainGroup = 1ull << 23;

@@ -1,9 +1,9 @@
-// Autotuner of the counting schedule: times gerbil_count over a small grid
-// of table placements, fill levels, pool sizes and workgroup shapes on the
-// caller's bins and
-// keeps the fastest choice that completes without a capacity error. Choices
-// are cached per (device, key width, m, bins, schedule, bin-size profile),
-// so later runs of the same shape skip the timing. The paper picks thread
+// Autotuner of the counting schedule: times gerbil_count with the caller's own
+// parameters and over a small grid of table placements, fill levels, pool sizes
+// and workgroup shapes on the caller's bins and keeps the fastest choice that
+// completes without a capacity error. Choices are cached per (device, k, m,
+// bins, schedule, the caller's choices, bin-size profile), so later runs of
+// the same shape skip the timing. The paper picks thread
 // counts at run time and re-estimates table sizes per file (Sec. 2.3,
 // Sec. 3.4.1); here the device-side analogs are tuned by measurement.
 #include <math.h>
@@ -15,8 +15,7 @@
 #include <tuple>
 #include <vector>
 
-#include "gerbil.h"
-#include "common.h"
+#include "piece_plan.h"
 
 namespace {
 
@@ -27,18 +26,34 @@ struct Candidate {
     uint32_t block;
 };
 
-using Key = std::tuple<int, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, int, int, int>;
+using Key = std::tuple<int, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, float, uint32_t, uint32_t, uint32_t, bool, int, int, int>;
 
 std::mutex g_mu;
 std::map<Key, gerbil_tune_result> g_cache;
 
 int quarter_octave(uint64_t x) { return x ? (int)floor(4.0 * log2((double)x)) : -1; }
 
-std::vector<Candidate> candidates(const gerbil_params* p) {
+// What may run for p, the caller's own parameters first: a choice is never
+// slower than them but for the noise of the timing. Where the pieces count
+// (piece_plan.h), pools only size their fallback and are left as they are; AUTO
+// stays AUTO where it alone takes them (PLAIN, and keys above 256 bases), and is
+// LDS where that is the same.
+std::vector<Candidate> candidates(const gerbil_params* p, uint64_t n_bytes) {
     std::vector<Candidate> c;
-    const bool batched = p->mode == GERBIL_BATCHED;
-    if (p->table != GERBIL_TABLE_HBM && (p->k + 31) / 32 <= GERBIL_MAX_LDS_W) {
-        // LDS: one 1024-thread workgroup per CU, or two of 512 with half-size tables
+    const bool batched = p->mode == GERBIL_BATCHED, lds_keys = (p->k + 31) / 32 <= GERBIL_MAX_LDS_W;
+    const bool pieces = gerbil::use_pieces(p, n_bytes);
+    const uint32_t own = p->table == GERBIL_TABLE_AUTO && lds_keys && (batched || !pieces) ? GERBIL_TABLE_LDS : p->table;
+    const uint32_t own_block = p->block ? p->block : own == GERBIL_TABLE_LDS ? 1024u : own == GERBIL_TABLE_HBM ? 256u : 0u;
+    c.push_back({own, p->load_factor, p->pool, own_block});
+    if (pieces) {
+        for (uint32_t b : {1024u, 512u}) {
+            if (b == 1024u && !lds_keys) continue;   // (one shape)
+            for (float f : {0.0f, 0.6f, 0.8f, 1.0f})
+                if (f != c[0].load || b != c[0].block) c.push_back({own, f, p->pool, b});
+        }
+    }
+    if (p->table != GERBIL_TABLE_HBM && lds_keys && !(batched && pieces)) {
+        // LDS by key hash: one 1024-thread workgroup per CU, or two of 512 with half-size tables
         const float fills[] = {0.6f, 0.8f, 1.0f, 1.2f};
         const uint32_t pools[] = {8, 16, 24};   // multiples of the XCD queues
         for (uint32_t b : {1024u, 512u}) {
@@ -88,8 +103,9 @@ int32_t profile_key(const gerbil_bins* bins, const gerbil_params* p, hipStream_t
     std::sort(km.begin(), km.end());
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return GERBIL_EDEVICE;
-    *key = Key(dev, (p->k + 31) / 32, p->m, p->n_bins, p->mode, p->table, quarter_octave(total),
-               quarter_octave(km.back()), quarter_octave(km[km.size() / 2]));
+    *key = Key(dev, p->k, p->m, p->n_bins, p->mode, p->table, p->load_factor, p->pool, p->block, p->size_sample,
+               gerbil::use_pieces(p, bins->n_bytes), quarter_octave(total), quarter_octave(km.back()),
+               quarter_octave(km[km.size() / 2]));
     return GERBIL_OK;
 }
 
@@ -101,11 +117,13 @@ int32_t gerbil_autotune_workspace(const gerbil_bins* bins, const gerbil_params* 
                                   hipStream_t stream) {
     if (!bins || !p || !bytes) return GERBIL_EINVAL;
     uint64_t mx = 0;
-    for (const Candidate& c : candidates(p)) {
+    bool own = true;
+    for (const Candidate& c : candidates(p, bins->n_bytes)) {
         gerbil_params q = apply(p, c);
         uint64_t b = 0;
         const int32_t st = gerbil_count_workspace(bins, &q, &b, stream);
-        if (st != GERBIL_OK) return st;
+        if (st != GERBIL_OK && !own) return st;   // (the caller's own load or block may be refused: gerbil_autotune says so)
+        own = false;
         mx = std::max(mx, b);
     }
     *bytes = mx;
@@ -146,7 +164,7 @@ int32_t gerbil_autotune(const gerbil_bins* bins, const gerbil_params* p, void* w
     memset(&res, 0, sizeof(res));
     res.best_ms = INFINITY;
     bool out_cap = false;
-    for (const Candidate& c : candidates(p)) {
+    for (const Candidate& c : candidates(p, bins->n_bytes)) {
         gerbil_params q = apply(p, c);
         uint64_t need = 0;
         if (gerbil_count_workspace(bins, &q, &need, stream) != GERBIL_OK || need > ws_bytes) continue;

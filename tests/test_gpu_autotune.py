@@ -65,3 +65,44 @@ def test_autotune_keeps_a_fixed_placement(table):
     res = job.result()
     keys, counts = res.sorted()
     assert np.array_equal(keys, ref.keys) and np.array_equal(counts, ref.counts)
+
+
+def long_reads(k, n_reads, seed):
+    rng = np.random.default_rng(seed)
+    gen = np.array(list(b"ACGT"), np.uint8)[rng.integers(0, 4, 400_000)]
+    L = 2 * k + 500
+    a = np.concatenate([gen[s:s + L] for s in rng.integers(0, gen.size - L, n_reads).tolist()])
+    return a, np.arange(n_reads + 1, dtype=np.uint64) * np.uint64(L)
+
+
+@pytest.mark.parametrize("mode,k,n_bins", [(g.GERBIL_BATCHED, 300, 16), (g.GERBIL_BATCHED, 479, 64), (g.GERBIL_PLAIN, 55, 256)])
+def test_autotune_keeps_the_piece_path(mode, k, n_bins):
+    """Keys above 256 bases and the per-bin schedule count by pieces only with AUTO, several times faster than any
+    fixed placement: the tuned job keeps it, and counts exactly."""
+    a, o = long_reads(k, 4000, k)
+    ref = oracle.count(a, o, k, threshold=2)
+    g.gerbil_autotune_reset()
+    ad, od = to_device(a, o)
+    job = g.Job(ad, od, int(o[-1]), g.make_params(k, 9, n_bins, 2, mode=mode), hist_len=512)
+    job.encode()
+    job.bin()
+    info = job.autotune()
+    assert info.table == g.GERBIL_TABLE_AUTO and job.p.table == g.GERBIL_TABLE_AUTO
+    job.count()
+    res = job.result()
+    keys, counts = res.sorted()
+    assert np.array_equal(keys, ref.keys) and np.array_equal(counts, ref.counts)
+    assert np.array_equal(res.hist, ref.folded_hist(512))
+
+
+def test_autotune_choices_of_other_key_lengths_are_not_shared():
+    """k = 17 is partitioned by key hash and k = 31 by pieces: the same key width is not the same shape (one
+    bin, of as many k-mers to a quarter octave)."""
+    a, o = long_reads(31, 500, 1)
+    g.gerbil_autotune_reset()
+    ad, od = to_device(a, o)
+    for k, cached in ((17, 0), (31, 0), (31, 1)):
+        job = g.Job(ad, od, int(o[-1]), g.make_params(k, 9, 1, 1, mode=g.GERBIL_BATCHED), hist_len=512)
+        job.encode()
+        job.bin()
+        assert job.autotune().cached == cached
