@@ -30,6 +30,7 @@ queueing delay (arrival -> admission) and service time.
 from __future__ import annotations
 
 import collections
+import threading
 import time
 from dataclasses import dataclass
 from typing import List
@@ -150,22 +151,48 @@ class _HipEventPair:
 
 class _PinnedPool:
     """Pinned host buffers reused across jobs (pinning memory costs far more
-    than a copy). Buffers come in power-of-two sizes of at least 1 MiB."""
+    than a copy). Buffers come in power-of-two sizes of at least 1 MiB. Safe
+    with several threads: results may be released by any."""
 
     def __init__(self, torch):
         self.torch = torch
         self.free = collections.defaultdict(list)
+        self.lock = threading.Lock()
 
     def take(self, nbytes: int):
         size = 1 << 20
         while size < nbytes:
             size <<= 1
-        if self.free[size]:
-            return self.free[size].pop()
+        with self.lock:
+            if self.free[size]:
+                return self.free[size].pop()
         return self.torch.empty(size, dtype=self.torch.uint8, pin_memory=True)
 
     def give(self, buf):
-        self.free[int(buf.numel())].append(buf)
+        with self.lock:
+            self.free[int(buf.numel())].append(buf)
+
+
+class _StreamPool:
+    """Streams of finished jobs, for the next ones: the allocator keeps freed
+    memory by stream, and a stream per job kept many times the memory in use.
+    At most `most` are kept. Safe with several threads that serve at once."""
+
+    def __init__(self, torch, device, most: int):
+        self.torch, self.device, self.most = torch, device, most
+        self.free: List = []
+        self.lock = threading.Lock()
+
+    def take(self):
+        with self.lock:
+            if self.free:
+                return self.free.pop()
+        return self.torch.cuda.Stream(device=self.device)   # default priority
+
+    def give(self, stream):
+        with self.lock:
+            if len(self.free) < self.most:
+                self.free.append(stream)
 
 
 class _Job:
@@ -318,9 +345,7 @@ class CountingServer:
         self.max_inflight = int(max_inflight)
         self.params_hook = params_hook   # optional: adjusts each job's gerbil_params (tests force capacities)
         self.pool = _PinnedPool(torch)
-        # the streams of finished jobs serve the next ones: the allocator keeps freed
-        # memory by stream, and a stream per job kept many times the memory in use
-        self.streams: List = []
+        self.streams = _StreamPool(torch, self.device, self.max_inflight)
         g.load()
 
     def serve(self, requests: List[Request], realtime: bool = True, poll_s: float = 2e-4,
@@ -348,9 +373,8 @@ class CountingServer:
                 if inflight and used + fp > self.budget:
                     break
                 pending.popleft()
-                stream = self.streams.pop() if self.streams else self.torch.cuda.Stream(device=self.device)   # default priority
-                inflight.append((_Job(r, time.perf_counter() - t0, self.device, self.torch, self.pool, stream,
-                                      self.params_hook), fp))
+                inflight.append((_Job(r, time.perf_counter() - t0, self.device, self.torch, self.pool,
+                                      self.streams.take(), self.params_hook), fp))
                 used += fp
             progressed = False
             still = []
@@ -362,7 +386,7 @@ class CountingServer:
                     else:
                         done.append(res)
                     used -= fp
-                    self.streams.append(job.stream)
+                    self.streams.give(job.stream)
                     progressed = True
                 else:
                     still.append((job, fp))
