@@ -108,8 +108,9 @@ typedef struct {
                                 repeat, so more than one per slot can fit; distinct keys beyond
                                 the slots take the emergency area)                               */
     uint32_t max_probes;     /* theta of Alg. 1: trials before the emergency path; 0 = default
-                                (8 buckets of 8 slots in HBM tables; LDS tables 32 buckets of two
-                                slots (BATCHED, k >= 20) or 64 slots)                            */
+                                (8 buckets of 8 slots in HBM tables, 64 slots in LDS tables; where
+                                the second minimizer splits the bins, slots are read two at a
+                                time, and an odd number is rounded up)                           */
     uint32_t block;          /* threads per workgroup for counting, 64..1024 in steps of 64. HBM
                                 tables: 0 = 256. LDS tables, BATCHED: 512 (and k > 256, always)
                                 runs two workgroups of 512 threads per CU with 80 KB of LDS each
@@ -144,7 +145,8 @@ typedef struct {
                                 never read). bin_map must be NULL with this order.               */
     uint64_t* probe_hist;    /* optional device uint64[GERBIL_PROBE_HIST], zeroed by the caller; LDS
                                 tables, BATCHED: entry t (1 <= t < GERBIL_PROBE_HIST - 1) counts the
-                                k-mer occurrences whose insert ended at its t-th probe, the last
+                                k-mer occurrences whose insert ended at its t-th probe (of two slots
+                                where the second minimizer splits the bins), the last
                                 entry those that needed more or took the emergency area, entry 0
                                 the occurrences sent to the emergency area without a probe (the
                                 probe statistic of Sec. 3.3.1). NULL = none (no cost)             */

@@ -714,7 +714,7 @@ int32_t count_pieces(const gerbil_bins* bins, const gerbil_params* p, void* ws, 
     t.tab_cap = q.tab_cap;
     t.buckets = z.C / 2;
     t.halves = z.max_halves;
-    t.theta = p->max_probes ? p->max_probes : kDefaultLdsTheta / 2;   // buckets of two slots
+    t.theta = ((p->max_probes ? p->max_probes : kDefaultLdsTheta) - 1) / 2 + 1;   // slots, in buckets of two
     t.max_kmers = z.max_kmers;
     t.slice_kmers = z.slice_kmers;
     t.probe_hist = batched ? p->probe_hist : nullptr;

@@ -236,3 +236,21 @@ def test_items_of_a_plain_group_are_of_its_own_super_mers():
         b = e
     assert groups >= 3
     assert int(clocks[4]) == items
+
+
+@pytest.mark.parametrize("probes", [1, 2, 3, 4, 7, 64])
+def test_probes_are_counted_in_slots(probes):
+    """max_probes slots, two at a time: no insert ends past that, and the rest takes the emergency area."""
+    import torch
+    k = 31
+    rng = np.random.default_rng(31)
+    a, o = reads_to_csr([bases(rng, 300_000)])   # every k-mer once
+    ph = torch.zeros(g.GERBIL_PROBE_HIST, dtype=torch.int64, device="cuda")
+    res = g.count_kmers(a, o, k, 9, 1, 1, 64, mode=B, load_factor=1.0, max_probes=probes, probe_hist=ph.data_ptr())
+    same(res, a, o, k, 1)
+    h = ph.tolist()
+    most = (probes + 1) // 2
+    assert sum(h) == res.report.n_valid
+    assert all(x == 0 for x in h[most + 1:-1])
+    if probes <= 7:
+        assert h[most] > 0 and h[-1] == res.report.n_overflow > 0
