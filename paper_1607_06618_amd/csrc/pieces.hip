@@ -8,8 +8,8 @@
 //            fallback;
 //   scatter  every piece to its sub-table's run.
 // A bin whose pieces do not fit the list (which is sized for random
-// sub-minimizers) is left to the fallback as a whole, so every input is
-// counted exactly whatever its sub-minimizers look like.
+// sub-minimizers), or of 2^32 k-mers and more, is left to the fallback as a
+// whole, so every input is counted exactly whatever its sub-minimizers look like.
 #include "piece_plan.h"
 #include "table.h"
 
@@ -487,6 +487,7 @@ __global__ void __launch_bounds__(kSplitB, 3) k_split(PieceArgs q) {
 // that the middle of its weight falls into.
 __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
     __shared__ uint32_t wsum[32];
+    __shared__ uint64_t wsum64[32];
     __shared__ uint64_t s_light, s_heavy, s_hk;
     __shared__ uint32_t s_nh, s_tab, s_fail;
     const uint32_t tid = threadIdx.x, b = blockIdx.x;
@@ -521,13 +522,11 @@ __global__ void __launch_bounds__(kScanB) k_sub_scan(PieceArgs q) {
             w += weight(c);
         }
     }
-    uint32_t tl, tw0, tw1;
+    uint32_t tl;
+    uint64_t tw;
     const uint32_t pl = block_excl_scan(nl, wsum, tl);
     if (nh) atomicAdd(&s_nh, nh);
-    // weights add up in 64 bits: 20 of them, and the ones above, at a time
-    uint64_t wr = block_excl_scan((uint32_t)w & 0xFFFFFu, wsum, tw0);
-    wr += (uint64_t)block_excl_scan((uint32_t)(w >> 20), wsum, tw1) << 20;
-    const uint64_t tw = ((uint64_t)tw1 << 20) + tw0;
+    uint64_t wr = block_excl_scan(w, wsum64, tw);
     const uint32_t th = s_nh;
     const uint32_t nt = tl ? bin_tables(tw) : 0u;
     if (hk) atomicAdd((unsigned long long*)&s_hk, (unsigned long long)hk);

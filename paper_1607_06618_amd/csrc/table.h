@@ -132,20 +132,21 @@ __device__ __forceinline__ bool table_insert(const CountArgs& a, const Table& t,
 }
 
 // Block-wide exclusive scan of one value per thread (blockDim.x <= 1024).
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wsum, uint32_t& total) {
+template <typename T>
+__device__ __forceinline__ T block_excl_scan(T v, T* wsum, T& total) {
     const uint32_t lane = __lane_id(), wave = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-    uint32_t incl = v;
+    T incl = v;
     for (int off = 1; off < 64; off <<= 1) {
-        uint32_t y = __shfl_up(incl, off);
+        T y = __shfl_up(incl, off);
         if (lane >= (uint32_t)off) incl += y;
     }
     if (lane == 63) wsum[wave] = incl;
     __syncthreads();
     if (wave == 0) {
-        uint32_t s = lane < nw ? wsum[lane] : 0u;
-        uint32_t si = s;
+        T s = lane < nw ? wsum[lane] : T(0);
+        T si = s;
         for (int off = 1; off < 64; off <<= 1) {
-            uint32_t y = __shfl_up(si, off);
+            T y = __shfl_up(si, off);
             if (lane >= (uint32_t)off) si += y;
         }
         if (lane < nw) wsum[lane] = si - s;
@@ -153,7 +154,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wsum, 
     }
     __syncthreads();
     total = wsum[16];
-    uint32_t r = wsum[wave] + incl - v;
+    T r = wsum[wave] + incl - v;
     __syncthreads();
     return r;
 }
