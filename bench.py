@@ -108,9 +108,21 @@ class HipEvents:
 
 # Kernel sources whose change invalidates the measured HBM traffic of the counting kernel.
 TRAFFIC_SOURCES = ["paper_1607_06618_amd/csrc/pieces.hip", "paper_1607_06618_amd/csrc/pieces.h",
-                   "paper_1607_06618_amd/csrc/subtable.h", "paper_1607_06618_amd/csrc/common.h",
+                   "paper_1607_06618_amd/csrc/piece_plan.h", "paper_1607_06618_amd/csrc/subtable.h",
+                   "paper_1607_06618_amd/csrc/common.h", "paper_1607_06618_amd/csrc/table.h",
                    "paper_1607_06618_amd/csrc/internal.h", "paper_1607_06618_amd/csrc/api.hip"]
 PIECES = "k_split+k_sub_scan+k_piece_scatter+k_sub_tables"   # the counting step, k >= 20
+
+
+def partition(p, n_bytes: int) -> str:
+    """How gerbil_count splits the bins for these parameters (include/gerbil.h, GERBIL_TABLE_*)."""
+    from paper_1607_06618_amd import gerbil as g
+    if p.table == g.GERBIL_TABLE_HBM or (p.k > 256 and p.mode == g.GERBIL_PLAIN):
+        return "none (HBM tables)"
+    pieces = p.k >= 20 and not (p.k < 24 and n_bytes // p.n_bins > 16 << 20)
+    if p.mode == g.GERBIL_PLAIN:
+        pieces = pieces and p.table == g.GERBIL_TABLE_AUTO and p.size_sample == 0
+    return "second minimizer" if pieces else "key hash"
 
 
 def sources_digest(paths) -> str:
@@ -480,7 +492,7 @@ def main(argv=None):
     # (key + 32-bit counter, E = 8W + 4 bytes) written once. Where keys are
     # distributed (PLAIN, HBM tables, k < 20), also every distinct entry written
     # once and read once.
-    pieces = head == "batched" and head_table == "lds" and w.k >= 20
+    pieces = partition(R["job"].p, int(ascii_.size)) == "second minimizer"
     W = (w.k + 31) // 32
     E = 8 * W + 4
     b_in = 0.25 * (n_valid + rep.n_superm * (w.k - 1))
@@ -536,6 +548,7 @@ def main(argv=None):
     for m, r in results.items():
         out[f"{m}_kmers_per_s"] = n_valid * args.steps / r["wall"]
         out[f"{m}_ms_per_step"] = 1000.0 * r["wall"] / args.steps
+        out[f"{m}_partition"] = partition(r["job"].p, int(ascii_.size))
         if r["kernel_ms"] is not None:
             out[f"{m}_count_kernel_ms"] = r["kernel_ms"]
         if r.get("tune"):
