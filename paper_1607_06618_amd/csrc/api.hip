@@ -81,7 +81,7 @@ uint64_t enc_layout(uint64_t n_bytes, void* ws, EncLayout* L) {
     l.valid = c.take<uint64_t>(n_mask + 1);
     l.read_start = c.take<uint64_t>(n_mask + 1);
     l.kmer_ok = c.take<uint64_t>(n_mask + 1);
-    l.scalars = c.take<uint64_t>(4);   // [0] n_superm [1] list slots handed out
+    l.scalars = c.take<uint64_t>(4);
     if (L) *L = l;
     return c.used;
 }

@@ -19,7 +19,7 @@ constexpr uint64_t kShortKeyBin = 16ull << 20;   // bases per bin
 // and nothing asks for the key partition's sampled run sizes: a group of bins
 // at a time, as many as their pieces fit in the workspace. Four launches per
 // bin left most of the chip idle: 256 bins of 0.3 M 55-mers took 23.2 ms, in
-// groups 2.8 ms.
+// groups 2.5 ms.
 inline bool use_pieces(const gerbil_params* p, uint64_t n_bytes) {
     if (p->k < kPieceMinK || p->n_bins == 0 || n_bytes >= (1ull << 38)) return false;
     // Short keys have few sub-minimizers (4^10 or 4^11 at k < 24, and the smallest
@@ -79,13 +79,13 @@ inline uint32_t split_lds_bytes(uint32_t n0) {
 
 // ----------------------------------------------------------------- sizes
 // K-mers per slot; sub-tables are cut to within a group's size of it. 0.6
-// costs 3 to 5 % (more sub-tables, each with its scan and dump); 0.8 gains
-// 1 % at k = 65 and 99 and loses 3 % at k = 28 (longer probes): 25.0 / 25.1 /
-// 26.4 ms for 0.8 / 0.7 / 0.6 at k = 65, 9.1 / 8.8 / 9.2 at k = 28.
+// costs 1 to 3 % (more sub-tables, each with its scan and dump), and 0.8 as much
+// where probes get longer: passes of 26.8 / 26.8 / 27.5 ms for 0.8 / 0.7 / 0.6 at
+// k = 65, 19.8 / 19.6 / 19.8 at k = 99, 9.20 / 9.10 / 9.18 at k = 28.
 constexpr double kPieceFill = 0.7;
 // Sub-tables wanted at least: one per CU. Small inputs get smaller ones for
 // it. Two or more per CU even out their ends, but cost more fixed time each: 2 M
-// bases at k = 55 take 191 us with one, 204 with two and 229 with four.
+// bases at k = 55 take 191 us with one, 203 with two and 226 with four.
 constexpr uint32_t kTablesGoal = 256;
 
 struct PieceSizing {
@@ -133,9 +133,9 @@ inline PieceSizing piece_sizing(const gerbil_params* p, uint64_t n_kmers, uint64
     z.heavy_kmers = std::min<uint32_t>(60000u, std::max<uint32_t>(4 * z.C, z.target + z.target / 2));
     // A turn of n windows costs n + w2 - 1 m2-mers, so long turns do less work a
     // window, but their minima take the LDS that more workgroups would need.
-    // Whole passes with 32 / 40 / 48 / 64 windows at most: k = 99 19.6 / 19.5 /
-    // 19.3 / 20.1 ms, k = 200 9.44 / 9.50 / 9.69 / 9.68 ms, k = 479 3.07 / 3.03 /
-    // 3.02 / 3.02 ms. (Narrow windows: super-mers are seldom longer than 48.)
+    // Whole passes with 32 / 40 / 48 / 64 windows at most: k = 99 19.9 / 19.6 /
+    // 19.5 / 19.9 ms, k = 200 8.87 / 8.96 / 9.22 / 9.22 ms, k = 479 3.07 / 2.96 /
+    // 2.91 / 2.87 ms. (Narrow windows: super-mers are seldom longer than 48.)
     // Of the last 16, the number with the most windows per step of 16 m2-mers.
     const uint32_t n_most = std::min(w2 >= kPieceMax ? 40u : 48u, w2);
     z.n0 = n_most;
