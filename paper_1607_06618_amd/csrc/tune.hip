@@ -37,12 +37,14 @@ int quarter_octave(uint64_t x) { return x ? (int)floor(4.0 * log2((double)x)) : 
 // slower than them but for the noise of the timing. Where the pieces count
 // (piece_plan.h), pools only size their fallback and are left as they are; AUTO
 // stays AUTO where it alone takes them (PLAIN, and keys above 256 bases), and is
-// LDS where that is the same.
+// LDS or HBM where that is the same.
 std::vector<Candidate> candidates(const gerbil_params* p, uint64_t n_bytes) {
     std::vector<Candidate> c;
     const bool batched = p->mode == GERBIL_BATCHED, lds_keys = (p->k + 31) / 32 <= GERBIL_MAX_LDS_W;
     const bool pieces = gerbil::use_pieces(p, n_bytes);
-    const uint32_t own = p->table == GERBIL_TABLE_AUTO && lds_keys && (batched || !pieces) ? GERBIL_TABLE_LDS : p->table;
+    const uint32_t own = p->table != GERBIL_TABLE_AUTO || (pieces && !(batched && lds_keys)) ? p->table
+                         : lds_keys                                                          ? GERBIL_TABLE_LDS
+                                                                                             : GERBIL_TABLE_HBM;
     const uint32_t own_block = p->block ? p->block : own == GERBIL_TABLE_LDS ? 1024u : own == GERBIL_TABLE_HBM ? 256u : 0u;
     c.push_back({own, p->load_factor, p->pool, own_block});
     if (pieces) {

@@ -106,3 +106,20 @@ def test_autotune_choices_of_other_key_lengths_are_not_shared():
         job.encode()
         job.bin()
         assert job.autotune().cached == cached
+
+
+@pytest.mark.parametrize("mode,k", [(g.GERBIL_PLAIN, 300), (g.GERBIL_PLAIN, 17), (g.GERBIL_BATCHED, 17)])
+def test_autotune_names_the_placement_where_auto_is_one(mode, k):
+    """Without pieces AUTO is LDS or HBM tables, and the choice says which."""
+    a, o = long_reads(k, 300, k)
+    g.gerbil_autotune_reset()
+    ad, od = to_device(a, o)
+    job = g.Job(ad, od, int(o[-1]), g.make_params(k, 9, 16, 1, mode=mode), hist_len=512)
+    job.encode()
+    job.bin()
+    info = job.autotune()
+    assert info.table in ((g.GERBIL_TABLE_LDS, g.GERBIL_TABLE_HBM) if k <= 256 else (g.GERBIL_TABLE_HBM,))
+    job.count()
+    ref = oracle.count(a, o, k, threshold=1)
+    keys, counts = job.result().sorted()
+    assert np.array_equal(keys, ref.keys) and np.array_equal(counts, ref.counts)
