@@ -269,9 +269,10 @@ LdsSizing lds_sizing(const gerbil_params* p, uint64_t n_bytes, uint32_t key_slot
 
 // Keys a slot must hold: the k-mers of the largest bin, plus the margins of
 // its sampled run capacities: with S the sampling step and L its segment
-// length, N keys in P runs, the capacities add up to at most N + 4 sqrt(S L N)
-// (error of the sampled total) + 4 sqrt(S L) sqrt(P (N + P L)) (sum of the
-// per-run margins, by Cauchy-Schwarz) + 32 P. A hash slice of a large bin is
+// length, N keys in P runs, the sampled total is at most E = N + 4 sqrt(S L N)
+// (its error) + S L (the first segment is always sampled: all of a bin that has
+// few), and the capacities add up to E + 4 sqrt(S L) sqrt(P (E + P L)) (sum of
+// the per-run margins, by Cauchy-Schwarz) + 32 P. A hash slice of a large bin is
 // bounded by the whole bin only: slices split distinct keys evenly, but a
 // key's occurrences all go to one slice, so repeats can load one slice with
 // most of the bin.
@@ -283,7 +284,8 @@ uint64_t lds_slot_keys(uint64_t max_kmers, const LdsSizing& z) {
     if (P < 1) P = 1;
     if (P > z.max_sub) P = z.max_sub;
     const double L = sample_seg_len(z.sample);
-    const double bound = N + 4.0 * std::sqrt(S * L * N) + 4.0 * std::sqrt(S * L) * std::sqrt(P * (N + P * L)) + 33.0 * P;
+    const double E = N + 4.0 * std::sqrt(S * L * N) + S * L;
+    const double bound = E + 4.0 * std::sqrt(S * L) * std::sqrt(P * (E + P * L)) + 33.0 * P;
     return (uint64_t)std::ceil(bound);
 }
 
