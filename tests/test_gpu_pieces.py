@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import bin_arrays, random_reads, reads_to_csr, to_device
+from gpu_util import random_reads, reads_to_csr, to_device
 from paper_1607_06618_amd import gerbil as g
 
 pytestmark = pytest.mark.gpu
@@ -212,6 +212,7 @@ def test_items_of_a_plain_group_are_of_its_own_super_mers():
     """The split's work items grow with the super-mers of the group (a 2048th of them, or 1024 if a 768th is more than that; 256 to 4096), not with those of
     the bins before it."""
     import torch
+    from gpu_util import bin_arrays
     k, n_bins = 41, 64
     rng = np.random.default_rng(5)
     gen = np.array(list(b"ACGT"), np.uint8)[rng.integers(0, 4, 20_000_000)]   # one sequence: about a super-mer for every 17 bases
