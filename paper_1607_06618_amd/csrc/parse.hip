@@ -175,7 +175,8 @@ __device__ uint64_t wg_scan_inplace(uint64_t* v, uint64_t n, uint64_t* wsum) {
 
 // --------------------------------------------------------------- kernels
 
-__global__ void k_parse_init(const uint8_t* __restrict__ text, uint64_t n, uint32_t format, gerbil_parsed* out) {
+__global__ void k_parse_init(const uint8_t* __restrict__ text, uint64_t n, uint32_t format,
+                             uint64_t* __restrict__ offsets, gerbil_parsed* out) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     uint32_t fmt = format, status = 0;
     if (fmt == GERBIL_FORMAT_DETECT && n) {
@@ -183,6 +184,7 @@ __global__ void k_parse_init(const uint8_t* __restrict__ text, uint64_t n, uint3
         fmt = c == '@' ? GERBIL_FORMAT_FASTQ : c == '>' ? GERBIL_FORMAT_FASTA : 0u;
         if (!fmt) status = GERBIL_PARSE_EFORMAT;
     }
+    offsets[0] = 0;   // (an empty text of no format has no later step)
     out->n_reads = 0;
     out->n_bytes = 0;
     out->n_lines = 0;
@@ -670,7 +672,7 @@ int32_t gerbil_parse(const uint8_t* text, uint64_t n, uint32_t format, void* ws,
     if (ws_bytes < ws_layout(n, lines_cap, (uint8_t*)ws, &w)) return GERBIL_EINVAL;
     const bool aligned = (((uintptr_t)text) & 15) == 0;
     const uint64_t bt = n_btiles_of(n), lt = n_ltiles_of(lines_cap);
-    hipLaunchKernelGGL(k_parse_init, dim3(1), dim3(64), 0, stream, text, n, format, out);
+    hipLaunchKernelGGL(k_parse_init, dim3(1), dim3(64), 0, stream, text, n, format, offsets, out);
     const bool big = rounds_of(n) == kRoundsBig;
     hipLaunchKernelGGL(big ? k_nl_count<kRoundsBig> : k_nl_count<kRoundsSmall>, dim3(grid_of(bt)), dim3(kPB), 0, stream, text,
                        n, aligned, w.tile_nl);

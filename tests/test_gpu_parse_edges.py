@@ -60,3 +60,25 @@ def test_long_lines_are_shared_out(lines):
     for i in range(lines):
         out += [b">", b"", line(rng, 3_000_000 // lines + int(rng.integers(0, 40))), b"AC"]
     compare(b"\n".join(out))
+
+
+@pytest.mark.parametrize("fmt", [g.GERBIL_FORMAT_DETECT, g.GERBIL_FORMAT_FASTQ, g.GERBIL_FORMAT_FASTA])
+@pytest.mark.parametrize("text", [b"", b"\n", b">", b"@\n\n+\n\n"])
+def test_first_offset_is_written(text, fmt):
+    """Offsets [0, n_reads] are the call's, whatever the buffer held: an empty text has the one offset 0."""
+    import ctypes
+
+    import torch
+    n = len(text)
+    t = torch.zeros(64, dtype=torch.uint8, device="cuda")
+    if n:
+        t[:n] = torch.frombuffer(bytearray(text), dtype=torch.uint8).cuda()
+    info_d = torch.zeros(ctypes.sizeof(g.gerbil_parsed), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(max(256, g.gerbil_parse_workspace(n, n + 1)), dtype=torch.uint8, device="cuda")
+    seq = torch.empty(n + 1, dtype=torch.uint8, device="cuda")
+    offsets = torch.full((n + 2,), 77, dtype=torch.int64, device="cuda")
+    assert g.gerbil_parse(t.data_ptr(), n, fmt, ws.data_ptr(), ws.numel(), n + 1, seq.data_ptr(), n, offsets.data_ptr(),
+                          n + 1, info_d.data_ptr(), g._stream_handle(None)) == g.GERBIL_OK
+    info = g.gerbil_parsed.from_buffer_copy(info_d.cpu().numpy().tobytes())
+    if info.status == 0:
+        assert int(offsets[0]) == 0 and int(offsets[info.n_reads]) == info.n_bytes
